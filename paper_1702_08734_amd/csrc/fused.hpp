@@ -855,6 +855,8 @@ struct FusedArgs {
     uint32_t* bound;
     // debug count of candidates a full pool had to drop (must stay zero)
     unsigned long long* drops;
+    // if given, only query blocks with a flagged query are searched
+    const uint32_t* qflag;
 };
 
 template <class Op, int KR, int DP, bool VEC, bool L2>
@@ -951,6 +953,10 @@ knn_fused(FusedArgs args) {
     const int64_t q0 = qblk * BQ;
     const int64_t c0 = chunk * args.chunk_len;
     const int64_t c1 = c0 + args.chunk_len < args.nb ? c0 + args.chunk_len : args.nb;
+    if (args.qflag) {  // the same answer in every wave
+        const int64_t q = q0 + lane;
+        if (!__ballot(lane < BQ && q < args.nq && args.qflag[q] != 0u)) return;
+    }
     // 32-bit step counters (scalar compares): a chunk has fewer than 2^31 rows
     const int nsteps = c1 > c0 ? (int)((c1 - c0 + BN - 1) / BN) : 0;
     const int64_t row_bytes = (int64_t)args.stride * Op::BYTES;
@@ -1344,6 +1350,8 @@ inline void plan_chunks(int64_t nq, int64_t nb, int BQ, int BN, int KS, int64_t*
     *nchunks = nb > 0 ? ceil_div(nb, cl) : 1;
 }
 
+// Candidates kept beyond k for the direct-form re-rank of the merge pass.
+constexpr int kSlack = 16;
 constexpr int kMergeWaves = 4;
 constexpr int kMaxDim = 512;
 
@@ -1448,7 +1456,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_merge_rerank(
     const uint64_t* __restrict__ part, int32_t nchunks, int32_t row, int32_t nread,
     const float* __restrict__ xq, int64_t nq,
     const float* __restrict__ xb, int32_t d, int32_t vec, int32_t l2, int32_t k, int32_t keff,
-    float* __restrict__ D, int64_t* __restrict__ I) {
+    float* __restrict__ D, int64_t* __restrict__ I, const uint32_t* __restrict__ qflag) {
     constexpr int T = SelParams<KR>::T;
     constexpr int KS = 64 * KR;
     __shared__ __align__(16) float xs[kMergeWaves][kMaxDim];
@@ -1457,7 +1465,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_merge_rerank(
     const int wave = threadIdx.x >> 6;
     const int lane = lane_id();
     const int64_t q = (int64_t)blockIdx.x * kMergeWaves + wave;
-    if (q >= nq) return;
+    if (q >= nq || (qflag && qflag[q] == 0u)) return;
 
     WaveSelect<KR, T> ws;
     ws.init(keff);

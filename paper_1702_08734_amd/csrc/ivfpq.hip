@@ -989,7 +989,7 @@ mk_status scan_fixed(mk_ivfpq* ix, const float* xq, int64_t nq, int32_t nprobe, 
     *ngroups = ceil_div(nprobe, G);
     MK_TRY(part.alloc(sizeof(uint64_t) * nq * *ngroups * kk, s));
     MK_TRY(knn_search(xq, nq, ix->coarse, ix->coarse_norms, ix->nlist, ix->d, nprobe,
-                      MK_METRIC_L2, cd.as<float>(), ci.as<int64_t>(), s));
+                      MK_METRIC_L2, cd.as<float>(), ci.as<int64_t>(), s, nullptr, true));
     {
         ProfScope prof("ivf_term3", s);
         MK_TRY(launch_term3(xq, nq, M, ix->dsub, ix->books, t3.as<float>(), s));
@@ -1031,7 +1031,7 @@ mk_status probe_features(const mk_ivfpq* ix, const float* xq, int64_t nq, float*
     MK_TRY(cd.alloc(sizeof(float) * nq * kProbeDists, s));
     MK_TRY(ci.alloc(sizeof(int64_t) * nq * kProbeDists, s));
     MK_TRY(knn_search(xq, nq, ix->coarse, ix->coarse_norms, ix->nlist, ix->d, kProbeDists,
-                      MK_METRIC_L2, cd.as<float>(), ci.as<int64_t>(), s));
+                      MK_METRIC_L2, cd.as<float>(), ci.as<int64_t>(), s, nullptr, true));
     hipLaunchKernelGGL(probe_features_kernel,
                        dim3(grid_of(nq * (ix->d + kProbeDists))), dim3(kBlock), 0, s, xq, nq,
                        ix->d, cd.as<float>(), kProbeDists, F);
@@ -1046,7 +1046,7 @@ mk_status probe_labels(const mk_ivfpq* ix, const float* xq, int64_t nq, const in
     MK_TRY(ci.alloc(sizeof(int64_t) * nq * cap, s));
     MK_TRY(lof.alloc(sizeof(int32_t) * (ix->ntotal > 0 ? ix->ntotal : 1), s));
     MK_TRY(knn_search(xq, nq, ix->coarse, ix->coarse_norms, ix->nlist, ix->d, cap, MK_METRIC_L2,
-                      cd.as<float>(), ci.as<int64_t>(), s));
+                      cd.as<float>(), ci.as<int64_t>(), s, nullptr, true));
     hipLaunchKernelGGL(list_of_kernel, dim3(ix->nlist), dim3(kBlock), 0, s, ix->offsets_dev,
                        ix->nlist, ix->ids, lof.as<int32_t>());
     MK_LAUNCHED();
@@ -1075,7 +1075,7 @@ mk_status search_learned(mk_ivfpq* ix, const mk_mlp* net, float delta, const flo
     // coarse order up to cap probes; its first kProbeDists distances are the
     // network's distance features
     MK_TRY(knn_search(xq, nq, ix->coarse, ix->coarse_norms, ix->nlist, ix->d, cap, MK_METRIC_L2,
-                      cd.as<float>(), ci.as<int64_t>(), s));
+                      cd.as<float>(), ci.as<int64_t>(), s, nullptr, true));
     hipLaunchKernelGGL(probe_features_kernel,
                        dim3(grid_of(nq * (ix->d + kProbeDists))), dim3(kBlock), 0, s, xq, nq,
                        ix->d, cd.as<float>(), cap, F.as<float>());

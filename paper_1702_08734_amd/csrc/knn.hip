@@ -22,7 +22,8 @@
 #include <mutex>
 #include <vector>
 
-#include "fused.hpp"
+#include "knn_classes.hpp"
+#include "sieve.hpp"
 
 namespace mk {
 
@@ -72,31 +73,27 @@ mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStre
 }
 
 
-// Fused search for padded dimension class DP (knn_impl.hpp, one translation
-// unit per class).
-template <int DP>
-mk_status knn_dispatch_k(const float* xq, int64_t nq, const float* xb, const float* yn,
-                         int64_t nb, int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
-                         hipStream_t s, Arena* arena);
-extern template mk_status knn_dispatch_k<32>(const float*, int64_t, const float*, const float*,
-                                              int64_t, int32_t, int32_t, bool, bool, float*,
-                                              int64_t*, hipStream_t, Arena*);
-extern template mk_status knn_dispatch_k<64>(const float*, int64_t, const float*, const float*,
-                                              int64_t, int32_t, int32_t, bool, bool, float*,
-                                              int64_t*, hipStream_t, Arena*);
-extern template mk_status knn_dispatch_k<96>(const float*, int64_t, const float*, const float*,
-                                              int64_t, int32_t, int32_t, bool, bool, float*,
-                                              int64_t*, hipStream_t, Arena*);
-extern template mk_status knn_dispatch_k<128>(const float*, int64_t, const float*, const float*,
-                                               int64_t, int32_t, int32_t, bool, bool, float*,
-                                               int64_t*, hipStream_t, Arena*);
-extern template mk_status knn_dispatch_k<256>(const float*, int64_t, const float*, const float*,
-                                               int64_t, int32_t, int32_t, bool, bool, float*,
-                                               int64_t*, hipStream_t, Arena*);
+namespace {
+
+// Whether the threshold-first search takes a call.
+bool sieve_pays(int64_t nq, int64_t nb, int32_t k) {
+    return nb >= 16384 && nb >= 8ll * (k + kSlack) && nq >= 64 &&
+           nq * nb >= (1ll << 24);
+}
+
+// Queries per batch: at most 1 GiB of pools and of sample scores each.
+int64_t sieve_batch(int64_t nq, int64_t nb, int32_t k) {
+    const SievePlan p = plan_sieve(nb, k + kSlack);
+    int64_t b = std::min<int64_t>((1ll << 30) / (8 * p.cap), (1ll << 30) / (4 * p.sample));
+    b = std::max<int64_t>(b / 256 * 256, 256);
+    return std::min(nq, b);
+}
+
+}  // namespace
 
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn_in, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
-                     hipStream_t s, Arena* arena) {
+                     hipStream_t s, Arena* arena, bool bounded) {
     MK_REQUIRE(nq >= 0 && nb >= 0, MK_ERR_INVALID_ARG, "nq and nb must be >= 0");
     MK_REQUIRE(d >= 1, MK_ERR_INVALID_ARG, "d must be >= 1");
     MK_REQUIRE(k >= 1, MK_ERR_INVALID_ARG, "k must be >= 1");
@@ -109,6 +106,25 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
     const bool l2 = metric == MK_METRIC_L2;
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
+    if (!arena && !bounded && sieve_pays(nq, nb, k)) {
+        // batches of queries bound the scratch memory; without room for it
+        // the fused search below, which needs less, takes the call
+        const int64_t batch = sieve_batch(nq, nb, k);
+        mk_status st = MK_OK;
+        for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch) {
+            const int64_t n = std::min(batch, nq - q0);
+            const float* x = xq + q0 * d;
+            float* Dq = D + q0 * k;
+            int64_t* Iq = I + q0 * k;
+            if (d <= 32) st = sieve_dispatch<32>(x, n, xb, yn_in, nb, d, k, l2, vec, Dq, Iq, s);
+            else if (d <= 64) st = sieve_dispatch<64>(x, n, xb, yn_in, nb, d, k, l2, vec, Dq, Iq, s);
+            else if (d <= 96) st = sieve_dispatch<96>(x, n, xb, yn_in, nb, d, k, l2, vec, Dq, Iq, s);
+            else if (d <= 128) st = sieve_dispatch<128>(x, n, xb, yn_in, nb, d, k, l2, vec, Dq, Iq, s);
+            else st = sieve_dispatch<256>(x, n, xb, yn_in, nb, d, k, l2, vec, Dq, Iq, s);
+        }
+        if (st != MK_ERR_OOM) return st;
+        (void)hipGetLastError();
+    }
     Scratch norms;
     const float* yn = yn_in;
     if (l2 && !yn && nb > 0) {
@@ -120,11 +136,11 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
         }
         yn = norms.as<float>();
     }
-    if (d <= 32) return knn_dispatch_k<32>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-    if (d <= 64) return knn_dispatch_k<64>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-    if (d <= 96) return knn_dispatch_k<96>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-    if (d <= 128) return knn_dispatch_k<128>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-    return knn_dispatch_k<256>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
+    if (d <= 32) return knn_dispatch_k<32>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, nullptr);
+    if (d <= 64) return knn_dispatch_k<64>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, nullptr);
+    if (d <= 96) return knn_dispatch_k<96>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, nullptr);
+    if (d <= 128) return knn_dispatch_k<128>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, nullptr);
+    return knn_dispatch_k<256>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, nullptr);
 }
 
 // ------------------------------------------------- device symbols

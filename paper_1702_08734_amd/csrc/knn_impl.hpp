@@ -1,4 +1,4 @@
-// Launch of the fused exact-search kernel for one padded dimension class DP
+// Launch of the exact-search kernels for one padded dimension class DP
 // (instantiated once per class in its own translation unit, knn_dNNN.hip,
 // so that the many kernel variants compile in parallel).
 #pragma once
@@ -7,13 +7,12 @@
 
 namespace mk {
 
-// Candidates kept beyond k for the direct-form re-rank of the merge pass.
-constexpr int kSlack = 16;
-
+// Fused search.  With qflag only the flagged queries are searched (whole
+// blocks of them, results written for the flagged ones alone).
 template <int KR, int DP>
 mk_status knn_launch(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
-                     hipStream_t stream, Arena* arena) {
+                     hipStream_t stream, Arena* arena, const uint32_t* qflag) {
     using S = FusedShape<KR, DP * 4, fused_consumers<OpF32, DP>()>;
     constexpr int KS = 64 * KR;
     const int keff = k + kSlack < KS ? k + kSlack : KS;
@@ -33,9 +32,9 @@ mk_status knn_launch(const float* xq, int64_t nq, const float* xb, const float* 
     unsigned long long* drops = nullptr;
     MK_TRY(pool_drop_counter(&drops));
     FusedArgs a{xq, xb, yn, nullptr, nullptr, nq, nb, d, d, chunk_len, (int32_t)nchunks,
-                (int32_t)nqb, keff, part.as<uint64_t>(), bound.as<uint32_t>(), drops};
+                (int32_t)nqb, keff, part.as<uint64_t>(), bound.as<uint32_t>(), drops, qflag};
     {
-        ProfScope prof("knn_fused", stream);
+        ProfScope prof(qflag ? "knn_fused_rest" : "knn_fused", stream);
         auto kern = vec ? (l2 ? knn_fused<OpF32, KR, DP, true, true> : knn_fused<OpF32, KR, DP, true, false>)
                         : (l2 ? knn_fused<OpF32, KR, DP, false, true> : knn_fused<OpF32, KR, DP, false, false>);
         hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(64 * (kProducers + S::NC)), 0, stream, a);
@@ -46,7 +45,7 @@ mk_status knn_launch(const float* xq, int64_t nq, const float* xb, const float* 
         hipLaunchKernelGGL((knn_merge_rerank<KR>), dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, stream, part.as<uint64_t>(),
                            (int32_t)nchunks, (int32_t)S::ROW, S::mem_queues ? KS : keff, xq, nq,
-                           xb, d, (int32_t)vec, (int32_t)l2, k, keff, D, I);
+                           xb, d, (int32_t)vec, (int32_t)l2, k, keff, D, I, qflag);
         MK_LAUNCHED();
     }
     return MK_OK;
@@ -55,14 +54,14 @@ mk_status knn_launch(const float* xq, int64_t nq, const float* xb, const float* 
 template <int DP>
 mk_status knn_dispatch_k(const float* xq, int64_t nq, const float* xb, const float* yn,
                          int64_t nb, int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
-                         hipStream_t s, Arena* arena) {
+                         hipStream_t s, Arena* arena, const uint32_t* qflag) {
     const int want = k + kSlack < kMaxK ? k + kSlack : kMaxK;
     switch (queue_regs(want)) {
-        case 1: return knn_launch<1, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-        case 2: return knn_launch<2, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-        case 4: return knn_launch<4, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-        case 8: return knn_launch<8, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
-        default: return knn_launch<16, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena);
+        case 1: return knn_launch<1, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, qflag);
+        case 2: return knn_launch<2, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, qflag);
+        case 4: return knn_launch<4, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, qflag);
+        case 8: return knn_launch<8, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, qflag);
+        default: return knn_launch<16, DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, arena, qflag);
     }
 }
 

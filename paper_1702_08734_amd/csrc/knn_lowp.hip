@@ -101,7 +101,7 @@ template <class Op, int KR, int DP>
 mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, int64_t nq,
                       const float* xb, const void* xb_lp, const float* xb_inv, const float* yn,
                       int64_t nb, int32_t d, int32_t k, int32_t R, bool l2, float* D, int64_t* I,
-                      hipStream_t stream) {
+                      hipStream_t stream, const uint32_t* qflag = nullptr) {
     using S = FusedShape<KR, DP * Op::BYTES, fused_consumers<Op, DP>()>;
     constexpr int KS = 64 * KR;
     int64_t nqb, nchunks, chunk_len;
@@ -119,7 +119,7 @@ mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, i
     unsigned long long* drops = nullptr;
     MK_TRY(pool_drop_counter(&drops));
     FusedArgs a{xq_lp, xb_lp, yn, xq_inv, xb_inv, nq, nb, ld, ld, chunk_len, (int32_t)nchunks,
-                (int32_t)nqb, R, part.as<uint64_t>(), bound.as<uint32_t>(), drops};
+                (int32_t)nqb, R, part.as<uint64_t>(), bound.as<uint32_t>(), drops, qflag};
     {
         ProfScope prof(Op::SCALED ? "knn_fused_fp8" : "knn_fused_bf16", stream);
         auto kern = l2 ? knn_fused<Op, KR, DP, true, true> : knn_fused<Op, KR, DP, true, false>;
@@ -134,7 +134,7 @@ mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, i
         hipLaunchKernelGGL((knn_merge_rerank<KR>), dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, stream, part.as<uint64_t>(),
                            (int32_t)nchunks, (int32_t)S::ROW, S::mem_queues ? KS : R, xq, nq, xb,
-                           d, (int32_t)vec, (int32_t)l2, k, R, D, I);
+                           d, (int32_t)vec, (int32_t)l2, k, R, D, I, qflag);
         MK_LAUNCHED();
     }
     return MK_OK;

@@ -29,6 +29,8 @@ template <> struct SelParams<2> { static constexpr int T = 2; };
 template <> struct SelParams<4> { static constexpr int T = 4; };
 template <> struct SelParams<8> { static constexpr int T = 4; };
 template <> struct SelParams<16> { static constexpr int T = 8; };
+// (1,024 results and the candidates beyond them that prove the set)
+template <> struct SelParams<32> { static constexpr int T = 8; };
 
 // Per row, select the k best of nseg sorted lists of k keys each
 // (partial[row][seg][k]) and write (score, index) pairs -- sentinel keys
@@ -45,11 +47,12 @@ mk_status merge_key_lists(const uint64_t* partial, int64_t nrows, int32_t nseg, 
 
 // Exact k-NN (knn.hip); yn may be null (then computed) for L2.
 // With an arena every scratch buffer is carved from it (nothing is
-// allocated); a workspace too small gives MK_ERR_UNSUPPORTED.
+// allocated); a workspace too small gives MK_ERR_UNSUPPORTED.  bounded: the
+// caller accounts for the fused search's scratch only.
 struct Arena;
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
-                     hipStream_t s, Arena* arena = nullptr);
+                     hipStream_t s, Arena* arena = nullptr, bool bounded = false);
 mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStream_t s);
 
 // Device address (current device) of the library's count of candidates that

@@ -1,0 +1,751 @@
+// Threshold-first exact search for batches of queries: the selector of the
+// fused kernel (fused.hpp) leaves the matrix waves.
+//
+//   1. A stratified sample of the database (a few thousand rows) is scored
+//      and the r-th best sample score of each query becomes its threshold,
+//      r chosen so that the threshold lets a few times keff rows of the whole
+//      database through.
+//   2. sieve_tiles streams the database once: every wave holds 64 queries
+//      (32 for wide rows) as MFMA operands in registers, compares each score
+//      with its query's threshold in the accumulator registers (one lane = one
+//      query, so the threshold is a register and a 16 x 16 block costs a
+//      minimum tree and one compare) and appends the few that pass to the
+//      query's pool in device memory.
+//   3. sieve_finish selects the keff best of the pool, re-ranks them in the
+//      direct FP32 form and writes the k best.
+//
+// What bounds it: the matrix cores.  10,000 queries x 1,000,000 x 128, k = 32:
+// sieve_tiles 6.7 ms (1,140 TFLOP/s of FP16 products; 5.8 ms, 1,330 TFLOP/s,
+// when no score passes), the whole search 6.7 ms against 27.1 ms by the fused
+// kernel (95 TFLOP/s of FP32 products, and FP32 products cannot take less than
+// 16.3 ms); 2,000 queries, k = 1000: 2.1 against 9.6 ms; 500 queries x 50,000 x
+// 64, k = 10: 0.12 against 0.39 ms.
+//
+// Nothing is taken on trust: a query whose pool overflowed or came out short,
+// or (FP32 search) whose result the error bound below does not prove, is
+// flagged and searched again by the fused kernel, whose workgroups return at
+// once when none of their queries is flagged.
+//
+// FP32 rows are multiplied as pairs of FP16 rows (h + l, each row scaled by a
+// power of two): three FP16 matrix products (h l, l h, h h) carry 22+ bits of
+// every product at a third of the FP16 rate, 5 times the FP32 matrix rate.
+#pragma once
+
+#include <cmath>
+
+#include "fused.hpp"
+
+namespace mk {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+
+// Relative bound on what the split product, the norm and the direct form can
+// err together: every score is lowered by kSplitErr * (||x||^2 + ||y||^2) (L2)
+// or 2 kSplitErr ||x|| ||y|| (inner product), which makes it a lower bound of
+// the row's true score.  Splitting leaves at most 2^-23 per factor and drops
+// l l <= 2^-24 of a product; the FP32 sums add the rest.  Measured against
+// float64 on five distributions, d = 17..256: at most 3.2e-7 (root mean square
+// 3e-8 to 7e-8) of that sum; the FP32 chain of the fused kernel 9.5e-7 (4e-8 to
+// 2e-7).
+constexpr float kSplitErr = 1.9073486328125e-6f;  // 2^-19
+
+struct SieveSplit {  // two FP16 planes per row: h, then l
+    static constexpr int EPG = 8, BYTES = 2, PLANES = 2;
+    static constexpr bool SCALED = true;
+    static constexpr bool SHIFTED = true;  // lower-bound shift (IP: per-row norm)
+    static constexpr int MMAS = 3;         // matrix products per granule step
+    template <int S4>
+    __device__ static __forceinline__ floatx4 mma(floatx4 c, const uint4 (&b)[2 * S4],
+                                                  const uint4 (&q)[2 * S4], int s4) {
+        const half8 bh = __builtin_bit_cast(half8, b[s4]), bl = __builtin_bit_cast(half8, b[S4 + s4]);
+        const half8 qh = __builtin_bit_cast(half8, q[s4]), ql = __builtin_bit_cast(half8, q[S4 + s4]);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(bh, ql, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(bl, qh, c, 0, 0, 0);
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(bh, qh, c, 0, 0, 0);
+    }
+};
+// The low-precision formats run the products of the fused kernel in its
+// order (so their scores, and with them the candidates they keep, are the
+// same bit for bit).
+struct SieveBF16 {
+    static constexpr int EPG = 8, BYTES = 2, PLANES = 1;
+    static constexpr bool SCALED = false, SHIFTED = false;
+    static constexpr int MMAS = 1;
+    template <int S4>
+    __device__ static __forceinline__ floatx4 mma(floatx4 c, const uint4 (&b)[S4],
+                                                  const uint4 (&q)[S4], int s4) {
+        return OpBF16::mma(c, b[s4], q[s4]);
+    }
+};
+struct SieveFP8 {
+    static constexpr int EPG = 16, BYTES = 1, PLANES = 1;
+    static constexpr bool SCALED = true, SHIFTED = false;
+    static constexpr int MMAS = 2;
+    template <int S4>
+    __device__ static __forceinline__ floatx4 mma(floatx4 c, const uint4 (&b)[S4],
+                                                  const uint4 (&q)[S4], int s4) {
+        return OpFP8::mma(c, b[s4], q[s4]);
+    }
+};
+
+// Workgroup of sieve_tiles: 8 waves (2 per SIMD) as 4 query groups x 2 row
+// groups.  A wave reads each 16-row operand block from LDS once per QB * 16
+// queries: with 64 queries the LDS reads take about a third of the matrix
+// time.  Tiles of about 32 KB, three in flight.
+template <class Op, int DP>
+struct SieveShape {
+    static constexpr int WAVES = 8, QG = 4, RG = 2;
+    static constexpr int GRP = DP / Op::EPG;          // granules per plane
+    static constexpr int GR = Op::PLANES * GRP;       // granules per row
+    static constexpr int S4 = GRP / 4;                // granule steps
+    static constexpr int QB = 4 * Op::PLANES * S4 * 4 <= 128 ? 4 : 2;
+    static constexpr int BQ = QG * QB * 16;
+    static constexpr int RBW = GR >= 64 ? 1 : GR >= 24 ? 2 : 4;  // row blocks per wave and step
+    static constexpr int BN = RG * RBW * 16;
+    static constexpr int NBUF = 3;
+    static constexpr int LPW = BN * GR / (64 * WAVES);  // tile loads per wave
+    static_assert(GRP % 4 == 0 && BN * GR % (64 * WAVES) == 0, "tile loads split evenly");
+};
+
+struct SieveArgs {
+    const void* xq;       // queries, rows of `stride` bytes
+    const float* qscale;  // per-query 1/scale (scaled formats)
+    const float* qnorm;   // per-query ||x||^2 (split, inner product)
+    const void* xb;       // database rows of this launch, same format
+    const float* ya;      // per-row 1/scale (scaled formats)
+    const float* yb;      // per-row ||y||^2 (L2) or ||y|| (split, inner product)
+    int64_t nq, nb;       // nb: rows of this launch
+    uint32_t row0;        // index of its first row
+    int32_t stride;       // bytes per row
+    int64_t chunk_len;
+    int32_t nchunks, nqb;
+    const float* thr;     // filter: threshold of query q at thr[q * thr_ld]
+    int64_t thr_ld;
+    uint32_t* cnt;        // filter: [nq] keys appended (may exceed cap)
+    uint64_t* pool;       // filter: [nq][cap] keys
+    uint32_t cap;
+    float* scores;        // store: [nq][ld] scores
+    int64_t ld;
+};
+
+template <class Op, int DP, bool L2, bool STORE>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void sieve_tiles(
+    SieveArgs args) {
+    using S = SieveShape<Op, DP>;
+    constexpr int GR = S::GR, S4 = S::S4, QB = S::QB, RBW = S::RBW, BN = S::BN, LPW = S::LPW;
+    constexpr int BQ = S::BQ, NBUF = S::NBUF, PL = Op::PLANES;
+    constexpr bool HASB = L2 || Op::SHIFTED;
+    constexpr int NSIDE = (Op::SCALED ? 1 : 0) + (HASB ? 1 : 0);
+    // granule c of tile row j sits at c ^ (j & SW): the 16 rows of an operand
+    // read fall in different banks
+    constexpr int SW = (GR % 16 == 0) ? 15 : (GR % 8 == 0) ? 7 : 3;
+    constexpr int SIDE_OPS = NSIDE * ((BN + 63) / 64);  // waves with one more load per tile
+    // Candidates staged in LDS by each wave for itself (no atomics, no
+    // barriers).  A lane whose four scores of a block hold one that passes
+    // stages all four and where they belong (6 bits of the wave's query, 26
+    // bits of the row inside the chunk): a dozen instructions; which of them
+    // pass is looked at when they are flushed.  Room for one block's 64 QB
+    // lanes above the level at which the waves flush.
+    constexpr int CLIM = STORE ? 0 : 112;
+    constexpr int CCAP = STORE ? 1 : CLIM + 64 * QB;
+    constexpr int kRowBits = 26;
+    __shared__ __align__(16) uint4 tiles[NBUF][BN * GR];
+    __shared__ __align__(16) float side[NBUF][NSIDE > 0 ? NSIDE : 1][BN];
+    __shared__ __align__(16) floatx4 cscore[STORE ? 1 : S::WAVES][CCAP];
+    __shared__ uint32_t cmeta[STORE ? 1 : S::WAVES][CCAP];
+    __shared__ float lthr[STORE ? 1 : BQ];
+    __shared__ int flush_at;
+
+    const int64_t logical = xcd_logical_id(blockIdx.x, (int64_t)args.nqb * args.nchunks);
+    const int64_t chunk = logical / args.nqb;
+    const int64_t q0 = (logical % args.nqb) * BQ;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = lane_id();
+    const int li = lane & 15, lh = lane >> 4;
+    const int qg = wave & 3, rg = wave >> 2;
+    // rows of a launch fit 31 bits
+    const int c0 = (int)(chunk * args.chunk_len);
+    const int c1 = (int)(c0 + args.chunk_len < args.nb ? c0 + args.chunk_len : args.nb);
+    const int nsteps = c1 > c0 ? (c1 - c0 + BN - 1) / BN : 0;
+    // (a split row is exactly its planes)
+    const int row_bytes = PL > 1 ? GR * 16 : args.stride;
+    const unsigned char* xb = static_cast<const unsigned char*>(args.xb);
+
+    // ---- this wave's queries: operands, scale factors, thresholds
+    uint4 qreg[QB][PL * S4];
+    float mq[QB], sh[QB], thr[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int64_t q = q0 + (qg * QB + qb) * 16 + li;
+        const bool ok = q < args.nq;
+        const unsigned char* row =
+            static_cast<const unsigned char*>(args.xq) + (ok ? q : 0) * (int64_t)row_bytes;
+#pragma unroll
+        for (int p = 0; p < PL; ++p)
+#pragma unroll
+            for (int s4 = 0; s4 < S4; ++s4) {
+                const int c = 4 * s4 + lh;
+                uint4 v = make_uint4(0, 0, 0, 0);
+                // (the planes of a split row are whole; a low-precision row
+                // may be shorter than DP)
+                if (ok && (PL > 1 || c * 16 < args.stride))
+                    v = *reinterpret_cast<const uint4*>(row + (p * S::GRP + c) * 16);
+                qreg[qb][p * S4 + s4] = v;
+            }
+        const float inv = Op::SCALED && ok ? args.qscale[q] : 1.f;
+        mq[qb] = (L2 ? -2.f : -1.f) * inv;
+        sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
+        thr[qb] = (!STORE && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        if (!STORE && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
+    }
+    if (!STORE && threadIdx.x == 0) flush_at = -1;
+
+    // ---- tile loads: row j, granule cc of load t of this lane
+    auto granule_of = [&](int t, int& j, int& cc) __attribute__((always_inline)) {
+        const int g = (wave + t * S::WAVES) * 64 + lane;
+        j = g / GR;
+        const int c = (g % GR) ^ (j & SW);
+        // granules past a short row repeat granule 0 (they meet zero queries)
+        cc = (PL > 1 || c * 16 < args.stride) ? c : 0;
+    };
+    // byte offsets inside a tile; where the loads of a lane are whole tile
+    // rows apart with the same swizzle, one offset and constants
+    constexpr int JT = 64 * S::WAVES / GR;  // rows between loads t and t + 1
+    constexpr bool EVEN = PL > 1 && 64 * S::WAVES % GR == 0 && JT % (SW + 1) == 0;
+    int32_t loff[EVEN ? 1 : LPW];
+#pragma unroll
+    for (int t = 0; t < (EVEN ? 1 : LPW); ++t) {
+        int j, cc;
+        granule_of(t, j, cc);
+        loff[t] = (int32_t)(j * row_bytes + cc * 16);
+    }
+    // direct global-to-LDS loads from asm, as in the fused kernel: the
+    // compiler does not see them, the explicit vmcnt waits below cover them
+    // (scalar base, 32-bit lane offset)
+    auto dma16 = [&](const unsigned char* base, int off, uint32_t m0) __attribute__((always_inline)) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(off), "s"(base), "s"(m0)
+                     : "memory", "m0");
+    };
+    auto dma4 = [&](const float* base, int off, uint32_t m0) __attribute__((always_inline)) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                     :
+                     : "v"(off), "s"(base), "s"(m0)
+                     : "memory", "m0");
+    };
+    const uint32_t tiles_lds = (uint32_t)(uintptr_t)(lds_ptr_t)&tiles[0][0];
+    const uint32_t side_lds = (uint32_t)(uintptr_t)(lds_ptr_t)&side[0][0][0];
+    auto load_tile = [&](int t0, int buf) __attribute__((always_inline)) {
+        const uint32_t base = tiles_lds + (uint32_t)(buf * BN * GR * 16 + wave * 64 * 16);
+        const unsigned char* tile = xb + (int64_t)t0 * row_bytes;
+        if (t0 + BN <= c1) {
+#pragma unroll
+            for (int t = 0; t < LPW; ++t) {
+                const uint32_t dst = base + (uint32_t)(t * S::WAVES * 64 * 16);
+                if constexpr (EVEN)
+                    dma16(tile + t * JT * GR * 16, loff[0], dst);
+                else
+                    dma16(tile, loff[t], dst);
+            }
+        } else {  // rows past the end repeat the last one
+            const int last = c1 - 1 - t0;
+#pragma unroll
+            for (int t = 0; t < LPW; ++t) {
+                int j, cc;
+                granule_of(t, j, cc);
+                j = j < last ? j : last;
+                dma16(tile, j * row_bytes + cc * 16, base + (uint32_t)(t * S::WAVES * 64 * 16));
+            }
+        }
+        if constexpr (NSIDE > 0) {
+            if (wave < SIDE_OPS) {
+                constexpr int PER = (BN + 63) / 64;
+                const int a = wave / PER, part = wave % PER;
+                const float* src = (Op::SCALED && a == 0) ? args.ya : args.yb;
+                const int last = c1 - 1 - t0;
+                int j = part * 64 + lane;
+                j = j < last ? j : last;
+                const uint32_t dst = side_lds + (uint32_t)(((buf * NSIDE + a) * BN + part * 64) * 4);
+                if (BN >= 64 || lane < BN) dma4(src + t0, j * 4, dst);
+            }
+        }
+    };
+    // at most the newest tile's loads of this wave outstanding
+    auto wait_tile = [&]() __attribute__((always_inline)) {
+        if (wave < SIDE_OPS)
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm<LPW + 1>());
+        else
+            __builtin_amdgcn_s_waitcnt(waitcnt_vm<LPW>());
+    };
+    auto step_barrier = [&]() __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    // The staged candidates to their queries' pools, positions from the
+    // queries' counters.  Stores may complete out of order with the tile
+    // loads, so the wave then waits for everything (its tile waits count
+    // loads only).
+    uint32_t staged = 0;  // wave-uniform
+    const int64_t qw0 = q0 + qg * QB * 16;
+    auto flush = [&]() {
+        __builtin_amdgcn_wave_barrier();
+        constexpr int U = 2;  // counters asked at a time
+#pragma unroll 1
+        for (uint32_t e0 = 0; e0 < staged; e0 += 64 * U) {
+            floatx4 c[U];
+            uint32_t meta[U], take[U], pos[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = e0 + u * 64 + lane;
+                take[u] = 0u;
+                pos[u] = 0u;
+                meta[u] = 0u;
+                c[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if (i < staged) {
+                    c[u] = cscore[wave][i];
+                    meta[u] = cmeta[wave][i];
+                    const uint32_t ql = meta[u] >> kRowBits;
+                    const int row = c0 + (int)(meta[u] & ((1u << kRowBits) - 1u));
+                    const float t = lthr[qg * QB * 16 + ql];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        take[u] |= (c[u][e] <= t && row + e < c1) ? 1u << e : 0u;
+                    if (take[u]) pos[u] = atomicAdd(&args.cnt[qw0 + ql], (uint32_t)__popc(take[u]));
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                uint64_t* p = args.pool + (qw0 + (meta[u] >> kRowBits)) * args.cap;
+                const uint32_t row =
+                    args.row0 + (uint32_t)c0 + (meta[u] & ((1u << kRowBits) - 1u));
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (take[u] & (1u << e)) {
+                        if (pos[u] < args.cap) p[pos[u]] = make_key(c[u][e], row + e);
+                        ++pos[u];
+                    }
+            }
+        }
+        staged = 0;
+        __builtin_amdgcn_s_waitcnt(0);
+    };
+
+    __builtin_amdgcn_s_waitcnt(0);
+    if (nsteps > 0) load_tile(c0, 0);
+    if (nsteps > 1) load_tile(c0 + BN, 1);
+    if (nsteps > 1)
+        wait_tile();
+    else
+        __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    // Scores of one 16-row block from its dot products, tested against the
+    // thresholds (lane = query li of each 16, register i = row + i).
+    auto scores_of = [&](const floatx4 (&acc)[QB], floatx4 av, floatx4 bv, float (&sc)[QB][4])
+                         __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float v = acc[qb][i];
+                if constexpr (Op::SCALED) v *= av[i];
+                if constexpr (L2)
+                    sc[qb][i] = fmaf(v, mq[qb], bv[i]);
+                else if constexpr (Op::SHIFTED)
+                    sc[qb][i] = fmaf(bv[i], sh[qb], v * mq[qb]);
+                else
+                    sc[qb][i] = v * mq[qb];
+            }
+    };
+    auto emit = [&](const float (&sc)[QB][4], int row) __attribute__((always_inline)) {
+        if constexpr (STORE) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int64_t q = q0 + (qg * QB + qb) * 16 + li;
+                floatx4 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = row + i < args.nb ? sc[qb][i] : INFINITY;
+                if (q < args.nq && row < args.ld)
+                    *reinterpret_cast<floatx4*>(&args.scores[q * args.ld + row]) = o;
+            }
+        } else {
+            // (room for every lane of the block: see the flush below)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const float m = fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3]));
+                const bool take = m <= thr[qb];
+                const uint64_t bal = __ballot(take);
+                if (bal) {
+                    if (take) {
+                        const uint32_t pos =
+                            staged + __builtin_amdgcn_mbcnt_hi(
+                                         (uint32_t)(bal >> 32),
+                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+                        cscore[wave][pos] = floatx4{sc[qb][0], sc[qb][1], sc[qb][2], sc[qb][3]};
+                        cmeta[wave][pos] =
+                            ((uint32_t)(qb * 16 + li) << kRowBits) | (uint32_t)(row - c0);
+                    }
+                    staged += (uint32_t)__popcll(bal);
+                }
+            }
+            if (staged > CLIM) flush();
+        }
+    };
+
+    // Blocks are software-pipelined: the scores of one block (vector ALU) are
+    // computed between the matrix products of the next, which leave three
+    // issue slots of four free; the first block of the loop tests an empty
+    // predecessor (row c1: every row past the end).  Not where the operands of
+    // one block leave no registers for it.
+    constexpr bool PIPE = PL * S4 * (QB + 1) * 4 <= 160;
+    floatx4 prev[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) prev[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    floatx4 pav = floatx4{0.f, 0.f, 0.f, 0.f}, pbv = floatx4{INFINITY, INFINITY, INFINITY, INFINITY};
+    int prow = STORE ? (int)args.ld : c1;
+    int buf = 0;
+#pragma unroll 1
+    for (int s = 0; s < nsteps; ++s) {
+        const int t0 = c0 + s * BN;
+        const bool issue = s + 2 < nsteps;
+        if (issue) load_tile(t0 + 2 * BN, buf >= 1 ? buf - 1 : NBUF - 1);
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb) {
+            const int r0 = (rg * RBW + rb) * 16;
+            const uint4* bt = &tiles[buf][(r0 + li) * GR];
+            uint4 b[PL * S4];
+#pragma unroll
+            for (int p = 0; p < PL; ++p)
+#pragma unroll
+                for (int s4 = 0; s4 < S4; ++s4)
+                    b[p * S4 + s4] = bt[(p * S::GRP + 4 * s4 + lh) ^ (li & SW)];
+            floatx4 av{}, bv{};
+            if constexpr (Op::SCALED)
+                av = *reinterpret_cast<const floatx4*>(&side[buf][0][r0 + 4 * lh]);
+            if constexpr (HASB)
+                bv = *reinterpret_cast<const floatx4*>(&side[buf][NSIDE - 1][r0 + 4 * lh]);
+            floatx4 acc[QB];
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            float sc[QB][4];
+            if constexpr (PIPE) scores_of(prev, pav, pbv, sc);
+#pragma unroll
+            for (int s4 = 0; s4 < S4; ++s4)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+                    acc[qb] = Op::template mma<S4>(acc[qb], b, qreg[qb], s4);
+            if constexpr (!PIPE) {
+                scores_of(acc, av, bv, sc);
+                emit(sc, t0 + r0 + 4 * lh);
+                continue;
+            }
+#pragma unroll
+            for (int t = 0; t < S4 * QB * Op::MMAS; ++t) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix product
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two vector operations
+            }
+            emit(sc, prow);
+            prow = t0 + r0 + 4 * lh;
+            pav = av;
+            pbv = bv;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) prev[qb] = acc[qb];
+        }
+        // the next tile has landed (stores: wait for everything, as above)
+        if (!issue || STORE)
+            __builtin_amdgcn_s_waitcnt(0);
+        else
+            wait_tile();
+        // waves flush together, before the fullest has to: one wave's flush
+        // would hold the others up at the next barrier all the same
+        if (!STORE && staged > CLIM * 3 / 4 && lane == 0) flush_at = s;
+        step_barrier();
+        if (!STORE && staged && *(volatile int*)&flush_at == s) flush();
+        buf = buf + 1 < NBUF ? buf + 1 : 0;
+    }
+    if (PIPE && nsteps > 0) {
+        float sc[QB][4];
+        scores_of(prev, pav, pbv, sc);
+        emit(sc, prow);
+    }
+    if constexpr (!STORE)
+        if (staged) flush();
+}
+
+// ------------------------------------------------------- FP16 pair rows
+// Row i of a stratified sample of n out of nb rows: one row of each of n
+// equal strata, at a hashed place inside it (no period of the data lines up
+// with it).
+__device__ __forceinline__ int64_t sample_row(int64_t i, int64_t n, int64_t nb) {
+    const int64_t lo = i * nb / n, hi = (i + 1) * nb / n;
+    uint64_t h = (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull;
+    h ^= h >> 29;
+    h *= 0xBF58476D1CE4E5B9ull;
+    h ^= h >> 32;
+    return lo + (int64_t)(h % (uint64_t)(hi - lo));
+}
+
+// Rows of d floats as two FP16 planes of DP elements (zero padded): x 2^p =
+// h + l, p the row's own power of two with max |x| 2^p in [2^13, 2^14).
+//   scale[i] = 2^-p;
+//   off[i]: DB rows, L2: ||y||^2 (1 - kSplitErr) (norms yn if given); DB rows,
+//   inner product: ||y||; queries: ||x||^2;
+//   raw[i] (if given): the row's ||x||^2.
+// A row that is not finite, or so large or small that scales and squares could
+// leave the normal range, raises *bad for database rows, bad[i] for queries.
+enum SplitKind { kSplitDbL2 = 0, kSplitDbIp = 1, kSplitQuery = 2 };
+template <int DP>
+__global__ __launch_bounds__(256) void split_rows_kernel(
+    const float* __restrict__ x, int64_t n, int32_t d, int32_t vec, int32_t kind,
+    const float* __restrict__ yn, int64_t sample_of, unsigned char* __restrict__ out,
+    float* __restrict__ scale, float* __restrict__ off, float* __restrict__ raw,
+    uint32_t* __restrict__ bad) {
+    constexpr int GRP = DP / 8;
+    constexpr int LPR = GRP >= 16 ? 16 : GRP > 8 ? 16 : GRP;  // lanes per row
+    constexpr int NG = (GRP + LPR - 1) / LPR;                 // granules per lane
+    const int lane = threadIdx.x & 63;
+    const int sub = lane % LPR;
+    const int64_t rows_per_wave = 64 / LPR;
+    const int64_t w0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+    const int64_t nw = (int64_t)gridDim.x * 4;
+    for (int64_t r0 = w0 * rows_per_wave; r0 < n; r0 += nw * rows_per_wave) {
+        const int64_t i = r0 + lane / LPR;
+        const bool live = i < n;
+        const int64_t src = !live ? 0 : sample_of > 0 ? sample_row(i, n, sample_of) : i;
+        const float* p = x + src * d;
+        float v[NG][8];
+        float m = 0.f, ss = 0.f;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const int e0 = (g * LPR + sub) * 8;
+            if (vec) {
+                float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+                if (live && e0 < d) a = *reinterpret_cast<const float4*>(p + e0);
+                if (live && e0 + 4 < d) b = *reinterpret_cast<const float4*>(p + e0 + 4);
+                v[g][0] = a.x; v[g][1] = a.y; v[g][2] = a.z; v[g][3] = a.w;
+                v[g][4] = b.x; v[g][5] = b.y; v[g][6] = b.z; v[g][7] = b.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[g][e] = (live && e0 + e < d) ? p[e0 + e] : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                m = fmaxf(m, fabsf(v[g][e]));
+                ss = fmaf(v[g][e], v[g][e], ss);
+            }
+        }
+#pragma unroll
+        for (int o = LPR / 2; o >= 1; o >>= 1) {
+            m = fmaxf(m, __shfl_xor(m, o, LPR));
+            ss += __shfl_xor(ss, o, LPR);
+        }
+        // (a NaN element leaves m alone but not the sum of squares)
+        const bool fine = ss == 0.f ? m == 0.f : (m >= 0x1p-50f && m < 0x1p50f && ss < 0x1p110f);
+        int ex = 0;
+        if (fine && m > 0.f) ex = 13 - ((int)((__float_as_uint(m) >> 23) & 0xFF) - 127);
+        const float up = __uint_as_float((uint32_t)(127 + ex) << 23);
+        const float dn = __uint_as_float((uint32_t)(127 - ex) << 23);
+        if (live) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (g * LPR + sub >= GRP) continue;
+                half8 h, l;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float xs = fine ? v[g][e] * up : 0.f;
+                    const _Float16 hh = (_Float16)xs;
+                    h[e] = hh;
+                    l[e] = (_Float16)(xs - (float)hh);
+                }
+                unsigned char* o = out + i * (int64_t)(DP * 4) + (g * LPR + sub) * 16;
+                *reinterpret_cast<half8*>(o) = h;
+                *reinterpret_cast<half8*>(o + DP * 2) = l;
+            }
+            if (sub == 0) {
+                scale[i] = dn;
+                if (raw) raw[i] = ss;
+                float of = ss;
+                if (kind == kSplitDbL2) {
+                    if (yn) of = yn[src];
+                    of *= 1.f - kSplitErr;
+                } else if (kind == kSplitDbIp) {
+                    of = sqrtf(ss);
+                }
+                off[i] = of;
+                if (!fine) {
+                    if (kind == kSplitQuery)
+                        bad[i] = 1u;
+                    else
+                        *bad = 1u;
+                }
+            }
+        }
+    }
+}
+
+// Gather of a stratified sample of low-precision rows (16-byte granules) and
+// their side values (either may be null).
+static __global__ void sample_rows_kernel(const unsigned char* __restrict__ xb, int32_t stride,
+                                          int64_t n, int64_t nb, const float* __restrict__ a,
+                                          const float* __restrict__ b,
+                                          unsigned char* __restrict__ out, float* __restrict__ oa,
+                                          float* __restrict__ ob) {
+    const int32_t gr = stride / 16;
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (g >= n * gr) return;
+    const int64_t i = g / gr;
+    const int32_t c = (int32_t)(g % gr);
+    const int64_t src = sample_row(i, n, nb);
+    reinterpret_cast<uint4*>(out + i * stride)[c] =
+        reinterpret_cast<const uint4*>(xb + src * stride)[c];
+    if (c == 0) {
+        if (a) oa[i] = a[src];
+        if (b) ob[i] = b[src];
+    }
+}
+
+static __global__ void sieve_clear_kernel(uint32_t* __restrict__ p, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        p[i] = 0u;
+}
+
+// ------------------------------------------------------------- finish
+// One wave per query: the keff best keys of its pool, re-ranked in the direct
+// FP32 form, the k best written.  flags[q] != 0 afterwards: the query has no
+// proven result (pool overflowed or short, values the split cannot hold, or,
+// with cert, a dropped row's lower bound does not clear the k-th distance) and
+// is left to the fused search.
+//
+// cert: the pool's scores are lower bounds of rows' true scores less the
+// per-query constant kSplitErr ||x||^2 (L2).  A dropped row's score is at least
+// the keff-th best score s; its distance in the direct form is then at least
+// (||x||^2 + s - kSplitErr ||x||^2)(1 - 2^-20), and its negated inner product at
+// least s.  When the k-th re-ranked value is below that, no dropped row can
+// enter, whatever the data.
+template <int KR>
+__global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish(
+    const uint64_t* __restrict__ pool, const uint32_t* __restrict__ cnt, uint32_t cap,
+    const float* __restrict__ xq, int64_t nq, const float* __restrict__ xb, int32_t d, int32_t vec,
+    int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
+    const uint32_t* __restrict__ bad_db, uint32_t* __restrict__ flags, uint32_t* __restrict__ any,
+    float* __restrict__ D, int64_t* __restrict__ I) {
+    constexpr int T = SelParams<KR>::T;
+    constexpr int KS = 64 * KR;
+    __shared__ __align__(16) float xs[kMergeWaves][kMaxDim];
+    __shared__ uint64_t kl[kMergeWaves][KS];
+    __shared__ float dist[kMergeWaves][KS];
+    const int wave = threadIdx.x >> 6;
+    const int lane = lane_id();
+    const int64_t q = (int64_t)blockIdx.x * kMergeWaves + wave;
+    if (q >= nq) return;
+    const uint32_t n = cnt[q];
+    if (n > cap || n < (uint32_t)keff || flags[q] != 0u || (bad_db && *bad_db != 0u)) {
+        if (lane == 0) flags[q] = *any = 1u;
+        return;
+    }
+    WaveSelect<KR, T> ws;
+    ws.init(keff);
+    const uint64_t* p = pool + q * (int64_t)cap;
+#pragma unroll 1
+    for (uint32_t e = 0; e < n; e += 64) {
+        const uint32_t i = e + lane;
+        if (ws.push(i < n ? p[i] : kSentinel)) ws.merge();
+    }
+    ws.finish();
+    const float s_last = key_score(ws_element<KR>(ws.w, keff - 1));
+
+    const float* x = xq + q * d;
+    for (int t = lane; t < d; t += 64) xs[wave][t] = x[t];
+#pragma unroll
+    for (int r = 0; r < KR; ++r) kl[wave][r * 64 + lane] = ws.w[r];
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    const float* xw = xs[wave];
+#pragma unroll 1
+    for (int e0 = 0; e0 < keff; e0 += 16)
+        rerank_rows16(xw, kl[wave], e0, keff, xb, d, vec, l2, dist[wave]);
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    uint64_t nk[KR];
+#pragma unroll
+    for (int r = 0; r < KR; ++r) {
+        const uint64_t key = ws.w[r];
+        const int e = r * 64 + lane;
+        nk[r] = kSentinel;
+        if (key != kSentinel && e < keff) {
+            const float sv = dist[wave][e];
+            nk[r] = make_key(l2 ? sv : -sv, key_index(key));
+        }
+    }
+    bitonic_sort<false, KR>(nk);
+    if (cert) {
+        const float worst = key_score(ws_element<KR>(nk, k - 1));
+        const float nx = qnorm[q];
+        const float edge = l2 ? (nx * (1.f - kSplitErr) + s_last) * (1.f - 0x1p-20f) : s_last;
+        if (!(worst < edge)) {
+            if (lane == 0) flags[q] = *any = 1u;
+            return;
+        }
+    }
+    emit_reranked<KR>(nk, k, l2, D + q * k, I + q * k);
+}
+
+// ------------------------------------------------------------- host side
+// Device words and buffers of one search.
+struct SieveScratch {
+    uint64_t* pool = nullptr;    // [nq][cap]
+    uint32_t cap = 0;
+    uint32_t* cnt = nullptr;     // [nq]
+    uint32_t* flags = nullptr;   // [nq]
+    uint32_t* bad_db = nullptr;  // [1] (may be null)
+    uint32_t* any = nullptr;     // [1] some query is flagged
+    const float* qnorm = nullptr;
+};
+
+// Sample size, threshold rank and pool capacity.  Of the keff best rows a
+// sample of fraction f holds about mu = f keff, so a rank of mu + 4.5
+// sqrt(mu) + 4.5 leaves a chance of about 1e-8 that the threshold admits fewer
+// than keff rows; it admits about r / f, and more than cap with a chance under 1e-8.
+struct SievePlan {
+    int64_t sample;
+    int32_t rank;
+    int64_t cap;
+};
+inline SievePlan plan_sieve(int64_t nb, int32_t keff) {
+    SievePlan p;
+    p.sample = 8192;
+    while (p.sample < 65536 && p.sample * 128 < nb) p.sample *= 2;
+    while (p.sample > 1024 && p.sample * 8 > nb) p.sample /= 2;
+    const double f = (double)p.sample / (double)nb;
+    const double mu = f * keff;
+    const double r = std::ceil(mu + 4.5 * std::sqrt(mu) + 4.5);
+    p.rank = (int32_t)r;
+    p.cap = (int64_t)std::ceil((r + 6.0 * std::sqrt(r) + 9.0) / f);
+    p.cap = ceil_div(p.cap < nb ? p.cap : nb, 64) * 64;
+    return p;
+}
+
+// Chunks of the rows of one launch: whole rounds of one workgroup per CU.
+inline void plan_sieve_chunks(int64_t nqb, int64_t nb, int BN, int64_t* nchunks,
+                              int64_t* chunk_len) {
+    constexpr int64_t kCUs = 256;
+    const int64_t steps = ceil_div(nb, BN);
+    double best = 1e300;
+    int64_t pick = 1;
+    for (int64_t w = 1; w <= 6; ++w) {
+        int64_t n = kCUs * w / nqb;
+        if (n < 1) n = 1;
+        if (n > steps) n = steps;
+        const int64_t rounds = ceil_div(nqb * n, kCUs);
+        // about 6 steps' worth to load the queries and fill the pipeline
+        const double cost = (double)rounds * ((double)ceil_div(steps, n) + 6.0);
+        if (cost < best) {
+            best = cost;
+            pick = n;
+        }
+    }
+    *chunk_len = ceil_div(steps, pick) * BN;
+    *nchunks = ceil_div(nb, *chunk_len);
+}
+
+}  // namespace mk

@@ -1,0 +1,173 @@
+"""GPU parity of the threshold-first batch search (large enough mk_knn_search
+calls) against the float64 oracle: tile edges, every dimension class, and data
+on which a query's result cannot be proven and the fused search takes over."""
+import numpy as np
+import pytest
+
+import oracle
+from band import check_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1702_08734_amd import api as a
+    a.lib()
+    return a
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def mixture(rng, n, d):
+    mu = 2.0 * np.random.default_rng(d).standard_normal((50, d))
+    return (mu[rng.integers(0, 50, n)] + rng.standard_normal((n, d))).astype(np.float32)
+
+
+def check(api, xq, xb, k, metric, yn=None, rows=None):
+    print(f"sieve nq={len(xq)} nb={len(xb)} d={xb.shape[1]} k={k} {metric}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k, metric, yn)
+    torch.cuda.synchronize()
+    rows = np.unique(np.linspace(0, len(xq) - 1, 24).astype(int)) if rows is None else rows
+    fails = check_rows(D.cpu().numpy()[rows], I.cpu().numpy()[rows], xq, xb, rows, k, metric)
+    assert not fails, fails[:10]
+    return D, I
+
+
+# every padded class and its edges, odd and unaligned dimensions, query counts
+# at and beside a workgroup's 256 (128 for d > 128), database sizes that fill
+# no tile, k at the edges of the 64-entry queues
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("nq,nb,d,k", [
+    (1024, 16384, 17, 1), (64, 262_145, 32, 48), (257, 70_001, 33, 49), (512, 32_769, 64, 112),
+    (300, 60_013, 90, 113), (256, 66_000, 96, 10), (255, 70_007, 100, 240), (1025, 20_000, 128, 7),
+    (129, 131_073, 129, 32), (128, 140_000, 200, 5), (385, 50_001, 256, 100),
+    (600, 30_011, 128, 1008), (513, 40_000, 64, 1009), (300, 65_537, 128, 1024)])
+def test_sieve_shapes(api, nq, nb, d, k, metric):
+    rng = np.random.default_rng(nq + nb + d + k)
+    check(api, mixture(rng, nq, d), mixture(rng, nb, d), k, metric)
+
+
+def test_sieve_unaligned_base(api):
+    # rows that start 4 bytes off a 16-byte boundary
+    rng = np.random.default_rng(1)
+    xb, xq = mixture(rng, 40_000, 64), mixture(rng, 500, 64)
+    flat = torch.empty(40_000 * 64 + 1, device="cuda")
+    flat[1:] = dev(xb).flatten()
+    D, I = api.knn_search(dev(xq), flat[1:].view(40_000, 64), 10)
+    D2, I2 = api.knn_search(dev(xq), dev(xb), 10)
+    assert torch.equal(I, I2) and torch.allclose(D, D2, rtol=1e-6)
+
+
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("k", [10, 1000])
+def test_sieve_sorted_rows(api, k, metric):
+    # rows and queries in the order of their clusters: thresholds from the
+    # sample, tiles full of one query's candidates
+    rng = np.random.default_rng(2)
+    mu = 2.0 * rng.standard_normal((40, 48))
+    xb = (np.repeat(mu, 2000, axis=0) + rng.standard_normal((80_000, 48))).astype(np.float32)
+    check(api, xb[:512] + np.float32(0.01), xb, k, metric)
+
+
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("k", [1, 40, 600])
+def test_sieve_integer_ties(api, k, metric):
+    # small integers, thousands of exact ties at rank k: no proof is possible,
+    # the fused search answers, lower index first
+    rng = np.random.default_rng(3 + k)
+    xb = rng.integers(-1, 2, size=(70_000, 12)).astype(np.float32)
+    xq = rng.integers(-1, 2, size=(256, 12)).astype(np.float32)
+    D, I = api.knn_search(dev(xq), dev(xb), k, metric)
+    torch.cuda.synchronize()
+    rows = np.arange(0, 256, 9)
+    Do, Io = oracle.knn(xq[rows], xb, k, oracle.METRIC_L2 if metric == "l2" else oracle.METRIC_IP)
+    np.testing.assert_array_equal(I.cpu().numpy()[rows], Io)
+    np.testing.assert_array_equal(D.cpu().numpy()[rows].astype(np.float64), Do)
+
+
+def test_sieve_equal_rows(api):
+    xb = np.ones((70_000, 20), np.float32)
+    D, I = api.knn_search(dev(xb[:256]), dev(xb), 30)
+    assert (D == 0).all() and torch.equal(I, torch.arange(30, device="cuda").expand(256, 30))
+
+
+def test_sieve_graded_columns(api):
+    # one column 2^60 times another, queries along the small one: FP16 planes
+    # cannot hold it, the proof fails and the fused search answers
+    rng = np.random.default_rng(4)
+    xb = rng.standard_normal((70_000, 8)).astype(np.float32)
+    xb[:, 0] *= 2.0 ** 30
+    xb[:, 1] *= 2.0 ** -30
+    xq = np.zeros((256, 8), np.float32)
+    xq[:, 1] = rng.standard_normal(256)
+    check(api, xq, xb, 20, "ip")
+
+
+@pytest.mark.parametrize("scale", [1e-18, 1e15])
+def test_sieve_scales(api, scale):
+    # magnitudes outside what the split rows take
+    rng = np.random.default_rng(5)
+    xb = (mixture(rng, 70_000, 24) * np.float32(scale)).astype(np.float32)
+    xq = (mixture(rng, 256, 24) * np.float32(scale)).astype(np.float32)
+    check(api, xq, xb, 10, "ip")
+
+
+def test_sieve_products_underflow(api):
+    # inner products (about 1e-60) that no FP32 value holds: the fused search's
+    # answer, which the allocation-free call gives
+    rng = np.random.default_rng(5)
+    xb, xq = (dev(mixture(rng, n, 24) * np.float32(1e-30)) for n in (70_000, 256))
+    D, I = api.knn_search(xq, xb, 10, "ip")
+    D2, I2 = api.knn_search_noalloc(xq, xb, 10, "ip")
+    assert torch.equal(I, I2) and torch.equal(D, D2)
+
+
+def test_sieve_far_from_origin(api):
+    # norms a million times the distances between neighbours
+    rng = np.random.default_rng(6)
+    xb = (rng.standard_normal((70_000, 16)) + 300.0).astype(np.float32)
+    check(api, xb[:256] + np.float32(0.25), xb, 10, "l2")
+
+
+def test_sieve_supplied_norms(api):
+    # rows whose supplied norm is infinite are left out
+    rng = np.random.default_rng(7)
+    xb, xq = mixture(rng, 70_000, 40), mixture(rng, 300, 40)
+    yn = api.norms(dev(xb))
+    keep = np.arange(0, 70_000, 2)
+    yn[1::2] = float("inf")
+    D, I = api.knn_search(dev(xq), dev(xb), 12, "l2", yn)
+    rows = np.arange(0, 300, 17)
+    fails = check_rows(D.cpu().numpy()[rows], I.cpu().numpy()[rows] // 2, xq,
+                       np.ascontiguousarray(xb[keep]), rows, 12, "l2")
+    assert not fails and (I % 2 == 0).all(), fails[:10]
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_sieve_rows_not_finite(api, value):
+    # a row that is not finite hides no other row's neighbours
+    rng = np.random.default_rng(8)
+    xb, xq = mixture(rng, 70_000, 40), mixture(rng, 256, 40)
+    D0, I0 = api.knn_search(dev(xq), dev(xb), 5)
+    used = set(I0.cpu().numpy().ravel().tolist())
+    spare = next(i for i in range(70_000) if i not in used)
+    xb[spare, 3] = value
+    D, I = api.knn_search(dev(xq), dev(xb), 5)
+    assert torch.equal(I, I0) and torch.equal(D, D0)
+
+
+def test_sieve_batches_alike(api):
+    # a query's result does not depend on the batch it comes in
+    rng = np.random.default_rng(9)
+    xb, xq = dev(mixture(rng, 100_000, 64)), dev(mixture(rng, 700, 64))
+    D, I = api.knn_search(xq, xb, 20)
+    for lo, hi in ((0, 64), (200, 500), (690, 700)):
+        d, i = api.knn_search(xq[lo:hi].contiguous(), xb, 20)
+        assert torch.equal(d, D[lo:hi]) and torch.equal(i, I[lo:hi])
