@@ -73,24 +73,6 @@ mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStre
 }
 
 
-namespace {
-
-// Whether the threshold-first search takes a call.
-bool sieve_pays(int64_t nq, int64_t nb, int32_t k) {
-    return nb >= 16384 && nb >= 8ll * (k + kSlack) && nq >= 64 &&
-           nq * nb >= (1ll << 24);
-}
-
-// Queries per batch: at most 1 GiB of pools and of sample scores each.
-int64_t sieve_batch(int64_t nq, int64_t nb, int32_t k) {
-    const SievePlan p = plan_sieve(nb, k + kSlack);
-    int64_t b = std::min<int64_t>((1ll << 30) / (8 * p.cap), (1ll << 30) / (4 * p.sample));
-    b = std::max<int64_t>(b / 256 * 256, 256);
-    return std::min(nq, b);
-}
-
-}  // namespace
-
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn_in, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
                      hipStream_t s, Arena* arena, bool bounded) {
@@ -106,10 +88,10 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
     const bool l2 = metric == MK_METRIC_L2;
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
-    if (!arena && !bounded && sieve_pays(nq, nb, k)) {
+    if (!arena && !bounded && sieve_pays(nq, nb, k + kSlack)) {
         // batches of queries bound the scratch memory; without room for it
         // the fused search below, which needs less, takes the call
-        const int64_t batch = sieve_batch(nq, nb, k);
+        const int64_t batch = sieve_batch(nq, nb, k + kSlack);
         mk_status st = MK_OK;
         for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch) {
             const int64_t n = std::min(batch, nq - q0);

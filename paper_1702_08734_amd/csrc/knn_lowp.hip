@@ -4,9 +4,11 @@
 // distances are then recomputed from the FP32 rows in the direct form and
 // re-ranked to the final k.  The paper computes distances in FP32 only
 // (Section 2); this is the reduced-precision variant of its exact search.
+#include <algorithm>
 #include <cmath>
 
 #include "fused.hpp"
+#include "sieve.hpp"
 
 namespace mk {
 
@@ -144,14 +146,121 @@ template <class Op, int DP>
 mk_status lowp_dispatch_k(const float* xq, const void* xq_lp, const float* xq_inv, int64_t nq,
                           const float* xb, const void* xb_lp, const float* xb_inv,
                           const float* yn, int64_t nb, int32_t d, int32_t k, int32_t R, bool l2,
-                          float* D, int64_t* I, hipStream_t s) {
+                          float* D, int64_t* I, hipStream_t s,
+                          const uint32_t* qflag = nullptr) {
     switch (queue_regs(R)) {
-        case 1: return lowp_launch<Op, 1, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        case 2: return lowp_launch<Op, 2, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        case 4: return lowp_launch<Op, 4, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        case 8: return lowp_launch<Op, 8, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        default: return lowp_launch<Op, 16, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        case 1: return lowp_launch<Op, 1, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
+        case 2: return lowp_launch<Op, 2, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
+        case 4: return lowp_launch<Op, 4, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
+        case 8: return lowp_launch<Op, 8, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
+        default: return lowp_launch<Op, 16, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
     }
+}
+
+// Batches: thresholds from a sample, then one pass that keeps what beats them
+// (sieve.hpp), with the products, scores and candidates of the fused kernel.
+// Bound by the matrix cores and the vector tests together (BF16: 40% of the
+// cycles each).  2*10^6 x 96, R = 400: BF16, inner product, 10^4 queries 14.7
+// -> 4.4 ms; FP8, L2, 3,000 queries 6.6 -> 1.6 ms.
+template <class Fused, class Op, int DP>
+mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, int64_t nq,
+                     const float* xb, const void* xb_lp, const float* xb_inv, const float* yn,
+                     int64_t nb, int32_t d, int32_t k, int32_t R, bool l2, float* D, int64_t* I,
+                     hipStream_t s) {
+    using S = SieveShape<Op, DP>;
+    const SievePlan plan = plan_sieve(nb, R);
+    const int32_t stride = lowp_stride(d) * Op::BYTES;
+    size_t used = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_s = part((size_t)plan.sample * stride), o_a = part(sizeof(float) * (size_t)plan.sample);
+    const size_t o_b = part(sizeof(float) * (size_t)plan.sample);
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
+    const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
+    const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
+    const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
+    const size_t o_ti = part(sizeof(int64_t) * (size_t)(nq * plan.rank));
+    Scratch mem;
+    MK_TRY(mem.alloc(used, s));
+    unsigned char* base = mem.as<unsigned char>();
+    auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
+    SieveScratch w;
+    w.pool = reinterpret_cast<uint64_t*>(base + o_p);
+    w.cap = (uint32_t)plan.cap;
+    w.cnt = reinterpret_cast<uint32_t*>(base + o_w);
+    w.flags = w.cnt + nq;
+    w.any = w.flags + nq;
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 2, 256), 1024)),
+                       dim3(256), 0, s, w.cnt, 2 * nq + 2);
+    MK_LAUNCHED();
+    const float* side_a = Op::SCALED ? xb_inv : nullptr;
+    const float* side_b = l2 ? yn : nullptr;
+    hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)ceil_div(plan.sample * (stride / 16), 256)),
+                       dim3(256), 0, s, static_cast<const unsigned char*>(xb_lp), stride,
+                       plan.sample, nb, side_a, side_b, base + o_s, floats(o_a), floats(o_b));
+    MK_LAUNCHED();
+    SieveArgs a{};
+    a.xq = xq_lp;
+    a.qscale = xq_inv;
+    a.nq = nq;
+    a.nqb = (int32_t)ceil_div(nq, S::BQ);
+    a.stride = stride;
+    a.cnt = w.cnt;
+    a.pool = w.pool;
+    a.cap = w.cap;
+    a.thr = floats(o_t) + (plan.rank - 1);
+    a.thr_ld = plan.rank;
+    a.scores = floats(o_sc);
+    a.ld = plan.sample / S::PER;
+    auto launch = [&](bool sample, const void* rows, const float* ya, const float* yb,
+                      int64_t n) -> mk_status {
+        a.xb = rows;
+        a.ya = ya;
+        a.yb = yb;
+        a.nb = n;
+        int64_t nchunks;
+        plan_sieve_chunks(a.nqb, n, S::BN, &nchunks, &a.chunk_len);
+        a.nchunks = (int32_t)nchunks;
+        ProfScope prof(sample ? "sieve_sample" : Op::SCALED ? "sieve_tiles_fp8" : "sieve_tiles_bf16", s);
+        auto kern = sample ? (l2 ? sieve_tiles<Op, DP, true, true> : sieve_tiles<Op, DP, false, true>)
+                          : (l2 ? sieve_tiles<Op, DP, true, false> : sieve_tiles<Op, DP, false, false>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(a.nqb * nchunks)), dim3(64 * S::WAVES), 0, s, a);
+        MK_LAUNCHED();
+        return MK_OK;
+    };
+    MK_TRY(launch(true, base + o_s, floats(o_a), floats(o_b), plan.sample));
+    MK_TRY(mk_kselect(a.scores, nq, a.ld, plan.rank, 0, floats(o_t),
+                      reinterpret_cast<int64_t*>(base + o_ti), s));
+    MK_TRY(launch(false, xb_lp, xb_inv, yn, nb));
+    const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
+                     (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
+    MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, R, false, D, I, s));
+    return lowp_dispatch_k<Fused, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2,
+                                      D, I, s, w.flags);
+}
+
+template <class Fused, class Op, int DP>
+mk_status lowp_search(const float* xq, const void* xq_lp, const float* xq_inv, int64_t nq,
+                      const float* xb, const void* xb_lp, const float* xb_inv, const float* yn,
+                      int64_t nb, int32_t d, int32_t k, int32_t R, bool l2, float* D, int64_t* I,
+                      hipStream_t s) {
+    if (sieve_pays(nq, nb, R)) {
+        const int64_t batch = sieve_batch(nq, nb, R);
+        const int64_t qbytes = (int64_t)lowp_stride(d) * Op::BYTES;
+        mk_status st = MK_OK;
+        for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch)
+            st = lowp_sieve<Fused, Op, DP>(
+                xq + q0 * d, static_cast<const unsigned char*>(xq_lp) + q0 * qbytes, xq_inv + q0,
+                std::min(batch, nq - q0), xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D + q0 * k,
+                I + q0 * k, s);
+        if (st != MK_ERR_OOM) return st;
+        (void)hipGetLastError();
+    }
+    return lowp_dispatch_k<Fused, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2,
+                                      D, I, s);
 }
 
 mk_status search_lowp(const float* xq, int64_t nq, const float* xb, const void* xb_lp,
@@ -171,15 +280,15 @@ mk_status search_lowp(const float* xq, int64_t nq, const float* xb, const void* 
         yn = norms.as<float>();
     }
     if (prec == 1) {
-        if (ld <= 32) return lowp_dispatch_k<OpBF16, 32>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        if (ld <= 64) return lowp_dispatch_k<OpBF16, 64>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        if (ld <= 96) return lowp_dispatch_k<OpBF16, 96>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        if (ld <= 128) return lowp_dispatch_k<OpBF16, 128>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-        return lowp_dispatch_k<OpBF16, 256>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        if (ld <= 32) return lowp_search<OpBF16, SieveBF16, 32>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        if (ld <= 64) return lowp_search<OpBF16, SieveBF16, 64>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        if (ld <= 96) return lowp_search<OpBF16, SieveBF16, 96>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        if (ld <= 128) return lowp_search<OpBF16, SieveBF16, 128>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+        return lowp_search<OpBF16, SieveBF16, 256>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
     }
-    if (ld <= 64) return lowp_dispatch_k<OpFP8, 64>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-    if (ld <= 128) return lowp_dispatch_k<OpFP8, 128>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
-    return lowp_dispatch_k<OpFP8, 256>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+    if (ld <= 64) return lowp_search<OpFP8, SieveFP8, 64>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+    if (ld <= 128) return lowp_search<OpFP8, SieveFP8, 128>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
+    return lowp_search<OpFP8, SieveFP8, 256>(xq, qlp.ptr, qinv.as<float>(), nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s);
 }
 
 }  // namespace

@@ -37,6 +37,19 @@ mk_status split_rows(const float* x, int64_t n, int32_t d, bool vec, int kind,
 
 }  // namespace
 
+mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, const float* xb,
+                           int32_t d, bool vec, bool l2, int32_t k, int32_t keff, bool cert,
+                           float* D, int64_t* I, hipStream_t s) {
+    switch (queue_regs(keff)) {
+        case 1: return sieve_finish_launch<1>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+        case 2: return sieve_finish_launch<2>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+        case 4: return sieve_finish_launch<4>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+        case 8: return sieve_finish_launch<8>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+        case 16: return sieve_finish_launch<16>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+        default: return sieve_finish_launch<32>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+    }
+}
+
 // Exact search by thresholds (sieve.hpp); yn may be null (norms of the rows
 // are then taken where the rows are split).
 template <int DP>
@@ -66,7 +79,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_ys = part(sizeof(float) * (size_t)slab), o_yo = part(sizeof(float) * (size_t)slab);
     const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
-    const size_t o_sc = part(sizeof(float) * (size_t)(nq * plan.sample));
+    const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
     const size_t o_ti = part(sizeof(int64_t) * (size_t)(nq * plan.rank));
     const size_t o_n = part(own_norms ? sizeof(float) * (size_t)nb : 0);
@@ -107,8 +120,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     a.thr = top + (plan.rank - 1);
     a.thr_ld = plan.rank;
     a.scores = scores;
-    a.ld = plan.sample;
-    auto launch = [&](bool store, const void* r, const float* ya, const float* yb, int64_t n,
+    a.ld = plan.sample / S::PER;
+    auto launch = [&](bool sample, const void* r, const float* ya, const float* yb, int64_t n,
                       int64_t row0) -> mk_status {
         a.xb = r;
         a.ya = ya;
@@ -118,15 +131,15 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
         int64_t nchunks;
         plan_sieve_chunks(a.nqb, n, S::BN, &nchunks, &a.chunk_len);
         a.nchunks = (int32_t)nchunks;
-        ProfScope prof(store ? "sieve_sample" : "sieve_tiles", s);
-        auto kern = store ? (l2 ? sieve_tiles<SieveSplit, DP, true, true> : sieve_tiles<SieveSplit, DP, false, true>)
+        ProfScope prof(sample ? "sieve_sample" : "sieve_tiles", s);
+        auto kern = sample ? (l2 ? sieve_tiles<SieveSplit, DP, true, true> : sieve_tiles<SieveSplit, DP, false, true>)
                           : (l2 ? sieve_tiles<SieveSplit, DP, true, false> : sieve_tiles<SieveSplit, DP, false, false>);
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.nqb * nchunks)), dim3(64 * S::WAVES), 0, s, a);
         MK_LAUNCHED();
         return MK_OK;
     };
     MK_TRY(launch(true, srows, sscale, soff, plan.sample, 0));
-    MK_TRY(mk_kselect(scores, nq, plan.sample, plan.rank, 0, top,
+    MK_TRY(mk_kselect(scores, nq, a.ld, plan.rank, 0, top,
                       reinterpret_cast<int64_t*>(base + o_ti), s));
     for (int64_t r0 = 0; r0 < nb; r0 += slab) {
         const int64_t n = std::min(slab, nb - r0);
@@ -134,14 +147,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
                               yscale, yoff, norms ? norms + r0 : nullptr, w.bad_db, s));
         MK_TRY(launch(false, rows, yscale, yoff, n, r0));
     }
-    switch (queue_regs(keff)) {
-        case 1: MK_TRY(sieve_finish_launch<1>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-        case 2: MK_TRY(sieve_finish_launch<2>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-        case 4: MK_TRY(sieve_finish_launch<4>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-        case 8: MK_TRY(sieve_finish_launch<8>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-        case 16: MK_TRY(sieve_finish_launch<16>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-        default: MK_TRY(sieve_finish_launch<32>(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s)); break;
-    }
+    MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s));
     // flagged queries (none, as a rule) take the fused search
     return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I, s, nullptr, w.flags);
 }

@@ -1,10 +1,10 @@
 // Threshold-first exact search for batches of queries: the selector of the
 // fused kernel (fused.hpp) leaves the matrix waves.
 //
-//   1. A stratified sample of the database (a few thousand rows) is scored
-//      and the r-th best sample score of each query becomes its threshold,
-//      r chosen so that the threshold lets a few times keff rows of the whole
-//      database through.
+//   1. A stratified sample of the database is scored; of every 4 to 16 of its
+//      rows the least score is kept, and the r-th best of these (at least the
+//      r-th best of the sample, and rarely more) is the query's threshold, r
+//      chosen so that it lets a few times keff rows of the database through.
 //   2. sieve_tiles streams the database once: every wave holds 64 queries
 //      (32 for wide rows) as MFMA operands in registers, compares each score
 //      with its query's threshold in the accumulator registers (one lane = one
@@ -90,22 +90,29 @@ struct SieveFP8 {
 
 // Workgroup of sieve_tiles: 8 waves (2 per SIMD) as 4 query groups x 2 row
 // groups.  A wave reads each 16-row operand block from LDS once per QB * 16
-// queries: with 64 queries the LDS reads take about a third of the matrix
-// time.  Tiles of about 32 KB, three in flight.
+// queries: with 64 queries of split rows the LDS reads take about a third of the
+// matrix time.  Tiles of 16 to 32 KB, three in flight.
 template <class Op, int DP>
 struct SieveShape {
     static constexpr int WAVES = 8, QG = 4, RG = 2;
     static constexpr int GRP = DP / Op::EPG;          // granules per plane
     static constexpr int GR = Op::PLANES * GRP;       // granules per row
     static constexpr int S4 = GRP / 4;                // granule steps
-    static constexpr int QB = 4 * Op::PLANES * S4 * 4 <= 128 ? 4 : 2;
+    // 16-query blocks per wave: what the registers hold beside two blocks'
+    // accumulators
+    static constexpr int QREGS = Op::PLANES * S4 * 4;
+    static constexpr int QB = 8 * QREGS <= 96 ? 8 : 4 * QREGS <= 128 ? 4 : 2;
     static constexpr int BQ = QG * QB * 16;
     static constexpr int RBW = GR >= 64 ? 1 : GR >= 24 ? 2 : 4;  // row blocks per wave and step
     static constexpr int BN = RG * RBW * 16;
+    static constexpr int PER = 4 * RBW;  // rows behind one entry of a sample's least scores
     static constexpr int NBUF = 3;
     static constexpr int LPW = BN * GR / (64 * WAVES);  // tile loads per wave
     static_assert(GRP % 4 == 0 && BN * GR % (64 * WAVES) == 0, "tile loads split evenly");
 };
+
+// rows of one chunk are staged as this many bits
+constexpr int kSieveRowBits = 25;
 
 struct SieveArgs {
     const void* xq;       // queries, rows of `stride` bytes
@@ -124,11 +131,13 @@ struct SieveArgs {
     uint32_t* cnt;        // filter: [nq] keys appended (may exceed cap)
     uint64_t* pool;       // filter: [nq][cap] keys
     uint32_t cap;
-    float* scores;        // store: [nq][ld] scores
+    float* scores;        // sample: [nq][ld] least scores
     int64_t ld;
 };
 
-template <class Op, int DP, bool L2, bool STORE>
+// SAMPLE: the least score of each lane's rows of a step (4 RBW of them), as the
+// entries of [nq][ld], instead of the filter.
+template <class Op, int DP, bool L2, bool SAMPLE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void sieve_tiles(
     SieveArgs args) {
     using S = SieveShape<Op, DP>;
@@ -136,24 +145,34 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int BQ = S::BQ, NBUF = S::NBUF, PL = Op::PLANES;
     constexpr bool HASB = L2 || Op::SHIFTED;
     constexpr int NSIDE = (Op::SCALED ? 1 : 0) + (HASB ? 1 : 0);
-    // granule c of tile row j sits at c ^ (j & SW): the 16 rows of an operand
-    // read fall in different banks
+    // granule c of tile row j sits at c ^ (j & SW), or where rows are 12
+    // granules at c + j / 2 (mod 12): the rows of an operand read fall in
+    // different banks
     constexpr int SW = (GR % 16 == 0) ? 15 : (GR % 8 == 0) ? 7 : 3;
+    constexpr bool ROT = GR == 12;
+    auto place = [](int c, int j) __attribute__((always_inline)) {
+        if constexpr (ROT) {
+            const int t = c + ((j >> 1) & 3);
+            return t >= GR ? t - GR : t;
+        } else {
+            return c ^ (GR == 4 ? (j >> 1) & 3 : j & SW);
+        }
+    };
     constexpr int SIDE_OPS = NSIDE * ((BN + 63) / 64);  // waves with one more load per tile
     // Candidates staged in LDS by each wave for itself (no atomics, no
     // barriers).  A lane whose four scores of a block hold one that passes
-    // stages all four and where they belong (6 bits of the wave's query, 26
+    // stages all four and where they belong (7 bits of the wave's query, 25
     // bits of the row inside the chunk): a dozen instructions; which of them
-    // pass is looked at when they are flushed.  Room for one block's 64 QB
-    // lanes above the level at which the waves flush.
-    constexpr int CLIM = STORE ? 0 : 112;
-    constexpr int CCAP = STORE ? 1 : CLIM + 64 * QB;
-    constexpr int kRowBits = 26;
+    // pass is looked at when they are flushed.  Room for the 256
+    // lanes of four query blocks above the level at which the waves flush.
+    constexpr int CLIM = SAMPLE ? 0 : 112;
+    constexpr int CCAP = SAMPLE ? 1 : CLIM + 64 * (QB < 4 ? QB : 4);
+    constexpr int kRowBits = kSieveRowBits;
     __shared__ __align__(16) uint4 tiles[NBUF][BN * GR];
     __shared__ __align__(16) float side[NBUF][NSIDE > 0 ? NSIDE : 1][BN];
-    __shared__ __align__(16) floatx4 cscore[STORE ? 1 : S::WAVES][CCAP];
-    __shared__ uint32_t cmeta[STORE ? 1 : S::WAVES][CCAP];
-    __shared__ float lthr[STORE ? 1 : BQ];
+    __shared__ __align__(16) floatx4 cscore[SAMPLE ? 1 : S::WAVES][CCAP];
+    __shared__ uint32_t cmeta[SAMPLE ? 1 : S::WAVES][CCAP];
+    __shared__ float lthr[SAMPLE ? 1 : BQ];
     __shared__ int flush_at;
 
     const int64_t logical = xcd_logical_id(blockIdx.x, (int64_t)args.nqb * args.nchunks);
@@ -195,16 +214,23 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const float inv = Op::SCALED && ok ? args.qscale[q] : 1.f;
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
         sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
-        thr[qb] = (!STORE && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
-        if (!STORE && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
+        thr[qb] = (!SAMPLE && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        if (!SAMPLE && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
     }
-    if (!STORE && threadIdx.x == 0) flush_at = -1;
+    if (!SAMPLE && threadIdx.x == 0) flush_at = -1;
 
     // ---- tile loads: row j, granule cc of load t of this lane
     auto granule_of = [&](int t, int& j, int& cc) __attribute__((always_inline)) {
         const int g = (wave + t * S::WAVES) * 64 + lane;
         j = g / GR;
-        const int c = (g % GR) ^ (j & SW);
+        // the granule whose place is g % GR
+        int c = g % GR;
+        if constexpr (ROT) {
+            c -= (j >> 1) & 3;
+            c = c < 0 ? c + GR : c;
+        } else {
+            c = place(c, j);
+        }
         // granules past a short row repeat granule 0 (they meet zero queries)
         cc = (PL > 1 || c * 16 < args.stride) ? c : 0;
     };
@@ -353,27 +379,33 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     sc[qb][i] = fmaf(v, mq[qb], bv[i]);
                 else if constexpr (Op::SHIFTED)
                     sc[qb][i] = fmaf(bv[i], sh[qb], v * mq[qb]);
-                else
+                else if constexpr (Op::SCALED)
                     sc[qb][i] = v * mq[qb];
+                else
+                    sc[qb][i] = v;  // negated where it is used (RAW)
             }
     };
+    constexpr bool RAW = !L2 && !Op::SCALED;  // scores are -sc
+    float least[QB];  // SAMPLE: of this step's rows
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) least[qb] = INFINITY;
     auto emit = [&](const float (&sc)[QB][4], int row) __attribute__((always_inline)) {
-        if constexpr (STORE) {
+        if constexpr (SAMPLE) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                const int64_t q = q0 + (qg * QB + qb) * 16 + li;
-                floatx4 o;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) o[i] = row + i < args.nb ? sc[qb][i] : INFINITY;
-                if (q < args.nq && row < args.ld)
-                    *reinterpret_cast<floatx4*>(&args.scores[q * args.ld + row]) = o;
+                float m = RAW ? -fmaxf(fmaxf(sc[qb][0], sc[qb][1]), fmaxf(sc[qb][2], sc[qb][3]))
+                              : fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3]));
+                least[qb] = fminf(least[qb], m);
             }
         } else {
             // (room for every lane of the block: see the flush below)
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                const float m = fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3]));
-                const bool take = m <= thr[qb];
+                bool take;
+                if constexpr (RAW)
+                    take = fmaxf(fmaxf(sc[qb][0], sc[qb][1]), fmaxf(sc[qb][2], sc[qb][3])) >= -thr[qb];
+                else
+                    take = fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3])) <= thr[qb];
                 const uint64_t bal = __ballot(take);
                 if (bal) {
                     if (take) {
@@ -381,14 +413,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                             staged + __builtin_amdgcn_mbcnt_hi(
                                          (uint32_t)(bal >> 32),
                                          __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-                        cscore[wave][pos] = floatx4{sc[qb][0], sc[qb][1], sc[qb][2], sc[qb][3]};
+                        floatx4 v = {sc[qb][0], sc[qb][1], sc[qb][2], sc[qb][3]};
+                        if constexpr (RAW) v = -v;
+                        cscore[wave][pos] = v;
                         cmeta[wave][pos] =
                             ((uint32_t)(qb * 16 + li) << kRowBits) | (uint32_t)(row - c0);
                     }
                     staged += (uint32_t)__popcll(bal);
                 }
+                if ((qb & 3) == 3 || qb == QB - 1)
+                    if (staged > CLIM) flush();
             }
-            if (staged > CLIM) flush();
         }
     };
 
@@ -397,12 +432,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // issue slots of four free; the first block of the loop tests an empty
     // predecessor (row c1: every row past the end).  Not where the operands of
     // one block leave no registers for it.
-    constexpr bool PIPE = PL * S4 * (QB + 1) * 4 <= 160;
+    constexpr bool PIPE = !SAMPLE && PL * S4 * (QB + 1) * 4 <= 160;
+    constexpr int VPM = Op::MMAS == 3 ? 2 : 4;  // vector operations per product
     floatx4 prev[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) prev[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
     floatx4 pav = floatx4{0.f, 0.f, 0.f, 0.f}, pbv = floatx4{INFINITY, INFINITY, INFINITY, INFINITY};
-    int prow = STORE ? (int)args.ld : c1;
+    int prow = c1;
     int buf = 0;
 #pragma unroll 1
     for (int s = 0; s < nsteps; ++s) {
@@ -418,7 +454,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int p = 0; p < PL; ++p)
 #pragma unroll
                 for (int s4 = 0; s4 < S4; ++s4)
-                    b[p * S4 + s4] = bt[(p * S::GRP + 4 * s4 + lh) ^ (li & SW)];
+                    b[p * S4 + s4] = bt[place(p * S::GRP + 4 * s4 + lh, li)];
             floatx4 av{}, bv{};
             if constexpr (Op::SCALED)
                 av = *reinterpret_cast<const floatx4*>(&side[buf][0][r0 + 4 * lh]);
@@ -442,7 +478,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int t = 0; t < S4 * QB * Op::MMAS; ++t) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one matrix product
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // two vector operations
+                __builtin_amdgcn_sched_group_barrier(0x002, VPM, 0);  // vector operations
             }
             emit(sc, prow);
             prow = t0 + r0 + 4 * lh;
@@ -451,16 +487,25 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) prev[qb] = acc[qb];
         }
+        if constexpr (SAMPLE) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int64_t q = q0 + (qg * QB + qb) * 16 + li;
+                if (q < args.nq)
+                    args.scores[q * args.ld + (int64_t)(t0 / BN) * (4 * S::RG) + rg * 4 + lh] = least[qb];
+                least[qb] = INFINITY;
+            }
+        }
         // the next tile has landed (stores: wait for everything, as above)
-        if (!issue || STORE)
+        if (!issue || SAMPLE)
             __builtin_amdgcn_s_waitcnt(0);
         else
             wait_tile();
         // waves flush together, before the fullest has to: one wave's flush
         // would hold the others up at the next barrier all the same
-        if (!STORE && staged > CLIM * 3 / 4 && lane == 0) flush_at = s;
+        if (!SAMPLE && staged > CLIM * 3 / 4 && lane == 0) flush_at = s;
         step_barrier();
-        if (!STORE && staged && *(volatile int*)&flush_at == s) flush();
+        if (!SAMPLE && staged && *(volatile int*)&flush_at == s) flush();
         buf = buf + 1 < NBUF ? buf + 1 : 0;
     }
     if (PIPE && nsteps > 0) {
@@ -468,7 +513,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         scores_of(prev, pav, pbv, sc);
         emit(sc, prow);
     }
-    if constexpr (!STORE)
+    if constexpr (!SAMPLE)
         if (staged) flush();
 }
 
@@ -702,10 +747,19 @@ struct SieveScratch {
     const float* qnorm = nullptr;
 };
 
+// Selection, re-rank and proof of every query of a search (sieve.hip).
+mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, const float* xb,
+                           int32_t d, bool vec, bool l2, int32_t k, int32_t keff, bool cert,
+                           float* D, int64_t* I, hipStream_t s);
+
 // Sample size, threshold rank and pool capacity.  Of the keff best rows a
 // sample of fraction f holds about mu = f keff, so a rank of mu + 4.5
 // sqrt(mu) + 4.5 leaves a chance of about 1e-8 that the threshold admits fewer
-// than keff rows; it admits about r / f, and more than cap with a chance under 1e-8.
+// than keff rows; it admits about r / f, and more than cap with a chance under
+// 1e-8.  Scoring a sample row costs a query about as much as a row of the
+// database, a row that passes about 40 times that: samples of the order of
+// the square root of the database (8192 rows of 2^18, twice as many for every
+// factor of four) keep both small.
 struct SievePlan {
     int64_t sample;
     int32_t rank;
@@ -714,7 +768,7 @@ struct SievePlan {
 inline SievePlan plan_sieve(int64_t nb, int32_t keff) {
     SievePlan p;
     p.sample = 8192;
-    while (p.sample < 65536 && p.sample * 128 < nb) p.sample *= 2;
+    for (int64_t n = 1ll << 18; n < nb && p.sample < 65536; n *= 4) p.sample *= 2;
     while (p.sample > 1024 && p.sample * 8 > nb) p.sample /= 2;
     const double f = (double)p.sample / (double)nb;
     const double mu = f * keff;
@@ -732,9 +786,10 @@ inline void plan_sieve_chunks(int64_t nqb, int64_t nb, int BN, int64_t* nchunks,
     const int64_t steps = ceil_div(nb, BN);
     double best = 1e300;
     int64_t pick = 1;
+    const int64_t least = ceil_div(nb, 1ll << kSieveRowBits);
     for (int64_t w = 1; w <= 6; ++w) {
         int64_t n = kCUs * w / nqb;
-        if (n < 1) n = 1;
+        if (n < least) n = least;
         if (n > steps) n = steps;
         const int64_t rounds = ceil_div(nqb * n, kCUs);
         // about 6 steps' worth to load the queries and fill the pipeline
@@ -746,6 +801,25 @@ inline void plan_sieve_chunks(int64_t nqb, int64_t nb, int BN, int64_t* nchunks,
     }
     *chunk_len = ceil_div(steps, pick) * BN;
     *nchunks = ceil_div(nb, *chunk_len);
+}
+
+// Whether the threshold-first search takes a call that keeps keff candidates:
+// the least scores of the sample (of up to 16 rows each) have to be several
+// times the rank taken of them.
+inline bool sieve_pays(int64_t nq, int64_t nb, int32_t keff) {
+    if (nb < 16384 || nq < 64 || nq * nb < (1ll << 24)) return false;
+    const SievePlan p = plan_sieve(nb, keff);
+    return p.sample >= 64ll * p.rank;
+}
+
+// Queries per batch: at most 1 GiB of pools and of the sample's scores.
+inline int64_t sieve_batch(int64_t nq, int64_t nb, int32_t keff) {
+    const SievePlan p = plan_sieve(nb, keff);
+    int64_t b = (1ll << 30) / (8 * p.cap);
+    if (b > (1ll << 30) / p.sample) b = (1ll << 30) / p.sample;
+    b = b / 256 * 256;
+    if (b < 256) b = 256;
+    return nq < b ? nq : b;
 }
 
 }  // namespace mk

@@ -171,3 +171,22 @@ def test_sieve_batches_alike(api):
     for lo, hi in ((0, 64), (200, 500), (690, 700)):
         d, i = api.knn_search(xq[lo:hi].contiguous(), xb, 20)
         assert torch.equal(d, D[lo:hi]) and torch.equal(i, I[lo:hi])
+
+
+# low-precision batches against calls of 32 queries, which the fused search
+# answers: the same candidates, so the same results bit for bit
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("nq,nb,d,k,R", [(300, 60_013, 17, 5, 40), (513, 33_000, 64, 20, 80),
+                                         (260, 70_001, 90, 100, 400), (257, 66_000, 128, 10, 64),
+                                         (200, 90_007, 200, 7, 28), (100, 400_000, 96, 256, 1024)])
+def test_sieve_lowp_equals_small_batches(api, nq, nb, d, k, R, prec, metric):
+    print(f"lowp sieve nq={nq} nb={nb} d={d} R={R} {prec} {metric}", flush=True)
+    rng = np.random.default_rng(nq + nb + d)
+    xb, xq = dev(mixture(rng, nb, d)), dev(mixture(rng, nq, d))
+    lp, inv = api.quantize_rows(xb, prec)
+    D, I = api.knn_search_lowp(xq, xb, lp, inv, k, R, prec, metric)
+    for lo in (0, 64, nq - 32):
+        q = xq[lo:lo + 32].contiguous()
+        d2, i2 = api.knn_search_lowp(q, xb, lp, inv, k, R, prec, metric)
+        assert torch.equal(I[lo:lo + 32], i2) and torch.equal(D[lo:lo + 32], d2)
