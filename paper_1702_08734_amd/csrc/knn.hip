@@ -88,6 +88,21 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
     const bool l2 = metric == MK_METRIC_L2;
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
+    if (!arena && !bounded && l2 && k == 1 && nearest_pays(nq, nb)) {
+        const int64_t batch = 1ll << 20;  // at most 1 GiB of split queries
+        mk_status st = MK_OK;
+        for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch) {
+            const int64_t n = std::min(batch, nq - q0);
+            const float* x = xq + q0 * d;
+            if (d <= 32) st = nearest_dispatch<32>(x, n, xb, yn_in, nb, d, vec, D + q0, I + q0, s);
+            else if (d <= 64) st = nearest_dispatch<64>(x, n, xb, yn_in, nb, d, vec, D + q0, I + q0, s);
+            else if (d <= 96) st = nearest_dispatch<96>(x, n, xb, yn_in, nb, d, vec, D + q0, I + q0, s);
+            else if (d <= 128) st = nearest_dispatch<128>(x, n, xb, yn_in, nb, d, vec, D + q0, I + q0, s);
+            else st = nearest_dispatch<256>(x, n, xb, yn_in, nb, d, vec, D + q0, I + q0, s);
+        }
+        if (st != MK_ERR_OOM) return st;
+        (void)hipGetLastError();
+    }
     if (!arena && !bounded && sieve_pays(nq, nb, k + kSlack)) {
         // batches of queries bound the scratch memory; without room for it
         // the fused search below, which needs less, takes the call

@@ -16,6 +16,9 @@ template <int DP>
 mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                          int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
                          hipStream_t s);
+template <int DP>
+mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const float* yn,
+                           int64_t nb, int32_t d, bool vec, float* D, int64_t* I, hipStream_t s);
 #define MK_KNN_CLASS(DP)                                                                         \
     extern template mk_status knn_dispatch_k<DP>(const float*, int64_t, const float*,            \
                                                  const float*, int64_t, int32_t, int32_t, bool,  \
@@ -23,7 +26,10 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
                                                  const uint32_t*);                               \
     extern template mk_status sieve_dispatch<DP>(const float*, int64_t, const float*,            \
                                                  const float*, int64_t, int32_t, int32_t, bool,  \
-                                                 bool, float*, int64_t*, hipStream_t);
+                                                 bool, float*, int64_t*, hipStream_t);           \
+    extern template mk_status nearest_dispatch<DP>(const float*, int64_t, const float*,          \
+                                                   const float*, int64_t, int32_t, bool, float*, \
+                                                   int64_t*, hipStream_t);
 MK_KNN_CLASS(32)
 MK_KNN_CLASS(64)
 MK_KNN_CLASS(96)

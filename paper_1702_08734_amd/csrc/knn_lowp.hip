@@ -178,7 +178,7 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     };
     const size_t o_s = part((size_t)plan.sample * stride), o_a = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_b = part(sizeof(float) * (size_t)plan.sample);
-    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq));
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
@@ -192,9 +192,8 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     w.cap = (uint32_t)plan.cap;
     w.cnt = reinterpret_cast<uint32_t*>(base + o_w);
     w.flags = w.cnt + nq;
-    w.any = w.flags + nq;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 2, 256), 1024)),
-                       dim3(256), 0, s, w.cnt, 2 * nq + 2);
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq, 256), 1024)),
+                       dim3(256), 0, s, w.cnt, 2 * nq);
     MK_LAUNCHED();
     const float* side_a = Op::SCALED ? xb_inv : nullptr;
     const float* side_b = l2 ? yn : nullptr;
@@ -225,8 +224,8 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
         plan_sieve_chunks(a.nqb, n, S::BN, &nchunks, &a.chunk_len);
         a.nchunks = (int32_t)nchunks;
         ProfScope prof(sample ? "sieve_sample" : Op::SCALED ? "sieve_tiles_fp8" : "sieve_tiles_bf16", s);
-        auto kern = sample ? (l2 ? sieve_tiles<Op, DP, true, true> : sieve_tiles<Op, DP, false, true>)
-                          : (l2 ? sieve_tiles<Op, DP, true, false> : sieve_tiles<Op, DP, false, false>);
+        auto kern = sample ? (l2 ? sieve_tiles<Op, DP, true, kSample> : sieve_tiles<Op, DP, false, kSample>)
+                          : (l2 ? sieve_tiles<Op, DP, true, kFilter> : sieve_tiles<Op, DP, false, kFilter>);
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.nqb * nchunks)), dim3(64 * S::WAVES), 0, s, a);
         MK_LAUNCHED();
         return MK_OK;

@@ -17,7 +17,7 @@ mk_status sieve_finish_launch(const SieveScratch& w, const float* xq, int64_t nq
     hipLaunchKernelGGL((sieve_finish<KR>), dim3((unsigned)ceil_div(nq, kMergeWaves)),
                        dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, xq, nq, xb, d,
                        (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
-                       w.flags, w.any, D, I);
+                       w.flags, D, I);
     MK_LAUNCHED();
     return MK_OK;
 }
@@ -77,7 +77,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_ss = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_so = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_ys = part(sizeof(float) * (size_t)slab), o_yo = part(sizeof(float) * (size_t)slab);
-    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 1));
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
@@ -98,10 +98,9 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     w.cnt = words;
     w.flags = w.cnt + nq;
     w.bad_db = w.flags + nq;
-    w.any = w.bad_db + 1;
     w.qnorm = qnorm;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 2, 256), 1024)),
-                       dim3(256), 0, s, words, 2 * nq + 2);
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 1, 256), 1024)),
+                       dim3(256), 0, s, words, 2 * nq + 1);
     MK_LAUNCHED();
     const int kind = l2 ? kSplitDbL2 : kSplitDbIp;
     MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, qrows, qscale, qnorm, nullptr, w.flags, s));
@@ -132,8 +131,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
         plan_sieve_chunks(a.nqb, n, S::BN, &nchunks, &a.chunk_len);
         a.nchunks = (int32_t)nchunks;
         ProfScope prof(sample ? "sieve_sample" : "sieve_tiles", s);
-        auto kern = sample ? (l2 ? sieve_tiles<SieveSplit, DP, true, true> : sieve_tiles<SieveSplit, DP, false, true>)
-                          : (l2 ? sieve_tiles<SieveSplit, DP, true, false> : sieve_tiles<SieveSplit, DP, false, false>);
+        auto kern = sample ? (l2 ? sieve_tiles<SieveSplit, DP, true, kSample> : sieve_tiles<SieveSplit, DP, false, kSample>)
+                          : (l2 ? sieve_tiles<SieveSplit, DP, true, kFilter> : sieve_tiles<SieveSplit, DP, false, kFilter>);
         hipLaunchKernelGGL(kern, dim3((unsigned)(a.nqb * nchunks)), dim3(64 * S::WAVES), 0, s, a);
         MK_LAUNCHED();
         return MK_OK;
@@ -153,10 +152,71 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
 }
 
 
+// Nearest row (k = 1, squared L2) of each query among few rows.
+template <int DP>
+mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const float* yn,
+                           int64_t nb, int32_t d, bool vec, float* D, int64_t* I, hipStream_t s) {
+    using S = SieveShape<SieveSplit, DP>;
+    constexpr int64_t RB = DP * 4;
+    size_t used = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = used;
+        used += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_q = part((size_t)(nq * RB)), o_y = part((size_t)(nb * RB));
+    const size_t o_qs = part(sizeof(float) * (size_t)nq), o_qn = part(sizeof(float) * (size_t)nq);
+    const size_t o_ys = part(sizeof(float) * (size_t)nb), o_yo = part(sizeof(float) * (size_t)nb);
+    const size_t o_n = part(yn ? 0 : sizeof(float) * (size_t)nb);
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(nq + 1));
+    const size_t o_r = part(sizeof(uint4) * (size_t)nq);
+    Scratch mem;
+    MK_TRY(mem.alloc(used, s));
+    unsigned char* base = mem.as<unsigned char>();
+    auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
+    uint32_t* flags = reinterpret_cast<uint32_t*>(base + o_w);
+    uint32_t* bad_db = flags + nq;
+    float* norms = yn ? nullptr : floats(o_n);
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 1, 256), 1024)),
+                       dim3(256), 0, s, flags, nq + 1);
+    MK_LAUNCHED();
+    MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, base + o_q, floats(o_qs),
+                          floats(o_qn), nullptr, flags, s));
+    MK_TRY(split_rows<DP>(xb, nb, d, vec, kSplitDbL2, yn, 0, base + o_y, floats(o_ys),
+                          floats(o_yo), norms, bad_db, s));
+    SieveArgs a{};
+    a.xq = base + o_q;
+    a.qscale = floats(o_qs);
+    a.qnorm = floats(o_qn);
+    a.xb = base + o_y;
+    a.ya = floats(o_ys);
+    a.yb = floats(o_yo);
+    a.nq = nq;
+    a.nb = nb;
+    a.stride = (int32_t)RB;
+    a.chunk_len = ceil_div(nb, S::BN) * S::BN;
+    a.nchunks = 1;
+    a.nqb = (int32_t)ceil_div(nq, S::BQ);
+    a.near = reinterpret_cast<uint4*>(base + o_r);
+    {
+        ProfScope prof("sieve_nearest", s);
+        hipLaunchKernelGGL((sieve_tiles<SieveSplit, DP, true, kNearest>), dim3((unsigned)a.nqb),
+                           dim3(64 * S::WAVES), 0, s, a);
+        MK_LAUNCHED();
+    }
+    hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
+                       xq, nq, xb, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, D, I);
+    MK_LAUNCHED();
+    return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I, s, nullptr,
+                              flags);
+}
+
 #define MK_SIEVE_CLASS(DP)                                                                        \
     template mk_status sieve_dispatch<DP>(const float*, int64_t, const float*, const float*,      \
                                           int64_t, int32_t, int32_t, bool, bool, float*,          \
-                                          int64_t*, hipStream_t);
+                                          int64_t*, hipStream_t);                                 \
+    template mk_status nearest_dispatch<DP>(const float*, int64_t, const float*, const float*,    \
+                                            int64_t, int32_t, bool, float*, int64_t*, hipStream_t);
 MK_SIEVE_CLASS(32)
 MK_SIEVE_CLASS(64)
 MK_SIEVE_CLASS(96)

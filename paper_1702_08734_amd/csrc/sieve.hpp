@@ -133,16 +133,50 @@ struct SieveArgs {
     uint32_t cap;
     float* scores;        // sample: [nq][ld] least scores
     int64_t ld;
+    uint4* near;          // nearest: [nq] (group, second group, its score, bound of the rest)
 };
 
-// SAMPLE: the least score of each lane's rows of a step (4 RBW of them), as the
-// entries of [nq][ld], instead of the filter.
-template <class Op, int DP, bool L2, bool SAMPLE>
+// kFilter: rows that pass their query's threshold, to the pools.
+// kSample: the least score of each lane's rows of a step (4 RBW of them), as the
+//   entries of [nq][ld].
+// kNearest: per query the two best groups of four rows (by their least scores)
+//   and the least score outside them; one chunk.
+enum SieveMode { kFilter = 0, kSample = 1, kNearest = 2 };
+
+// Two best groups of four rows and a lower bound of everything else.
+struct Nearest {
+    float b1, b2, b3;
+    uint32_t g1, g2;
+    __device__ __forceinline__ void init() {
+        b1 = b2 = b3 = INFINITY;
+        g1 = g2 = ~0u;
+    }
+    __device__ __forceinline__ void offer(float s, uint32_t g) {
+        b3 = __builtin_amdgcn_fmed3f(s, b2, b3);
+        const bool lt2 = s < b2, lt1 = s < b1;
+        g2 = lt1 ? g1 : lt2 ? g : g2;
+        b2 = __builtin_amdgcn_fmed3f(s, b1, b2);
+        g1 = lt1 ? g : g1;
+        b1 = fminf(s, b1);
+    }
+    // another lane's findings; its third score has no group, so it only
+    // lowers the bound (which may then lie below b1 or b2)
+    __device__ __forceinline__ void merge(const Nearest& o) {
+        const float third = fminf(b3, o.b3);
+        b3 = INFINITY;
+        offer(o.b1, o.g1);
+        offer(o.b2, o.g2);
+        b3 = fminf(b3, third);
+    }
+};
+
+template <class Op, int DP, bool L2, int MODE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void sieve_tiles(
     SieveArgs args) {
     using S = SieveShape<Op, DP>;
     constexpr int GR = S::GR, S4 = S::S4, QB = S::QB, RBW = S::RBW, BN = S::BN, LPW = S::LPW;
     constexpr int BQ = S::BQ, NBUF = S::NBUF, PL = Op::PLANES;
+    constexpr bool SAMPLE = MODE == kSample, FILTER = MODE == kFilter, NEAREST = MODE == kNearest;
     constexpr bool HASB = L2 || Op::SHIFTED;
     constexpr int NSIDE = (Op::SCALED ? 1 : 0) + (HASB ? 1 : 0);
     // granule c of tile row j sits at c ^ (j & SW), or where rows are 12
@@ -165,14 +199,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // bits of the row inside the chunk): a dozen instructions; which of them
     // pass is looked at when they are flushed.  Room for the 256
     // lanes of four query blocks above the level at which the waves flush.
-    constexpr int CLIM = SAMPLE ? 0 : 112;
-    constexpr int CCAP = SAMPLE ? 1 : CLIM + 64 * (QB < 4 ? QB : 4);
+    constexpr int CLIM = FILTER ? 112 : 0;
+    constexpr int CCAP = FILTER ? CLIM + 64 * (QB < 4 ? QB : 4) : 1;
     constexpr int kRowBits = kSieveRowBits;
     __shared__ __align__(16) uint4 tiles[NBUF][BN * GR];
     __shared__ __align__(16) float side[NBUF][NSIDE > 0 ? NSIDE : 1][BN];
-    __shared__ __align__(16) floatx4 cscore[SAMPLE ? 1 : S::WAVES][CCAP];
-    __shared__ uint32_t cmeta[SAMPLE ? 1 : S::WAVES][CCAP];
-    __shared__ float lthr[SAMPLE ? 1 : BQ];
+    __shared__ __align__(16) floatx4 cscore[FILTER ? S::WAVES : 1][CCAP];
+    __shared__ uint32_t cmeta[FILTER ? S::WAVES : 1][CCAP];
+    __shared__ float lthr[FILTER ? BQ : 1];
     __shared__ int flush_at;
 
     const int64_t logical = xcd_logical_id(blockIdx.x, (int64_t)args.nqb * args.nchunks);
@@ -214,10 +248,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const float inv = Op::SCALED && ok ? args.qscale[q] : 1.f;
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
         sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
-        thr[qb] = (!SAMPLE && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
-        if (!SAMPLE && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
+        thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
     }
-    if (!SAMPLE && threadIdx.x == 0) flush_at = -1;
+    if (FILTER && threadIdx.x == 0) flush_at = -1;
 
     // ---- tile loads: row j, granule cc of load t of this lane
     auto granule_of = [&](int t, int& j, int& cc) __attribute__((always_inline)) {
@@ -389,7 +423,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     float least[QB];  // SAMPLE: of this step's rows
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) least[qb] = INFINITY;
-    auto emit = [&](const float (&sc)[QB][4], int row) __attribute__((always_inline)) {
+    Nearest best[NEAREST ? QB : 1];
+#pragma unroll
+    for (int qb = 0; qb < (NEAREST ? QB : 1); ++qb) best[qb].init();
+    auto emit = [&](float (&sc)[QB][4], int row) __attribute__((always_inline)) {
         if constexpr (SAMPLE) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
@@ -397,6 +434,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                               : fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3]));
                 least[qb] = fminf(least[qb], m);
             }
+        } else if constexpr (NEAREST) {
+            if (row - 4 * lh + 16 > c1) {  // (wave-uniform) rows past the end
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (row + i >= c1) sc[qb][i] = INFINITY;
+            }
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+                best[qb].offer(fminf(fminf(sc[qb][0], sc[qb][1]), fminf(sc[qb][2], sc[qb][3])),
+                               (uint32_t)row >> 2);
         } else {
             // (room for every lane of the block: see the flush below)
 #pragma unroll
@@ -432,7 +481,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // issue slots of four free; the first block of the loop tests an empty
     // predecessor (row c1: every row past the end).  Not where the operands of
     // one block leave no registers for it.
-    constexpr bool PIPE = !SAMPLE && PL * S4 * (QB + 1) * 4 <= 160;
+    constexpr bool PIPE = FILTER && PL * S4 * (QB + 1) * 4 <= 160;
     constexpr int VPM = Op::MMAS == 3 ? 2 : 4;  // vector operations per product
     floatx4 prev[QB];
 #pragma unroll
@@ -503,9 +552,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             wait_tile();
         // waves flush together, before the fullest has to: one wave's flush
         // would hold the others up at the next barrier all the same
-        if (!SAMPLE && staged > CLIM * 3 / 4 && lane == 0) flush_at = s;
+        if (FILTER && staged > CLIM * 3 / 4 && lane == 0) flush_at = s;
         step_barrier();
-        if (!SAMPLE && staged && *(volatile int*)&flush_at == s) flush();
+        if (FILTER && staged && *(volatile int*)&flush_at == s) flush();
         buf = buf + 1 < NBUF ? buf + 1 : 0;
     }
     if (PIPE && nsteps > 0) {
@@ -513,8 +562,39 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         scores_of(prev, pav, pbv, sc);
         emit(sc, prow);
     }
-    if constexpr (!SAMPLE)
+    if constexpr (FILTER)
         if (staged) flush();
+    if constexpr (NEAREST) {
+        // the four lanes of a query, then the two row groups (through the
+        // tile buffers, which the last barrier has freed)
+        Nearest* other = reinterpret_cast<Nearest*>(&tiles[0][0]);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+                Nearest x;
+                x.b1 = __shfl_xor(best[qb].b1, o);
+                x.b2 = __shfl_xor(best[qb].b2, o);
+                x.b3 = __shfl_xor(best[qb].b3, o);
+                x.g1 = (uint32_t)__shfl_xor((int)best[qb].g1, o);
+                x.g2 = (uint32_t)__shfl_xor((int)best[qb].g2, o);
+                best[qb].merge(x);
+            }
+            if (rg == 1 && lh == 0) other[(qg * QB + qb) * 16 + li] = best[qb];
+        }
+        __syncthreads();
+        if (rg == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int ql = (qg * QB + qb) * 16 + li;
+                best[qb].merge(other[ql]);
+                if (lh == 0 && q0 + ql < args.nq)
+                    args.near[q0 + ql] =
+                        make_uint4(best[qb].g1, best[qb].g2, __float_as_uint(best[qb].b2),
+                                   __float_as_uint(best[qb].b3));
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------- FP16 pair rows
@@ -672,7 +752,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish(
     const uint64_t* __restrict__ pool, const uint32_t* __restrict__ cnt, uint32_t cap,
     const float* __restrict__ xq, int64_t nq, const float* __restrict__ xb, int32_t d, int32_t vec,
     int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
-    const uint32_t* __restrict__ bad_db, uint32_t* __restrict__ flags, uint32_t* __restrict__ any,
+    const uint32_t* __restrict__ bad_db, uint32_t* __restrict__ flags,
     float* __restrict__ D, int64_t* __restrict__ I) {
     constexpr int T = SelParams<KR>::T;
     constexpr int KS = 64 * KR;
@@ -685,7 +765,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish(
     if (q >= nq) return;
     const uint32_t n = cnt[q];
     if (n > cap || n < (uint32_t)keff || flags[q] != 0u || (bad_db && *bad_db != 0u)) {
-        if (lane == 0) flags[q] = *any = 1u;
+        if (lane == 0) flags[q] = 1u;
         return;
     }
     WaveSelect<KR, T> ws;
@@ -728,11 +808,127 @@ __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish(
         const float nx = qnorm[q];
         const float edge = l2 ? (nx * (1.f - kSplitErr) + s_last) * (1.f - 0x1p-20f) : s_last;
         if (!(worst < edge)) {
-            if (lane == 0) flags[q] = *any = 1u;
+            if (lane == 0) flags[q] = 1u;
             return;
         }
     }
     emit_reranked<KR>(nk, k, l2, D + q * k, I + q * k);
+}
+
+// Nearest row of each query from kNearest's groups (L2): the rows of the best
+// group, in the direct form, and those of the second only when the first
+// distance does not clear its score; flagged when the rest's bound is not
+// cleared either (the bound: see sieve_finish).  16 lanes per row as in
+// rerank_rows16, so the same distances; a wave does four queries at a time.
+static __global__ __launch_bounds__(256) void nearest_finish(
+    const uint4* __restrict__ near, const float* __restrict__ xq, int64_t nq,
+    const float* __restrict__ xb, int32_t nb, int32_t d, int32_t vec,
+    const float* __restrict__ qnorm, const uint32_t* __restrict__ bad_db,
+    uint32_t* __restrict__ flags, float* __restrict__ D, int64_t* __restrict__ I) {
+    constexpr int NQ = 4;
+    const int lane = lane_id(), sub = lane & 15, rsel = lane >> 4;
+    const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
+    const int64_t q0 = w * NQ;
+    if (q0 >= nq) return;
+    // distances of the four rows of group g[p] to query q0 + p, as keys; the
+    // least of the four in every lane
+    auto group_best = [&](const uint32_t (&g)[NQ], uint64_t (&key)[NQ]) __attribute__((always_inline)) {
+        float acc[NQ];
+        const float *x[NQ], *y[NQ];
+        bool live[NQ];
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+            const int64_t row = (int64_t)g[p] * 4 + rsel;
+            live[p] = q0 + p < nq && row < nb;
+            x[p] = xq + (q0 + p < nq ? q0 + p : q0) * d;
+            y[p] = xb + (live[p] ? row : 0) * d;
+            acc[p] = 0.f;
+        }
+        if (vec) {
+            for (int t = 4 * sub; t < d; t += 64) {
+                float4 a[NQ], b[NQ];
+#pragma unroll
+                for (int p = 0; p < NQ; ++p) {
+                    a[p] = *reinterpret_cast<const float4*>(x[p] + t);
+                    b[p] = *reinterpret_cast<const float4*>(y[p] + t);
+                }
+#pragma unroll
+                for (int p = 0; p < NQ; ++p) {
+                    const float e0 = a[p].x - b[p].x, e1 = a[p].y - b[p].y, e2 = a[p].z - b[p].z,
+                                e3 = a[p].w - b[p].w;
+                    acc[p] = fmaf(e0, e0, acc[p]);
+                    acc[p] = fmaf(e1, e1, acc[p]);
+                    acc[p] = fmaf(e2, e2, acc[p]);
+                    acc[p] = fmaf(e3, e3, acc[p]);
+                }
+            }
+        } else {
+            for (int t = sub; t < d; t += 16) {
+#pragma unroll
+                for (int p = 0; p < NQ; ++p) {
+                    const float e = x[p][t] - y[p][t];
+                    acc[p] = fmaf(e, e, acc[p]);
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+            float v = acc[p];
+#pragma unroll
+            for (int o = 8; o >= 1; o >>= 1) v += __shfl_xor(v, o, 16);
+            uint64_t k = live[p] ? make_key(v, g[p] * 4u + (uint32_t)rsel) : kSentinel;
+            k = umin64(k, xor_lane64<16>(k));
+            key[p] = umin64(k, xor_lane64<32>(k));
+        }
+    };
+    uint4 c[NQ];
+    uint32_t g[NQ];
+    uint64_t key[NQ];
+    bool bad[NQ], more = false;
+    float edge[NQ];
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) {
+        const int64_t q = q0 + p < nq ? q0 + p : q0;
+        c[p] = near[q];
+        g[p] = c[p].x;
+        const float nx = qnorm[q];
+        edge[p] = nx * (1.f - kSplitErr);
+        bad[p] = flags[q] != 0u || *bad_db != 0u;
+    }
+    group_best(g, key);
+    uint32_t g2[NQ];
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) {
+        const float s = fminf(__uint_as_float(c[p].z), __uint_as_float(c[p].w));
+        const bool sure = key_score(key[p]) < (edge[p] + s) * (1.f - 0x1p-20f);
+        g2[p] = sure ? 0x3FFFFFFFu : c[p].y;  // (no such group)
+        if (!sure && c[p].y >= 0x3FFFFFFFu) g2[p] = 0x3FFFFFFFu;
+        more |= !sure;
+    }
+    if (__ballot(more)) {
+        uint64_t k2[NQ];
+        group_best(g2, k2);
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+            const float s1 = fminf(__uint_as_float(c[p].z), __uint_as_float(c[p].w));
+            if (!(key_score(key[p]) < (edge[p] + s1) * (1.f - 0x1p-20f))) {
+                key[p] = umin64(key[p], k2[p]);
+                if (!(key_score(key[p]) < (edge[p] + __uint_as_float(c[p].w)) * (1.f - 0x1p-20f)))
+                    bad[p] = true;
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) {
+        if (lane == p && q0 + p < nq) {
+            if (bad[p]) {
+                flags[q0 + p] = 1u;
+            } else {
+                D[q0 + p] = key_score(key[p]);
+                I[q0 + p] = (int64_t)key_index(key[p]);
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------------- host side
@@ -743,7 +939,6 @@ struct SieveScratch {
     uint32_t* cnt = nullptr;     // [nq]
     uint32_t* flags = nullptr;   // [nq]
     uint32_t* bad_db = nullptr;  // [1] (may be null)
-    uint32_t* any = nullptr;     // [1] some query is flagged
     const float* qnorm = nullptr;
 };
 
@@ -810,6 +1005,13 @@ inline bool sieve_pays(int64_t nq, int64_t nb, int32_t keff) {
     if (nb < 16384 || nq < 64 || nq * nb < (1ll << 24)) return false;
     const SievePlan p = plan_sieve(nb, keff);
     return p.sample >= 64ll * p.rank;
+}
+
+// Whether the nearest-row search (k = 1: k-means assignment, list assignment of
+// added rows) takes a call: enough queries to fill the chip with workgroups that
+// each stream every row, and few enough rows for one stream of them.
+inline bool nearest_pays(int64_t nq, int64_t nb) {
+    return nq >= 8192 && nb >= 256 && nb <= 65536 && nq * nb >= (1ll << 25);
 }
 
 // Queries per batch: at most 1 GiB of pools and of the sample's scores.

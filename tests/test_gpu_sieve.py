@@ -190,3 +190,46 @@ def test_sieve_lowp_equals_small_batches(api, nq, nb, d, k, R, prec, metric):
         q = xq[lo:lo + 32].contiguous()
         d2, i2 = api.knn_search_lowp(q, xb, lp, inv, k, R, prec, metric)
         assert torch.equal(I[lo:lo + 32], i2) and torch.equal(D[lo:lo + 32], d2)
+
+
+# nearest row (k = 1) of many queries among few rows: class edges, row counts
+# around a tile and a group of four, duplicate rows (lower index first), rows
+# equal to queries
+@pytest.mark.parametrize("n,K,d", [(8192, 4096, 128), (9001, 4099, 33), (16_385, 2305, 96),
+                                   (131_072, 256, 8), (131_073, 257, 64), (8200, 5001, 200),
+                                   (8192, 65_536, 17)])
+def test_nearest_rows(api, n, K, d):
+    print(f"nearest n={n} K={K} d={d}", flush=True)
+    rng = np.random.default_rng(n + K + d)
+    x, c = mixture(rng, n, d), mixture(rng, K, d)
+    c[K - 1] = c[3]
+    c[K // 2] = c[7]
+    x[5], x[6], x[n - 1] = c[3], c[7], c[K - 2]
+    a, dist = api.kmeans_assign(dev(x), dev(c))
+    rows = np.unique(np.concatenate([np.linspace(0, n - 1, 60).astype(int), [5, 6, n - 1]]))
+    fails = check_rows(dist.cpu().numpy()[rows, None], a.cpu().numpy()[rows, None], x, c, rows, 1)
+    assert not fails, fails[:10]
+    assert a[5] == 3 and a[6] == 7 and a[n - 1] == K - 2 and dist[5] == 0
+    # the same bits as small batches (fused search)
+    a2, d2 = api.kmeans_assign(dev(x[:200]), dev(c))
+    assert torch.equal(a[:200], a2) and torch.equal(dist[:200], d2)
+
+
+def test_nearest_ties_and_bad_rows(api):
+    # integer rows: thousands of ties for the nearest; then a row that is not
+    # finite and one too large to split
+    rng = np.random.default_rng(12)
+    x = rng.integers(-1, 2, size=(9000, 16)).astype(np.float32)
+    c = rng.integers(-1, 2, size=(4000, 16)).astype(np.float32)
+    for bad in (None, np.nan, 1e30):
+        if bad is not None:
+            c[17, 2] = bad
+        a, dist = api.kmeans_assign(dev(x), dev(c))
+        a2, d2 = api.kmeans_assign(dev(x[:300]), dev(c))
+        assert torch.equal(a[:300], a2) and torch.equal(dist[:300], d2)
+    a, dist = a.cpu().numpy(), dist.cpu().numpy()
+    c64 = np.delete(c.astype(np.float64), 17, axis=0)
+    keep = np.delete(np.arange(4000), 17)
+    for i in range(0, 9000, 301):
+        d64 = ((x[i].astype(np.float64) - c64) ** 2).sum(1)
+        assert dist[i] == d64.min() and a[i] == keep[d64.argmin()]
