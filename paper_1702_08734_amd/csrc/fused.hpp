@@ -201,36 +201,6 @@ struct MultiSelect {
 constexpr int waitcnt_lgkm0() { return 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14); }
 
 // Wave-wide reductions and scans over all 64 lanes.
-__device__ __forceinline__ uint64_t wave_min64(uint64_t v) {
-    v = umin64(v, xor_lane64<1>(v));
-    v = umin64(v, xor_lane64<2>(v));
-    v = umin64(v, xor_lane64<4>(v));
-    v = umin64(v, xor_lane64<8>(v));
-    v = umin64(v, xor_lane64<16>(v));
-    return umin64(v, xor_lane64<32>(v));
-}
-__device__ __forceinline__ uint64_t wave_max64(uint64_t v) {
-    v = umax64(v, xor_lane64<1>(v));
-    v = umax64(v, xor_lane64<2>(v));
-    v = umax64(v, xor_lane64<4>(v));
-    v = umax64(v, xor_lane64<8>(v));
-    v = umax64(v, xor_lane64<16>(v));
-    return umax64(v, xor_lane64<32>(v));
-}
-// Inclusive prefix sum over the wave's 64 lanes with DPP moves (no LDS
-// round trip): shifts by 1, 2, 4 and 8 lanes inside each 16-lane row, then
-// lane 15 of rows 0 and 2 added to rows 1 and 3 and lane 31 to rows 2 and 3.
-// A lane whose source lies outside its row, or whose row is masked off,
-// adds 0.
-__device__ __forceinline__ int wave_inclusive_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
 
 // QW selectors for queues of 256 entries and more, whose candidates live in
 // device memory -- the kernel's own partial-result rows.  A candidate that
@@ -1514,15 +1484,14 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_merge_rerank(
     emit_reranked<KR>(nk, k, l2, D + q * k, I + q * k);
 }
 
-// Exact re-rank of one query's short list (the first R keys of its row of
-// 64 * KR) by a whole workgroup: the waves share the rows' exact distances,
+// Exact re-rank of one query's short list (the first R keys of its row) by a whole workgroup: the waves share the rows' exact distances,
 // 16 rows per wave per step, then wave 0 sorts the (distance, row) keys and
 // writes the first k.  The same rows, distances and final sort as
 // knn_merge_rerank over one chunk of R, so the same results, with a quarter
 // of its gather latency per query.
 template <int KR>
 __global__ __launch_bounds__(64 * kMergeWaves) void knn_rerank_block(
-    const uint64_t* __restrict__ keys, int32_t R, const float* __restrict__ xq,
+    const uint64_t* __restrict__ keys, int64_t stride, int32_t R, const float* __restrict__ xq,
     const float* __restrict__ xb, int32_t d, int32_t vec, int32_t l2, int32_t k,
     float* __restrict__ D, int64_t* __restrict__ I) {
     constexpr int KS = 64 * KR;
@@ -1532,7 +1501,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_rerank_block(
     const int wave = threadIdx.x >> 6;
     const int lane = lane_id();
     const int64_t q = blockIdx.x;
-    const uint64_t* p = keys + q * KS;
+    const uint64_t* p = keys + q * stride;
     for (int e = threadIdx.x; e < KS; e += 64 * kMergeWaves) kl[e] = e < R ? p[e] : kSentinel;
     for (int t = threadIdx.x; t < d; t += 64 * kMergeWaves) xs[t] = xq[q * d + t];
     __syncthreads();

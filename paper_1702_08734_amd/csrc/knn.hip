@@ -22,6 +22,7 @@
 #include <mutex>
 #include <vector>
 
+#include "dense.hpp"
 #include "knn_classes.hpp"
 #include "sieve.hpp"
 
@@ -75,7 +76,7 @@ mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStre
 
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn_in, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
-                     hipStream_t s, Arena* arena, bool bounded) {
+                     hipStream_t s, Arena* arena, const Lend* lend) {
     MK_REQUIRE(nq >= 0 && nb >= 0, MK_ERR_INVALID_ARG, "nq and nb must be >= 0");
     MK_REQUIRE(d >= 1, MK_ERR_INVALID_ARG, "d must be >= 1");
     MK_REQUIRE(k >= 1, MK_ERR_INVALID_ARG, "k must be >= 1");
@@ -88,7 +89,7 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
     const bool l2 = metric == MK_METRIC_L2;
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
-    if (!arena && !bounded && l2 && k == 1 && nearest_pays(nq, nb)) {
+    if (!arena && !lend && l2 && k == 1 && nearest_pays(nq, nb)) {
         const int64_t batch = 1ll << 20;  // at most 1 GiB of split queries
         mk_status st = MK_OK;
         for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch) {
@@ -103,7 +104,7 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
         if (st != MK_ERR_OOM) return st;
         (void)hipGetLastError();
     }
-    if (!arena && !bounded && sieve_pays(nq, nb, k + kSlack)) {
+    if (!arena && !lend && sieve_pays(nq, nb, k + kSlack)) {
         // batches of queries bound the scratch memory; without room for it
         // the fused search below, which needs less, takes the call
         const int64_t batch = sieve_batch(nq, nb, k + kSlack);
@@ -121,6 +122,20 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
         }
         if (st != MK_ERR_OOM) return st;
         (void)hipGetLastError();
+    }
+    if (!arena && dense_pays(nq, nb, k)) {
+        // as many queries at a time as fit the lent memory, or 512 MiB
+        const int64_t per = dense_query_bytes(nb, k);
+        const int64_t batch =
+            std::min<int64_t>(nq, ((lend ? (int64_t)lend->bytes : 512ll << 20) - 1024) / per);
+        if (batch > 0 && (batch >= nq || batch >= 512)) {
+            mk_status st = MK_OK;
+            for (int64_t q0 = 0; q0 < nq && st == MK_OK; q0 += batch)
+                st = dense_search(xq + q0 * d, std::min(batch, nq - q0), xb, yn_in, nb, d, k, l2,
+                                  vec, D + q0 * k, I + q0 * k, lend ? lend->ptr : nullptr, s);
+            if (st != MK_ERR_OOM) return st;
+            (void)hipGetLastError();
+        }
     }
     Scratch norms;
     const float* yn = yn_in;
@@ -202,32 +217,32 @@ __global__ void chunk_keys_kernel(const float* __restrict__ D, const int64_t* __
 template <int KR>
 mk_status rerank_launch(const uint64_t* keys, int64_t nq, int32_t R, const float* xq,
                         const float* xb, int32_t d, bool l2, bool vec, int32_t k, float* D,
-                        int64_t* I, hipStream_t s) {
+                        int64_t* I, hipStream_t s, int64_t stride) {
     ProfScope prof("rerank", s);
     // a workgroup per query: a quarter of the gather latency per query, and
     // a quarter of the LDS per workgroup of the wave-per-query merge kernel,
     // so more waves in flight (10^4 queries, R = 1024, 5*10^7 x 128 rows:
     // 0.99 ms against 1.44 ms; 64 queries: 0.06 against 0.22 ms)
     hipLaunchKernelGGL((knn_rerank_block<KR>), dim3((unsigned)nq), dim3(64 * kMergeWaves), 0, s,
-                       keys, R, xq, xb, d, (int32_t)vec, (int32_t)l2, k, D, I);
+                       keys, stride ? stride : 64 * KR, R, xq, xb, d, (int32_t)vec, (int32_t)l2, k, D, I);
     MK_LAUNCHED();
     return MK_OK;
 }
 
 mk_status rerank_keys(const uint64_t* keys, int64_t nq, int32_t R, const float* xq,
                       const float* xb, int32_t d, bool l2, int32_t k, float* D, int64_t* I,
-                      hipStream_t s) {
+                      hipStream_t s, int64_t stride) {
     MK_REQUIRE(d >= 1 && d <= kMaxDim, MK_ERR_UNSUPPORTED, "re-rank needs 1 <= d <= 512");
     MK_REQUIRE(k >= 1 && k <= R && R <= kMaxK, MK_ERR_INVALID_ARG, "need 1 <= k <= R <= 1024");
     if (nq == 0) return MK_OK;
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
     switch (queue_regs(R)) {
-        case 1: return rerank_launch<1>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s);
-        case 2: return rerank_launch<2>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s);
-        case 4: return rerank_launch<4>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s);
-        case 8: return rerank_launch<8>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s);
-        default: return rerank_launch<16>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s);
+        case 1: return rerank_launch<1>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s, stride);
+        case 2: return rerank_launch<2>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s, stride);
+        case 4: return rerank_launch<4>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s, stride);
+        case 8: return rerank_launch<8>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s, stride);
+        default: return rerank_launch<16>(keys, nq, R, xq, xb, d, l2, vec, k, D, I, s, stride);
     }
 }
 

@@ -47,12 +47,17 @@ mk_status merge_key_lists(const uint64_t* partial, int64_t nrows, int32_t nseg, 
 
 // Exact k-NN (knn.hip); yn may be null (then computed) for L2.
 // With an arena every scratch buffer is carved from it (nothing is
-// allocated); a workspace too small gives MK_ERR_UNSUPPORTED.  bounded: the
-// caller accounts for the fused search's scratch only.
+// allocated); a workspace too small gives MK_ERR_UNSUPPORTED.  lend: device
+// memory (256-byte aligned) the search may use until its work on the stream is
+// done, by a caller that accounts for no scratch beyond the fused search's.
 struct Arena;
+struct Lend {
+    void* ptr;
+    size_t bytes;
+};
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
-                     hipStream_t s, Arena* arena = nullptr, bool bounded = false);
+                     hipStream_t s, Arena* arena = nullptr, const Lend* lend = nullptr);
 mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStream_t s);
 
 // Device address (current device) of the library's count of candidates that
@@ -60,12 +65,13 @@ mk_status launch_norms(const float* x, int64_t n, int32_t d, float* out, hipStre
 // before they can overflow, so the count stays zero; it is a debug check.
 mk_status pool_drop_counter(unsigned long long** out);
 
-// Exact re-rank of candidate lists: keys[row] holds 64 * queue_regs(R) keys
-// whose first R are the row's candidates (score, database row); each
+// Exact re-rank of candidate lists: keys[row] holds `stride` keys (0: 64 *
+// queue_regs(R)) whose first R are the row's candidates (score, database row),
+// in any order; each
 // candidate is re-scored in the FP32 direct form against xb (rows of d
 // floats) and the k best by (distance, row) are written to D, I.
 mk_status rerank_keys(const uint64_t* keys, int64_t nq, int32_t R, const float* xq,
                       const float* xb, int32_t d, bool l2, int32_t k, float* D, int64_t* I,
-                      hipStream_t s);
+                      hipStream_t s, int64_t stride = 0);
 
 }  // namespace mk

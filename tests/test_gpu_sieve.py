@@ -233,3 +233,31 @@ def test_nearest_ties_and_bad_rows(api):
     for i in range(0, 9000, 301):
         d64 = ((x[i].astype(np.float64) - c64) ** 2).sum(1)
         assert dist[i] == d64.min() and a[i] == keep[d64.argmin()]
+
+
+# few queries over any database (16 queries a block, 64 from 17 on), group and
+# tile remainders, short and long result lists
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("nq,nb,d,k", [(1, 2048, 128, 64), (1, 100_003, 128, 10), (16, 70_001, 33, 5),
+                                       (17, 65_537, 64, 100), (63, 40_001, 96, 1000), (40, 33_000, 200, 7),
+                                       (5, 300_000, 256, 1024), (200, 2049, 32, 63), (700, 5003, 100, 150)])
+def test_dense_shapes(api, nq, nb, d, k, metric):
+    rng = np.random.default_rng(nq + nb + d + k)
+    xb, xq = mixture(rng, nb, d), mixture(rng, nq, d)
+    xb[nb // 2], xq[0] = xb[3], xb[3]
+    yn = api.norms(dev(xb)) if nq % 2 else None
+    check(api, xq, xb, k, metric, yn)
+
+
+def test_dense_rows_without_score(api):
+    # rows whose supplied norm is infinite, and rows with a NaN, are left out
+    rng = np.random.default_rng(21)
+    xb, xq = mixture(rng, 20_000, 24), mixture(rng, 9, 24)
+    yn = api.norms(dev(xb))
+    yn[1::2] = float("inf")
+    xb[4::8, 5] = np.nan
+    keep = np.array([i for i in range(0, 20_000, 2) if i % 8 != 4])
+    D, I = api.knn_search(dev(xq), dev(xb), 12, "l2", yn)
+    fails = check_rows(D.cpu().numpy(), np.searchsorted(keep, I.cpu().numpy()), xq,
+                       np.ascontiguousarray(xb[keep]), np.arange(9), 12, "l2")
+    assert not fails and np.isin(I.cpu().numpy(), keep).all(), fails[:10]
