@@ -12,6 +12,7 @@
 #include "common.hpp"
 #include "fileio.hpp"
 #include "kselect.hpp"
+#include "sieve.hpp"
 #include "mlp.hpp"
 #include "profile.hpp"
 #include "wave_select.hpp"
@@ -101,37 +102,141 @@ __global__ void km_finalize(const double* __restrict__ sums,
     }
 }
 
+__global__ void fill_u32_kernel(unsigned int* __restrict__ a, int64_t n);
+
+// Sums by cluster without an atomic per coordinate: the points' indices are put
+// in cluster order (a count and a cursor per cluster), and a workgroup adds up
+// each stretch of at most kSegRows points of one cluster, 16-byte loads, FP64
+// sums in registers, one FP64 atomic per coordinate and stretch.  500,000 x 128
+// points, 4,096 clusters: 156 us in all; 64 million FP64 atomics took 437 us.
+constexpr int kSegRows = 256;
+
+__global__ void km_count(const int64_t* __restrict__ assign, int64_t n, int32_t K,
+                         uint32_t* __restrict__ counts) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += kStride) {
+        const int64_t a = assign[i];
+        if (a >= 0 && a < K) atomicAdd(&counts[a], 1u);  // others are ignored
+    }
+}
+
+// Exclusive prefix of the counts (first[K]: their sum) and of the stretches, the
+// cursors, and the counts as 64-bit words.  One workgroup.
+__global__ __launch_bounds__(1024) void km_prefix(const uint32_t* __restrict__ counts, int32_t K,
+                                                  uint32_t* __restrict__ first,
+                                                  uint32_t* __restrict__ cursor,
+                                                  uint32_t* __restrict__ seg,
+                                                  unsigned long long* __restrict__ counts64) {
+    __shared__ uint32_t w1[16], w2[16], c1, c2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) c1 = c2 = 0u;
+    __syncthreads();
+    for (int32_t base = 0; base < K; base += 1024) {
+        const int32_t j = base + threadIdx.x;
+        const uint32_t n = j < K ? counts[j] : 0u;
+        const uint32_t s = (n + kSegRows - 1) / kSegRows;
+        const uint32_t i1 = (uint32_t)wave_inclusive_sum((int)n);
+        const uint32_t i2 = (uint32_t)wave_inclusive_sum((int)s);
+        if (lane == 63) {
+            w1[wave] = i1;
+            w2[wave] = i2;
+        }
+        __syncthreads();
+        uint32_t b1 = c1, b2 = c2;
+        for (int w = 0; w < wave; ++w) {
+            b1 += w1[w];
+            b2 += w2[w];
+        }
+        if (j < K) {
+            first[j] = cursor[j] = b1 + i1 - n;
+            seg[j] = b2 + i2 - s;
+            counts64[j] = n;
+        }
+        __syncthreads();
+        if (threadIdx.x == 1023) {
+            c1 = b1 + i1;
+            c2 = b2 + i2;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        first[K] = c1;
+        seg[K] = c2;
+    }
+}
+
+// Points in cluster order, and the cluster of each stretch.
+__global__ void km_order(const int64_t* __restrict__ assign, int64_t n, int32_t K,
+                         uint32_t* __restrict__ cursor, uint32_t* __restrict__ order,
+                         const uint32_t* __restrict__ seg, uint32_t* __restrict__ seg_cluster) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += kStride) {
+        const int64_t a = assign[i];
+        if (a >= 0 && a < K) order[atomicAdd(&cursor[a], 1u)] = (uint32_t)i;
+    }
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < K; j += kStride)
+        for (uint32_t t = seg[j]; t < seg[j + 1]; ++t) seg_cluster[t] = (uint32_t)j;
+}
+
+// d % 4 == 0, d <= 4 kBlock, 16-byte aligned rows.
+__global__ __launch_bounds__(kBlock) void km_segment_sums(
+    const float* __restrict__ x, int32_t d, int32_t K, const uint32_t* __restrict__ first,
+    const uint32_t* __restrict__ seg, const uint32_t* __restrict__ seg_cluster,
+    const uint32_t* __restrict__ order, double* __restrict__ sums) {
+    __shared__ double red[kBlock][4];
+    const uint32_t t = blockIdx.x;
+    if (t >= seg[K]) return;  // the grid covers the largest possible count
+    const uint32_t j = seg_cluster[t];
+    const uint32_t lo = first[j] + (t - seg[j]) * kSegRows;
+    const uint32_t hi = lo + kSegRows < first[j + 1] ? lo + kSegRows : first[j + 1];
+    const int gpr = d / 4, rows = kBlock / gpr;  // granules per row, rows at a time
+    const int r = threadIdx.x / gpr, c = threadIdx.x % gpr;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (r < rows) {
+#pragma unroll 4
+        for (uint32_t i = lo + r; i < hi; i += rows) {
+            const float4 v = *reinterpret_cast<const float4*>(x + (int64_t)order[i] * d + 4 * c);
+            s[0] += (double)v.x;
+            s[1] += (double)v.y;
+            s[2] += (double)v.z;
+            s[3] += (double)v.w;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = s[e];
+    __syncthreads();
+    for (int g = threadIdx.x; g < d; g += kBlock) {
+        double v = 0.0;
+        for (int q = 0; q < rows; ++q) v += red[q * gpr + g / 4][g % 4];
+        atomicAdd(&sums[(int64_t)j * d + g], v);
+    }
+}
+
 // Empty clusters, in increasing index order, split the currently largest
 // cluster (ties to the lower index): multiplicative offsets 1 +- 2^-10 with
 // alternating sign per coordinate, products in FP64 rounded to FP32, and the
-// empty cluster takes floor(count / 2).  One workgroup walks the clusters.
+// empty cluster takes floor(count / 2).  One workgroup; each round finds the next
+// empty cluster and the largest one together (a single thread's walk over 4,096
+// counts took 420 us).
 __global__ __launch_bounds__(kBlock) void km_split_empty(float* __restrict__ c,
                                                          int64_t* __restrict__ counts, int32_t K,
                                                          int32_t d) {
     __shared__ int64_t s_cnt[kBlock];
-    __shared__ int32_t s_idx[kBlock];
-    __shared__ int32_t s_j;
+    __shared__ int32_t s_idx[kBlock], s_zero[kBlock];
     const int tid = threadIdx.x;
-    int32_t j = 0;
+    int32_t next = 0;  // first cluster not yet looked at
     for (;;) {
-        if (tid == 0) {
-            while (j < K && counts[j] != 0) ++j;
-            s_j = j;
-        }
-        __syncthreads();
-        j = s_j;
-        if (j >= K) break;
         int64_t best = -1;
-        int32_t bi = 0;
+        int32_t bi = 0, zero = K;
         for (int32_t q = tid; q < K; q += kBlock) {
             const int64_t v = counts[q];
             if (v > best) {
                 best = v;
                 bi = q;
             }
+            if (v == 0 && q >= next && q < zero) zero = q;
         }
         s_cnt[tid] = best;
         s_idx[tid] = bi;
+        s_zero[tid] = zero;
         __syncthreads();
         for (int w = kBlock / 2; w > 0; w >>= 1) {
             if (tid < w) {
@@ -141,10 +246,13 @@ __global__ __launch_bounds__(kBlock) void km_split_empty(float* __restrict__ c,
                     s_cnt[tid] = o;
                     s_idx[tid] = oi;
                 }
+                s_zero[tid] = min(s_zero[tid], s_zero[tid + w]);
             }
             __syncthreads();
         }
-        const int32_t b = s_idx[0];
+        const int32_t b = s_idx[0], j = s_zero[0];
+        __syncthreads();  // read before the next round writes
+        if (j >= K) break;
         const double eps = 1.0 / 1024.0;
         for (int32_t t = tid; t < d; t += kBlock) {
             const double s = (t % 2 == 0) ? 1.0 : -1.0;
@@ -152,14 +260,13 @@ __global__ __launch_bounds__(kBlock) void km_split_empty(float* __restrict__ c,
             c[(int64_t)j * d + t] = (float)(v * (1.0 + s * eps));
             c[(int64_t)b * d + t] = (float)(v * (1.0 - s * eps));
         }
-        __syncthreads();
         if (tid == 0) {
             const int64_t half = counts[b] / 2;
             counts[j] = half;
             counts[b] -= half;
         }
         __syncthreads();
-        ++j;
+        next = j + 1;
     }
 }
 
@@ -175,7 +282,31 @@ mk_status kmeans_update(const float* x, int64_t n, int32_t d, const int64_t* ass
     }
     MK_HIP(hipMemsetAsync(sums.ptr, 0, sizeof(double) * (size_t)K * d, s));
     MK_HIP(hipMemsetAsync(cnt.ptr, 0, sizeof(unsigned long long) * (size_t)K, s));
-    if (n > 0) {
+    // long rows by cluster; short ones (a sub-quantizer's) are cheaper to add
+    // where they belong than to gather (32-byte rows: 27 us for 500,000 x 8)
+    const bool by_cluster = d >= 32 && d % 4 == 0 && d <= 4 * kBlock && n >= 4096 &&
+                            n < (1ll << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    if (by_cluster) {
+        const int64_t segs = ceil_div(n, kSegRows) + K;
+        Scratch words;
+        MK_TRY(words.alloc(sizeof(uint32_t) * (size_t)(4 * (int64_t)K + 2 + n + segs), s));
+        uint32_t* count = words.as<uint32_t>();
+        uint32_t *cursor = count + K, *first = cursor + K, *seg = first + K + 1;
+        uint32_t *order = seg + K + 1, *seg_cluster = order + n;
+        hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_of(K)), dim3(kBlock), 0, s, count, (int64_t)K);
+        MK_LAUNCHED();
+        hipLaunchKernelGGL(km_count, dim3(grid_of(n)), dim3(kBlock), 0, s, assign, n, K, count);
+        MK_LAUNCHED();
+        hipLaunchKernelGGL(km_prefix, dim3(1), dim3(1024), 0, s, count, K, first, cursor, seg,
+                           cnt.as<unsigned long long>());
+        MK_LAUNCHED();
+        hipLaunchKernelGGL(km_order, dim3(grid_of(std::max<int64_t>(n, K))), dim3(kBlock), 0, s,
+                           assign, n, K, cursor, order, seg, seg_cluster);
+        MK_LAUNCHED();
+        hipLaunchKernelGGL(km_segment_sums, dim3((unsigned)segs), dim3(kBlock), 0, s, x, d, K, first,
+                           seg, seg_cluster, order, sums.as<double>());
+        MK_LAUNCHED();
+    } else if (n > 0) {
         hipLaunchKernelGGL(km_accumulate, dim3(grid_of(n * d)), dim3(kBlock), 0,
                            s, x, n, d, assign, K, sums.as<double>(), cnt.as<unsigned long long>());
         MK_LAUNCHED();
@@ -270,10 +401,296 @@ __global__ __launch_bounds__(kBlock) void pq_encode_any(const float* __restrict_
     codes[i * M + m] = (uint8_t)arg;
 }
 
+// Encoding on the matrix cores, for sub-vectors of up to 16 components: FP16
+// pairs (h + l, scaled by a power of two) laid side by side along the 32 products
+// of one v_mfma_f32_16x16x32_f16,
+//   up to 8 components:  code [ h | h | l | 0 ] . row [ h | l | h | h ],
+//   up to 16: code [ h h | h h ] . row [ h h | l l ], then code [ l l | - ] .
+//   row [ h h | 0 ],
+// so a 16 x 16 block of code words and rows costs one or two products.  The code
+// words (A, all 256 of one sub-quantizer) stay in registers while a wave walks
+// its rows 16 at a time (B: lane = row); each lane keeps the two best groups of
+// four code words and a bound of the rest (LowKeys).  The best group is then
+// evaluated as the plain kernel does, the second where the bound asks for it, and
+// every code word where that proves nothing either, so codes are the plain
+// kernel's.  Scores are lowered by kSplitErr (|r|^2 + |c|^2) as in sieve.hpp, and
+// by what the code words' common scale can lose.
+// Bound by vector operations (11 per lane and block of 4 x 16 scores, and as many
+// again per row for the split and the exact distances): 500,000 x 128, M = 16: 427
+// us; the plain kernel's 16 operations per row and code word took 764 us.
+struct PqGroup {
+    float score;
+    int32_t code;
+};
+
+// Lowest three of a stream of 32-bit keys; a key is a distance, its low 6 bits
+// replaced by the number of its group of four code words (rounding it towards
+// zero), compared as an integer.
+struct LowKeys {
+    int32_t k1, k2, k3;
+    __device__ __forceinline__ void init() { k1 = k2 = k3 = 0x7F800000; }
+    __device__ __forceinline__ void offer(int32_t k) {
+        k3 = med3(k, k2, k3);
+        k2 = med3(k, k1, k2);
+        k1 = min(k, k1);
+    }
+    // k1 <= k2 <= k3
+    static __device__ __forceinline__ int32_t med3(int32_t a, int32_t b, int32_t c) {
+        int32_t r;
+        asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+        return r;
+    }
+};
+
+template <int DS, bool VEC>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ? 2 : 3))) void pq_encode_mfma(const float* __restrict__ r, int64_t n,
+                                                         int32_t d, int32_t M, int32_t ds,
+                                                         const float* __restrict__ books,
+                                                         uint8_t* __restrict__ codes) {
+    constexpr int C = DS > 8 ? 2 : 1;   // products per block
+    constexpr int NB = DS > 8 ? 1 : 2;  // blocks of 16 rows in flight
+    __shared__ __align__(16) float cb[256 * DS];  // the code words, zero padded
+    __shared__ __align__(16) float cn[256];       // |c|^2 (1 - kSplitErr)
+    const int m = blockIdx.x % M;
+    const int64_t wg = blockIdx.x / M, nwg = gridDim.x / M;
+    const int lane = lane_id(), li = lane & 15, lh = lane >> 4, wave = threadIdx.x >> 6;
+    for (int e = threadIdx.x; e < 256 * DS; e += kBlock) {
+        const int j = e / DS, t = e % DS;
+        cb[e] = t < ds ? books[((int64_t)m * 256 + j) * ds + t] : 0.f;
+    }
+    __syncthreads();
+    // largest component and norm, each wave for itself (256 words, 4 per lane)
+    float big = 0.f;
+    bool fine = true;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const int j = w * 64 + lane;
+        float ss = 0.f;
+        for (int t = 0; t < DS; ++t) {
+            const float v = cb[j * DS + t];
+            big = fmaxf(big, fabsf(v));
+            ss = fmaf(v, v, ss);
+        }
+        fine = fine && ss < 0x1p100f;  // (false for a NaN)
+        if (wave == 0) cn[j] = ss * (1.f - kSplitErr);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) big = fmaxf(big, __shfl_xor(big, o));
+    fine = __ballot(fine) == ~0ull && (big == 0.f || (big >= 0x1p-50f && big < 0x1p50f));
+    const int ce = fine && big > 0.f ? 13 - ((int)((__float_as_uint(big) >> 23) & 0xFF) - 127) : 0;
+    const float cup = __uint_as_float((uint32_t)(127 + ce) << 23);
+    const float cdn = __uint_as_float((uint32_t)(127 - ce) << 23);
+    __syncthreads();
+    // which half of the components and which plane this lane's slots hold
+    const int t0 = C == 1 ? 0 : 8 * (lh & 1);
+    half8 a[16][C];
+#pragma unroll
+    for (int b = 0; b < 16; ++b) {
+        half8 h, l;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = fine ? cb[(b * 16 + li) * DS + t0 + e] * cup : 0.f;
+            h[e] = (_Float16)v;
+            l[e] = (_Float16)(v - (float)h[e]);
+        }
+        if constexpr (C == 1) {
+            const half8 zero = {};
+            a[b][0] = lh < 2 ? h : lh == 2 ? l : zero;
+        } else {
+            a[b][0] = h;
+            a[b][1] = l;
+        }
+    }
+    // distance of this lane's row to code word j, as the plain kernel takes it
+    auto direct = [&](const float (&v)[DS], int j) __attribute__((always_inline)) {
+        // (the padding's differences are zero)
+        float s = 0.f;
+#pragma unroll
+        for (int t = 0; t < DS; t += 4) {
+            const floatx4 w = *reinterpret_cast<const floatx4*>(&cb[j * DS + t]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float df = v[t + e] - w[e];
+                s = fmaf(df, df, s);
+            }
+        }
+        return s;
+    };
+    // the lower distance of the four lanes of a row, the lower code on ties
+    auto row_best = [&](PqGroup g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int o = 16; o <= 32; o <<= 1) {
+            const float s = __shfl_xor(g.score, o);
+            const int c = __shfl_xor(g.code, o);
+            if (s < g.score || (s == g.score && c < g.code)) {
+                g.score = s;
+                g.code = c;
+            }
+        }
+        return g;
+    };
+    // NB blocks of 16 rows at a time, the next ones' components loaded ahead
+    float next[NB][DS];
+    auto load = [&](int64_t i0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            int64_t i = i0 + x * 16 + li;
+            i = i < n ? i : n - 1;
+            const float* rp = r + i * d + (int64_t)m * ds;
+            if constexpr (VEC) {
+#pragma unroll
+                for (int t = 0; t < DS; t += 4) {
+                    float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (t < ds) w = *reinterpret_cast<const float4*>(rp + t);
+                    next[x][t] = w.x;
+                    next[x][t + 1] = w.y;
+                    next[x][t + 2] = w.z;
+                    next[x][t + 3] = w.w;
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < DS; ++t) next[x][t] = t < ds ? rp[t] : 0.f;
+            }
+        }
+    };
+    const int64_t step = nwg * (kBlock / 64) * 16 * NB;
+    const int64_t start = (wg * (kBlock / 64) + wave) * 16 * NB;
+    if (start < n) load(start);
+#pragma unroll 1
+    for (int64_t i0 = start; i0 < n; i0 += step) {
+        float v[NB][DS], nr[NB], mq[NB];
+        bool ok[NB];
+        half8 q[NB][C];
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+            for (int t = 0; t < DS; ++t) v[x][t] = next[x][t];
+        if (i0 + step < n) load(i0 + step);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            float top = 0.f;
+            nr[x] = 0.f;
+#pragma unroll
+            for (int t = 0; t < DS; ++t) {
+                top = fmaxf(top, fabsf(v[x][t]));
+                nr[x] = fmaf(v[x][t], v[x][t], nr[x]);
+            }
+            // (a row that is not finite, or far outside, takes the plain loop)
+            ok[x] = fine && (nr[x] == 0.f ? top == 0.f
+                                          : (top >= 0x1p-50f && top < 0x1p50f && nr[x] < 0x1p100f));
+            const int re =
+                ok[x] && top > 0.f ? 13 - ((int)((__float_as_uint(top) >> 23) & 0xFF) - 127) : 0;
+            const float rup = __uint_as_float((uint32_t)(127 + re) << 23);
+            mq[x] = -2.f * __uint_as_float((uint32_t)(127 - re) << 23) * cdn;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float y = C == 1 || !(lh & 1) ? v[x][e] : v[x][(8 + e) % DS];
+                // (what is not finite spoils its own row's scores only)
+                const float xs = y * rup;
+                const _Float16 h = (_Float16)xs, l = (_Float16)(xs - (float)h), z = (_Float16)0.f;
+                if constexpr (C == 1) {
+                    q[x][0][e] = lh == 1 ? l : h;
+                } else {
+                    q[x][0][e] = lh < 2 ? h : l;
+                    q[x][1][e] = lh < 2 ? h : z;
+                }
+            }
+        }
+        // a score plus |r|^2 (a little more than it, so that none is negative)
+        // is a lower bound of a distance
+        LowKeys best[NB];
+        float shift[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            best[x].init();
+            shift[x] = nr[x] * (1.f + 4.f * kSplitErr) + 0x1p-120f;
+        }
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            const floatx4 cnv = *reinterpret_cast<const floatx4*>(&cn[b * 16 + 4 * lh]);
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < C; ++c)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b][c], q[x][c], acc, 0, 0, 0);
+                float s[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e] = fmaf(acc[e], mq[x], cnv[e]);
+                const float low = fminf(fminf(fminf(s[0], s[1]), s[2]), s[3]) + shift[x];
+                best[x].offer((int32_t)((__float_as_uint(low) & ~63u) | (uint32_t)(b * 4 + lh)));
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+                const int32_t k1 = __shfl_xor(best[x].k1, o), k2 = __shfl_xor(best[x].k2, o),
+                              k3 = __shfl_xor(best[x].k3, o);
+                best[x].offer(k1);
+                best[x].offer(k2);
+                best[x].offer(k3);
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            // lane lh takes word lh of the best group
+            const float edge =
+                -nr[x] * (6.f * kSplitErr) - sqrtf(nr[x]) * big * 0x1p-24f - 0x1p-119f;
+            const float b2 = __uint_as_float((uint32_t)best[x].k2 & ~63u);
+            const float b3 = __uint_as_float((uint32_t)best[x].k3 & ~63u);
+            const int g1 = best[x].k1 & 63;
+            PqGroup g{direct(v[x], 4 * g1 + lh), 4 * g1 + lh};
+            g = row_best(g);
+            bool sure = ok[x] && g.score < (edge + b2) * (1.f - 0x1p-20f);
+            if (__ballot(!sure)) {
+                const int g2 = best[x].k2 & 63;
+                PqGroup h{direct(v[x], 4 * g2 + lh), 4 * g2 + lh};
+                h = row_best(h);
+                if (!sure) {
+                    if (h.score < g.score || (h.score == g.score && h.code < g.code)) g = h;
+                    sure = ok[x] && g.score < (edge + b3) * (1.f - 0x1p-20f);
+                }
+                if (__ballot(!sure)) {
+                    // every word, 64 per lane, in the plain kernel's order of
+                    // preference (a row of NaN distances: code 0)
+                    PqGroup f{INFINITY, lh == 0 ? 0 : 256};
+#pragma unroll 1
+                    for (int j = 64 * lh; j < 64 * lh + 64; ++j) {
+                        const float s = direct(v[x], j);
+                        if (s < f.score) {
+                            f.score = s;
+                            f.code = j;
+                        }
+                    }
+                    f = row_best(f);
+                    if (!sure) g = f;
+                }
+            }
+            const int64_t i = i0 + x * 16 + li;
+            if (lh == 0 && i < n) codes[i * M + m] = (uint8_t)g.code;
+        }
+    }
+}
+
 mk_status pq_encode(const float* r, int64_t n, int32_t d, int32_t M, const float* books,
                     uint8_t* codes, hipStream_t s) {
     if (n == 0) return MK_OK;
     const int32_t ds = d / M;
+    // enough rows that a workgroup's set-up (256 code words into operands) is
+    // small beside them
+    if (ds >= 2 && ds <= 16 && n >= 2048) {
+        // about two rounds of the workgroups that fit (three per CU)
+        int64_t wgs = ceil_div(n, 64 * 4);
+        if (wgs > 1536 / M) wgs = std::max<int64_t>(1, 1536 / M);
+        const dim3 g((unsigned)(wgs * M));
+        const bool vec = ds % 4 == 0 && reinterpret_cast<uintptr_t>(r) % 16 == 0;
+        auto kern = ds <= 8 ? (vec ? pq_encode_mfma<8, true> : pq_encode_mfma<8, false>)
+                            : (vec ? pq_encode_mfma<16, true> : pq_encode_mfma<16, false>);
+        hipLaunchKernelGGL(kern, g, dim3(kBlock), 0, s, r, n, d, M, ds, books, codes);
+        MK_LAUNCHED();
+        return MK_OK;
+    }
     const dim3 grid((unsigned)ceil_div(n, kBlock), (unsigned)M), block(kBlock);
     switch (ds) {
         case 1: hipLaunchKernelGGL(pq_encode_fixed<1>, grid, block, 0, s, r, n, d, M, books, codes); break;

@@ -143,6 +143,19 @@ struct SieveArgs {
 //   and the least score outside them; one chunk.
 enum SieveMode { kFilter = 0, kSample = 1, kNearest = 2 };
 
+// Select and minimum as single instructions: the compiler turns chains of selects
+// into branches, and quiets the inputs of fminf.
+__device__ __forceinline__ uint32_t pick(uint64_t mask, uint32_t yes, uint32_t no) {
+    uint32_t r;
+    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(no), "v"(yes), "s"(mask));
+    return r;
+}
+__device__ __forceinline__ float min_raw(float a, float b) {
+    float r;
+    asm("v_min_f32_e32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // Two best groups of four rows and a lower bound of everything else.
 struct Nearest {
     float b1, b2, b3;
@@ -153,11 +166,11 @@ struct Nearest {
     }
     __device__ __forceinline__ void offer(float s, uint32_t g) {
         b3 = __builtin_amdgcn_fmed3f(s, b2, b3);
-        const bool lt2 = s < b2, lt1 = s < b1;
-        g2 = lt1 ? g1 : lt2 ? g : g2;
+        const uint64_t lt2 = __ballot(s < b2), lt1 = __ballot(s < b1);
+        g2 = pick(lt1, g1, pick(lt2, g, g2));
         b2 = __builtin_amdgcn_fmed3f(s, b1, b2);
-        g1 = lt1 ? g : g1;
-        b1 = fminf(s, b1);
+        g1 = pick(lt1, g, g1);
+        b1 = min_raw(s, b1);
     }
     // another lane's findings; its third score has no group, so it only
     // lowers the bound (which may then lie below b1 or b2)
