@@ -3,13 +3,16 @@
 // per-segment partial results (the second pass of the two-pass k-selection of
 // Section 5.3).
 //
-// Pass 1: one wave per (row, segment) streams the segment once with 16-byte
-// coalesced loads and feeds WaveSelect.  A row that fits one segment writes
-// its final result directly; otherwise the wave writes its k best keys and
-// pass 2 (one wave per row) selects over the segments' keys.
+// Pass 1 streams each (row, segment) once with 16-byte coalesced loads: k <= 64 one
+// wave and its sorted register queue, more one workgroup and an unsorted LDS pool
+// (pool.hpp).  A row that fits one segment writes its final result directly;
+// otherwise its k best keys go to a scratch list and pass 2 (one workgroup per
+// row) selects over the segments' keys.
+#include <algorithm>
+
 #include "common.hpp"
-#include "fused.hpp"
 #include "kselect.hpp"
+#include "pool.hpp"
 #include "profile.hpp"
 #include "wave_select.hpp"
 
@@ -129,206 +132,185 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void kselect_pass1(
     }
 }
 
-// Pass 1 for queues of 256+ entries: a sorted queue is the wrong structure
-// there (every merge runs a network over the whole queue for a buffer of
-// new keys), so candidates that beat the current threshold are appended to
-// an unsorted pool of 2 * 64 * KR keys in device memory, cut back by a
-// radix selection inside the wave whenever it nears capacity (PoolSelect,
-// the fused search's selector).  At the end the pool is cut to 64 * KR keys,
-// which one WaveSelect pass sorts.
+// Pass 1 for k > 64: a workgroup per (row, segment), one candidate pool in LDS
+// (pool.hpp).  A step is 2,048 values, 8 per thread, 16-byte loads (4-byte ones
+// where rows start off the 16-byte grid), the next step's in flight; values that
+// do not beat the pool's threshold cost one compare, and a step without any costs
+// one barrier.  The pool is cut when a step's values do not fit beside its keys:
+// a row of L values sees about k (1 + ln(L / k)) insertions and a cut for every
+// P - k of them.  (Steps of 4,096 values need a second place for cuts in the loop
+// and the registers for it: fewer waves, 5 to 10% slower.)
 //
-// Most of a segment would be offered early, while the pool's threshold is
-// still loose, so the threshold starts from a guess: the score of rank
-// about 1.5 k SN / L + 32 among the segment's first SN = 8192 scores (a
-// 512-bin histogram over their range), which about 1.5 k of the L scores
-// beat when the prefix is typical.  Values at or below the guess (and the
-// pool's own threshold) are appended in bulk: a lane counts its candidates
-// among its 16 values, a wave prefix sum places them, and each lane writes
-// its own.  The guess is no bound, so it is checked: when fewer than k
-// values were appended, fewer than k scores lie at or below it and the
-// segment is streamed again without it (the plain pool selection).
-// Otherwise the k best scores are all at or below it and the result is
-// exact.
-template <int KR, bool LARGEST>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void kselect_pool(
-    const float* __restrict__ a, int64_t nrows, int64_t len, int32_t k, int32_t nseg,
-    int64_t seg_len, float* __restrict__ vals, int64_t* __restrict__ idx,
-    uint64_t* __restrict__ partial, uint64_t* __restrict__ pools,
-    unsigned long long* drops) {
-    constexpr int U = 4;
-    constexpr int NB = 512;
-    constexpr int SN = 8192;  // prefix that yields the guess
-    constexpr int T = SelParams<KR>::T;
-    // cuts load 8 pool rows per lane at a time: few registers, so that
-    // enough waves stream the input
-    using Pool = PoolSelect<KR, 1, NB, 8>;
-    __shared__ float stage[kWavesPerBlock][4 * U][64];
-    __shared__ uint32_t bins[kWavesPerBlock][NB];
-    const int wave = threadIdx.x / 64;
-    const int lane = lane_id();
-    const int64_t unit = (int64_t)blockIdx.x * kWavesPerBlock + wave;
-    if (unit >= nrows * (int64_t)nseg) return;  // wave-uniform
-    const int64_t row = unit / nseg;
-    const int64_t seg = unit % nseg;
+// 10^4 rows, k = 100 / 300 / 1000, against a wave per row with a sorted queue (or,
+// for 300 and more and long rows, a pool in device memory): 128,000 values 896 /
+// 960 / 1,251 us (972 / 1,209 / 1,414), 16,000 values 201 / 228 / 367 (238 / 414 /
+// 1,049), 1,000 values 56 / 62 / 98 (80 / 158 / 263); 1,000 rows of 128,000, 140 /
+// 144 / 202 us (230 / 395 / 830).
+template <int P, bool LARGEST>  // k <= P - 2048
+__global__ __launch_bounds__(kPoolThreads) void kselect_rows(
+    const float* __restrict__ a, int64_t len, int32_t k, int32_t nseg, int64_t seg_len,
+    float* __restrict__ vals, int64_t* __restrict__ idx, uint64_t* __restrict__ partial) {
+    constexpr int NT = kPoolThreads, U = 2, STEP = NT * 4 * U;
+    __shared__ uint64_t pool[P];
+    __shared__ uint32_t bins[kCutBins];
+    __shared__ PoolState st;
+    __shared__ uint32_t ws[2][kPoolWaves];
+    const int tid = threadIdx.x;
+    const int64_t unit = blockIdx.x;
+    const int64_t row = unit / nseg, seg = unit % nseg;
+    // (rows are shorter than 2^32: 32-bit places inside the segment)
     const int64_t lo = seg * seg_len;
-    const int64_t hi = lo + seg_len < len ? lo + seg_len : len;
-    const float* rp = a + row * len;
-    uint64_t* pool_keys = pools + unit * Pool::CAP;
-    auto score = [&](float v) __attribute__((always_inline)) { return LARGEST ? -v : v; };
-
-    const bool aligned = (reinterpret_cast<uintptr_t>(rp + lo) & 15) == 0;
-    const int64_t vec_end = aligned ? lo + ((hi - lo) / (256 * U)) * (256 * U) : lo;
-
-    // ---- the guess (aligned segments of at least 4 SN values)
-    float guess = INFINITY;
-    if (aligned && hi - lo >= 4 * (int64_t)SN) {
-        uint32_t omin = ~0u, omax = 0u;
-#pragma unroll 4
-        for (int t = 0; t < SN / 256; ++t) {
-            const float4 v = *reinterpret_cast<const float4*>(rp + lo + t * 256 + lane * 4);
-            const uint32_t o0 = float_order(score(v.x) + 0.f), o1 = float_order(score(v.y) + 0.f);
-            const uint32_t o2 = float_order(score(v.z) + 0.f), o3 = float_order(score(v.w) + 0.f);
-            omin = min(min(omin, min(o0, o1)), min(o2, o3));
-            omax = max(max(omax, max(o0, o1)), max(o2, o3));
-        }
+    const uint32_t n = (uint32_t)(lo + seg_len < len ? seg_len : len - lo);
+    const float* rp = a + row * len + lo;
+    const bool aligned = (reinterpret_cast<uintptr_t>(rp) & 15) == 0;
+    // value j of quarter u is 1,024 u + 4 tid + j (aligned) or + 256 j + tid
+    const uint32_t mine = aligned ? 4u * tid : (uint32_t)tid, stride = aligned ? 1u : (uint32_t)NT;
+    uint32_t have = 0;
+    uint64_t limit = kSentinel;
+    float limit_f = INFINITY;
+    int turn = 0;
+    auto cut = [&]() __attribute__((always_inline)) {
+        pool_cut<P>(pool, bins, &st, have, k);
+        have = (uint32_t)k;
+        limit = st.limit;
+        limit_f = key_score(limit - 1);
+    };
+    // a step's values, the next step's while this one is looked at
+    float next[U][4];
+    auto load = [&](uint32_t e) __attribute__((always_inline)) {
+        if (aligned && n - e >= (uint32_t)STEP) {
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            omin = min(omin, (uint32_t)__shfl_xor((int)omin, o));
-            omax = max(omax, (uint32_t)__shfl_xor((int)omax, o));
-        }
-        const uint32_t range = omax - omin;
-        const int bits = range ? 32 - __builtin_clz(range) : 0;
-        const int shift = bits > 9 ? bits - 9 : 0;
-        uint32_t* h = bins[wave];
-#pragma unroll
-        for (int j = 0; j < NB / 64; ++j) h[lane * (NB / 64) + j] = 0u;
-#pragma unroll 4
-        for (int t = 0; t < SN / 256; ++t) {
-            const float4 v = *reinterpret_cast<const float4*>(rp + lo + t * 256 + lane * 4);
-            atomicAdd(&h[(float_order(score(v.x) + 0.f) - omin) >> shift], 1u);
-            atomicAdd(&h[(float_order(score(v.y) + 0.f) - omin) >> shift], 1u);
-            atomicAdd(&h[(float_order(score(v.z) + 0.f) - omin) >> shift], 1u);
-            atomicAdd(&h[(float_order(score(v.w) + 0.f) - omin) >> shift], 1u);
-        }
-        __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
-        // rank of the guess among the SN prefix scores
-        const int64_t want = (3 * (int64_t)k * SN) / (2 * (hi - lo)) + 32;
-        constexpr int NBL = NB / 64;
-        int c[NBL], tot = 0;
-#pragma unroll
-        for (int j = 0; j < NBL; ++j) {
-            c[j] = (int)h[lane * NBL + j];
-            tot += c[j];
-            h[lane * NBL + j] = 0u;  // the pool expects zeroed bins
-        }
-        const int incl = wave_inclusive_sum(tot);
-        const uint64_t m = __ballot(incl - tot < want && want <= incl);
-        if (m) {
-            const int L = __builtin_ctzll(m);
-            int run = incl - tot, jb = NBL - 1;
-            bool f = false;
-#pragma unroll
-            for (int j = 0; j < NBL; ++j) {
-                run += c[j];
-                if (!f && run >= want) {
-                    jb = j;
-                    f = true;
-                }
+            for (int u = 0; u < U; ++u) {
+                const float4 w = *reinterpret_cast<const float4*>(rp + e + u * (NT * 4) + mine);
+                next[u][0] = w.x;
+                next[u][1] = w.y;
+                next[u][2] = w.z;
+                next[u][3] = w.w;
             }
-            const uint32_t b = (uint32_t)(L * NBL + __builtin_amdgcn_readlane(jb, L));
-            const uint64_t edge = (uint64_t)omin + (((uint64_t)b + 1) << shift) - 1;
-            guess = order_float(edge >= omax ? omax : (uint32_t)edge);
-        }
-    }
-
-    Pool pool;
-#pragma unroll 1
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        pool.init(k, pool_keys, 0, 1, nullptr, 1, bins[wave], drops);
-        int appended = 0;
-        auto offer = [&](float v, uint32_t i, bool ok) __attribute__((always_inline)) {
-            pool.refine_pools(false);  // room for the up to 64 keys one offer appends
-            const float sc[1] = {score(v)};
-            const int before = pool.cnt[0];
-            pool.offer(sc, i, ok && score(v) <= guess);
-            appended += pool.cnt[0] - before;
-        };
-        for (int64_t e = lo; e < vec_end; e += 256 * U) {
-            float4 v[U];
+        } else {
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                v[u] = *reinterpret_cast<const float4*>(rp + e + u * 256 + lane * 4);
-            const float th = fminf(guess, pool.kf[0]);
-            int c = 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                c += score(v[u].x) <= th;
-                c += score(v[u].y) <= th;
-                c += score(v[u].z) <= th;
-                c += score(v[u].w) <= th;
-            }
-            const int incl = wave_inclusive_sum(c);
-            const int total = __builtin_amdgcn_readlane(incl, 63);
-            if (total == 0) continue;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                stage[wave][4 * u + 0][lane] = v[u].x;
-                stage[wave][4 * u + 1][lane] = v[u].y;
-                stage[wave][4 * u + 2][lane] = v[u].z;
-                stage[wave][4 * u + 3][lane] = v[u].w;
-            }
-            __builtin_amdgcn_wave_barrier();
-            // room first: a cut keeps at least k keys and tightens the
-            // threshold (the candidates counted above stay a superset)
-            if (pool.cnt[0] + total > Pool::CAP) pool.refine(0, k + 128);
-            if (pool.cnt[0] + total <= Pool::CAP) {
-                // bulk append: this lane's candidates at its prefix position
-                int pos = pool.cnt[0] + incl - c;
-#pragma unroll 1
-                for (int j = 0; c > 0; ++j) {
-                    const float x = stage[wave][j][lane];
-                    if (score(x) <= th) {
-                        const uint32_t i = (uint32_t)(e + (j >> 2) * 256 + lane * 4 + (j & 3));
-                        pool_keys[pos++] = make_key(score(x), i);
-                        --c;
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t i = u * (NT * 4) + mine + j * stride;
+                    next[u][j] = i < n - e ? rp[e + i] : NAN;  // (never taken)
                 }
-                pool.cnt[0] += total;
-                appended += total;
-                // an offer (up to 64 keys) must find room: cut before it
-                pool.need_cut = pool.cnt[0] > Pool::CAP - 64;
-            } else {
+        }
+    };
+    if (n > 0) load(0);
 #pragma unroll 1
-                for (int j = 0; j < 4 * U; ++j)
-                    offer(stage[wave][j][lane], (uint32_t)(e + (j >> 2) * 256 + lane * 4 + (j & 3)),
-                          true);
+    for (uint32_t e0 = 0; e0 < n;) {
+        float v[U][4];
+        const uint32_t place = (uint32_t)lo + e0 + mine;  // column of this thread's first value
+        auto at = [&](int u, int j) __attribute__((always_inline)) -> uint32_t {
+            return place + u * (NT * 4) + j * stride;
+        };
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[u][j] = next[u][j];
+        // (e0 + STEP may pass 2^32 - 1 on the last step)
+        const bool last = n - e0 <= (uint32_t)STEP;
+        if (!last) load(e0 + STEP);
+        e0 = last ? n : e0 + STEP;
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (LARGEST) v[u][j] = -v[u][j];
+                any |= v[u][j] <= limit_f;
             }
-            __builtin_amdgcn_wave_barrier();
+        if (!__syncthreads_or(any)) continue;
+        // which values enter: below the threshold's score, or at it and before it
+        auto takes = [&](int u) __attribute__((always_inline)) {
+            uint32_t mask = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool t = v[u][j] < limit_f ||
+                               (v[u][j] == limit_f && at(u, j) < (uint32_t)limit);
+                mask |= t ? 1u << j : 0u;
+            }
+            return mask;
+        };
+        uint32_t mask[U], add, pos;
+        auto count = [&]() __attribute__((always_inline)) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                mask[u] = takes(u);
+                c += __popc(mask[u]);
+            }
+            add = pool_sum(c, ws[turn ^= 1], pos);
+        };
+        count();
+        if (have + add > (uint32_t)P) {  // (k <= P - STEP: after a cut they fit)
+            cut();
+            count();
         }
-#pragma unroll 1
-        for (int64_t e = vec_end; e < hi; e += 64) {
-            const int64_t i = e + lane;
-            offer(i < hi ? rp[i] : 0.f, (uint32_t)i, i < hi);
+        pos += have;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (mask[u] & (1u << j)) pool[pos++] = make_key(v[u][j], at(u, j));
+        have += add;
+    }
+    if (nseg > 1) {
+        if (have > (uint32_t)k) cut();
+        __syncthreads();
+        for (int e = tid; e < k; e += NT)
+            partial[unit * k + e] = e < (int)have ? pool[e] : kSentinel;
+        return;
+    }
+    float* vr = vals + row * k;
+    int64_t* ir = idx + row * k;
+    pool_emit<P>(pool, bins, &st, have, (uint32_t)k, [&](uint32_t r, uint64_t key) {
+        const float s = key_score(key);
+        vr[r] = LARGEST ? -s : s;
+        ir[r] = (int64_t)key_index(key);
+    });
+    for (int e = tid; e < k; e += NT)
+        if (e >= (int)have) {
+            vr[e] = LARGEST ? -INFINITY : INFINITY;
+            ir[e] = -1;
         }
-        // every score at or below the guess was appended (or beaten by k
-        // appended ones): with k of them the result is exact
-        if (appended >= k || guess == INFINITY) break;
-        guess = INFINITY;
+}
+
+// Pass 2 for k > 64: the k best of a row's lists of k keys by one workgroup.
+template <int P, bool LARGEST>
+__global__ __launch_bounds__(kPoolThreads) void kselect_lists(
+    const uint64_t* __restrict__ partial, int32_t nseg, int32_t k, float* __restrict__ vals,
+    int64_t* __restrict__ idx, uint64_t* __restrict__ keys_out, int32_t out_len,
+    const int64_t* __restrict__ seg_offs) {
+    __shared__ uint64_t pool[P];
+    __shared__ uint32_t bins[kCutBins];
+    __shared__ PoolState st;
+    const int64_t row = blockIdx.x;
+    const int64_t s0 = seg_offs ? seg_offs[row] : row * (int64_t)nseg;
+    const int64_t s1 = seg_offs ? seg_offs[row + 1] : s0 + nseg;
+    uint64_t limit;
+    const uint32_t have = pool_stream<P>(partial + s0 * k, (s1 - s0) * k, pool, bins, &st, k, limit);
+    if (keys_out) {
+        uint64_t* o = keys_out + row * out_len;
+        pool_emit<P>(pool, bins, &st, have, (uint32_t)k, [&](uint32_t r, uint64_t key) { o[r] = key; });
+        for (int e = threadIdx.x; e < out_len; e += kPoolThreads)
+            if (e >= (int)have) o[e] = kSentinel;
+        return;
     }
-    pool.finish();  // at most 64 KR keys left, sentinel padded to that length
-    // the pool's appends by every lane are visible to this wave's loads
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    WaveSelect<KR, T> ws;
-    ws.init(k);
-#pragma unroll 1
-    for (int r = 0; r < KR; ++r)
-        if (ws.push(pool_keys[r * 64 + lane])) ws.merge();
-    ws.finish();
-    if (nseg == 1) {
-        emit_values<KR, LARGEST>(ws.w, k, vals + row * k, idx + row * k);
-    } else {
-        emit_keys<KR>(ws.w, k, partial + unit * k);
-    }
+    float* vr = vals + row * k;
+    int64_t* ir = idx + row * k;
+    pool_emit<P>(pool, bins, &st, have, (uint32_t)k, [&](uint32_t r, uint64_t key) {
+        const float s = key_score(key);
+        const bool pad = key == kSentinel;
+        vr[r] = pad ? (LARGEST ? -INFINITY : INFINITY) : LARGEST ? -s : s;
+        ir[r] = pad ? -1 : (int64_t)key_index(key);
+    });
+    for (int e = threadIdx.x; e < k; e += kPoolThreads)
+        if (e >= (int)have) {
+            vr[e] = LARGEST ? -INFINITY : INFINITY;
+            ir[e] = -1;
+        }
 }
 
 // Pass 2: per row, select the k best of nseg * k partial keys (or, with
@@ -361,10 +343,10 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void kselect_merge(
         emit_values<KR, LARGEST>(ws.w, k, vals + row * k, idx + row * k);
 }
 
-template <int KR, int T, bool LARGEST>
-mk_status kselect_launch(const float* a, int64_t nrows, int64_t len, int32_t k, float* vals,
-                         int64_t* idx, hipStream_t stream) {
-    constexpr int KS = 64 * KR;
+template <int KR, bool LARGEST>
+mk_status kselect_waves(const float* a, int64_t nrows, int64_t len, int32_t k, float* vals,
+                        int64_t* idx, hipStream_t stream) {
+    constexpr int KS = 64 * KR, T = SelParams<KR>::T;
     // Enough waves to fill the chip, but segments long enough that the
     // partial keys stay a small fraction of the input.
     int64_t want = ceil_div(8192, nrows > 0 ? nrows : 1);
@@ -376,33 +358,15 @@ mk_status kselect_launch(const float* a, int64_t nrows, int64_t len, int32_t k, 
     nseg = len > 0 ? ceil_div(len, seg_len) : 1;
     if (seg_len == 0) seg_len = 256;
 
-    Scratch part, pools;
-    if (nseg > 1) {
-        mk_status st = part.alloc(sizeof(uint64_t) * (size_t)nrows * (size_t)nseg * (size_t)k, stream);
-        if (st != MK_OK) return st;
-    }
+    Scratch part;
+    if (nseg > 1) MK_TRY(part.alloc(sizeof(uint64_t) * (size_t)nrows * (size_t)nseg * (size_t)k, stream));
     const int64_t units = nrows * nseg;
-    // queues of 256+ entries over segments of at least 16 queue lengths:
-    // there most values are rejected and the pool's cuts are rare; short
-    // segments (every value a candidate) sort faster in the register queue
-    const bool pool = KR >= 4 && seg_len >= 16 * (int64_t)KS;
     {
         ProfScope prof("kselect_pass1", stream);
-        if (pool) {
-            MK_TRY(pools.alloc(sizeof(uint64_t) * (size_t)units * 2 * KS, stream));
-            unsigned long long* drops = nullptr;
-            MK_TRY(pool_drop_counter(&drops));
-            hipLaunchKernelGGL((kselect_pool<KR, LARGEST>),
-                               dim3((unsigned)ceil_div(units, kWavesPerBlock)),
-                               dim3(64 * kWavesPerBlock), 0, stream, a, nrows, len, k,
-                               (int32_t)nseg, seg_len, vals, idx, part.as<uint64_t>(),
-                               pools.as<uint64_t>(), drops);
-        } else {
-            hipLaunchKernelGGL((kselect_pass1<KR, T, LARGEST>),
-                               dim3((unsigned)ceil_div(units, kWavesPerBlock)),
-                               dim3(64 * kWavesPerBlock), 0, stream, a, nrows, len, k,
-                               (int32_t)nseg, seg_len, vals, idx, part.as<uint64_t>());
-        }
+        hipLaunchKernelGGL((kselect_pass1<KR, T, LARGEST>),
+                           dim3((unsigned)ceil_div(units, kWavesPerBlock)),
+                           dim3(64 * kWavesPerBlock), 0, stream, a, nrows, len, k,
+                           (int32_t)nseg, seg_len, vals, idx, part.as<uint64_t>());
         MK_LAUNCHED();
     }
     if (nseg > 1) {
@@ -415,16 +379,49 @@ mk_status kselect_launch(const float* a, int64_t nrows, int64_t len, int32_t k, 
     return MK_OK;
 }
 
+template <int P, bool LARGEST>
+mk_status kselect_pools(const float* a, int64_t nrows, int64_t len, int32_t k, float* vals,
+                        int64_t* idx, hipStream_t stream) {
+    // segments that give about 1,024 workgroups, of at least 16,384 values and
+    // 16 result lists
+    int64_t nseg = std::min(ceil_div(1024, nrows), len / std::max<int64_t>(16384, 16 * (int64_t)k));
+    if (nseg < 1) nseg = 1;
+    int64_t seg_len = ceil_div(ceil_div(len, nseg), 256) * 256;
+    if (seg_len == 0) seg_len = 256;
+    nseg = len > 0 ? ceil_div(len, seg_len) : 1;
+    Scratch part;
+    if (nseg > 1) MK_TRY(part.alloc(sizeof(uint64_t) * (size_t)nrows * (size_t)nseg * (size_t)k, stream));
+    {
+        ProfScope prof("kselect_pass1", stream);
+        hipLaunchKernelGGL((kselect_rows<P, LARGEST>), dim3((unsigned)(nrows * nseg)),
+                           dim3(kPoolThreads), 0, stream, a, len, k, (int32_t)nseg, seg_len, vals,
+                           idx, part.as<uint64_t>());
+        MK_LAUNCHED();
+    }
+    if (nseg > 1) {
+        constexpr int PL = P > 2560 ? 4096 : 2048;
+        hipLaunchKernelGGL((kselect_lists<PL, LARGEST>), dim3((unsigned)nrows), dim3(kPoolThreads), 0,
+                           stream, part.as<uint64_t>(), (int32_t)nseg, k, vals, idx,
+                           (uint64_t*)nullptr, 0, (const int64_t*)nullptr);
+        MK_LAUNCHED();
+    }
+    return MK_OK;
+}
+
 template <bool LARGEST>
 mk_status kselect_dispatch(const float* a, int64_t nrows, int64_t len, int32_t k, float* vals,
                            int64_t* idx, hipStream_t s) {
-    switch (queue_regs(k)) {
-        case 1: return kselect_launch<1, SelParams<1>::T, LARGEST>(a, nrows, len, k, vals, idx, s);
-        case 2: return kselect_launch<2, SelParams<2>::T, LARGEST>(a, nrows, len, k, vals, idx, s);
-        case 4: return kselect_launch<4, SelParams<4>::T, LARGEST>(a, nrows, len, k, vals, idx, s);
-        case 8: return kselect_launch<8, SelParams<8>::T, LARGEST>(a, nrows, len, k, vals, idx, s);
-        default: return kselect_launch<16, SelParams<16>::T, LARGEST>(a, nrows, len, k, vals, idx, s);
+    // a register queue of 64 costs a wave little; from there on a pool per
+    // workgroup (one dimension of a grid: fewer than 2^24 workgroups of 256)
+    if (k <= 64) return kselect_waves<1, LARGEST>(a, nrows, len, k, vals, idx, s);
+    if (nrows >= (1ll << 23)) {
+        const int64_t half = nrows / 2;
+        MK_TRY((kselect_dispatch<LARGEST>(a, half, len, k, vals, idx, s)));
+        return kselect_dispatch<LARGEST>(a + half * len, nrows - half, len, k, vals + half * k,
+                                         idx + half * k, s);
     }
+    return k <= 512 ? kselect_pools<2560, LARGEST>(a, nrows, len, k, vals, idx, s)
+                    : kselect_pools<3072, LARGEST>(a, nrows, len, k, vals, idx, s);
 }
 
 }  // namespace
@@ -433,37 +430,28 @@ mk_status merge_key_lists(const uint64_t* partial, int64_t nrows, int32_t nseg, 
                           float* vals, int64_t* idx, hipStream_t s, uint64_t* keys_out,
                           const int64_t* seg_offs, bool largest) {
     if (nrows == 0) return MK_OK;
-    const dim3 grid((unsigned)ceil_div(nrows, kWavesPerBlock)), block(64 * kWavesPerBlock);
-    if (largest) {
-        MK_REQUIRE(!keys_out, MK_ERR_INVALID_ARG, "largest-first merges emit values");
-        switch (queue_regs(k)) {
-            case 1: hipLaunchKernelGGL((kselect_merge<1, SelParams<1>::T, true>), grid, block, 0,
-                                       s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-            case 2: hipLaunchKernelGGL((kselect_merge<2, SelParams<2>::T, true>), grid, block, 0,
-                                       s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-            case 4: hipLaunchKernelGGL((kselect_merge<4, SelParams<4>::T, true>), grid, block, 0,
-                                       s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-            case 8: hipLaunchKernelGGL((kselect_merge<8, SelParams<8>::T, true>), grid, block, 0,
-                                       s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-            default: hipLaunchKernelGGL((kselect_merge<16, SelParams<16>::T, true>), grid, block, 0,
-                                        s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-        }
+    MK_REQUIRE(!(largest && keys_out), MK_ERR_INVALID_ARG, "largest-first merges emit values");
+    const int32_t out_len = 64 * queue_regs(k);
+    if (k <= 64) {
+        auto kern = largest ? kselect_merge<1, SelParams<1>::T, true> : kselect_merge<1, SelParams<1>::T, false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(nrows, kWavesPerBlock)),
+                           dim3(64 * kWavesPerBlock), 0, s, partial, nrows, nseg, k, vals, idx,
+                           keys_out, seg_offs);
         MK_LAUNCHED();
         return MK_OK;
     }
-    switch (queue_regs(k)) {
-        case 1: hipLaunchKernelGGL((kselect_merge<1, SelParams<1>::T, false>), grid, block, 0, s,
-                                   partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-        case 2: hipLaunchKernelGGL((kselect_merge<2, SelParams<2>::T, false>), grid, block, 0, s,
-                                   partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-        case 4: hipLaunchKernelGGL((kselect_merge<4, SelParams<4>::T, false>), grid, block, 0, s,
-                                   partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-        case 8: hipLaunchKernelGGL((kselect_merge<8, SelParams<8>::T, false>), grid, block, 0, s,
-                                   partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
-        default: hipLaunchKernelGGL((kselect_merge<16, SelParams<16>::T, false>), grid, block, 0,
-                                    s, partial, nrows, nseg, k, vals, idx, keys_out, seg_offs); break;
+    auto kern = k <= 512 ? (largest ? kselect_lists<2048, true> : kselect_lists<2048, false>)
+                         : (largest ? kselect_lists<4096, true> : kselect_lists<4096, false>);
+    constexpr int64_t kRows = 1ll << 23;  // (one dimension of a grid)
+    for (int64_t r0 = 0; r0 < nrows; r0 += kRows) {
+        const int64_t n = std::min(kRows, nrows - r0);
+        hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kPoolThreads), 0, s,
+                           seg_offs ? partial : partial + r0 * nseg * k, nseg, k,
+                           vals ? vals + r0 * k : nullptr, idx ? idx + r0 * k : nullptr,
+                           keys_out ? keys_out + r0 * out_len : nullptr, out_len,
+                           seg_offs ? seg_offs + r0 : nullptr);
+        MK_LAUNCHED();
     }
-    MK_LAUNCHED();
     return MK_OK;
 }
 
