@@ -14,6 +14,7 @@
 #include "kselect.hpp"
 #include "sieve.hpp"
 #include "mlp.hpp"
+#include "pool.hpp"
 #include "profile.hpp"
 #include "wave_select.hpp"
 
@@ -908,7 +909,7 @@ __global__ void move_old_kernel(const int64_t* __restrict__ old_off,
 }
 
 // ---------------------------------------------------------------- list scan
-constexpr int kScanWaves = 4;
+constexpr int kScanWaves = kPoolThreads / 64;
 
 // One workgroup per (query, probe rank).  The list's lookup tables
 // LUT[m][j] = term1[L][m][j] - 2 term3[q][m][j] are staged in LDS; each lane
@@ -1031,17 +1032,19 @@ __global__ void entry_term1_kernel(const int64_t* __restrict__ offsets, int32_t 
 // table -2 term3[q] (Eq. 11) is staged in LDS once for the group; each
 // scanned entry's ADC distance is term 2 (the coarse distance of its list)
 // + its stored term 1 + the M table lookups of its code bytes (Eq. 10-11).
-// The four waves share one pool of candidates in LDS, keyed (distance, id), and
-// its threshold, the kk-th best key at the last cut; the id is read only for
-// entries at or below the threshold's distance (Section 5.3 resolves ids only
-// for selected entries).  Each step takes 1,024 entries of a list, four loads
-// in flight per lane; when the next step's candidates might not fit, the whole
-// workgroup cuts the pool back to its kk best (pool_cut).  A queue per wave, as
-// sorted registers, took four times the insertions (every wave fills its own),
-// a sorting network over the queue for every 64 to 512 of them, and a serial
-// merge of the four queues: 10^4 queries, 8 lists of about 1,000 entries, 256
-// kept, 919 us against 608 us; 64 queries, 32 lists, 100 kept, 80 against 44 us.
-// What is left is the table lookups (LDS gathers).
+// The four waves share one pool of candidates in LDS (pool.hpp), keyed (distance,
+// id), and its threshold, the kk-th best key at the last cut; the id is read only
+// for entries at or below the threshold's distance (Section 5.3 resolves ids only
+// for selected entries).  A queue per wave, as sorted registers, took four times the
+// insertions (every wave fills its own), a sorting network over the queue for
+// every 64 to 512 of them, and a serial merge of the four queues.
+// The lists of a group (64 at a time) are one range of entries, taken in steps of
+// 1,024, the next step's codes and terms in flight: a step of its own per list
+// leaves most of its last lanes idle and starts with three loads in a row (list,
+// offset, code).  10^4 queries, 8 lists of about 1,000 entries, 256 kept: queues
+// 919, pool 608, one range 506 us; 64 queries, 32 lists, 100 kept: 80, 44, 41 us.
+// What is left is the table lookups: 1.25 * 10^9 LDS gathers with random banks,
+// about 7 cycles per wave and gather, are 230 of the 506 us.
 // Item -> (query, group): fixed probe count nprobe (= ld) when work is null,
 // else query q owns items work[q] .. work[q + 1] - 1 and probes tau[q] lists.
 
@@ -1059,130 +1062,16 @@ template <> struct LutT<true> {
     static __device__ __forceinline__ float get(__half v) { return __half2float(v); }
 };
 
-constexpr int kCutBins = 1024;
-
-// LDS words of one workgroup's pool.
-struct PoolState {
-    uint64_t limit;             // threshold key: only smaller keys are kept
-    unsigned long long lo, hi;  // range of the keys being cut
-    uint32_t count;             // keys in the pool
-    uint32_t bin, below, edge;  // bin of the rank looked for, keys below it, keys in it
-    uint32_t front, back;       // cursors
-    uint32_t wsum[kScanWaves];
+// Lists a workgroup scans as one range of entries.
+constexpr int kScanLists = 64;
+struct ScanLists {
+    int64_t end[kScanLists];    // entries of the lists up to and with this one
+    uint32_t shift[kScanLists]; // entry -> row of codes, t1e and ids (below 2^32, as sums wrap)
+    float term2[kScanLists];
 };
 
-// Cut the pool of st->count > kk keys to exactly its kk smallest, and the
-// threshold to the largest of them + 1 (ids are unique, so keys are).  All
-// threads of the workgroup; the keys pass through registers (PER per thread).
-// A histogram of the keys over their range finds the bin of rank kk; the keys
-// of that bin (a few, as a rule) are ranked against each other, or, where they
-// are many, cut again by their own range.
-template <int P>
-__device__ __forceinline__ void pool_cut(uint64_t* pool, uint32_t* bins, PoolState* st, int kk) {
-    constexpr int NT = 64 * kScanWaves, PER = P / NT, BPT = kCutBins / NT;
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    uint32_t first = 0, n = st->count, want = (uint32_t)kk;  // the keys looked at, and the rank
-#pragma unroll 1
-    for (;;) {
-        uint64_t key[PER], lo = ~0ull, hi = 0ull;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t i = j * NT + tid;
-            key[j] = i < n ? pool[first + i] : kSentinel;
-            if (i < n) {
-                lo = umin64(lo, key[j]);
-                hi = umax64(hi, key[j]);
-            }
-        }
-        if (n <= 64) break;
-        if (tid == 0) {
-            st->lo = ~0ull;
-            st->hi = 0ull;
-            st->front = st->back = 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) bins[j * NT + tid] = 0u;
-        __syncthreads();
-        lo = wave_min64(lo);
-        hi = wave_max64(hi);
-        if (lane == 0) {
-            atomicMin(&st->lo, (unsigned long long)lo);
-            atomicMax(&st->hi, (unsigned long long)hi);
-        }
-        __syncthreads();
-        const uint64_t base = st->lo, range = st->hi - base;
-        if (range == 0) {  // (only where a file repeats ids) any of them will do
-            if (tid == 0) {
-                st->limit = base + 1;
-                st->count = (uint32_t)kk;
-            }
-            __syncthreads();
-            return;
-        }
-        const int bits = 64 - __builtin_clzll(range);
-        const int shift = bits > 10 ? bits - 10 : 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (j * NT + tid < (int)n) atomicAdd(&bins[(key[j] - base) >> shift], 1u);
-        __syncthreads();
-        // prefix over the bins, BPT consecutive ones per thread
-        uint32_t c[BPT], tot = 0;
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            c[j] = bins[tid * BPT + j];
-            tot += c[j];
-        }
-        const uint32_t incl = (uint32_t)wave_inclusive_sum((int)tot);
-        if (lane == 63) st->wsum[wave] = incl;
-        __syncthreads();
-        uint32_t run = incl - tot;
-#pragma unroll
-        for (int w = 0; w < kScanWaves; ++w) run += w < wave ? st->wsum[w] : 0u;
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            if (run < want && run + c[j] >= want) {
-                st->bin = tid * BPT + j;
-                st->below = run;
-                st->edge = c[j];
-            }
-            run += c[j];
-        }
-        __syncthreads();
-        const uint32_t bin = st->bin, below = st->below;
-        // keys below the bin to the front, the bin's own behind them
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (j * NT + tid < (int)n) {
-                const uint32_t b = (uint32_t)((key[j] - base) >> shift);
-                if (b < bin) pool[first + atomicAdd(&st->front, 1u)] = key[j];
-                if (b == bin) pool[first + below + atomicAdd(&st->back, 1u)] = key[j];
-            }
-        }
-        first += below;
-        want -= below;
-        n = st->edge;
-        __syncthreads();
-    }
-    // up to 64 keys: each counts the smaller ones
-    const bool live = tid < (int)n;
-    const uint64_t mine = live ? pool[first + tid] : kSentinel;
-    uint32_t rank = 0;
-    if (live)
-        for (uint32_t e = 0; e < n; ++e) {
-            const uint64_t o = pool[first + e];
-            rank += o < mine || (o == mine && e < (uint32_t)tid) ? 1u : 0u;
-        }
-    __syncthreads();
-    if (live && rank < want) {
-        pool[first + rank] = mine;
-        if (rank == want - 1) st->limit = mine + 1;
-    }
-    if (tid == 0) st->count = (uint32_t)kk;
-    __syncthreads();
-}
-
 template <bool H16, int P>
-__global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
+__global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(4))) void ivf_scan(
     const float* __restrict__ term3, const float* __restrict__ t1e,
     const float* __restrict__ coarse_d, const int64_t* __restrict__ coarse_i, int32_t ld,
     const int64_t* __restrict__ offsets, const uint8_t* __restrict__ codes,
@@ -1196,6 +1085,7 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
     static_assert(P >= 2 * STEP, "the pool takes a step beside kk <= P - STEP keys");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ PoolState state;
+    __shared__ ScanLists lists;
     uint64_t* pool = reinterpret_cast<uint64_t*>(smem);
     uint32_t* bins = reinterpret_cast<uint32_t*>(smem + sizeof(uint64_t) * P);
     lut_t* lut = reinterpret_cast<lut_t*>(smem + sizeof(uint64_t) * P + sizeof(uint32_t) * kCutBins);
@@ -1221,7 +1111,7 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
     }
     const int32_t p0 = (int32_t)(g * G);
     const int32_t ns = np - p0 < G ? np - p0 : G;  // lists in this group
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     uint64_t* out = part + item * k;
     // k-NN graph construction: query q is node excl_base + q, not its own
@@ -1242,37 +1132,79 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
     uint64_t limit = kSentinel;  // the threshold and its score
     float limit_f = INFINITY;
 #pragma unroll 1
-    for (int32_t sl = 0; sl < ns; ++sl) {
-        const int64_t L = cirow[sl];
-        if (L < 0) continue;  // fewer lists than probes (wave-uniform)
-        const float term2 = cdrow[sl];
-        const int64_t lo = offsets[L];
-        const int64_t n = offsets[L + 1] - lo;
-        const uint8_t* lc = codes + lo * M;
-        const float* lt = t1e + lo;
-        const int64_t* lid = ids + lo;
-#pragma unroll 1
-        for (int64_t s0 = 0; s0 < n; s0 += STEP) {
-            // entry u of this lane; steps of short lists spread over the waves
-            const int64_t e0 = s0 + (int64_t)wave * 64 + lane;
-            float dist[U];
-            if (vec16) {
+    for (int32_t c0 = 0; c0 < ns; c0 += kScanLists) {
+        // the next lists as one range of entries: list i covers [begin[i], begin[i + 1])
+        if (c0) __syncthreads();
+        if (wave == 0) {
+            const int64_t L = c0 + lane < ns ? cirow[c0 + lane] : -1;  // -1: fewer lists than probes
+            int64_t lo = 0, n = 0;
+            if (L >= 0) {
+                lo = offsets[L];
+                n = offsets[L + 1] - lo;
+            }
+            int64_t incl = n;
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int64_t e = e0 + u * 64 * kScanWaves;
-                    dist[u] = e < n ? term2 + lt[e] : INFINITY;
+            for (int o = 1; o < 64; o *= 2) {
+                const int64_t v = __shfl_up(incl, o);
+                if (lane >= o) incl += v;
+            }
+            lists.end[lane] = incl;
+            lists.shift[lane] = (uint32_t)(lo - (incl - n));
+            lists.term2[lane] = L >= 0 ? cdrow[c0 + lane] : 0.f;
+        }
+        __syncthreads();
+        const int64_t total = lists.end[kScanLists - 1];
+        if (total == 0) continue;
+        // this lane's list: entries are looked up in ascending order
+        int cur = -1;
+        int64_t cur_end = 0;
+        uint32_t cur_shift = 0;
+        float cur_term2 = 0.f;
+        struct Step {
+            uint4 w[U];     // first 16 code bytes (M a multiple of 16)
+            float t1[U], t2[U];
+            uint32_t pos[U];
+        } now, next;
+        // entries s0 + u 256 + 64 wave + lane; beyond the last one, the last one's data
+        auto load = [&](Step& st, int64_t s0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                int64_t e = s0 + u * 64 * kScanWaves + wave * 64 + lane;
+                e = e < total ? e : total - 1;
+                if (e >= cur_end) {
+                    do ++cur; while (e >= lists.end[cur]);  // (e < total = end of the last)
+                    cur_end = lists.end[cur];
+                    cur_shift = lists.shift[cur];
+                    cur_term2 = lists.term2[cur];
                 }
+                st.pos[u] = (uint32_t)e + cur_shift;
+                st.t2[u] = cur_term2;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                st.t1[u] = t1e[st.pos[u]];
+                if (vec16) st.w[u] = *reinterpret_cast<const uint4*>(codes + (int64_t)st.pos[u] * M);
+            }
+        };
+        load(now, 0);
+#pragma unroll 1
+        for (int64_t s0 = 0; s0 < total; s0 += STEP) {
+            if (s0 + STEP < total) load(next, s0 + STEP);
+            // of the entries s0 + u 256 + 64 wave + lane, those u with any for this wave
+            const int64_t rest = total - s0 - wave * 64;
+            float dist[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) dist[u] = now.t2[u] + now.t1[u];
+            if (vec16) {
                 for (int m0 = 0; m0 < M; m0 += 16) {
-                    uint4 w[U];
+                    if (m0)
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            now.w[u] = *reinterpret_cast<const uint4*>(codes + (int64_t)now.pos[u] * M + m0);
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int64_t e = e0 + u * 64 * kScanWaves;
-                        if (e < n) w[u] = *reinterpret_cast<const uint4*>(lc + e * M + m0);
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (e0 + u * 64 * kScanWaves >= n) continue;
-                        const uint32_t ww[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+                        if (u * 64 * kScanWaves >= rest) continue;  // (wave-uniform)
+                        const uint32_t ww[4] = {now.w[u].x, now.w[u].y, now.w[u].z, now.w[u].w};
 #pragma unroll
                         for (int h = 0; h < 4; ++h)
 #pragma unroll
@@ -1285,11 +1217,8 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
             } else {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int64_t e = e0 + u * 64 * kScanWaves;
-                    dist[u] = INFINITY;
-                    if (e >= n) continue;
-                    dist[u] = term2 + lt[e];
-                    const uint8_t* c = lc + e * M;
+                    if (u * 64 * kScanWaves >= rest) continue;
+                    const uint8_t* c = codes + (int64_t)now.pos[u] * M;
                     for (int m0 = 0; m0 < M; m0 += 4) {
                         const uint32_t w = *reinterpret_cast<const uint32_t*>(c + m0);
 #pragma unroll
@@ -1305,9 +1234,8 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
             bool may[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t e = e0 + u * 64 * kScanWaves;
-                may[u] = e < n && dist[u] <= limit_f;
-                id[u] = may[u] ? lid[e] : 0;
+                may[u] = u * 64 * kScanWaves + lane < rest && dist[u] <= limit_f;
+                id[u] = may[u] ? ids[now.pos[u]] : 0;
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -1329,14 +1257,18 @@ __global__ __launch_bounds__(64 * kScanWaves) void ivf_scan(
             __syncthreads();  // every wave has read it
             if (have > (uint32_t)(P - STEP)) {
                 // (kk <= P - STEP, so there is something to cut)
-                pool_cut<P>(pool, bins, &state, k);
+                pool_cut<P>(pool, bins, &state, have, k);
+                if (threadIdx.x == 0) state.count = (uint32_t)k;
+                __syncthreads();
                 limit = state.limit;
                 limit_f = key_score(limit - 1);
             }
+            now = next;
         }
     }
-    if (state.count > (uint32_t)k) pool_cut<P>(pool, bins, &state, k);
-    const int have = (int)state.count;
+    const uint32_t found = state.count;
+    if (found > (uint32_t)k) pool_cut<P>(pool, bins, &state, found, k);
+    const int have = (int)(found < (uint32_t)k ? found : (uint32_t)k);
     for (int e = threadIdx.x; e < k; e += 64 * kScanWaves) out[e] = e < have ? pool[e] : kSentinel;
 }
 

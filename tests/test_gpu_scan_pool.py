@@ -73,3 +73,35 @@ def test_scan_pool_rerank_from_scan(api):
             ix.set_scan_options(lists_per_group=g)
             out.append(ix.search_rerank(xq, k, 3, R, xb))
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# lists of a group as one range of entries: more lists than one range takes (64),
+# empty lists at its ends, ranges of less and more than a step of 1,024 entries
+@pytest.mark.parametrize("M", [4, 16, 32])
+@pytest.mark.parametrize("n,nlist", [(40, 150), (900, 150), (20_000, 150), (20_000, 64)])
+def test_scan_ranges(api, M, n, nlist):
+    print(f"scan ranges M={M} n={n} nlist={nlist}", flush=True)
+    rng = np.random.default_rng(n + nlist + M)
+    d = 2 * M
+    x = rng.standard_normal((max(n, nlist), d)).astype(np.float32)
+    ix = api.IVFPQ(d, nlist, M)
+    ix.set_quantizers(x[:nlist], rng.standard_normal((M, 256, 2)).astype(np.float32))
+    ix.add(torch.from_numpy(x[:n]).cuda())
+    coarse, books = ix.get_quantizers()
+    offs, codes, ids = ix.get_lists()
+    xq = rng.standard_normal((9, d)).astype(np.float32)
+    for nprobe, k in ((64, 20), (65, 300), (140, 100), (nlist, 600)):
+        nprobe = min(nprobe, nlist)
+        ix.set_scan_options(lists_per_group=-1)
+        D, I = ix.search(torch.from_numpy(xq).cuda(), k, nprobe)
+        ix.set_scan_options(lists_per_group=1)
+        D1, I1 = ix.search(torch.from_numpy(xq).cuda(), k, nprobe)
+        ix.set_scan_options()
+        assert torch.equal(I, I1) and torch.equal(D, D1)
+        Do, Io = oracle.ivfpq_search(xq, coarse, books, offs, codes, ids, k, nprobe)
+        D, I = D.cpu().numpy().astype(np.float64), I.cpu().numpy()
+        got = np.isfinite(Do)
+        assert ((I < 0) == (Io < 0)).all()
+        # sums of M + 2 terms in FP32 (term 1 holds M more), distances of a few d
+        tol = (2 * M + 4) * 2.0 ** -24 * 8 * np.maximum(np.abs(Do), d)
+        assert (np.abs(D[got] - Do[got]) <= tol[got]).all()
