@@ -5,21 +5,26 @@
 //      products in its order) of every query with every row, straight from
 //      memory to the matrix operands; of every four rows the least score is
 //      stored.  One read of the database, nq * nb bytes written.
-//   2. k-selection of the k + 16 best groups of four.  A row of the k best has
-//      at most k - 1 groups before its own, so these groups hold every candidate
-//      that the fused search would keep.
-//   3. quad_finish_kernel: direct-form FP32 distances of the groups' rows, the k
-//      best written.
+//   2. The k + 16 best groups of four.  A row of the k best has at most k - 1 groups
+//      before its own, so these groups hold every candidate that the fused search
+//      would keep.
+//   3. Direct-form FP32 distances of the groups' rows, the k best written.
+// 2 and 3 are one kernel (a wave or a workgroup per query); where few queries have
+// long rows of minima, workgroups first select in segments of them.
 //
-// Bound by memory for few queries: one query over 10^6 x 128 rows, k = 10: 154 us
-// (the rows' read 96 us, 5.3 TB/s) against 2,422 us by the fused search, which has
-// 16 workgroups for it (one per chunk).  By the FP32 matrix products for many:
-// 10^4 queries over 4,096 x 128 centroids, k = 8: 270 us against 450 us.
+// Bound by memory for few queries: one query over 10^6 x 128 rows, k = 10: 130 us
+// (the rows' read 96 us, 5.3 TB/s; selections and finish in two kernels 24 us less
+// than in three) against 2,422 us by the fused search, which has 16 workgroups for
+// it (one per chunk).  By the FP32 matrix products for many: 10^4 queries over
+// 4,096 x 128 centroids, k = 8: products 175 us, selection and finish 93 us (by a
+// workgroup per query 150 us) against 450 us by the fused search.
 #include <algorithm>
+#include <cmath>
 
 #include "dense.hpp"
 #include "fused.hpp"
 #include "kselect.hpp"
+#include "pool.hpp"
 
 namespace mk {
 
@@ -134,48 +139,155 @@ __global__ __launch_bounds__(256) void quad_min_kernel(QuadArgs a) {
     }
 }
 
-// A workgroup per query: exact distances of the rows of its kq groups (16 rows
-// per wave and step, as in the fused search's re-rank), then wave 0 selects the
-// k best by (distance, row).
-template <int KR>
-__global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_kernel(
-    const int64_t* __restrict__ groups, int32_t kq, const float* __restrict__ xq,
-    const float* __restrict__ xb, const float* __restrict__ yn, int64_t nb, int32_t d, int32_t vec,
-    int32_t l2, int32_t k, float* __restrict__ D, int64_t* __restrict__ I) {
-    constexpr int T = SelParams<KR>::T;
-    extern __shared__ __align__(16) unsigned char smem[];
-    float* xs = reinterpret_cast<float*>(smem);
-    uint64_t* kl = reinterpret_cast<uint64_t*>(smem + sizeof(float) * kMaxDim);
-    float* dist = reinterpret_cast<float*>(kl + 4 * kq);
-    const int wave = threadIdx.x >> 6, lane = lane_id();
+// Steps 2 and 3 by a workgroup per query: the kq best groups, from the row of group minima itself
+// (lists null) or from the nlists lists of kq keys of a first pass over its
+// segments; exact distances of the groups' rows (16 rows per wave and step, as in
+// the fused search's re-rank); the k best of them by (distance, row).
+template <int P, int U, int N>  // kq <= P - 1024 U, kq <= P / 2, 4 kq <= N <= P
+__global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
+    const float* __restrict__ least, int64_t ld, const uint64_t* __restrict__ lists,
+    int32_t nlists, int32_t kq, const float* __restrict__ xq, const float* __restrict__ xb,
+    const float* __restrict__ yn, int64_t nb, int32_t d, int32_t vec, int32_t l2, int32_t k,
+    float* __restrict__ D, int64_t* __restrict__ I) {
+    __shared__ __align__(16) float xs[kMaxDim];
+    __shared__ uint64_t pool[P];
+    __shared__ float dist[N];
+    __shared__ uint32_t bins[kCutBins];
+    __shared__ PoolState st;
+    __shared__ uint32_t ws[2][kPoolWaves];
+    const int tid = threadIdx.x;
     const int64_t q = blockIdx.x;
-    const int n = 4 * kq;
-    for (int e = threadIdx.x; e < n; e += 64 * kMergeWaves) {
-        const int64_t g = groups[q * kq + (e >> 2)];
-        const int64_t row = 4 * g + (e & 3);
-        // (a row without a finite norm has no score: it was no candidate)
-        kl[e] = g >= 0 && row < nb && (!yn || yn[row] < INFINITY) ? (uint64_t)row : kSentinel;
+    for (int t = tid; t < d; t += kPoolThreads) xs[t] = xq[q * d + t];
+    uint32_t found;
+    if (lists) {
+        uint64_t limit;
+        found = pool_stream<P>(lists + q * (int64_t)nlists * kq, (int64_t)nlists * kq, pool, bins,
+                               &st, kq, limit);
+    } else {
+        found = pool_values<P, U, false>(least + q * ld, (uint32_t)ld, 0u, kq, pool, bins, &st, ws);
+        if (found > (uint32_t)kq) {
+            pool_cut<P>(pool, bins, &st, found, kq);
+            found = (uint32_t)kq;
+        }
     }
-    for (int t = threadIdx.x; t < d; t += 64 * kMergeWaves) xs[t] = xq[q * d + t];
+    __syncthreads();
+    // the groups' rows in the groups' place
+    const int n = 4 * (int)found;
+    uint64_t row[N / kPoolThreads];
+#pragma unroll
+    for (int j = 0; j < N / kPoolThreads; ++j) {
+        const int e = j * kPoolThreads + tid;
+        row[j] = kSentinel;
+        if (e >= n || pool[e >> 2] == kSentinel) continue;
+        const int64_t r = 4 * (int64_t)key_index(pool[e >> 2]) + (e & 3);
+        // (a row without a finite norm has no score: it was no candidate)
+        if (r < nb && (!yn || yn[r] < INFINITY)) row[j] = (uint64_t)r;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N / kPoolThreads; ++j) {
+        const int e = j * kPoolThreads + tid;
+        if (e < n) pool[e] = row[j];
+    }
+    if (tid == 0) st.count = 0u;
     __syncthreads();
 #pragma unroll 1
-    for (int e0 = 16 * wave; e0 < n; e0 += 16 * kMergeWaves)
-        rerank_rows16(xs, kl, e0, n, xb, d, vec, l2, dist);
+    for (int e0 = 16 * (tid >> 6); e0 < n; e0 += 16 * kPoolWaves)
+        rerank_rows16(xs, pool, e0, n, xb, d, vec, l2, dist);
     __syncthreads();
-    if (wave != 0) return;
-    WaveSelect<KR, T> ws;
+    // live rows to the front (a NaN is no distance)
+    uint64_t key[N / kPoolThreads];
+#pragma unroll
+    for (int j = 0; j < N / kPoolThreads; ++j) {
+        const int e = j * kPoolThreads + tid;
+        key[j] = kSentinel;
+        if (e < n && pool[e] != kSentinel && dist[e] == dist[e])
+            key[j] = make_key(l2 ? dist[e] : -dist[e], (uint32_t)pool[e]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < N / kPoolThreads; ++j)
+        if (key[j] != kSentinel) pool[atomicAdd(&st.count, 1u)] = key[j];
+    __syncthreads();
+    const uint32_t have = st.count;
+    float* Dq = D + q * k;
+    int64_t* Iq = I + q * k;
+    pool_emit<P>(pool, bins, &st, have, (uint32_t)k, [&](uint32_t r, uint64_t key) {
+        const float s = key_score(key);
+        Dq[r] = l2 ? s : -s;
+        Iq[r] = (int64_t)key_index(key);
+    });
+    for (int e = tid; e < k; e += kPoolThreads)
+        if (e >= (int)have) {
+            Dq[e] = l2 ? INFINITY : -INFINITY;
+            Iq[e] = -1;
+        }
+}
+
+// The same with one wave per query and sorted register queues, for kq <= 64 and
+// whole rows: no barriers, so it is the better one where there are more queries
+// than the chip takes workgroups at a time.
+__global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_wave(
+    const float* __restrict__ least, int64_t ld, int64_t nq, int32_t kq,
+    const float* __restrict__ xq, const float* __restrict__ xb, const float* __restrict__ yn,
+    int64_t nb, int32_t d, int32_t vec, int32_t l2, int32_t k, float* __restrict__ D,
+    int64_t* __restrict__ I) {
+    constexpr int T = SelParams<1>::T;
+    __shared__ __align__(16) float xs[kMergeWaves][kMaxDim];
+    __shared__ uint64_t kl[kMergeWaves][256];
+    __shared__ float dist[kMergeWaves][256];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    const int64_t q = (int64_t)blockIdx.x * kMergeWaves + wave;
+    if (q >= nq) return;
+    for (int t = lane; t < d; t += 64) xs[wave][t] = xq[q * d + t];
+    const float* row = least + q * ld;
+    WaveSelect<1, T> ws;
+    ws.init(kq);
+    constexpr int AHEAD = 4;  // values in flight per lane
+    auto value = [&](int64_t e) { return e + lane < ld ? row[e + lane] : INFINITY; };
+    float v[AHEAD];
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) v[j] = value(64 * j);
+#pragma unroll 1
+    for (int64_t e = 0; e < ld; e += 64) {
+        const float now = v[0];
+#pragma unroll
+        for (int j = 0; j + 1 < AHEAD; ++j) v[j] = v[j + 1];
+        v[AHEAD - 1] = value(e + 64 * AHEAD);
+        const uint64_t key = e + lane < ld ? make_key(now, (uint32_t)(e + lane)) : kSentinel;
+        if (ws.push(key)) ws.merge();
+    }
+    ws.finish();
+    // the groups' rows
+    const uint64_t group = ws.w[0];
+    const int n = 4 * kq;
+    if (lane < kq) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t r = 4 * (int64_t)key_index(group) + j;
+            // (a row without a finite norm has no score: it was no candidate)
+            kl[wave][4 * lane + j] =
+                group != kSentinel && r < nb && (!yn || yn[r] < INFINITY) ? (uint64_t)r : kSentinel;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll 1
+    for (int e0 = 0; e0 < n; e0 += 16) rerank_rows16(xs[wave], kl[wave], e0, n, xb, d, vec, l2, dist[wave]);
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     ws.init(k);
 #pragma unroll 1
     for (int e0 = 0; e0 < n; e0 += 64) {
         const int e = e0 + lane;
         uint64_t key = kSentinel;
         // (a NaN is no distance)
-        if (e < n && kl[e] != kSentinel && dist[e] == dist[e])
-            key = make_key(l2 ? dist[e] : -dist[e], (uint32_t)kl[e]);
+        if (e < n && kl[wave][e] != kSentinel && dist[wave][e] == dist[wave][e])
+            key = make_key(l2 ? dist[wave][e] : -dist[wave][e], (uint32_t)kl[wave][e]);
         if (ws.push(key)) ws.merge();
     }
     ws.finish();
-    emit_reranked<KR>(ws.w, k, l2, D + q * k, I + q * k);
+    emit_reranked<1>(ws.w, k, l2, D + q * k, I + q * k);
 }
 
 template <int DP, int QB>
@@ -201,24 +313,25 @@ mk_status quads(QuadArgs a, bool vec, bool l2, hipStream_t s) {
                    : launch_quads<DP, WIDE>(a, vec, l2, waves, s);
 }
 
-template <int KR>
-mk_status finish(const int64_t* groups, int32_t kq, const float* xq, int64_t nq, const float* xb,
-                 const float* yn, int64_t nb, int32_t d, bool vec, bool l2, int32_t k, float* D,
-                 int64_t* I, hipStream_t s) {
-    ProfScope prof("dense_finish", s);
-    const size_t lds = sizeof(float) * kMaxDim + 12 * 4 * (size_t)kq;
-    hipLaunchKernelGGL((quad_finish_kernel<KR>), dim3((unsigned)nq), dim3(64 * kMergeWaves), lds, s,
-                       groups, kq, xq, xb, l2 ? yn : nullptr, nb, d, (int32_t)vec, (int32_t)l2, k, D, I);
-    MK_LAUNCHED();
-    return MK_OK;
-}
-
 int32_t groups_kept(int32_t k) { return std::min(k + kSlack, kMaxK); }
+
+// Segments that a row of ld minima is selected in: a workgroup takes a segment of
+// it and leaves kq keys to the finish, so their number is best where a segment is
+// about as long as the keys of all segments; with enough queries to fill the chip
+// the finish takes whole rows.
+int64_t segments(int64_t ld, int32_t kq, int64_t nq) {
+    const int64_t even = (int64_t)std::sqrt((double)ld / kq);
+    const int64_t n = std::min({even, ld / 2048, ceil_div(1024, nq)});
+    return n < 4 ? 1 : n;
+}
 
 }  // namespace
 
 int64_t dense_query_bytes(int64_t nb, int32_t k) {
-    return ceil_div(nb, 64) * 64 + 12 * (int64_t)groups_kept(k);
+    const int64_t ld = ceil_div(nb, 64) * 16;
+    const int32_t kq = groups_kept(k);
+    const int64_t n = segments(ld, kq, 1);
+    return 4 * ld + (n > 1 ? 8 * n * kq : 0);
 }
 
 mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
@@ -227,29 +340,42 @@ mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float
     const int32_t kq = groups_kept(k);
     const int64_t ld = ceil_div(nb, 64) * 16;
     Scratch mem;
-    const size_t b_out = ((size_t)(nq * ld) * sizeof(float) + 255) & ~(size_t)255;
-    const size_t b_val = ((size_t)nq * kq * sizeof(float) + 255) & ~(size_t)255;
     if (!scratch) {
-        MK_TRY(mem.alloc(b_out + b_val + (size_t)nq * kq * sizeof(int64_t), s));
+        MK_TRY(mem.alloc((size_t)(nq * dense_query_bytes(nb, k) + 256), s));
         scratch = mem.ptr;
     }
-    unsigned char* base = static_cast<unsigned char*>(scratch);
-    float* vals = reinterpret_cast<float*>(base + b_out);
-    int64_t* groups = reinterpret_cast<int64_t*>(base + b_out + b_val);
-    QuadArgs a{xq, xb, yn, nq, nb, d, ceil_div(nb, 64), 1, 1, reinterpret_cast<float*>(base), ld};
+    float* least = static_cast<float*>(scratch);
+    QuadArgs a{xq, xb, yn, nq, nb, d, ceil_div(nb, 64), 1, 1, least, ld};
     if (d <= 32) MK_TRY(quads<32>(a, vec, l2, s));
     else if (d <= 64) MK_TRY(quads<64>(a, vec, l2, s));
     else if (d <= 96) MK_TRY(quads<96>(a, vec, l2, s));
     else if (d <= 128) MK_TRY(quads<128>(a, vec, l2, s));
     else MK_TRY(quads<256>(a, vec, l2, s));
-    MK_TRY(mk_kselect(a.out, nq, ld, kq, 0, vals, groups, s));
-    switch (queue_regs(k)) {
-        case 1: return finish<1>(groups, kq, xq, nq, xb, yn, nb, d, vec, l2, k, D, I, s);
-        case 2: return finish<2>(groups, kq, xq, nq, xb, yn, nb, d, vec, l2, k, D, I, s);
-        case 4: return finish<4>(groups, kq, xq, nq, xb, yn, nb, d, vec, l2, k, D, I, s);
-        case 8: return finish<8>(groups, kq, xq, nq, xb, yn, nb, d, vec, l2, k, D, I, s);
-        default: return finish<16>(groups, kq, xq, nq, xb, yn, nb, d, vec, l2, k, D, I, s);
+    uint64_t* lists = nullptr;
+    int64_t nseg = segments(ld, kq, nq);
+    if (nseg > 1) {
+        const int64_t seg_len = ceil_div(ceil_div(ld, nseg), 256) * 256;
+        nseg = ceil_div(ld, seg_len);
+        lists = reinterpret_cast<uint64_t*>(
+            (reinterpret_cast<uintptr_t>(least + nq * ld) + 255) & ~(uintptr_t)255);
+        MK_TRY(kselect_segments(least, nq, ld, kq, seg_len, lists, s));
     }
+    ProfScope prof("dense_finish", s);
+    if (kq <= 64 && nseg == 1 && nq >= 1024) {
+        hipLaunchKernelGGL(quad_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
+                           dim3(64 * kMergeWaves), 0, s, least, ld, nq, kq, xq, xb,
+                           l2 ? yn : nullptr, nb, d, (int32_t)vec, (int32_t)l2, k, D, I);
+        MK_LAUNCHED();
+        return MK_OK;
+    }
+    auto kern = kq <= 64    ? quad_finish_kernel<1280, 1, 256>
+                : kq <= 512 ? quad_finish_kernel<2560, 2, 2048>
+                            : quad_finish_kernel<4096, 2, 4096>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, least, ld, lists,
+                       (int32_t)nseg, kq, xq, xb, l2 ? yn : nullptr, nb, d, (int32_t)vec,
+                       (int32_t)l2, k, D, I);
+    MK_LAUNCHED();
+    return MK_OK;
 }
 
 }  // namespace mk

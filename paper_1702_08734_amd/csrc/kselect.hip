@@ -133,13 +133,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void kselect_pass1(
 }
 
 // Pass 1 for k > 64: a workgroup per (row, segment), one candidate pool in LDS
-// (pool.hpp).  A step is 2,048 values, 8 per thread, 16-byte loads (4-byte ones
-// where rows start off the 16-byte grid), the next step's in flight; values that
-// do not beat the pool's threshold cost one compare, and a step without any costs
-// one barrier.  The pool is cut when a step's values do not fit beside its keys:
-// a row of L values sees about k (1 + ln(L / k)) insertions and a cut for every
-// P - k of them.  (Steps of 4,096 values need a second place for cuts in the loop
-// and the registers for it: fewer waves, 5 to 10% slower.)
+// (pool_values).
 //
 // 10^4 rows, k = 100 / 300 / 1000, against a wave per row with a sorted queue (or,
 // for 300 and more and long rows, a pool in device memory): 128,000 values 896 /
@@ -150,7 +144,6 @@ template <int P, bool LARGEST>  // k <= P - 2048
 __global__ __launch_bounds__(kPoolThreads) void kselect_rows(
     const float* __restrict__ a, int64_t len, int32_t k, int32_t nseg, int64_t seg_len,
     float* __restrict__ vals, int64_t* __restrict__ idx, uint64_t* __restrict__ partial) {
-    constexpr int NT = kPoolThreads, U = 2, STEP = NT * 4 * U;
     __shared__ uint64_t pool[P];
     __shared__ uint32_t bins[kCutBins];
     __shared__ PoolState st;
@@ -162,104 +155,11 @@ __global__ __launch_bounds__(kPoolThreads) void kselect_rows(
     const int64_t lo = seg * seg_len;
     const uint32_t n = (uint32_t)(lo + seg_len < len ? seg_len : len - lo);
     const float* rp = a + row * len + lo;
-    const bool aligned = (reinterpret_cast<uintptr_t>(rp) & 15) == 0;
-    // value j of quarter u is 1,024 u + 4 tid + j (aligned) or + 256 j + tid
-    const uint32_t mine = aligned ? 4u * tid : (uint32_t)tid, stride = aligned ? 1u : (uint32_t)NT;
-    uint32_t have = 0;
-    uint64_t limit = kSentinel;
-    float limit_f = INFINITY;
-    int turn = 0;
-    auto cut = [&]() __attribute__((always_inline)) {
-        pool_cut<P>(pool, bins, &st, have, k);
-        have = (uint32_t)k;
-        limit = st.limit;
-        limit_f = key_score(limit - 1);
-    };
-    // a step's values, the next step's while this one is looked at
-    float next[U][4];
-    auto load = [&](uint32_t e) __attribute__((always_inline)) {
-        if (aligned && n - e >= (uint32_t)STEP) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float4 w = *reinterpret_cast<const float4*>(rp + e + u * (NT * 4) + mine);
-                next[u][0] = w.x;
-                next[u][1] = w.y;
-                next[u][2] = w.z;
-                next[u][3] = w.w;
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t i = u * (NT * 4) + mine + j * stride;
-                    next[u][j] = i < n - e ? rp[e + i] : NAN;  // (never taken)
-                }
-        }
-    };
-    if (n > 0) load(0);
-#pragma unroll 1
-    for (uint32_t e0 = 0; e0 < n;) {
-        float v[U][4];
-        const uint32_t place = (uint32_t)lo + e0 + mine;  // column of this thread's first value
-        auto at = [&](int u, int j) __attribute__((always_inline)) -> uint32_t {
-            return place + u * (NT * 4) + j * stride;
-        };
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[u][j] = next[u][j];
-        // (e0 + STEP may pass 2^32 - 1 on the last step)
-        const bool last = n - e0 <= (uint32_t)STEP;
-        if (!last) load(e0 + STEP);
-        e0 = last ? n : e0 + STEP;
-        bool any = false;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (LARGEST) v[u][j] = -v[u][j];
-                any |= v[u][j] <= limit_f;
-            }
-        if (!__syncthreads_or(any)) continue;
-        // which values enter: below the threshold's score, or at it and before it
-        auto takes = [&](int u) __attribute__((always_inline)) {
-            uint32_t mask = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const bool t = v[u][j] < limit_f ||
-                               (v[u][j] == limit_f && at(u, j) < (uint32_t)limit);
-                mask |= t ? 1u << j : 0u;
-            }
-            return mask;
-        };
-        uint32_t mask[U], add, pos;
-        auto count = [&]() __attribute__((always_inline)) {
-            uint32_t c = 0;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                mask[u] = takes(u);
-                c += __popc(mask[u]);
-            }
-            add = pool_sum(c, ws[turn ^= 1], pos);
-        };
-        count();
-        if (have + add > (uint32_t)P) {  // (k <= P - STEP: after a cut they fit)
-            cut();
-            count();
-        }
-        pos += have;
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (mask[u] & (1u << j)) pool[pos++] = make_key(v[u][j], at(u, j));
-        have += add;
-    }
+    const uint32_t have = pool_values<P, 2, LARGEST>(rp, n, (uint32_t)lo, k, pool, bins, &st, ws);
     if (nseg > 1) {
-        if (have > (uint32_t)k) cut();
+        if (have > (uint32_t)k) pool_cut<P>(pool, bins, &st, have, k);
         __syncthreads();
-        for (int e = tid; e < k; e += NT)
+        for (int e = tid; e < k; e += kPoolThreads)
             partial[unit * k + e] = e < (int)have ? pool[e] : kSentinel;
         return;
     }
@@ -270,7 +170,7 @@ __global__ __launch_bounds__(kPoolThreads) void kselect_rows(
         vr[r] = LARGEST ? -s : s;
         ir[r] = (int64_t)key_index(key);
     });
-    for (int e = tid; e < k; e += NT)
+    for (int e = tid; e < k; e += kPoolThreads)
         if (e >= (int)have) {
             vr[e] = LARGEST ? -INFINITY : INFINITY;
             ir[e] = -1;
@@ -452,6 +352,18 @@ mk_status merge_key_lists(const uint64_t* partial, int64_t nrows, int32_t nseg, 
                            seg_offs ? seg_offs + r0 : nullptr);
         MK_LAUNCHED();
     }
+    return MK_OK;
+}
+
+mk_status kselect_segments(const float* a, int64_t nrows, int64_t len, int32_t k, int64_t seg_len,
+                           uint64_t* partial, hipStream_t s) {
+    const int64_t nseg = ceil_div(len, seg_len);
+    MK_REQUIRE(nrows * nseg < (1ll << 24), MK_ERR_UNSUPPORTED, "too many segments for one launch");
+    auto kern = k <= 512 ? kselect_rows<2560, false> : kselect_rows<3072, false>;
+    ProfScope prof("kselect_pass1", s);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nrows * nseg)), dim3(kPoolThreads), 0, s, a, len, k,
+                       (int32_t)nseg, seg_len, (float*)nullptr, (int64_t*)nullptr, partial);
+    MK_LAUNCHED();
     return MK_OK;
 }
 

@@ -29,8 +29,6 @@ template <> struct SelParams<2> { static constexpr int T = 2; };
 template <> struct SelParams<4> { static constexpr int T = 4; };
 template <> struct SelParams<8> { static constexpr int T = 4; };
 template <> struct SelParams<16> { static constexpr int T = 8; };
-// (1,024 results and the candidates beyond them that prove the set)
-template <> struct SelParams<32> { static constexpr int T = 8; };
 
 // Per row, select the k best of nseg sorted lists of k keys each
 // (partial[row][seg][k]) and write (score, index) pairs -- sentinel keys
@@ -44,6 +42,12 @@ mk_status merge_key_lists(const uint64_t* partial, int64_t nrows, int32_t nseg, 
                           float* vals, int64_t* idx, hipStream_t s,
                           uint64_t* keys_out = nullptr, const int64_t* seg_offs = nullptr,
                           bool largest = false);
+
+// First pass of a k-selection alone: of every segment of seg_len values of a row
+// the k smallest as keys (score, column), sentinel padded, in no order:
+// partial[row][seg][k].  k <= 1,024.
+mk_status kselect_segments(const float* a, int64_t nrows, int64_t len, int32_t k, int64_t seg_len,
+                           uint64_t* partial, hipStream_t s);
 
 // Exact k-NN (knn.hip); yn may be null (then computed) for L2.
 // With an arena every scratch buffer is carved from it (nothing is

@@ -286,4 +286,118 @@ __device__ __forceinline__ uint32_t pool_stream(const uint64_t* __restrict__ p, 
     return have;
 }
 
+// Values rp[0 .. n) of one row into an empty pool, keyed (value, first + place):
+// afterwards it holds the kk smallest (largest: negated values) and perhaps more,
+// unsorted; returns how many.  A step is 1,024 U values, 4 U per thread, 16-byte
+// loads (4-byte ones where rows start off the 16-byte grid), the next step's in
+// flight; values that do not beat the pool's threshold cost one compare, and a
+// step without any costs one barrier.  The pool is cut when a step's values do not
+// fit beside its keys: a row of L values sees about kk (1 + ln(L / kk)) insertions
+// and a cut for every P - kk of them.  (Steps of 4,096 values need a second place
+// for cuts in the loop and the registers for it: fewer waves, 5 to 10% slower.)
+// NaN never enters.  ws: LDS words of its own.
+template <int P, int U, bool LARGEST>  // kk <= P - 1024 U
+__device__ __forceinline__ uint32_t pool_values(const float* __restrict__ rp, uint32_t n,
+                                                uint32_t first, int32_t kk, uint64_t* pool,
+                                                uint32_t* bins, PoolState* st,
+                                                uint32_t (*ws)[kPoolWaves]) {
+    constexpr int NT = kPoolThreads, STEP = NT * 4 * U;
+    const int tid = threadIdx.x;
+    const bool aligned = (reinterpret_cast<uintptr_t>(rp) & 15) == 0;
+    // value j of quarter u is 1,024 u + 4 tid + j (aligned) or + 256 j + tid
+    const uint32_t mine = aligned ? 4u * tid : (uint32_t)tid, stride = aligned ? 1u : (uint32_t)NT;
+    uint32_t have = 0;
+    uint64_t limit = kSentinel;
+    float limit_f = INFINITY;
+    int turn = 0;
+    auto cut = [&]() __attribute__((always_inline)) {
+        pool_cut<P>(pool, bins, st, have, kk);
+        have = (uint32_t)kk;
+        limit = st->limit;
+        limit_f = key_score(limit - 1);
+    };
+    // a step's values, the next step's while this one is looked at
+    float next[U][4];
+    auto load = [&](uint32_t e) __attribute__((always_inline)) {
+        if (aligned && n - e >= (uint32_t)STEP) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float4 w = *reinterpret_cast<const float4*>(rp + e + u * (NT * 4) + mine);
+                next[u][0] = w.x;
+                next[u][1] = w.y;
+                next[u][2] = w.z;
+                next[u][3] = w.w;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t i = u * (NT * 4) + mine + j * stride;
+                    next[u][j] = i < n - e ? rp[e + i] : NAN;  // (never taken)
+                }
+        }
+    };
+    if (n > 0) load(0);
+#pragma unroll 1
+    for (uint32_t e0 = 0; e0 < n;) {
+        float v[U][4];
+        const uint32_t place = first + e0 + mine;  // column of this thread's first value
+        auto at = [&](int u, int j) __attribute__((always_inline)) -> uint32_t {
+            return place + u * (NT * 4) + j * stride;
+        };
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[u][j] = next[u][j];
+        // (e0 + STEP may pass 2^32 - 1 on the last step)
+        const bool last = n - e0 <= (uint32_t)STEP;
+        if (!last) load(e0 + STEP);
+        e0 = last ? n : e0 + STEP;
+        bool any = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (LARGEST) v[u][j] = -v[u][j];
+                any |= v[u][j] <= limit_f;
+            }
+        if (!__syncthreads_or(any)) continue;
+        // which values enter: below the threshold's score, or at it and before it
+        auto takes = [&](int u) __attribute__((always_inline)) {
+            uint32_t mask = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool t = v[u][j] < limit_f ||
+                               (v[u][j] == limit_f && at(u, j) < (uint32_t)limit);
+                mask |= t ? 1u << j : 0u;
+            }
+            return mask;
+        };
+        uint32_t mask[U], add, pos;
+        auto count = [&]() __attribute__((always_inline)) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                mask[u] = takes(u);
+                c += __popc(mask[u]);
+            }
+            add = pool_sum(c, ws[turn ^= 1], pos);
+        };
+        count();
+        if (have + add > (uint32_t)P) {  // (kk <= P - STEP: after a cut they fit)
+            cut();
+            count();
+        }
+        pos += have;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (mask[u] & (1u << j)) pool[pos++] = make_key(v[u][j], at(u, j));
+        have += add;
+    }
+    return have;
+}
+
 }  // namespace mk

@@ -8,20 +8,6 @@ namespace mk {
 
 namespace {
 
-template <int KR>
-mk_status sieve_finish_launch(const SieveScratch& w, const float* xq, int64_t nq,
-                              const float* xb, int32_t d, bool vec, bool l2, int32_t k,
-                              int32_t keff, bool cert, float* D, int64_t* I,
-                              hipStream_t s) {
-    ProfScope prof("sieve_finish", s);
-    hipLaunchKernelGGL((sieve_finish<KR>), dim3((unsigned)ceil_div(nq, kMergeWaves)),
-                       dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, xq, nq, xb, d,
-                       (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
-                       w.flags, D, I);
-    MK_LAUNCHED();
-    return MK_OK;
-}
-
 template <int DP>
 mk_status split_rows(const float* x, int64_t n, int32_t d, bool vec, int kind,
                      const float* yn, int64_t sample_of, void* out, float* scale,
@@ -40,14 +26,23 @@ mk_status split_rows(const float* x, int64_t n, int32_t d, bool vec, int kind,
 mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, const float* xb,
                            int32_t d, bool vec, bool l2, int32_t k, int32_t keff, bool cert,
                            float* D, int64_t* I, hipStream_t s) {
-    switch (queue_regs(keff)) {
-        case 1: return sieve_finish_launch<1>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
-        case 2: return sieve_finish_launch<2>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
-        case 4: return sieve_finish_launch<4>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
-        case 8: return sieve_finish_launch<8>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
-        case 16: return sieve_finish_launch<16>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
-        default: return sieve_finish_launch<32>(w, xq, nq, xb, d, vec, l2, k, keff, cert, D, I, s);
+    ProfScope prof("sieve_finish", s);
+    if (keff <= 64) {
+        hipLaunchKernelGGL(sieve_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
+                           dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, xq, nq, xb, d,
+                           (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
+                           w.flags, D, I);
+        MK_LAUNCHED();
+        return MK_OK;
     }
+    auto kern = keff <= 256    ? sieve_finish<1024>
+                : keff <= 1024 ? sieve_finish<2048>
+                               : sieve_finish<4096>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, w.pool, w.cnt, w.cap, xq,
+                       xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
+                       w.flags, D, I);
+    MK_LAUNCHED();
+    return MK_OK;
 }
 
 // Exact search by thresholds (sieve.hpp); yn may be null (norms of the rows

@@ -261,3 +261,26 @@ def test_dense_rows_without_score(api):
     fails = check_rows(D.cpu().numpy(), np.searchsorted(keep, I.cpu().numpy()), xq,
                        np.ascontiguousarray(xb[keep]), np.arange(9), 12, "l2")
     assert not fails and np.isin(I.cpu().numpy(), keep).all(), fails[:10]
+
+
+# both sides of the dense search's selection rules: a wave or a workgroup per query
+# (1,024 queries; 48 results), whole rows of minima or segments of them; ties and
+# rows without a score among the candidates, the same answers on both sides
+@pytest.mark.parametrize("nq,nb,d,k", [(1023, 2049, 20, 48), (1024, 2049, 20, 48), (1025, 4096, 32, 1),
+                                       (1030, 2500, 33, 49), (3, 40_000, 16, 48), (3, 140_001, 16, 49),
+                                       (9, 500_000, 8, 500), (2, 131_072, 24, 1000)])
+def test_dense_selection(api, nq, nb, d, k):
+    rng = np.random.default_rng(nq + nb + k)
+    xb = rng.integers(-2, 3, size=(nb, d)).astype(np.float32)  # many equal distances
+    xq = rng.integers(-2, 3, size=(nq, d)).astype(np.float32)
+    yn = api.norms(dev(xb))
+    yn[5::7] = float("inf")
+    D, I = api.knn_search(dev(xq), dev(xb), k, "l2", yn)
+    D, I = D.cpu().numpy(), I.cpu().numpy()
+    live = np.ones(nb, bool)
+    live[5::7] = False
+    rows = np.flatnonzero(live)
+    for i in range(0, nq, max(1, nq // 12)):
+        d64 = ((xq[i].astype(np.float64) - xb[rows]) ** 2).sum(1)
+        order = np.argsort(d64, kind="stable")[:k]  # integers: exact, ties by row
+        assert (I[i] == rows[order]).all() and (D[i] == d64[order]).all(), i
