@@ -16,10 +16,11 @@
 // (the rows' read 96 us, 5.3 TB/s; selections and finish in two kernels 24 us less
 // than in three) against 2,422 us by the fused search, which has 16 workgroups for
 // it (one per chunk).  By the FP32 matrix products for many: 10^4 queries over
-// 4,096 x 128 centroids, k = 8: products 175 us, selection and finish 93 us (by a
+// 4,096 x 128 centroids, k = 8: products 135 us, selection and finish 93 us (by a
 // workgroup per query 150 us) against 450 us by the fused search.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "dense.hpp"
 #include "fused.hpp"
@@ -47,9 +48,18 @@ struct QuadArgs {
 // at a time: block b of four, A row m is row 16 (m / 4) + 4 b + m % 4 of them, so
 // that lane (query li, quarter lh) ends up with groups 4 lh .. 4 lh + 3 of four
 // consecutive rows: one 16-byte store.  The next block's rows are loaded while
-// this block's products run; enough waves per CU keep the memory busy.
-template <int DP, int QB, bool VEC, bool L2>
-__global__ __launch_bounds__(256) void quad_min_kernel(QuadArgs a) {
+// this block's products run.  No load is under a branch (rows and granules beyond
+// the end are clamped, and made zero or given no score), so that the waits before
+// the products are for this block's rows alone: with branches the compiler waited
+// for everything in flight, and kept twice the registers (500 queries, 50,000 x 64
+// rows: 69 -> 47 us; 10^4 queries, 4,096 x 128 rows 175 -> 135 us, half of the
+// matrix cores' rate).
+enum class QuadNorms { kNone, kGiven, kOwn };  // inner products; L2 with and without yn
+template <int DP, int QB, bool VEC, QuadNorms NORMS>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(DP <= 32 || (DP <= 64 && QB == 1) ? 3 : DP <= 128 ? 2 : 1))) void
+quad_min_kernel(QuadArgs a) {
+    constexpr bool L2 = NORMS != QuadNorms::kNone;
     constexpr int S4 = DP / 16;  // granule steps of four floats per lane
     const int lane = lane_id(), li = lane & 15, lh = lane >> 4;
     const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -68,48 +78,57 @@ __global__ __launch_bounds__(256) void quad_min_kernel(QuadArgs a) {
 #pragma unroll
         for (int s = 0; s < S4; ++s) q[qb][s] = load_granule<OpF32, VEC>(row, 4 * s + lh, a.d, ok);
     }
+    // (d > DP - 32, or more than 128 for DP = 256: the first granules always exist)
+    constexpr int WHOLE = DP > 128 ? 8 : S4 - 2;
     auto load = [&](int64_t g, int b, uint4 (&y)[S4]) __attribute__((always_inline)) {
         int64_t r = g * 64 + 16 * (li >> 2) + 4 * b + (li & 3);
         r = r < a.nb ? r : a.nb - 1;
         const float* row = a.xb + r * a.d;
 #pragma unroll
-        for (int s = 0; s < S4; ++s) y[s] = load_granule<OpF32, VEC>(row, 4 * s + lh, a.d, true);
+        for (int s = 0; s < S4; ++s) {
+            if constexpr (VEC) {
+                const int e = 16 * s + 4 * lh;
+                y[s] = *reinterpret_cast<const uint4*>(row + (s < WHOLE || e < a.d ? e : a.d - 4));
+            } else {
+                y[s] = load_granule<OpF32, false>(row, 4 * s + lh, a.d, true);
+            }
+        }
     };
-    uint4 y[S4], next[S4];
-    load(g0, 0, next);
+    uint4 y[2][S4];
+    load(g0, 0, y[0]);
 #pragma unroll 1
     for (int64_t g = g0; g < g1; ++g) {
         float least[QB][4];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
-#pragma unroll
-            for (int s = 0; s < S4; ++s) y[s] = next[s];
-            if (b < 3)
-                load(g, b + 1, next);
-            else if (g + 1 < g1)
-                load(g + 1, 0, next);
+            uint4 (&now)[S4] = y[b & 1];
+            __builtin_amdgcn_sched_barrier(0);  // (loads further ahead cost registers)
             const int64_t r = g * 64 + 16 * lh + 4 * b;  // first of this lane's four rows
-            float yn[4] = {0.f, 0.f, 0.f, 0.f};
-            if constexpr (L2) {
-                if (a.yn) {
+            float add[4] = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (NORMS == QuadNorms::kGiven)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) yn[i] = a.yn[r + i < a.nb ? r + i : a.nb - 1];
-                } else {
-                    float s2 = 0.f;
+                for (int i = 0; i < 4; ++i) add[i] = a.yn[r + i < a.nb ? r + i : a.nb - 1];
+            // (the last group's last block loads its own rows again)
+            load(b < 3 || g + 1 == g1 ? g : g + 1, (b + 1) & 3, y[(b + 1) & 1]);
+            if constexpr (VEC)
 #pragma unroll
-                    for (int s = 0; s < S4; ++s) {
-                        const float e0 = __uint_as_float(y[s].x), e1 = __uint_as_float(y[s].y);
-                        const float e2 = __uint_as_float(y[s].z), e3 = __uint_as_float(y[s].w);
-                        s2 = fmaf(e0, e0, s2);
-                        s2 = fmaf(e1, e1, s2);
-                        s2 = fmaf(e2, e2, s2);
-                        s2 = fmaf(e3, e3, s2);
-                    }
-                    s2 += __shfl_xor(s2, 16);
-                    s2 += __shfl_xor(s2, 32);
+                for (int s = WHOLE; s < S4; ++s)
+                    if (16 * s + 4 * lh >= a.d) now[s] = make_uint4(0, 0, 0, 0);
+            if constexpr (NORMS == QuadNorms::kOwn) {
+                float s2 = 0.f;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) yn[i] = __shfl(s2, 4 * lh + i);
+                for (int s = 0; s < S4; ++s) {
+                    const float e0 = __uint_as_float(now[s].x), e1 = __uint_as_float(now[s].y);
+                    const float e2 = __uint_as_float(now[s].z), e3 = __uint_as_float(now[s].w);
+                    s2 = fmaf(e0, e0, s2);
+                    s2 = fmaf(e1, e1, s2);
+                    s2 = fmaf(e2, e2, s2);
+                    s2 = fmaf(e3, e3, s2);
                 }
+                s2 += __shfl_xor(s2, 16);
+                s2 += __shfl_xor(s2, 32);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) add[i] = __shfl(s2, 4 * lh + i);
             }
             floatx4 acc[QB];
 #pragma unroll
@@ -117,15 +136,25 @@ __global__ __launch_bounds__(256) void quad_min_kernel(QuadArgs a) {
 #pragma unroll
             for (int s = 0; s < S4; ++s)
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) acc[qb] = OpF32::mma(acc[qb], y[s], q[qb][s]);
+                for (int qb = 0; qb < QB; ++qb) acc[qb] = OpF32::mma(acc[qb], now[s], q[qb][s]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) add[i] = r + i < a.nb ? add[i] : INFINITY;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 float m = INFINITY;
+                bool first = false;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float sc = L2 ? fmaf(-2.f, acc[qb][i], yn[i]) : -acc[qb][i];
-                    m = fminf(m, r + i < a.nb ? sc : INFINITY);
+                    const float sc = fmaf(L2 ? -2.f : -1.f, acc[qb][i], add[i]);
+                    // A NaN is left out, as by the fused search, but for two kinds:
+                    // rows whose norm and product overflow (their direct distance
+                    // may not), and, beside rows with a score, inner products whose
+                    // NaN has a key before all numbers.
+                    first |= sc != sc && r + i < a.nb &&
+                             (L2 ? add[i] == INFINITY : !(__float_as_uint(acc[qb][i]) >> 31));
+                    m = fminf(m, sc);
                 }
+                if (first && (L2 || m < INFINITY)) m = -INFINITY;
                 least[qb][b] = m;
             }
         }
@@ -137,6 +166,28 @@ __global__ __launch_bounds__(256) void quad_min_kernel(QuadArgs a) {
                     make_float4(least[qb][0], least[qb][1], least[qb][2], least[qb][3]);
         }
     }
+}
+
+// Whether row r is a candidate beside the others of its group: not one whose norm
+// is NaN, nor one that the caller left out by an infinite norm (an infinite norm
+// that the row itself has does not leave it out).
+__device__ __forceinline__ bool has_score(const float* __restrict__ yn,
+                                          const float* __restrict__ xb, int64_t r, int32_t d) {
+    if (!yn || yn[r] < INFINITY) return true;
+    if (yn[r] != INFINITY) return false;
+    float s = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < d; ++t) s = fmaf(xb[r * d + t], xb[r * d + t], s);
+    return s == INFINITY;
+}
+
+// Row r in the place of its group's key; whether its direct value counts: a NaN only
+// where it made its group the first of the inner products.
+__device__ __forceinline__ uint64_t row_key(uint64_t group, int64_t r) {
+    return (group & ~0xFFFFFFFFull) | (uint64_t)r;
+}
+__device__ __forceinline__ bool is_distance(float v, uint64_t key, int32_t l2) {
+    return v == v || (!l2 && key_score(key) == -INFINITY);
 }
 
 // Steps 2 and 3 by a workgroup per query: the kq best groups, from the row of group minima itself
@@ -180,8 +231,7 @@ __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
         row[j] = kSentinel;
         if (e >= n || pool[e >> 2] == kSentinel) continue;
         const int64_t r = 4 * (int64_t)key_index(pool[e >> 2]) + (e & 3);
-        // (a row without a finite norm has no score: it was no candidate)
-        if (r < nb && (!yn || yn[r] < INFINITY)) row[j] = (uint64_t)r;
+        if (r < nb && has_score(yn, xb, r, d)) row[j] = row_key(pool[e >> 2], r);
     }
     __syncthreads();
 #pragma unroll
@@ -195,13 +245,13 @@ __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
     for (int e0 = 16 * (tid >> 6); e0 < n; e0 += 16 * kPoolWaves)
         rerank_rows16(xs, pool, e0, n, xb, d, vec, l2, dist);
     __syncthreads();
-    // live rows to the front (a NaN is no distance)
+    // live rows to the front
     uint64_t key[N / kPoolThreads];
 #pragma unroll
     for (int j = 0; j < N / kPoolThreads; ++j) {
         const int e = j * kPoolThreads + tid;
         key[j] = kSentinel;
-        if (e < n && pool[e] != kSentinel && dist[e] == dist[e])
+        if (e < n && pool[e] != kSentinel && is_distance(dist[e], pool[e], l2))
             key[j] = make_key(l2 ? dist[e] : -dist[e], (uint32_t)pool[e]);
     }
     __syncthreads();
@@ -265,9 +315,8 @@ __global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_wave(
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int64_t r = 4 * (int64_t)key_index(group) + j;
-            // (a row without a finite norm has no score: it was no candidate)
             kl[wave][4 * lane + j] =
-                group != kSentinel && r < nb && (!yn || yn[r] < INFINITY) ? (uint64_t)r : kSentinel;
+                group != kSentinel && r < nb && has_score(yn, xb, r, d) ? row_key(group, r) : kSentinel;
         }
     }
     __builtin_amdgcn_wave_barrier();
@@ -281,8 +330,7 @@ __global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_wave(
     for (int e0 = 0; e0 < n; e0 += 64) {
         const int e = e0 + lane;
         uint64_t key = kSentinel;
-        // (a NaN is no distance)
-        if (e < n && kl[wave][e] != kSentinel && dist[wave][e] == dist[wave][e])
+        if (e < n && kl[wave][e] != kSentinel && is_distance(dist[wave][e], kl[wave][e], l2))
             key = make_key(l2 ? dist[wave][e] : -dist[wave][e], (uint32_t)kl[wave][e]);
         if (ws.push(key)) ws.merge();
     }
@@ -293,8 +341,13 @@ __global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_wave(
 template <int DP, int QB>
 mk_status launch_quads(const QuadArgs& a, bool vec, bool l2, int64_t waves, hipStream_t s) {
     ProfScope prof("dense_quads", s);
-    auto kern = vec ? (l2 ? quad_min_kernel<DP, QB, true, true> : quad_min_kernel<DP, QB, true, false>)
-                    : (l2 ? quad_min_kernel<DP, QB, false, true> : quad_min_kernel<DP, QB, false, false>);
+    auto of = [&](auto v) {
+        constexpr bool V = decltype(v)::value;
+        return !l2    ? quad_min_kernel<DP, QB, V, QuadNorms::kNone>
+               : a.yn ? quad_min_kernel<DP, QB, V, QuadNorms::kGiven>
+                      : quad_min_kernel<DP, QB, V, QuadNorms::kOwn>;
+    };
+    auto kern = vec ? of(std::true_type{}) : of(std::false_type{});
     hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(waves, 4)), dim3(256), 0, s, a);
     MK_LAUNCHED();
     return MK_OK;
@@ -303,11 +356,13 @@ mk_status launch_quads(const QuadArgs& a, bool vec, bool l2, int64_t waves, hipS
 template <int DP>
 mk_status quads(QuadArgs a, bool vec, bool l2, hipStream_t s) {
     // query blocks of 64 (32 for wide rows), or 16 when that is all there is
-    constexpr int WIDE = DP > 128 ? 2 : 4;
+    constexpr int WIDE = DP > 96 ? 2 : 4;
     const int qb = a.nq <= 16 ? 1 : WIDE;
     a.nqb = (int32_t)ceil_div(a.nq, 16 * qb);
-    // about 8 waves per SIMD's worth, of at least one group each
-    a.groups_per_wave = std::max<int64_t>(1, a.groups * a.nqb / 8192);
+    // few queries: long runs of rows per wave (one query, 10^6 x 64 rows, 2 waves per
+    // SIMD's worth 68 us, 8 waves 82); more: four, for an even end
+    a.groups_per_wave = qb == 1 ? ceil_div(a.groups, 2048)
+                                : std::max<int64_t>(1, a.groups * a.nqb / 4096);
     const int64_t waves = ceil_div(a.groups, a.groups_per_wave) * a.nqb;
     return qb == 1 ? launch_quads<DP, 1>(a, vec, l2, waves, s)
                    : launch_quads<DP, WIDE>(a, vec, l2, waves, s);
@@ -361,7 +416,9 @@ mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float
         MK_TRY(kselect_segments(least, nq, ld, kq, seg_len, lists, s));
     }
     ProfScope prof("dense_finish", s);
-    if (kq <= 64 && nseg == 1 && nq >= 1024) {
+    // (a wave takes 64 minima in the time that a workgroup takes 1,024: 1,024 queries,
+    // 8,192 minima 55 us more, 10^4 queries, 1,024 minima 57 us less)
+    if (kq <= 64 && nseg == 1 && nq >= 1024 && 2 * nq >= ld) {
         hipLaunchKernelGGL(quad_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, s, least, ld, nq, kq, xq, xb,
                            l2 ? yn : nullptr, nb, d, (int32_t)vec, (int32_t)l2, k, D, I);

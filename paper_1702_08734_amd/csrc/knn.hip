@@ -104,7 +104,7 @@ mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* 
         if (st != MK_ERR_OOM) return st;
         (void)hipGetLastError();
     }
-    if (!arena && !lend && sieve_pays(nq, nb, k + kSlack)) {
+    if (!arena && !lend && sieve_pays(nq, nb, k + kSlack) && !dense_beats_sieve(nq, nb, d, k)) {
         // batches of queries bound the scratch memory; without room for it
         // the fused search below, which needs less, takes the call
         const int64_t batch = sieve_batch(nq, nb, k + kSlack);

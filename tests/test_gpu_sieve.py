@@ -284,3 +284,23 @@ def test_dense_selection(api, nq, nb, d, k):
         d64 = ((xq[i].astype(np.float64) - xb[rows]) ** 2).sum(1)
         order = np.argsort(d64, kind="stable")[:k]  # integers: exact, ties by row
         assert (I[i] == rows[order]).all() and (D[i] == d64[order]).all(), i
+
+
+# few queries go through the small-side search, many through the threshold-first
+# one: the same rows and distances, whatever the granules of a row and the norms
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("d", [8, 30, 64, 100, 128, 132])
+@pytest.mark.parametrize("given", [False, True])
+def test_dense_equals_sieve(api, d, given, metric):
+    rng = np.random.default_rng(d)
+    nb, k = 70_003, 30
+    xb, xq = mixture(rng, nb, d), mixture(rng, 2000, d)
+    if metric == "l2":  # (no distance; a NaN inner product has no place in the order)
+        xb[5, 0], xb[nb - 2, d - 1] = np.nan, np.nan
+    xb_d, xq_d = dev(xb), dev(xq)
+    yn = api.norms(xb_d) if given and metric == "l2" else None
+    D, I = api.knn_search(xq_d, xb_d, k, metric, yn)
+    for nq in (1, 15, 17, 65):
+        D2, I2 = api.knn_search(xq_d[:nq].contiguous(), xb_d, k, metric, yn)
+        assert torch.equal(torch.nan_to_num(D2, 0, 1e38, -1e38), torch.nan_to_num(D[:nq], 0, 1e38, -1e38))
+        assert torch.equal(I2, I[:nq])
