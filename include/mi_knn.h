@@ -93,9 +93,10 @@ mk_status mk_kselect(const float* a, int64_t nrows, int64_t len, int32_t k, int3
 
 /*
  * Exact k-NN search (Section 2 Eq. 1-2; Section 5.1): distances of every
- * query to every database row, with the q.y GEMM term computed by FP32 MFMA
- * tiles whose outputs feed a register-resident k-selection in the same
- * kernel, followed by a merge of database-chunk partial results.
+ * query to every database row.  Large calls score rows by matrix products of FP16
+ * pairs against sampled thresholds, with a proof for every query; few queries or
+ * rows, and queries without a proof, by FP32 MFMA products.  The results are the
+ * same.
  *   xq [nq, d] float32, xb [nb, d] float32
  *   D  [nq, k] float32 -- squared L2 (ascending) or inner product
  *                         (descending), recomputed in the direct form
@@ -105,7 +106,11 @@ mk_status mk_kselect(const float* a, int64_t nrows, int64_t len, int32_t k, int3
  * The selection keeps extra candidates beyond k (up to the 1024-entry
  * selector) and re-ranks them by the direct form, which removes the
  * cancellation error of ||x||^2 + ||y||^2 - 2<x,y>.  nb must be < 2^31.
- * Supported d: 1..256.  Scratch (device): nq x nchunks x S keys of 8 bytes,
+ * Supported d: 1..256.  Scratch (device), large calls: 4 DP bytes per query and per
+ * row (DP: d rounded up to 32, 64, 96, 128 or 256; at most 512 MiB of rows at a
+ * time), pools of a few times k + 16 keys and at most 1 GiB per batch of queries;
+ * small calls: about nb bytes per query, at most 512 MiB.  Where that cannot be
+ * allocated the fused search takes the call: nq x nchunks x S keys of 8 bytes,
  * nchunks <= 16, S = 64 R with R the smallest power of two such that 64 R
  * >= min(k + 16, 1024), doubled when 64 R >= 256 (candidate pools); plus
  * 16 bytes per (query, chunk) of shared rank points and, for L2 without

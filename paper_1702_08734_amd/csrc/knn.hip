@@ -1,6 +1,9 @@
 // Exact k-NN search (Section 2 Eq. 1-2, Section 5.1).
 //
-// Layout of one call:
+// Which search takes a call: k = 1 with many queries and few rows the nearest-row
+// search, large calls the threshold-first one (both sieve.hpp), those with few
+// queries or few rows dense.hpp's, and everything else -- and calls with a caller's
+// workspace, and queries that the others cannot prove -- the fused search:
 //   1. norms: ||y||^2 per database row (one pass, Eq. 2), skipped for inner
 //      products or when the caller supplies them;
 //   2. knn_fused (fused.hpp): the grid is (query block) x (database chunk).

@@ -113,6 +113,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     a.cap = w.cap;
     a.thr = top + (plan.rank - 1);
     a.thr_ld = plan.rank;
+    a.tail = std::log((float)keff / (float)k) / std::log((float)plan.rank);
     a.scores = scores;
     a.ld = plan.sample / S::PER;
     auto launch = [&](bool sample, const void* r, const float* ya, const float* yb, int64_t n,

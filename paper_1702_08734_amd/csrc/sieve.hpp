@@ -129,6 +129,7 @@ struct SieveArgs {
     int32_t nchunks, nqb;
     const float* thr;     // filter: threshold of query q at thr[q * thr_ld]
     int64_t thr_ld;
+    float tail;           // filter (split, L2): see the queries without a chance below
     uint32_t* cnt;        // filter: [nq] keys appended (may exceed cap)
     uint64_t* pool;       // filter: [nq][cap] keys
     uint32_t cap;
@@ -263,7 +264,28 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
         sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
         thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        // Queries without a chance of a proof: far from the origin the error bound of
+        // the scores is more than the k-th and the keff-th best row lie apart.  These
+        // are about ln(keff / k) / ln(rank) of the sample's best `rank` scores apart
+        // (their number grows exponentially); where that is less than the bound, no
+        // row is let through, the finish finds too few, and a block of such queries
+        // ends here.  2,000 queries, 10^6 x 64 rows 100 standard deviations from the
+        // origin, k = 100: 5.1 ms, 5.7 without this, 4.9 by the fused search alone.
+        // (Twice the bound gives up many that are proven: 10 deviations, k = 1,000 7.5
+        // against 4.7 ms.)
+        if constexpr (FILTER && L2 && PL > 1)
+            if (ok) {
+                const float* t = args.thr + q * args.thr_ld;
+                if ((t[0] - t[1 - args.thr_ld]) * args.tail < 2.f * kSplitErr * args.qnorm[q])
+                    thr[qb] = -INFINITY;
+            }
         if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
+    }
+    if constexpr (FILTER && L2 && PL > 1) {
+        bool any = false;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) any |= thr[qb] > -INFINITY;
+        if (!__syncthreads_or(any)) return;
     }
     if (FILTER && threadIdx.x == 0) flush_at = -1;
 
