@@ -304,3 +304,15 @@ def test_dense_equals_sieve(api, d, given, metric):
         D2, I2 = api.knn_search(xq_d[:nq].contiguous(), xb_d, k, metric, yn)
         assert torch.equal(torch.nan_to_num(D2, 0, 1e38, -1e38), torch.nan_to_num(D[:nq], 0, 1e38, -1e38))
         assert torch.equal(I2, I[:nq])
+
+
+# both sides of the host-resident search's choice for a chunk
+@pytest.mark.parametrize("nq", [3500, 3501])
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+def test_host_chunks_alike(api, nq, metric):
+    rng = np.random.default_rng(nq)
+    xb = torch.from_numpy(mixture(rng, 60_000, 40)).pin_memory()
+    xq = dev(mixture(rng, nq, 40))
+    D, I = api.knn_search_host(xq, xb, 12, metric, 25_000)
+    D2, I2 = api.knn_search(xq, xb.cuda(), 12, metric)
+    assert torch.equal(D, D2) and torch.equal(I, I2)
