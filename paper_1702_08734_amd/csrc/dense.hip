@@ -168,19 +168,6 @@ quad_min_kernel(QuadArgs a) {
     }
 }
 
-// Whether row r is a candidate beside the others of its group: not one whose norm
-// is NaN, nor one that the caller left out by an infinite norm (an infinite norm
-// that the row itself has does not leave it out).
-__device__ __forceinline__ bool has_score(const float* __restrict__ yn,
-                                          const float* __restrict__ xb, int64_t r, int32_t d) {
-    if (!yn || yn[r] < INFINITY) return true;
-    if (yn[r] != INFINITY) return false;
-    float s = 0.f;
-#pragma unroll 1
-    for (int t = 0; t < d; ++t) s = fmaf(xb[r * d + t], xb[r * d + t], s);
-    return s == INFINITY;
-}
-
 // Row r in the place of its group's key; whether its direct value counts: a NaN only
 // where it made its group the first of the inner products.
 __device__ __forceinline__ uint64_t row_key(uint64_t group, int64_t r) {

@@ -1397,6 +1397,19 @@ __device__ __forceinline__ void rerank_rows16(const float* xw, const uint64_t* k
     }
 }
 
+// Whether row r is a candidate beside the others of its group of four, which was
+// kept for one row's score: not one whose norm is NaN, nor one that the caller left
+// out by an infinite norm (an infinite norm that the row itself has does not leave
+// it out).  yn: the supplied norms, or null.
+__device__ __forceinline__ bool has_score(const float* __restrict__ yn,
+                                          const float* __restrict__ xb, int64_t r, int32_t d) {
+    if (!yn || yn[r] < INFINITY) return true;
+    if (yn[r] != INFINITY) return false;
+    float s = 0.f;
+#pragma unroll 1
+    for (int t = 0; t < d; ++t) s = fmaf(xb[r * d + t], xb[r * d + t], s);
+    return s == INFINITY;
+}
 
 // The first k of a wave's sorted (score, row) keys as distances (L2) or
 // inner products and row ids; sentinels become (+-inf, -1).

@@ -201,7 +201,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
         MK_LAUNCHED();
     }
     hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
-                       xq, nq, xb, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, D, I);
+                       xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, D, I);
     MK_LAUNCHED();
     return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I, s, nullptr,
                               flags);

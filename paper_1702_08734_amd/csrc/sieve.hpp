@@ -909,11 +909,12 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
 // Nearest row of each query from kNearest's groups (L2): the rows of the best
 // group, in the direct form, and those of the second only when the first
 // distance does not clear its score; flagged when the rest's bound is not
-// cleared either (the bound: see sieve_finish).  16 lanes per row as in
-// rerank_rows16, so the same distances; a wave does four queries at a time.
+// cleared either (the bound: see sieve_finish).  Rows that the supplied norms yn
+// (or null) leave out are no candidates, as they had no score.  16 lanes per row as
+// in rerank_rows16, so the same distances; a wave does four queries at a time.
 static __global__ __launch_bounds__(256) void nearest_finish(
     const uint4* __restrict__ near, const float* __restrict__ xq, int64_t nq,
-    const float* __restrict__ xb, int32_t nb, int32_t d, int32_t vec,
+    const float* __restrict__ xb, const float* __restrict__ yn, int32_t nb, int32_t d, int32_t vec,
     const float* __restrict__ qnorm, const uint32_t* __restrict__ bad_db,
     uint32_t* __restrict__ flags, float* __restrict__ D, int64_t* __restrict__ I) {
     constexpr int NQ = 4;
@@ -930,7 +931,7 @@ static __global__ __launch_bounds__(256) void nearest_finish(
 #pragma unroll
         for (int p = 0; p < NQ; ++p) {
             const int64_t row = (int64_t)g[p] * 4 + rsel;
-            live[p] = q0 + p < nq && row < nb;
+            live[p] = q0 + p < nq && row < nb && has_score(yn, xb, row, d);
             x[p] = xq + (q0 + p < nq ? q0 + p : q0) * d;
             y[p] = xb + (live[p] ? row : 0) * d;
             acc[p] = 0.f;

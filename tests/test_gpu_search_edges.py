@@ -1,0 +1,53 @@
+"""GPU parity of the exact searches where their routes meet: calls on both sides of a
+routing rule, rows left out by supplied norms, database slabs and query batches, data
+on which few or all queries lack a proof."""
+import numpy as np
+import pytest
+
+import oracle
+from band import check_rows
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def api():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1702_08734_amd import api as a
+    a.lib()
+    return a
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def mixture(rng, n, d):
+    mu = 2.0 * np.random.default_rng(d).standard_normal((50, d))
+    return (mu[rng.integers(0, 50, n)] + rng.standard_normal((n, d))).astype(np.float32)
+
+
+# k = 1 on both sides of the nearest-row search's 8,192 queries: rows that the caller
+# left out by an infinite or NaN norm are never the answer, though queries equal them
+# and every group of four rows holds one with a score
+@pytest.mark.parametrize("left_out", [float("inf"), float("nan")])
+@pytest.mark.parametrize("nq", [8191, 8192])
+@pytest.mark.parametrize("d", [30, 64, 200])
+def test_nearest_rows_left_out(api, d, nq, left_out):
+    rng = np.random.default_rng(d)
+    nb = 4099
+    xb, xq = mixture(rng, nb, d), mixture(rng, nq, d)
+    xb[1::2] = xb[:-1:2] + np.float32(0.01) * rng.standard_normal((nb // 2, d)).astype(np.float32)
+    xq[:2000] = xb[1:4001:2]
+    yn = api.norms(dev(xb))
+    yn[1::2] = left_out
+    print(f"nearest rows left out d={d} nq={nq} {left_out}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), 1, "l2", yn)
+    D, I = D.cpu().numpy(), I.cpu().numpy()
+    assert (I % 2 == 0).all()
+    rows = np.arange(0, nq, 61)
+    fails = check_rows(D[rows], I[rows] // 2, xq, np.ascontiguousarray(xb[::2]), rows, 1, "l2")
+    assert not fails, fails[:10]
