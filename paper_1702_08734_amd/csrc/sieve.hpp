@@ -31,10 +31,9 @@
 // every product at a third of the FP16 rate, 5 times the FP32 matrix rate.
 #pragma once
 
-#include <cmath>
-
 #include "fused.hpp"
 #include "pool.hpp"
+#include "sieve_plan.hpp"
 
 namespace mk {
 
@@ -111,9 +110,6 @@ struct SieveShape {
     static constexpr int LPW = BN * GR / (64 * WAVES);  // tile loads per wave
     static_assert(GRP % 4 == 0 && BN * GR % (64 * WAVES) == 0, "tile loads split evenly");
 };
-
-// rows of one chunk are staged as this many bits
-constexpr int kSieveRowBits = 25;
 
 struct SieveArgs {
     const void* xq;       // queries, rows of `stride` bytes
@@ -231,13 +227,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int lane = lane_id();
     const int li = lane & 15, lh = lane >> 4;
     const int qg = wave & 3, rg = wave >> 2;
-    // rows of a launch fit 31 bits
-    const int c0 = (int)(chunk * args.chunk_len);
-    const int c1 = (int)(c0 + args.chunk_len < args.nb ? c0 + args.chunk_len : args.nb);
-    const int nsteps = c1 > c0 ? (c1 - c0 + BN - 1) / BN : 0;
+    // rows are counted from the chunk's first one (below 2^kSieveRowBits)
+    const int64_t c0 = chunk * args.chunk_len;
+    const int len = (int)(c0 + args.chunk_len < args.nb ? args.chunk_len : args.nb - c0);
+    const int nsteps = len > 0 ? (len + BN - 1) / BN : 0;
     // (a split row is exactly its planes)
     const int row_bytes = PL > 1 ? GR * 16 : args.stride;
-    const unsigned char* xb = static_cast<const unsigned char*>(args.xb);
+    const unsigned char* xb = static_cast<const unsigned char*>(args.xb) + c0 * row_bytes;
 
     // ---- this wave's queries: operands, scale factors, thresholds
     uint4 qreg[QB][PL * S4];
@@ -335,7 +331,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     auto load_tile = [&](int t0, int buf) __attribute__((always_inline)) {
         const uint32_t base = tiles_lds + (uint32_t)(buf * BN * GR * 16 + wave * 64 * 16);
         const unsigned char* tile = xb + (int64_t)t0 * row_bytes;
-        if (t0 + BN <= c1) {
+        if (t0 + BN <= len) {
 #pragma unroll
             for (int t = 0; t < LPW; ++t) {
                 const uint32_t dst = base + (uint32_t)(t * S::WAVES * 64 * 16);
@@ -345,7 +341,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     dma16(tile, loff[t], dst);
             }
         } else {  // rows past the end repeat the last one
-            const int last = c1 - 1 - t0;
+            const int last = len - 1 - t0;
 #pragma unroll
             for (int t = 0; t < LPW; ++t) {
                 int j, cc;
@@ -358,8 +354,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (wave < SIDE_OPS) {
                 constexpr int PER = (BN + 63) / 64;
                 const int a = wave / PER, part = wave % PER;
-                const float* src = (Op::SCALED && a == 0) ? args.ya : args.yb;
-                const int last = c1 - 1 - t0;
+                const float* src = ((Op::SCALED && a == 0) ? args.ya : args.yb) + c0;
+                const int last = len - 1 - t0;
                 int j = part * 64 + lane;
                 j = j < last ? j : last;
                 const uint32_t dst = side_lds + (uint32_t)(((buf * NSIDE + a) * BN + part * 64) * 4);
@@ -401,11 +397,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     c[u] = cscore[wave][i];
                     meta[u] = cmeta[wave][i];
                     const uint32_t ql = meta[u] >> kRowBits;
-                    const int row = c0 + (int)(meta[u] & ((1u << kRowBits) - 1u));
+                    const int row = (int)(meta[u] & ((1u << kRowBits) - 1u));
                     const float t = lthr[qg * QB * 16 + ql];
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        take[u] |= (c[u][e] <= t && row + e < c1) ? 1u << e : 0u;
+                        take[u] |= (c[u][e] <= t && row + e < len) ? 1u << e : 0u;
                     if (take[u]) pos[u] = atomicAdd(&args.cnt[qw0 + ql], (uint32_t)__popc(take[u]));
                 }
             }
@@ -427,8 +423,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
 
     __builtin_amdgcn_s_waitcnt(0);
-    if (nsteps > 0) load_tile(c0, 0);
-    if (nsteps > 1) load_tile(c0 + BN, 1);
+    if (nsteps > 0) load_tile(0, 0);
+    if (nsteps > 1) load_tile(BN, 1);
     if (nsteps > 1)
         wait_tile();
     else
@@ -471,12 +467,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 least[qb] = fminf(least[qb], m);
             }
         } else if constexpr (NEAREST) {
-            if (row - 4 * lh + 16 > c1) {  // (wave-uniform) rows past the end
+            if (row - 4 * lh + 16 > len) {  // (wave-uniform) rows past the end
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (row + i >= c1) sc[qb][i] = INFINITY;
+                        if (row + i >= len) sc[qb][i] = INFINITY;
             }
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
@@ -502,7 +498,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         if constexpr (RAW) v = -v;
                         cscore[wave][pos] = v;
                         cmeta[wave][pos] =
-                            ((uint32_t)(qb * 16 + li) << kRowBits) | (uint32_t)(row - c0);
+                            ((uint32_t)(qb * 16 + li) << kRowBits) | (uint32_t)row;
                     }
                     staged += (uint32_t)__popcll(bal);
                 }
@@ -515,7 +511,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // Blocks are software-pipelined: the scores of one block (vector ALU) are
     // computed between the matrix products of the next, which leave three
     // issue slots of four free; the first block of the loop tests an empty
-    // predecessor (row c1: every row past the end).  Not where the operands of
+    // predecessor (row len: every row past the end).  Not where the operands of
     // one block leave no registers for it.
     constexpr bool PIPE = FILTER && PL * S4 * (QB + 1) * 4 <= 160;
     constexpr int VPM = Op::MMAS == 3 ? 2 : 4;  // vector operations per product
@@ -523,11 +519,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) prev[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
     floatx4 pav = floatx4{0.f, 0.f, 0.f, 0.f}, pbv = floatx4{INFINITY, INFINITY, INFINITY, INFINITY};
-    int prow = c1;
+    int prow = len;
     int buf = 0;
 #pragma unroll 1
     for (int s = 0; s < nsteps; ++s) {
-        const int t0 = c0 + s * BN;
+        const int t0 = s * BN;
         const bool issue = s + 2 < nsteps;
         if (issue) load_tile(t0 + 2 * BN, buf >= 1 ? buf - 1 : NBUF - 1);
 #pragma unroll
@@ -577,7 +573,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int qb = 0; qb < QB; ++qb) {
                 const int64_t q = q0 + (qg * QB + qb) * 16 + li;
                 if (q < args.nq)
-                    args.scores[q * args.ld + (int64_t)(t0 / BN) * (4 * S::RG) + rg * 4 + lh] = least[qb];
+                    args.scores[q * args.ld + (c0 / BN + s) * (4 * S::RG) + rg * 4 + lh] = least[qb];
                 least[qb] = INFINITY;
             }
         }
@@ -1038,82 +1034,5 @@ struct SieveScratch {
 mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, const float* xb,
                            int32_t d, bool vec, bool l2, int32_t k, int32_t keff, bool cert,
                            float* D, int64_t* I, hipStream_t s);
-
-// Sample size, threshold rank and pool capacity.  Of the keff best rows a
-// sample of fraction f holds about mu = f keff, so a rank of mu + 4.5
-// sqrt(mu) + 4.5 leaves a chance of about 1e-8 that the threshold admits fewer
-// than keff rows; it admits about r / f, and more than cap with a chance under
-// 1e-8.  Scoring a sample row costs a query about as much as a row of the
-// database, a row that passes about 40 times that: samples of the order of
-// the square root of the database (8192 rows of 2^18, twice as many for every
-// factor of four) keep both small.
-struct SievePlan {
-    int64_t sample;
-    int32_t rank;
-    int64_t cap;
-};
-inline SievePlan plan_sieve(int64_t nb, int32_t keff) {
-    SievePlan p;
-    p.sample = 8192;
-    for (int64_t n = 1ll << 18; n < nb && p.sample < 65536; n *= 4) p.sample *= 2;
-    while (p.sample > 1024 && p.sample * 8 > nb) p.sample /= 2;
-    const double f = (double)p.sample / (double)nb;
-    const double mu = f * keff;
-    const double r = std::ceil(mu + 4.5 * std::sqrt(mu) + 4.5);
-    p.rank = (int32_t)r;
-    p.cap = (int64_t)std::ceil((r + 6.0 * std::sqrt(r) + 9.0) / f);
-    p.cap = ceil_div(p.cap < nb ? p.cap : nb, 64) * 64;
-    return p;
-}
-
-// Chunks of the rows of one launch: whole rounds of one workgroup per CU.
-inline void plan_sieve_chunks(int64_t nqb, int64_t nb, int BN, int64_t* nchunks,
-                              int64_t* chunk_len) {
-    constexpr int64_t kCUs = 256;
-    const int64_t steps = ceil_div(nb, BN);
-    double best = 1e300;
-    int64_t pick = 1;
-    const int64_t least = ceil_div(nb, 1ll << kSieveRowBits);
-    for (int64_t w = 1; w <= 6; ++w) {
-        int64_t n = kCUs * w / nqb;
-        if (n < least) n = least;
-        if (n > steps) n = steps;
-        const int64_t rounds = ceil_div(nqb * n, kCUs);
-        // about 6 steps' worth to load the queries and fill the pipeline
-        const double cost = (double)rounds * ((double)ceil_div(steps, n) + 6.0);
-        if (cost < best) {
-            best = cost;
-            pick = n;
-        }
-    }
-    *chunk_len = ceil_div(steps, pick) * BN;
-    *nchunks = ceil_div(nb, *chunk_len);
-}
-
-// Whether the threshold-first search takes a call that keeps keff candidates:
-// the least scores of the sample (of up to 16 rows each) have to be several
-// times the rank taken of them.
-inline bool sieve_pays(int64_t nq, int64_t nb, int32_t keff) {
-    if (nb < 16384 || nq < 64 || nq * nb < (1ll << 24)) return false;
-    const SievePlan p = plan_sieve(nb, keff);
-    return p.sample >= 64ll * p.rank;
-}
-
-// Whether the nearest-row search (k = 1: k-means assignment, list assignment of
-// added rows) takes a call: enough queries to fill the chip with workgroups that
-// each stream every row, and few enough rows for one stream of them.
-inline bool nearest_pays(int64_t nq, int64_t nb) {
-    return nq >= 8192 && nb >= 256 && nb <= 65536 && nq * nb >= (1ll << 25);
-}
-
-// Queries per batch: at most 1 GiB of pools and of the sample's scores.
-inline int64_t sieve_batch(int64_t nq, int64_t nb, int32_t keff) {
-    const SievePlan p = plan_sieve(nb, keff);
-    int64_t b = (1ll << 30) / (8 * p.cap);
-    if (b > (1ll << 30) / p.sample) b = (1ll << 30) / p.sample;
-    b = b / 256 * 256;
-    if (b < 256) b = 256;
-    return nq < b ? nq : b;
-}
 
 }  // namespace mk
