@@ -177,37 +177,41 @@ __global__ void km_order(const int64_t* __restrict__ assign, int64_t n, int32_t 
         for (uint32_t t = seg[j]; t < seg[j + 1]; ++t) seg_cluster[t] = (uint32_t)j;
 }
 
-// d % 4 == 0, d <= 4 kBlock, 16-byte aligned rows.
+// d % 4 == 0, d <= 4 kBlock, 16-byte aligned rows.  Workgroups walk the stretches
+// (nlist may be 2^24 and more: a workgroup each would pass what a grid can hold).
 __global__ __launch_bounds__(kBlock) void km_segment_sums(
     const float* __restrict__ x, int32_t d, int32_t K, const uint32_t* __restrict__ first,
     const uint32_t* __restrict__ seg, const uint32_t* __restrict__ seg_cluster,
     const uint32_t* __restrict__ order, double* __restrict__ sums) {
     __shared__ double red[kBlock][4];
-    const uint32_t t = blockIdx.x;
-    if (t >= seg[K]) return;  // the grid covers the largest possible count
-    const uint32_t j = seg_cluster[t];
-    const uint32_t lo = first[j] + (t - seg[j]) * kSegRows;
-    const uint32_t hi = lo + kSegRows < first[j + 1] ? lo + kSegRows : first[j + 1];
+    const uint32_t segs = seg[K];
     const int gpr = d / 4, rows = kBlock / gpr;  // granules per row, rows at a time
     const int r = threadIdx.x / gpr, c = threadIdx.x % gpr;
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    if (r < rows) {
+#pragma unroll 1
+    for (uint32_t t = blockIdx.x; t < segs; t += gridDim.x) {
+        const uint32_t j = seg_cluster[t];
+        const uint32_t lo = first[j] + (t - seg[j]) * kSegRows;
+        const uint32_t hi = lo + kSegRows < first[j + 1] ? lo + kSegRows : first[j + 1];
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        if (r < rows) {
 #pragma unroll 4
-        for (uint32_t i = lo + r; i < hi; i += rows) {
-            const float4 v = *reinterpret_cast<const float4*>(x + (int64_t)order[i] * d + 4 * c);
-            s[0] += (double)v.x;
-            s[1] += (double)v.y;
-            s[2] += (double)v.z;
-            s[3] += (double)v.w;
+            for (uint32_t i = lo + r; i < hi; i += rows) {
+                const float4 v = *reinterpret_cast<const float4*>(x + (int64_t)order[i] * d + 4 * c);
+                s[0] += (double)v.x;
+                s[1] += (double)v.y;
+                s[2] += (double)v.z;
+                s[3] += (double)v.w;
+            }
         }
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = s[e];
-    __syncthreads();
-    for (int g = threadIdx.x; g < d; g += kBlock) {
-        double v = 0.0;
-        for (int q = 0; q < rows; ++q) v += red[q * gpr + g / 4][g % 4];
-        atomicAdd(&sums[(int64_t)j * d + g], v);
+        for (int e = 0; e < 4; ++e) red[threadIdx.x][e] = s[e];
+        __syncthreads();
+        for (int g = threadIdx.x; g < d; g += kBlock) {
+            double v = 0.0;
+            for (int q = 0; q < rows; ++q) v += red[q * gpr + g / 4][g % 4];
+            atomicAdd(&sums[(int64_t)j * d + g], v);
+        }
+        __syncthreads();
     }
 }
 
@@ -285,12 +289,18 @@ mk_status kmeans_update(const float* x, int64_t n, int32_t d, const int64_t* ass
     MK_HIP(hipMemsetAsync(cnt.ptr, 0, sizeof(unsigned long long) * (size_t)K, s));
     // long rows by cluster; short ones (a sub-quantizer's) are cheaper to add
     // where they belong than to gather (32-byte rows: 27 us for 500,000 x 8)
-    const bool by_cluster = d >= 32 && d % 4 == 0 && d <= 4 * kBlock && n >= 4096 &&
-                            n < (1ll << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    bool by_cluster = d >= 32 && d % 4 == 0 && d <= 4 * kBlock && n >= 4096 &&
+                      n < (1ll << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    const int64_t segs = ceil_div(n, kSegRows) + K;
+    Scratch words;
     if (by_cluster) {
-        const int64_t segs = ceil_div(n, kSegRows) + K;
-        Scratch words;
-        MK_TRY(words.alloc(sizeof(uint32_t) * (size_t)(4 * (int64_t)K + 2 + n + segs), s));
+        // (without room for the points' order the plain sums, which need none)
+        const mk_status st = words.alloc(sizeof(uint32_t) * (size_t)(4 * (int64_t)K + 2 + n + segs), s);
+        if (st != MK_OK && st != MK_ERR_OOM) return st;
+        if (st == MK_ERR_OOM) (void)hipGetLastError();
+        by_cluster = st == MK_OK;
+    }
+    if (by_cluster) {
         uint32_t* count = words.as<uint32_t>();
         uint32_t *cursor = count + K, *first = cursor + K, *seg = first + K + 1;
         uint32_t *order = seg + K + 1, *seg_cluster = order + n;
@@ -304,7 +314,7 @@ mk_status kmeans_update(const float* x, int64_t n, int32_t d, const int64_t* ass
         hipLaunchKernelGGL(km_order, dim3(grid_of(std::max<int64_t>(n, K))), dim3(kBlock), 0, s,
                            assign, n, K, cursor, order, seg, seg_cluster);
         MK_LAUNCHED();
-        hipLaunchKernelGGL(km_segment_sums, dim3((unsigned)segs), dim3(kBlock), 0, s, x, d, K, first,
+        hipLaunchKernelGGL(km_segment_sums, dim3((unsigned)std::min<int64_t>(segs, 1 << 16)), dim3(kBlock), 0, s, x, d, K, first,
                            seg, seg_cluster, order, sums.as<double>());
         MK_LAUNCHED();
     } else if (n > 0) {
