@@ -71,10 +71,13 @@ mk_status mk_norms(const float* x, int64_t n, int32_t d, float* out, mk_stream_t
  *   x   [n, d] float32     rot [dout, d] float32 (a rotation: dout = d; a
  *                          projection: dout < d)     out [n, dout] float32
  * Device pointers, row-major; out must not overlap x (MK_ERR_INVALID_ARG).
- * FP32 matrix-core products, one fixed summation order per element, so the
- * result is deterministic; it errs from the exact product by at most about
- * d * 2^-24 * sum_t |rot[j][t] x[i][t]|.  Learning the rotation is not part
- * of the library.
+ * Matrix-core products of FP32 operands: on the FP32 units, or (24 <= d <= 128
+ * and 16,384 rows or more) of the operands as three BF16 numbers each that add
+ * up to them.  One fixed summation order per element, so the same call gives the
+ * same bits; in larger calls the last bits of a row may depend on n and on
+ * whether one of the 31 rows beside it has a component that the three numbers
+ * cannot hold.  Errs from the exact product by at most about d * 2^-24 *
+ * sum_t |rot[j][t] x[i][t]|.  Learning the rotation is not part of the library.
  */
 mk_status mk_rotate_rows(const float* x, int64_t n, int32_t d, const float* rot, int32_t dout,
                          float* out, mk_stream_t stream);

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void rotate_rows_kernel(const float* __restric
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-// x = h + m + l, three BF16 numbers (8 + 8 + 8 bits: exact for 2^-50 <= |x| <
+// x = h + m + l, three BF16 numbers (8 + 8 + 8 bits: exact for 2^-100 <= |x| <
 // 2^60 and zero).
 __device__ __forceinline__ void split3(const float (&v)[8], bf16x8& h, bf16x8& m, bf16x8& l) {
 #pragma unroll
@@ -115,10 +115,6 @@ __device__ __forceinline__ void split3(const float (&v)[8], bf16x8& h, bf16x8& m
         l[e] = (__bf16)(r - (float)m[e]);
     }
 }
-__device__ __forceinline__ bool splittable(float v) {
-    const float a = fabsf(v);
-    return a == 0.f || (a >= 0x1p-50f && a < 0x1p60f);
-}
 
 // Products of BF16 triples on v_mfma_f32_16x16x32_bf16: h h in one accumulator,
 // the five products of 2^-8 and 2^-16 of it in another (l l, m l and l m, under
@@ -126,24 +122,49 @@ __device__ __forceinline__ bool splittable(float v) {
 // sixteen times its rate, with FP32 accumulation.  The error against 64 bits is
 // smaller than the FP32 chain's (measured below).
 //
-// A workgroup keeps the triples of up to 96 KB of rot (128 x 128: all of it) in
-// LDS in operand order (A: 16 outputs) and walks the rows, 32 per wave and step
-// (B: lane = row; component 32 s + 16 half + 4 lh + e in slot 8 lh + 4 half + e,
-// so that each load takes 64 consecutive bytes of a row), the next rows' loads in
-// flight.  Lane (row, lh) ends up with outputs 4 lh .. 4 lh + 3: one 16-byte
-// store.  Rows with a component that the triples cannot hold (not finite, huge or
-// tiny) take FP32 products, a wave at a time.
+// A workgroup keeps the triples of up to 96 KB of rot (128 x 128: all of it; less
+// where the rows alone do not fill the chip) in LDS in operand order (16 outputs)
+// and walks the rows, 32 per wave and step (lane = row; component 32 s + 16 half +
+// 4 lh + e in slot 8 lh + 4 half + e, so that each load takes 64 consecutive bytes
+// of a row), the next rows' loads in flight.  Where 16-byte stores are aligned (kQuads)
+// rows are the columns of a product: lane (row, lh) ends up with outputs 4 lh ..
+// 4 lh + 3.  Others are its rows: lane li has output li of four rows.  These go out
+// as 64 consecutive bytes of a row at a time (kColumns) or, where a workgroup has
+// short rows whole, through LDS as the one block that 16 rows of the result are
+// (kBlocks: 2*10^6 x 64 rows, 57 outputs 318 -> 197 us).
 //
-// Bound by memory: 2*10^6 x 128 rows, 2 GB in and out, 779 -> 500 us (4.1 TB/s); error
-// against 64 bits 2.0e-7 -> 6.5e-8 of the largest value.
-template <int S, bool VEC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void rotate_split_kernel(
-    const float* __restrict__ x, int64_t n, int32_t d, const float* __restrict__ rot, int32_t dout,
-    float* __restrict__ out, int32_t tiles_per_wg, int32_t nchunks, int32_t vec_out) {
-    constexpr int NB = 2, WAVES = 8;
+// Triples hold a component exactly from 2^-100 on, and every product of parts stays
+// a normal number where the least |x| (zeros aside) times the least |rot| is 2^-100
+// or more; components below 2^60 cannot overflow.  Rows that are out of these
+// bounds take FP32 products, a wave (32 rows) at a time, with rot from LDS (one
+// component of 10^-17 in rot, 2*10^6 x 128 rows: 449 us, 2,023 with every such call
+// on products with rot from memory; 768 by the FP32 kernel).
+//
+// Bound by memory: 2*10^6 x 128 rows, 2 GB in and out, 447 us (4.6 TB/s), 765 by the
+// FP32 kernel; error against 64 bits 2.0e-7 -> 6.5e-8 of the largest value.
+enum RotateOut { kQuads, kColumns, kBlocks };
+template <int S, int OUT>
+struct SplitShape {
+    // two workgroups per CU where the registers allow it (64 outputs of 64 components,
+    // which they don't: 211 us with one, 229 with two and spills; 57 outputs 200, 197)
+    static constexpr int WPE = S == 1 || (S == 2 && OUT == kBlocks) ? 4 : 2, WAVES = 8, NB = 2;
+    static constexpr int TILE_BYTES = S * 3 * 1024;
+};
+constexpr uint32_t float_bits(int exponent) { return (uint32_t)(127 + exponent) << 23; }
+
+template <int S, bool VEC, int OUT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(SplitShape<S, OUT>::WPE, SplitShape<S, OUT>::WPE)))
+void rotate_split_kernel(const float* __restrict__ x, int64_t n, int32_t d,
+                         const float* __restrict__ rot, int32_t dout, float* __restrict__ out,
+                         int32_t tiles_per_wg, int32_t nchunks, int32_t vec_rot,
+                         int32_t vec_out) {
+    constexpr int NB = SplitShape<S, OUT>::NB, WAVES = SplitShape<S, OUT>::WAVES;
+    constexpr bool QUADS = OUT == kQuads;
+    constexpr int AHEAD = S <= 2 ? 2 : 4;  // operand blocks of rot in flight per wave
     extern __shared__ __align__(16) unsigned char smem[];
     bf16x8* planes = reinterpret_cast<bf16x8*>(smem);  // [tile][s][plane][lane]
-    __shared__ uint32_t rot_bad;
+    floatx4* whole = reinterpret_cast<floatx4*>(smem);  // [tile][s][half][lane], three planes apart
+    __shared__ uint32_t rot_least, rot_most;  // bits of |rot| (least: less one, zeros aside)
     const int lane = threadIdx.x & 63, li = lane & 15, lh = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunk = blockIdx.x % nchunks;
@@ -151,32 +172,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int t0 = chunk * tiles_per_wg;
     const int all = (dout + 15) / 16;
     const int ntiles = all - t0 < tiles_per_wg ? all - t0 : tiles_per_wg;
-    if (threadIdx.x == 0) rot_bad = 0u;
-    __syncthreads();
-    // component of slot e of step s
-    auto comp = [&](int s, int e) __attribute__((always_inline)) {
-        return 32 * s + 16 * (e >> 2) + 4 * lh + (e & 3);
-    };
-    for (int f = wave; f < ntiles * S; f += WAVES) {
-        const int tile = f / S, s = f % S;
-        const int j = (t0 + tile) * 16 + li;
-        float v[8];
-        bool ok = true;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int t = comp(s, e);
-            v[e] = j < dout && t < d ? rot[(int64_t)j * d + t] : 0.f;
-            ok = ok && splittable(v[e]);
-        }
-        if (!ok) rot_bad = 1u;
-        bf16x8 h, m, l;
-        split3(v, h, m, l);
-        planes[(f * 3 + 0) * 64 + lane] = h;
-        planes[(f * 3 + 1) * 64 + lane] = m;
-        planes[(f * 3 + 2) * 64 + lane] = l;
-    }
-    __syncthreads();
-    const bool rot_ok = rot_bad == 0u;
 
     float next[NB][S][8];
     auto load = [&](int64_t r0) __attribute__((always_inline)) {
@@ -205,50 +200,149 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 }
         }
     };
-    auto store = [&](int64_t row, int col, floatx4 v) __attribute__((always_inline)) {
-        if (row >= n) return;
-        float* o = out + row * dout + col;
-        if (vec_out && col + 4 <= dout) {
-            *reinterpret_cast<floatx4*>(o) = v;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (col + e < dout) o[e] = v[e];
-        }
-    };
     const int64_t step = nwg * WAVES * 16 * NB;
     const int64_t start = (wg * WAVES + wave) * 16 * NB;
     if (start < n) load(start);
+
+    // this lane's eight components of operand block f of rot
+    auto rot_block = [&](int f, float (&v)[8]) __attribute__((always_inline)) {
+        const int j = (t0 + f / S) * 16 + li;
+        const float* p = rot + (int64_t)j * d;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int t = 32 * (f % S) + 16 * half + 4 * lh;
+            if (vec_rot) {
+                float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (j < dout && t < d) w = *reinterpret_cast<const float4*>(p + t);
+                v[4 * half] = w.x;
+                v[4 * half + 1] = w.y;
+                v[4 * half + 2] = w.z;
+                v[4 * half + 3] = w.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * half + e] = j < dout && t + e < d ? p[t + e] : 0.f;
+            }
+        }
+    };
+    auto range = [&](float v, uint32_t& least, uint32_t& most) __attribute__((always_inline)) {
+        const uint32_t u = __float_as_uint(v) & 0x7FFFFFFFu;
+        least = min(least, u - 1u);  // (a zero: 2^32 - 1)
+        most = max(most, u);
+    };
+    if (threadIdx.x == 0) {
+        rot_least = ~0u;
+        rot_most = 0u;
+    }
+    __syncthreads();
+    {
+        uint32_t least = ~0u, most = 0u;
+#pragma unroll 1
+        for (int f0 = wave; f0 < ntiles * S; f0 += WAVES * AHEAD) {
+            float v[AHEAD][8];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                const int f = f0 + a * WAVES;
+                if (f < ntiles * S) rot_block(f, v[a]);
+            }
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) {
+                const int f = f0 + a * WAVES;
+                if (f >= ntiles * S) break;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) range(v[a][e], least, most);
+                bf16x8 h, m, l;
+                split3(v[a], h, m, l);
+                planes[(f * 3 + 0) * 64 + lane] = h;
+                planes[(f * 3 + 1) * 64 + lane] = m;
+                planes[(f * 3 + 2) * 64 + lane] = l;
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o *= 2) {
+            least = min(least, (uint32_t)__shfl_xor((int)least, o));
+            most = max(most, (uint32_t)__shfl_xor((int)most, o));
+        }
+        if (lane == 0) {
+            atomicMin(&rot_least, least);
+            atomicMax(&rot_most, most);
+        }
+    }
+    __syncthreads();
+    const bool rot_ok = rot_most < float_bits(60) && rot_least >= float_bits(-100) - 1u;
+    // |x| from here on (bits, less one)
+    uint32_t x_least = float_bits(-100) - 1u;
+    if (rot_ok && rot_least != ~0u) {
+        const int e = (int)((rot_least + 1u) >> 23) - 127;
+        if (e < 0) x_least = float_bits(-100 - e) - 1u;
+    }
+    if (!rot_ok) {  // rot itself in the triples' place
+        for (int f = wave; f < ntiles * S; f += WAVES) {
+            float v[8];
+            rot_block(f, v);
+            whole[f * 3 * 64 + lane] = floatx4{v[0], v[1], v[2], v[3]};
+            whole[(f * 3 + 1) * 64 + lane] = floatx4{v[4], v[5], v[6], v[7]};
+        }
+        __syncthreads();
+    }
+
+    // block b of a wave's rows, outputs of a tile
+    auto store = [&](int64_t r0, int tile, floatx4 v) __attribute__((always_inline)) {
+        const int64_t row = r0 + (QUADS ? li : 4 * lh);
+        const int col = (t0 + tile) * 16 + (QUADS ? 4 * lh : li);
+        if constexpr (QUADS) {
+            if (row < n && col < dout) *reinterpret_cast<floatx4*>(out + row * dout + col) = v;
+        } else if (col < dout) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (row + i < n) out[(row + i) * dout + col] = v[i];
+        }
+    };
+    auto mma = [&](floatx4 acc, bf16x8 a, bf16x8 b) __attribute__((always_inline)) {
+        return QUADS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, acc, 0, 0, 0);
+    };
 #pragma unroll 1
     for (int64_t r0 = start; r0 < n; r0 += step) {
-        bool ok = rot_ok;
+        uint32_t least = ~0u, most = 0u;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int s = 0; s < S; ++s)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) ok = ok && splittable(next[b][s][e]);
-        if (__ballot(!ok)) {
-            // FP32 products, rot from memory
+                for (int e = 0; e < 8; ++e) range(next[b][s][e], least, most);
+        if (!rot_ok || __ballot(least < x_least || most >= float_bits(60))) {
+            // FP32 products
 #pragma unroll 1
             for (int tile = 0; tile < ntiles; ++tile) {
-                const int j = (t0 + tile) * 16 + li;
                 floatx4 acc[NB];
 #pragma unroll
                 for (int b = 0; b < NB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < S; ++s)
+                for (int s = 0; s < S; ++s) {
+                    const int f = tile * S + s;
+                    float v[8];
+                    if (rot_ok) {
+                        const bf16x8 h = planes[(f * 3 + 0) * 64 + lane], m = planes[(f * 3 + 1) * 64 + lane],
+                                     l = planes[(f * 3 + 2) * 64 + lane];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int t = comp(s, e);
-                        const float a = j < dout && t < d ? rot[(int64_t)j * d + t] : 0.f;
+                        for (int e = 0; e < 8; ++e) v[e] = (float)h[e] + ((float)m[e] + (float)l[e]);
+                    } else {
+                        const floatx4 a = whole[f * 3 * 64 + lane], c = whole[(f * 3 + 1) * 64 + lane];
 #pragma unroll
-                        for (int b = 0; b < NB; ++b)
-                            acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, next[b][s][e], acc[b], 0, 0, 0);
+                        for (int e = 0; e < 4; ++e) {
+                            v[e] = a[e];
+                            v[4 + e] = c[e];
+                        }
                     }
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    store(r0 + b * 16 + li, (t0 + tile) * 16 + 4 * lh, acc[b]);
+                    for (int e = 0; e < 8; ++e)
+#pragma unroll
+                        for (int b = 0; b < NB; ++b)
+                            acc[b] = QUADS ? __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], next[b][s][e], acc[b], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_16x16x4f32(next[b][s][e], v[e], acc[b], 0, 0, 0);
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) store(r0 + b * 16, tile, acc[b]);
             }
             if (r0 + step < n) load(r0 + step);
             continue;
@@ -259,6 +353,46 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int s = 0; s < S; ++s) split3(next[b][s], h[b][s], m[b][s], l[b][s]);
         if (r0 + step < n) load(r0 + step);
+        if constexpr (OUT == kBlocks) {
+            float* stage = reinterpret_cast<float*>(planes + ntiles * S * 3 * 64) + wave * 16 * dout;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll 1
+                for (int tile = 0; tile < ntiles; ++tile) {
+                    const bf16x8* a = planes + (int64_t)tile * S * 3 * 64 + lane;
+                    floatx4 big = {0.f, 0.f, 0.f, 0.f}, rest = big;
+#pragma unroll
+                    for (int s = 0; s < S; ++s) {
+                        const bf16x8 ah = a[(s * 3 + 0) * 64], am = a[(s * 3 + 1) * 64], al = a[(s * 3 + 2) * 64];
+                        rest = mma(rest, al, h[b][s]);
+                        big = mma(big, ah, h[b][s]);
+                        rest = mma(rest, ah, l[b][s]);
+                        rest = mma(rest, am, m[b][s]);
+                        rest = mma(rest, am, h[b][s]);
+                        rest = mma(rest, ah, m[b][s]);
+                    }
+                    big += rest;
+                    if (tile * 16 + li < dout)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) stage[(4 * lh + i) * dout + tile * 16 + li] = big[i];
+                }
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                const int64_t row = r0 + b * 16, rows = n - row < 16 ? n - row : 16;
+                float* o = out + row * dout;
+                int e = lane;
+                if (vec_out) {  // (16 rows: a multiple of 64 bytes)
+                    const int quads = (int)rows * dout / 4;
+                    for (int g = lane; g < quads; g += 64)
+                        reinterpret_cast<floatx4*>(o)[g] = reinterpret_cast<const floatx4*>(stage)[g];
+                    e += 4 * quads;
+                }
+                for (; e < (int)rows * dout; e += 64) o[e] = stage[e];
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            }
+            continue;
+        }
 #pragma unroll 1
         for (int tile = 0; tile < ntiles; ++tile) {
             const bf16x8* a = planes + (int64_t)tile * S * 3 * 64 + lane;
@@ -268,43 +402,63 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int s = 0; s < S; ++s) {
                 const bf16x8 ah = a[(s * 3 + 0) * 64], am = a[(s * 3 + 1) * 64], al = a[(s * 3 + 2) * 64];
-#define MK_MFMA(acc, p, q) \
-    _Pragma("unroll") for (int b = 0; b < NB; ++b) \
-        acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p, q[b][s], acc[b], 0, 0, 0)
-                MK_MFMA(rest, al, h);
-                MK_MFMA(big, ah, h);
-                MK_MFMA(rest, ah, l);
-                MK_MFMA(rest, am, m);
-                MK_MFMA(rest, am, h);
-                MK_MFMA(rest, ah, m);
-#undef MK_MFMA
+#pragma unroll
+                for (int b = 0; b < NB; ++b) rest[b] = mma(rest[b], al, h[b][s]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) big[b] = mma(big[b], ah, h[b][s]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) rest[b] = mma(rest[b], ah, l[b][s]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) rest[b] = mma(rest[b], am, m[b][s]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) rest[b] = mma(rest[b], am, h[b][s]);
+#pragma unroll
+                for (int b = 0; b < NB; ++b) rest[b] = mma(rest[b], ah, m[b][s]);
             }
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
-                store(r0 + b * 16 + li, (t0 + tile) * 16 + 4 * lh, big[b] + rest[b]);
+            for (int b = 0; b < NB; ++b) store(r0 + b * 16, tile, big[b] + rest[b]);
         }
     }
+}
+
+template <int S, int OUT>
+mk_status rotate_split_as(const float* x, int64_t n, int32_t d, const float* rot, int32_t dout,
+                          float* out, bool vec, hipStream_t s) {
+    using Sh = SplitShape<S, OUT>;
+    // at most 96 KB of rot's triples per CU; where the rows give fewer workgroups
+    // than the chip takes, the outputs are shared out too, and each workgroup has
+    // less of rot to lay out
+    constexpr int64_t kWgs = 256 * (Sh::WPE / 2), kTiles = 98304 / (Sh::WPE / 2) / Sh::TILE_BYTES;
+    const int64_t all = ceil_div(dout, 16), rows = ceil_div(n, 16 * Sh::NB * Sh::WAVES);
+    int64_t nchunks = std::max(ceil_div(all, kTiles), std::min(all, kWgs / std::min(rows, kWgs)));
+    if (OUT == kBlocks) nchunks = 1;
+    const int32_t tiles = (int32_t)ceil_div(all, nchunks);
+    nchunks = ceil_div(all, tiles);
+    const int64_t wgs = std::min(std::max<int64_t>(kWgs / nchunks, 1), rows);
+    const size_t lds = (size_t)tiles * Sh::TILE_BYTES +
+                       (OUT == kBlocks ? sizeof(float) * Sh::WAVES * 16 * (size_t)dout : 0);
+    const bool vec_rot = d % 4 == 0 && reinterpret_cast<uintptr_t>(rot) % 16 == 0;
+    const bool vec_out = reinterpret_cast<uintptr_t>(out) % 16 == 0;
+    auto kern = vec ? rotate_split_kernel<S, true, OUT> : rotate_split_kernel<S, false, OUT>;
+    if (lds > 65536)
+        MK_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(wgs * nchunks)), dim3(512), lds, s, x, n, d, rot, dout,
+                       out, tiles, (int32_t)nchunks, (int32_t)vec_rot, (int32_t)vec_out);
+    MK_LAUNCHED();
+    return MK_OK;
 }
 
 template <int S>
 mk_status rotate_split(const float* x, int64_t n, int32_t d, const float* rot, int32_t dout,
                        float* out, bool vec, hipStream_t s) {
-    // at most 96 KB of rot's triples per workgroup, one workgroup per CU
-    constexpr int kTileBytes = S * 3 * 1024;
-    const int32_t all = (int32_t)ceil_div(dout, 16);
-    const int32_t nchunks = (int32_t)ceil_div(all, 98304 / kTileBytes);
-    const int32_t tiles = (int32_t)ceil_div(all, nchunks);
-    const int64_t wgs = std::min<int64_t>(std::max<int64_t>(256 / nchunks, 1), ceil_div(n, 256));
-    const size_t lds = (size_t)tiles * kTileBytes;
-    const bool vec_out = dout % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
-    auto kern = vec ? rotate_split_kernel<S, true> : rotate_split_kernel<S, false>;
-    if (lds > 65536)
-        MK_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(kern, dim3((unsigned)(wgs * nchunks)), dim3(512), lds, s, x, n, d, rot, dout,
-                       out, tiles, nchunks, (int32_t)vec_out);
-    MK_LAUNCHED();
-    return MK_OK;
+    if (dout % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0)
+        return rotate_split_as<S, kQuads>(x, n, d, rot, dout, out, vec, s);
+    // (two workgroups per CU with up to 64 outputs; of few rows each has a share of
+    // the outputs)
+    if constexpr (S <= 2)
+        if (dout <= 64 && n >= 65536) return rotate_split_as<S, kBlocks>(x, n, d, rot, dout, out, vec, s);
+    return rotate_split_as<S, kColumns>(x, n, d, rot, dout, out, vec, s);
 }
 
 }  // namespace
@@ -324,9 +478,13 @@ extern "C" mk_status mk_rotate_rows(const float* x, int64_t n, int32_t d, const 
     MK_REQUIRE(blocks < ((int64_t)1 << 32), MK_ERR_UNSUPPORTED, "too many rows for one call");
     const bool vec = d % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                      reinterpret_cast<uintptr_t>(rot) % 16 == 0;
-    // enough rows that a workgroup's set-up (rot into triples) is small beside
-    // them; rows of 128 components are what the registers hold; sums of a few
-    // products are rounded less often in FP32 (d = 1: once)
+    // Rows of 128 components are what the registers hold; sums of a few products are
+    // rounded less often in FP32 (d = 1: once).  From about 30,000 rows on faster
+    // (FP32 kernel, this one; 128 outputs of 128 components: 16,384 rows 10.4, 12.3 us,
+    // 30,000 rows 17.4, 14.2, 50,000 rows 25, 18, 200,000 rows 77, 57, 2*10^6 rows 765,
+    // 447; the worst of 24 to 128 components and 16 to 128 outputs: 100,000 x 64 rows,
+    // 57 outputs 16.0, 17.6, and 200,000 rows 26.7, 26.5); between 16,384 rows and that
+    // for its smaller error.
     if (d >= 24 && d <= 128 && n >= 16384) {
         const bool vx = d % 4 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0;
         const hipStream_t s = static_cast<hipStream_t>(stream);
