@@ -808,6 +808,12 @@ struct FusedShape {
     static_assert(BN == 64, "consumers take one column per lane");
 };
 
+// Chunks of a search over the queries that are left (written by rest_bounds_kernel).
+struct RestPlan {
+    int64_t chunk_len;
+    int32_t nq, nchunks, nqb, pad;
+};
+
 // Per-call arguments of the fused kernel.
 struct FusedArgs {
     const void* xq;       // queries, `stride` elements per row
@@ -825,8 +831,10 @@ struct FusedArgs {
     uint32_t* bound;
     // debug count of candidates a full pool had to drop (must stay zero)
     unsigned long long* drops;
-    // if given, only query blocks with a flagged query are searched
-    const uint32_t* qflag;
+    // if given, queries qlist[0 .. rest->nq) are searched, in the place of queries
+    // 0 .. nq - 1, with rest's chunks (fewer queries: more chunks each)
+    const uint32_t* qlist;
+    const RestPlan* rest;
 };
 
 template <class Op, int KR, int DP, bool VEC, bool L2>
@@ -914,6 +922,13 @@ knn_fused(FusedArgs args) {
     __shared__ uint32_t bins[S::mem_queues ? S::NC : 1][NBINS];
     __shared__ uint32_t urgent_flags[2][S::NC];
 
+    if (args.rest) {
+        args.nq = args.rest->nq;
+        args.nqb = args.rest->nqb;
+        args.nchunks = args.rest->nchunks;
+        args.chunk_len = args.rest->chunk_len;
+        if (blockIdx.x >= (uint32_t)(args.nqb * args.nchunks)) return;
+    }
     const int64_t logical = xcd_logical_id(blockIdx.x, (int64_t)args.nqb * args.nchunks);
     const int64_t chunk = logical / args.nqb;
     const int64_t qblk = logical % args.nqb;
@@ -923,10 +938,6 @@ knn_fused(FusedArgs args) {
     const int64_t q0 = qblk * BQ;
     const int64_t c0 = chunk * args.chunk_len;
     const int64_t c1 = c0 + args.chunk_len < args.nb ? c0 + args.chunk_len : args.nb;
-    if (args.qflag) {  // the same answer in every wave
-        const int64_t q = q0 + lane;
-        if (!__ballot(lane < BQ && q < args.nq && args.qflag[q] != 0u)) return;
-    }
     // 32-bit step counters (scalar compares): a chunk has fewer than 2^31 rows
     const int nsteps = c1 > c0 ? (int)((c1 - c0 + BN - 1) / BN) : 0;
     const int64_t row_bytes = (int64_t)args.stride * Op::BYTES;
@@ -1032,7 +1043,8 @@ knn_fused(FusedArgs args) {
         for (int qb = 0; qb < QPB; ++qb) {
             const int64_t q = q0 + (qg * QPB + qb) * 16 + li;
             const bool ok = q < args.nq;
-            const unsigned char* row = xq + (ok ? q : 0) * row_bytes;
+            const int64_t src = !ok ? 0 : args.rest ? (int64_t)args.qlist[q] : q;
+            const unsigned char* row = xq + src * row_bytes;
 #pragma unroll
             for (int s4 = 0; s4 < S4; ++s4) areg[qb][s4] = load_granule<Op, VEC>(row, 4 * s4 + lh, args.valid, ok);
         }
@@ -1174,7 +1186,7 @@ knn_fused(FusedArgs args) {
 #pragma unroll
         for (int qq = 0; qq < QW; ++qq) {
             const int64_t q = q0 + cw * QW + qq;
-            qs[qq] = (Op::SCALED && q < args.nq) ? args.qinv[q] : 1.f;
+            qs[qq] = (Op::SCALED && q < args.nq) ? args.qinv[args.rest ? (int64_t)args.qlist[q] : q] : 1.f;
         }
         __syncthreads();
         // bound exchanges: often early, while the queues fill (steps 0, 4, 8,
@@ -1320,6 +1332,54 @@ inline void plan_chunks(int64_t nq, int64_t nb, int BQ, int BN, int KS, int64_t*
     *nchunks = nb > 0 ? ceil_div(nb, cl) : 1;
 }
 
+// Chunks of a search over the *count queries that are left, in a grid of `blocks`
+// workgroups: as many as the grid holds, up to max_chunks (one query of 10^6 x 128
+// rows: 2.4 ms with 16 chunks, each workgroup as slow as with 64 queries).  Clears
+// the rank points that it needs.
+static __global__ void rest_bounds_kernel(const uint32_t* __restrict__ count, int32_t blocks, int64_t nb,
+                                          int32_t BQ, int32_t BN, int32_t max_chunks,
+                                          RestPlan* __restrict__ plan, uint32_t* __restrict__ bound) {
+    const int32_t n = (int32_t)*count;
+    RestPlan r{BN, n, 1, (n + BQ - 1) / BQ, 0};
+    if (n > 0 && nb > 0) {
+        int64_t c = blocks / r.nqb;
+        c = c < max_chunks ? c : max_chunks;
+        c = c > 1 ? c : 1;
+        r.chunk_len = ((nb + c - 1) / c + BN - 1) / BN * BN;
+        r.nchunks = (int32_t)((nb + r.chunk_len - 1) / r.chunk_len);
+    }
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t == 0) *plan = r;
+    const int64_t words = (int64_t)n * r.nchunks * kRankPoints;
+    for (int64_t i = t; i < words; i += (int64_t)gridDim.x * 256) bound[i] = kNoBound;
+}
+
+// Scratch and set-up of a fused search: all queries, or those of `rest` with chunks
+// chosen on the device.
+template <class S, int KR>
+mk_status fused_scratch(int64_t nq, int64_t nb, int64_t nqb, int64_t nchunks, const RestQueries* rest,
+                        Scratch& part, Scratch& bound, RestPlan** plan, hipStream_t s, Arena* arena) {
+    // (whole blocks of queries: any number of them times its chunks fits)
+    const int64_t rows = rest ? nqb * S::BQ * nchunks : nq * nchunks;
+    const size_t words = (size_t)bound_words(KR, rows, 1);
+    MK_TRY(part.alloc(sizeof(uint64_t) * (size_t)rows * S::ROW, s, arena));
+    const size_t at = (words * sizeof(uint32_t) + 15) & ~(size_t)15;
+    MK_TRY(bound.alloc(rest ? at + sizeof(RestPlan) : words * sizeof(uint32_t), s, arena));
+    *plan = nullptr;
+    if (sizing_only(arena)) return MK_OK;
+    if (!rest) return clear_bounds(KR, bound.as<uint32_t>(), nq, nchunks, s);
+    *plan = reinterpret_cast<RestPlan*>(bound.as<unsigned char>() + at);
+    int64_t most = nb / (8 * 64 * KR);
+    most = most < kMaxRankChunks ? most : kMaxRankChunks;
+    most = most > nchunks ? most : nchunks;
+    const int64_t grid = ceil_div((int64_t)words, 1024);
+    hipLaunchKernelGGL(rest_bounds_kernel, dim3((unsigned)(grid < 1024 ? grid : 1024)), dim3(256), 0, s,
+                       rest->count, (int32_t)(nqb * nchunks), nb, (int32_t)S::BQ, (int32_t)S::BN,
+                       (int32_t)most, *plan, bound.as<uint32_t>());
+    MK_LAUNCHED();
+    return MK_OK;
+}
+
 // Candidates kept beyond k for the direct-form re-rank of the merge pass.
 constexpr int kSlack = 16;
 constexpr int kMergeWaves = 4;
@@ -1439,7 +1499,8 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_merge_rerank(
     const uint64_t* __restrict__ part, int32_t nchunks, int32_t row, int32_t nread,
     const float* __restrict__ xq, int64_t nq,
     const float* __restrict__ xb, int32_t d, int32_t vec, int32_t l2, int32_t k, int32_t keff,
-    float* __restrict__ D, int64_t* __restrict__ I, const uint32_t* __restrict__ qflag) {
+    float* __restrict__ D, int64_t* __restrict__ I, const uint32_t* __restrict__ qlist,
+    const RestPlan* __restrict__ rest) {
     constexpr int T = SelParams<KR>::T;
     constexpr int KS = 64 * KR;
     __shared__ __align__(16) float xs[kMergeWaves][kMaxDim];
@@ -1447,12 +1508,14 @@ __global__ __launch_bounds__(64 * kMergeWaves) void knn_merge_rerank(
     __shared__ float dist[kMergeWaves][KS];
     const int wave = threadIdx.x >> 6;
     const int lane = lane_id();
-    const int64_t q = (int64_t)blockIdx.x * kMergeWaves + wave;
-    if (q >= nq || (qflag && qflag[q] == 0u)) return;
+    int64_t q = (int64_t)blockIdx.x * kMergeWaves + wave;
+    if (q >= (rest ? rest->nq : nq)) return;
+    if (rest) nchunks = rest->nchunks;
 
     WaveSelect<KR, T> ws;
     ws.init(keff);
     const uint64_t* p = part + q * nchunks * row;
+    if (rest) q = qlist[q];
     // The first nread entries of each chunk's row hold its candidates (a
     // sorted list needs only its first keff).
     const int per = (nread + 63) & ~63;

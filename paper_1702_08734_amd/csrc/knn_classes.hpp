@@ -3,6 +3,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "kselect.hpp"
 
 namespace mk {
 
@@ -11,7 +12,7 @@ namespace mk {
 template <int DP>
 mk_status knn_dispatch_k(const float* xq, int64_t nq, const float* xb, const float* yn,
                          int64_t nb, int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
-                         hipStream_t s, Arena* arena, const uint32_t* qflag);
+                         hipStream_t s, Arena* arena, const RestQueries* rest);
 template <int DP>
 mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                          int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
@@ -23,7 +24,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     extern template mk_status knn_dispatch_k<DP>(const float*, int64_t, const float*,            \
                                                  const float*, int64_t, int32_t, int32_t, bool,  \
                                                  bool, float*, int64_t*, hipStream_t, Arena*,    \
-                                                 const uint32_t*);                               \
+                                                 const RestQueries*);                               \
     extern template mk_status sieve_dispatch<DP>(const float*, int64_t, const float*,            \
                                                  const float*, int64_t, int32_t, int32_t, bool,  \
                                                  bool, float*, int64_t*, hipStream_t);           \

@@ -4,5 +4,5 @@
 namespace mk {
 template mk_status knn_dispatch_k<64>(const float*, int64_t, const float*, const float*, int64_t,
                                        int32_t, int32_t, bool, bool, float*, int64_t*,
-                                       hipStream_t, Arena*, const uint32_t*);
+                                       hipStream_t, Arena*, const RestQueries*);
 }  // namespace mk

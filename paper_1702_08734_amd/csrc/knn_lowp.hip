@@ -103,16 +103,14 @@ template <class Op, int KR, int DP>
 mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, int64_t nq,
                       const float* xb, const void* xb_lp, const float* xb_inv, const float* yn,
                       int64_t nb, int32_t d, int32_t k, int32_t R, bool l2, float* D, int64_t* I,
-                      hipStream_t stream, const uint32_t* qflag = nullptr) {
+                      hipStream_t stream, const RestQueries* rest = nullptr) {
     using S = FusedShape<KR, DP * Op::BYTES, fused_consumers<Op, DP>()>;
     constexpr int KS = 64 * KR;
     int64_t nqb, nchunks, chunk_len;
     plan_chunks(nq, nb, S::BQ, S::BN, KS, &nqb, &nchunks, &chunk_len);
     Scratch part, bound;
-    mk_status st = part.alloc(sizeof(uint64_t) * (size_t)nq * (size_t)nchunks * S::ROW, stream);
-    if (st != MK_OK) return st;
-    MK_TRY(bound.alloc(sizeof(uint32_t) * (size_t)bound_words(KR, nq, nchunks), stream));
-    MK_TRY(clear_bounds(KR, bound.as<uint32_t>(), nq, nchunks, stream));
+    RestPlan* plan = nullptr;
+    MK_TRY((fused_scratch<S, KR>(nq, nb, nqb, nchunks, rest, part, bound, &plan, stream, nullptr)));
     const int64_t nblocks = nqb * nchunks;
     // the grid's work-item count must fit 32 bits
     MK_REQUIRE(nblocks * 64 * (kProducers + S::NC) < (1ll << 32), MK_ERR_UNSUPPORTED,
@@ -121,7 +119,8 @@ mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, i
     unsigned long long* drops = nullptr;
     MK_TRY(pool_drop_counter(&drops));
     FusedArgs a{xq_lp, xb_lp, yn, xq_inv, xb_inv, nq, nb, ld, ld, chunk_len, (int32_t)nchunks,
-                (int32_t)nqb, R, part.as<uint64_t>(), bound.as<uint32_t>(), drops, qflag};
+                (int32_t)nqb, R, part.as<uint64_t>(), bound.as<uint32_t>(), drops,
+                rest ? rest->list : nullptr, plan};
     {
         ProfScope prof(Op::SCALED ? "knn_fused_fp8" : "knn_fused_bf16", stream);
         auto kern = l2 ? knn_fused<Op, KR, DP, true, true> : knn_fused<Op, KR, DP, true, false>;
@@ -136,7 +135,7 @@ mk_status lowp_launch(const float* xq, const void* xq_lp, const float* xq_inv, i
         hipLaunchKernelGGL((knn_merge_rerank<KR>), dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, stream, part.as<uint64_t>(),
                            (int32_t)nchunks, (int32_t)S::ROW, S::mem_queues ? KS : R, xq, nq, xb,
-                           d, (int32_t)vec, (int32_t)l2, k, R, D, I, qflag);
+                           d, (int32_t)vec, (int32_t)l2, k, R, D, I, a.qlist, plan);
         MK_LAUNCHED();
     }
     return MK_OK;
@@ -147,13 +146,13 @@ mk_status lowp_dispatch_k(const float* xq, const void* xq_lp, const float* xq_in
                           const float* xb, const void* xb_lp, const float* xb_inv,
                           const float* yn, int64_t nb, int32_t d, int32_t k, int32_t R, bool l2,
                           float* D, int64_t* I, hipStream_t s,
-                          const uint32_t* qflag = nullptr) {
+                          const RestQueries* rest = nullptr) {
     switch (queue_regs(R)) {
-        case 1: return lowp_launch<Op, 1, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
-        case 2: return lowp_launch<Op, 2, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
-        case 4: return lowp_launch<Op, 4, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
-        case 8: return lowp_launch<Op, 8, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
-        default: return lowp_launch<Op, 16, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, qflag);
+        case 1: return lowp_launch<Op, 1, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, rest);
+        case 2: return lowp_launch<Op, 2, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, rest);
+        case 4: return lowp_launch<Op, 4, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, rest);
+        case 8: return lowp_launch<Op, 8, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, rest);
+        default: return lowp_launch<Op, 16, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2, D, I, s, rest);
     }
 }
 
@@ -178,7 +177,7 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     };
     const size_t o_s = part((size_t)plan.sample * stride), o_a = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_b = part(sizeof(float) * (size_t)plan.sample);
-    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq));
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(3 * nq + 1));
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
@@ -192,8 +191,10 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     w.cap = (uint32_t)plan.cap;
     w.cnt = reinterpret_cast<uint32_t*>(base + o_w);
     w.flags = w.cnt + nq;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq, 256), 1024)),
-                       dim3(256), 0, s, w.cnt, 2 * nq);
+    w.nrest = w.flags + nq;
+    w.rest = w.nrest + 1;
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 1, 256), 1024)),
+                       dim3(256), 0, s, w.cnt, 2 * nq + 1);
     MK_LAUNCHED();
     const float* side_a = Op::SCALED ? xb_inv : nullptr;
     const float* side_b = l2 ? yn : nullptr;
@@ -237,8 +238,9 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, R, false, D, I, s));
+    const RestQueries rest{w.rest, w.nrest};
     return lowp_dispatch_k<Fused, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2,
-                                      D, I, s, w.flags);
+                                      D, I, s, &rest);
 }
 
 template <class Fused, class Op, int DP>

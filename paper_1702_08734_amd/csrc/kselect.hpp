@@ -59,6 +59,12 @@ struct Lend {
     void* ptr;
     size_t bytes;
 };
+// Queries that another search left to the fused one: list[0 .. *count), in device
+// memory, in any order.
+struct RestQueries {
+    const uint32_t* list;
+    const uint32_t* count;
+};
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,
                      hipStream_t s, Arena* arena = nullptr, const Lend* lend = nullptr);

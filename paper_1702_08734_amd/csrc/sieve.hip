@@ -31,7 +31,7 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
         hipLaunchKernelGGL(sieve_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, xq, nq, xb, d,
                            (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
-                           w.flags, D, I);
+                           w.flags, w.rest, w.nrest, D, I);
         MK_LAUNCHED();
         return MK_OK;
     }
@@ -40,7 +40,7 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
                                : sieve_finish<4096>;
     hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, w.pool, w.cnt, w.cap, xq,
                        xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
-                       w.flags, D, I);
+                       w.flags, w.rest, w.nrest, D, I);
     MK_LAUNCHED();
     return MK_OK;
 }
@@ -72,7 +72,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_ss = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_so = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_ys = part(sizeof(float) * (size_t)slab), o_yo = part(sizeof(float) * (size_t)slab);
-    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 1));
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(3 * nq + 2));
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
@@ -93,9 +93,11 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     w.cnt = words;
     w.flags = w.cnt + nq;
     w.bad_db = w.flags + nq;
+    w.nrest = w.bad_db + 1;
+    w.rest = w.nrest + 1;
     w.qnorm = qnorm;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 1, 256), 1024)),
-                       dim3(256), 0, s, words, 2 * nq + 1);
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 2, 256), 1024)),
+                       dim3(256), 0, s, words, 2 * nq + 2);
     MK_LAUNCHED();
     const int kind = l2 ? kSplitDbL2 : kSplitDbIp;
     MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, qrows, qscale, qnorm, nullptr, w.flags, s));
@@ -143,8 +145,9 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
         MK_TRY(launch(false, rows, yscale, yoff, n, r0));
     }
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s));
-    // flagged queries (none, as a rule) take the fused search
-    return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I, s, nullptr, w.flags);
+    // the queries that are left (none, as a rule) take the fused search
+    const RestQueries rest{w.rest, w.nrest};
+    return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I, s, nullptr, &rest);
 }
 
 
@@ -164,17 +167,18 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     const size_t o_qs = part(sizeof(float) * (size_t)nq), o_qn = part(sizeof(float) * (size_t)nq);
     const size_t o_ys = part(sizeof(float) * (size_t)nb), o_yo = part(sizeof(float) * (size_t)nb);
     const size_t o_n = part(yn ? 0 : sizeof(float) * (size_t)nb);
-    const size_t o_w = part(sizeof(uint32_t) * (size_t)(nq + 1));
+    const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
     const size_t o_r = part(sizeof(uint4) * (size_t)nq);
     Scratch mem;
     MK_TRY(mem.alloc(used, s));
     unsigned char* base = mem.as<unsigned char>();
     auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
     uint32_t* flags = reinterpret_cast<uint32_t*>(base + o_w);
-    uint32_t* bad_db = flags + nq;
+    uint32_t *bad_db = flags + nq, *nrest = bad_db + 1;
+    const RestQueries rest{nrest + 1, nrest};
     float* norms = yn ? nullptr : floats(o_n);
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 1, 256), 1024)),
-                       dim3(256), 0, s, flags, nq + 1);
+    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 2, 256), 1024)),
+                       dim3(256), 0, s, flags, nq + 2);
     MK_LAUNCHED();
     MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, base + o_q, floats(o_qs),
                           floats(o_qn), nullptr, flags, s));
@@ -201,10 +205,10 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
         MK_LAUNCHED();
     }
     hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
-                       xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, D, I);
+                       xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, nrest + 1, nrest, D, I);
     MK_LAUNCHED();
     return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I, s, nullptr,
-                              flags);
+                              &rest);
 }
 
 #define MK_SIEVE_CLASS(DP)                                                                        \

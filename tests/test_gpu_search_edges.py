@@ -51,3 +51,35 @@ def test_nearest_rows_left_out(api, d, nq, left_out):
     rows = np.arange(0, nq, 61)
     fails = check_rows(D[rows], I[rows] // 2, xq, np.ascontiguousarray(xb[::2]), rows, 1, "l2")
     assert not fails, fails[:10]
+
+
+# a few queries in a batch without a proof (zero rows under inner products: every row
+# ties), as many as fill no block or several, beside others that have one
+@pytest.mark.parametrize("nq,every", [(1500, 1499), (1500, 30), (257, 2), (4000, 3)])
+@pytest.mark.parametrize("k", [10, 100])
+def test_few_unproven_queries(api, nq, every, k):
+    rng = np.random.default_rng(nq + every)
+    nb, d = 40_003, 40
+    xb, xq = mixture(rng, nb, d), mixture(rng, nq, d)
+    xq[::every] = 0.0
+    print(f"few unproven nq={nq} every={every} k={k}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k, "ip")
+    D, I = D.cpu().numpy(), I.cpu().numpy()
+    assert (D[::every] == 0).all() and (I[::every] == np.arange(k)).all()
+    rows = np.setdiff1d(np.arange(1, nq, 37), np.arange(0, nq, every))
+    fails = check_rows(D[rows], I[rows], xq, xb, rows, k, "ip")
+    assert not fails, fails[:10]
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+def test_few_unproven_queries_lowp(api, prec):
+    # the same candidates as calls of 32 queries, which the fused search answers
+    rng = np.random.default_rng(3)
+    xb, xq = dev(mixture(rng, 60_001, 40)), dev(mixture(rng, 700, 40))
+    xq[::9] = 0.0
+    lp, inv = api.quantize_rows(xb, prec)
+    print(f"few unproven {prec}", flush=True)
+    D, I = api.knn_search_lowp(xq, xb, lp, inv, 10, 40, prec, "ip")
+    for lo in (0, 300, 668):
+        d2, i2 = api.knn_search_lowp(xq[lo:lo + 32].contiguous(), xb, lp, inv, 10, 40, prec, "ip")
+        assert torch.equal(I[lo:lo + 32], i2) and torch.equal(D[lo:lo + 32], d2)
