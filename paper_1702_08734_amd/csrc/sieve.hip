@@ -115,6 +115,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     a.cap = w.cap;
     a.thr = top + (plan.rank - 1);
     a.thr_ld = plan.rank;
+    a.flags = w.flags;
+    a.bad_db = w.bad_db;
     a.tail = std::log((float)keff / (float)k) / std::log((float)plan.rank);
     a.scores = scores;
     a.ld = plan.sample / S::PER;
@@ -198,6 +200,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     a.nchunks = 1;
     a.nqb = (int32_t)ceil_div(nq, S::BQ);
     a.near = reinterpret_cast<uint4*>(base + o_r);
+    a.bad_db = bad_db;
     {
         ProfScope prof("sieve_nearest", s);
         hipLaunchKernelGGL((sieve_tiles<SieveSplit, DP, true, kNearest>), dim3((unsigned)a.nqb),

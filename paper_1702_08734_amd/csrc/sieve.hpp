@@ -127,6 +127,8 @@ struct SieveArgs {
     const float* thr;     // filter: threshold of query q at thr[q * thr_ld]
     int64_t thr_ld;
     float tail;           // filter (split, L2): see the queries without a chance below
+    const uint32_t* flags;   // filter (split): [nq] queries that the split cannot hold
+    const uint32_t* bad_db;  // filter, nearest (split): a row that it cannot hold was seen
     uint32_t* cnt;        // filter: [nq] keys appended (may exceed cap)
     uint64_t* pool;       // filter: [nq][cap] keys
     uint32_t cap;
@@ -236,6 +238,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int row_bytes = PL > 1 ? GR * 16 : args.stride;
     const unsigned char* xb = static_cast<const unsigned char*>(args.xb) + c0 * row_bytes;
 
+    // a row that the split cannot hold: every query is searched again
+    if constexpr (PL > 1 && !SAMPLE)
+        if (*args.bad_db != 0u) return;
+
     // ---- this wave's queries: operands, scale factors, thresholds
     uint4 qreg[QB][PL * S4];
     float mq[QB], sh[QB], thr[QB];
@@ -261,6 +267,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
         sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
         thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        if constexpr (FILTER && PL > 1)
+            if (ok && args.flags[q] != 0u) thr[qb] = -INFINITY;
         // Queries without a chance of a proof: far from the origin the error bound of
         // the scores is more than the k-th and the keff-th best row lie apart.  These
         // are about ln(keff / k) / ln(rank) of the sample's best `rank` scores apart
@@ -278,7 +286,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
     }
-    if constexpr (FILTER && L2 && PL > 1) {
+    if constexpr (FILTER && PL > 1) {
         bool any = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) any |= thr[qb] > -INFINITY;
