@@ -386,10 +386,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // queries' counters.  Stores may complete out of order with the tile
     // loads, so the wave then waits for everything (its tile waits count
     // loads only).
+    // A query whose pool overflowed (ties by the thousand, a threshold that the
+    // sample put too high) is searched again whatever else passes, so its threshold
+    // is withdrawn.
     uint32_t staged = 0;  // wave-uniform
     const int64_t qw0 = q0 + qg * QB * 16;
     auto flush = [&]() {
         __builtin_amdgcn_wave_barrier();
+        bool full = false;
         constexpr int U = 2;  // counters asked at a time
 #pragma unroll 1
         for (uint32_t e0 = 0; e0 < staged; e0 += 64 * U) {
@@ -425,9 +429,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         if (pos[u] < args.cap) p[pos[u]] = make_key(c[u][e], row + e);
                         ++pos[u];
                     }
+                full |= take[u] != 0u && pos[u] > args.cap;
             }
         }
         staged = 0;
+        if (__ballot(full)) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const int64_t q = qw0 + qb * 16 + li;
+                if (q < args.nq &&
+                    __hip_atomic_load(&args.cnt[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > args.cap)
+                    thr[qb] = -INFINITY;
+            }
+        }
         __builtin_amdgcn_s_waitcnt(0);
     };
 
