@@ -29,7 +29,7 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
     ProfScope prof("sieve_finish", s);
     if (keff <= 64) {
         hipLaunchKernelGGL(sieve_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
-                           dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, xq, nq, xb, d,
+                           dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, w.thr, w.thr_ld, xq, nq, xb, d,
                            (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
                            w.flags, w.rest, w.nrest, D, I);
         MK_LAUNCHED();
@@ -38,8 +38,8 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
     auto kern = keff <= 256    ? sieve_finish<1024>
                 : keff <= 1024 ? sieve_finish<2048>
                                : sieve_finish<4096>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, w.pool, w.cnt, w.cap, xq,
-                       xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
+    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, w.pool, w.cnt, w.cap, w.thr,
+                       w.thr_ld, xq, xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
                        w.flags, w.rest, w.nrest, D, I);
     MK_LAUNCHED();
     return MK_OK;
@@ -117,7 +117,10 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     a.thr_ld = plan.rank;
     a.flags = w.flags;
     a.bad_db = w.bad_db;
-    a.tail = std::log((float)keff / (float)k) / std::log((float)plan.rank);
+    w.thr = a.thr;
+    w.thr_ld = a.thr_ld;
+    const double fk = (double)plan.sample / (double)nb * k;  // of the k best, in the sample
+    a.tail = (float)(std::log(plan.rank / fk) / std::log((double)plan.rank));
     a.scores = scores;
     a.ld = plan.sample / S::PER;
     auto launch = [&](bool sample, const void* r, const float* ya, const float* yb, int64_t n,

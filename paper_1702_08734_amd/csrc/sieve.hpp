@@ -270,14 +270,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if constexpr (FILTER && PL > 1)
             if (ok && args.flags[q] != 0u) thr[qb] = -INFINITY;
         // Queries without a chance of a proof: far from the origin the error bound of
-        // the scores is more than the k-th and the keff-th best row lie apart.  These
-        // are about ln(keff / k) / ln(rank) of the sample's best `rank` scores apart
-        // (their number grows exponentially); where that is less than the bound, no
-        // row is let through, the finish finds too few, and a block of such queries
-        // ends here.  2,000 queries, 10^6 x 64 rows 100 standard deviations from the
-        // origin, k = 100: 5.1 ms, 5.7 without this, 4.9 by the fused search alone.
-        // (Twice the bound gives up many that are proven: 10 deviations, k = 1,000 7.5
-        // against 4.7 ms.)
+        // the scores is more than the k-th best row and the threshold lie apart.  By the
+        // sample's best `rank` scores (their number grows exponentially) these are about
+        // ln(rank / (f k)) / ln(rank) of the best and the last of them apart, f the
+        // sample's share of the rows; where that is less than the bound, no row is let
+        // through, the finish finds too few, and a block of such queries ends here.
         if constexpr (FILTER && L2 && PL > 1)
             if (ok) {
                 const float* t = args.thr + q * args.thr_ld;
@@ -790,6 +787,13 @@ static __global__ void sieve_clear_kernel(uint32_t* __restrict__ p, int64_t n) {
 }
 
 // ------------------------------------------------------------- finish
+// What the direct-form value (squared distance, or negated inner product) of a row
+// is at least, by its score in a pool: the scores are lower bounds of rows' true
+// scores less the per-query constant kSplitErr ||x||^2 (L2).
+__device__ __forceinline__ float row_bound(float score, float nx, int32_t l2) {
+    return l2 ? (nx * (1.f - kSplitErr) + score) * (1.f - 0x1p-20f) : score;
+}
+
 // Query q to the list of those that the fused search takes.
 __device__ __forceinline__ void leave_query(int64_t q, uint32_t* __restrict__ rest,
                                             uint32_t* __restrict__ nrest) {
@@ -802,18 +806,19 @@ __device__ __forceinline__ void leave_query(int64_t q, uint32_t* __restrict__ re
 // dropped row's lower bound does not clear the k-th distance) is left to the fused
 // search.
 //
-// cert: the pool's scores are lower bounds of rows' true scores less the
-// per-query constant kSplitErr ||x||^2 (L2).  A dropped row's score is at least
-// the keff-th best score s; its distance in the direct form is then at least
-// (||x||^2 + s - kSplitErr ||x||^2)(1 - 2^-20), and its negated inner product at
-// least s.  When the k-th re-ranked value is below that, no dropped row can
-// enter, whatever the data.
+// cert: a row of the pool that is not among the keff best has at least the keff-th
+// best score, a row outside the pool at least the threshold.  When the k-th
+// re-ranked value is below the bound (row_bound) of the former, no other row can
+// enter.  When it is only below the bound of the latter (rows far from the origin
+// for their distances, ties), the pool's other rows whose bound is not cleared are
+// re-ranked as well.
 // 2,000 queries, keff = 1,016, pools of about 2,500 keys: 210 us against 330 us by a
 // wave per query with a sorted register queue; 10^4 queries, keff = 400: 284 against
 // 450 us.  Bound by the gathers of the re-ranked rows (4.8 TB/s and 5.4 TB/s).
 template <int P>  // keff <= P / 2
 __global__ __launch_bounds__(kPoolThreads) void sieve_finish(
     const uint64_t* __restrict__ pools, const uint32_t* __restrict__ cnt, uint32_t cap,
+    const float* __restrict__ thr, int64_t thr_ld,
     const float* __restrict__ xq, const float* __restrict__ xb, int32_t d, int32_t vec,
     int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
     const uint32_t* __restrict__ bad_db, const uint32_t* __restrict__ flags,
@@ -848,10 +853,39 @@ __global__ __launch_bounds__(kPoolThreads) void sieve_finish(
         pool_cut<P>(pool, bins, &st, left, k);
         left = (uint32_t)k;
         const float worst = key_score(st.limit - 1), s_last = key_score(limit - 1), nx = qnorm[q];
-        const float edge = l2 ? (nx * (1.f - kSplitErr) + s_last) * (1.f - 0x1p-20f) : s_last;
-        if (!(worst < edge)) {  // (uniform)
-            if (tid == 0) leave_query(q, rest, nrest);
-            return;
+        if (!(worst < row_bound(s_last, nx, l2))) {  // (uniform)
+            if (!(worst < row_bound(thr[q * thr_ld], nx, l2))) {
+                if (tid == 0) leave_query(q, rest, nrest);
+                return;
+            }
+            // the rest of the pool's rows whose bound does not clear the k-th
+            __shared__ uint64_t strip[kPoolThreads];
+            uint64_t enter = st.limit;
+#pragma unroll 1
+            for (uint32_t e0 = 0; e0 < n; e0 += kPoolThreads) {
+                uint64_t key = e0 + tid < n ? pools[q * (int64_t)cap + e0 + tid] : kSentinel;
+                if (key < limit || !(row_bound(key_score(key), nx, l2) <= worst)) key = kSentinel;
+                if (!__syncthreads_or(key != kSentinel)) continue;
+                strip[tid] = key;
+                __syncthreads();
+#pragma unroll 1
+                for (int e = 16 * (tid >> 6); e < kPoolThreads; e += 16 * kPoolWaves)
+                    rerank_rows16(xs, strip, e, kPoolThreads, xb, d, vec, l2, dist);
+                __syncthreads();
+                const uint64_t nk =
+                    key != kSentinel ? make_key(l2 ? dist[tid] : -dist[tid], key_index(key)) : kSentinel;
+                const bool take = nk < enter;
+                uint32_t at;
+                const uint32_t add = pool_sum(take ? 1u : 0u, st.wsum, at);
+                if (take) pool[left + at] = nk;
+                left += add;
+                if (left > (uint32_t)(P - kPoolThreads)) {
+                    pool_cut<P>(pool, bins, &st, left, k);
+                    left = (uint32_t)k;
+                    enter = st.limit;
+                }
+                __syncthreads();
+            }
         }
     }
     pool_emit<P>(pool, bins, &st, left, (uint32_t)k, [&](uint32_t r, uint64_t key) {
@@ -866,7 +900,7 @@ __global__ __launch_bounds__(kPoolThreads) void sieve_finish(
 // against 104 by a workgroup each).
 static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
     const uint64_t* __restrict__ pool, const uint32_t* __restrict__ cnt, uint32_t cap,
-    const float* __restrict__ xq, int64_t nq, const float* __restrict__ xb, int32_t d, int32_t vec,
+    const float* __restrict__ thr, int64_t thr_ld, const float* __restrict__ xq, int64_t nq, const float* __restrict__ xb, int32_t d, int32_t vec,
     int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
     const uint32_t* __restrict__ bad_db, const uint32_t* __restrict__ flags,
     uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest, float* __restrict__ D,
@@ -894,7 +928,7 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
         if (ws.push(i < n ? p[i] : kSentinel)) ws.merge();
     }
     ws.finish();
-    const float s_last = key_score(ws_element<KR>(ws.w, keff - 1));
+    const uint64_t last = ws_element<KR>(ws.w, keff - 1);
 
     const float* x = xq + q * d;
     for (int t = lane; t < d; t += 64) xs[wave][t] = x[t];
@@ -923,10 +957,34 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
     if (cert) {
         const float worst = key_score(ws_element<KR>(nk, k - 1));
         const float nx = qnorm[q];
-        const float edge = l2 ? (nx * (1.f - kSplitErr) + s_last) * (1.f - 0x1p-20f) : s_last;
-        if (!(worst < edge)) {
-            if (lane == 0) leave_query(q, rest, nrest);
-            return;
+        if (!(worst < row_bound(key_score(last), nx, l2))) {
+            if (!(worst < row_bound(thr[q * thr_ld], nx, l2))) {
+                if (lane == 0) leave_query(q, rest, nrest);
+                return;
+            }
+            // the rest of the pool's rows whose bound does not clear the k-th
+            ws.init(k);
+            if (ws.push(nk[0])) ws.merge();
+#pragma unroll 1
+            for (uint32_t e0 = 0; e0 < n; e0 += 64) {
+                uint64_t key = e0 + lane < n ? p[e0 + lane] : kSentinel;
+                if (key <= last || !(row_bound(key_score(key), nx, l2) <= worst)) key = kSentinel;
+                if (!__ballot(key != kSentinel)) continue;
+                kl[wave][lane] = key;
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+#pragma unroll 1
+                for (int e = 0; e < 64; e += 16)
+                    rerank_rows16(xw, kl[wave], e, 64, xb, d, vec, l2, dist[wave]);
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                const float v = dist[wave][lane];
+                if (ws.push(key != kSentinel ? make_key(l2 ? v : -v, key_index(key)) : kSentinel))
+                    ws.merge();
+                __builtin_amdgcn_wave_barrier();
+            }
+            ws.finish();
+            nk[0] = ws.w[0];
         }
     }
     emit_reranked<KR>(nk, k, l2, D + q * k, I + q * k);
@@ -1061,6 +1119,8 @@ struct SieveScratch {
     uint32_t* rest = nullptr;    // [nq] queries that are left to the fused search
     uint32_t* nrest = nullptr;   // [1] how many
     const float* qnorm = nullptr;
+    const float* thr = nullptr;  // threshold of query q at thr[q * thr_ld] (exact search)
+    int64_t thr_ld = 0;
 };
 
 // Selection, re-rank and proof of every query of a search (sieve.hip).

@@ -83,3 +83,36 @@ def test_few_unproven_queries_lowp(api, prec):
     for lo in (0, 300, 668):
         d2, i2 = api.knn_search_lowp(xq[lo:lo + 32].contiguous(), xb, lp, inv, 10, 40, prec, "ip")
         assert torch.equal(I[lo:lo + 32], i2) and torch.equal(D[lo:lo + 32], d2)
+
+
+# data on which the first candidates prove nothing: clusters far apart for their width,
+# rows far from the origin, integers with many equal distances; short and long lists
+# (a wave or a workgroup per query finishes)
+@pytest.mark.parametrize("kind,scale", [("spread", 30), ("spread", 300), ("far", 30), ("far", 300),
+                                        ("integers", 1)])
+@pytest.mark.parametrize("d,k", [(24, 10), (64, 48), (64, 49), (128, 300), (33, 1000)])
+def test_unproven_by_the_first_candidates(api, kind, scale, d, k):
+    rng = np.random.default_rng(d + k)
+    nb, nq = 80_009, 520
+    if kind == "spread":
+        mu = scale * rng.standard_normal((40, d))
+        xb = (mu[rng.integers(0, 40, nb)] + rng.standard_normal((nb, d))).astype(np.float32)
+    elif kind == "far":
+        xb = (mixture(rng, nb, d) + np.float32(scale)).astype(np.float32)
+    else:
+        xb = np.round(mixture(rng, nb, d) * 0.7).astype(np.float32)
+    xq = xb[rng.integers(0, nb, nq)].copy()
+    if kind != "integers":
+        xq += np.float32(0.1) * rng.standard_normal((nq, d)).astype(np.float32)
+    print(f"unproven {kind} {scale} d={d} k={k}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k)
+    D, I = D.cpu().numpy(), I.cpu().numpy()
+    rows = np.arange(0, nq, 41)
+    if kind == "integers":  # exact: ties by the lower row
+        for i in rows:
+            d64 = ((xq[i].astype(np.float64) - xb) ** 2).sum(1)
+            order = np.argsort(d64, kind="stable")[:k]
+            assert (I[i] == order).all() and (D[i] == d64[order]).all(), i
+    else:
+        fails = check_rows(D[rows], I[rows], xq, xb, rows, k, "l2")
+        assert not fails, fails[:10]
