@@ -304,10 +304,9 @@ int64_t mk_ivfpq_ntotal(const mk_ivfpq* index);
  * coarse centroids (Eq. 5), scan their lists with PQ lookup tables built
  * from the three-term split of Eq. 11 and staged in LDS, select the k
  * nearest of the scanned entries (Eq. 6).  D are ADC squared distances
- * (FP32), I the ids.  1 <= nprobe <= min(nlist, 1024).  The tables and the
- * per-list merge buffers must fit 64 KiB of LDS: 1024 M + 32 k <= 65536
- * bytes (any k for M <= 32, k <= 256 for M = 64); with 16-bit tables
- * (mk_ivfpq_set_scan_options) 512 M + 32 k <= 65536.
+ * (FP32), I the ids.  1 <= nprobe <= min(nlist, 1024).  Tables and results
+ * are limited by LDS: 1024 M + 32 k <= 65536 (any k for M <= 32, k <= 128 for
+ * M = 60); with 16-bit tables (mk_ivfpq_set_scan_options) 512 M + 32 k <= 65536.
  *   xq [nq, d] float32, D [nq, k] float32, I [nq, k] int64
  */
 mk_status mk_ivfpq_search(mk_ivfpq* index, const float* xq, int64_t nq, int32_t k,

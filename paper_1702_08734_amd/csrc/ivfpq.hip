@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -921,13 +922,6 @@ __global__ void move_old_kernel(const int64_t* __restrict__ old_off,
 // ---------------------------------------------------------------- list scan
 constexpr int kScanWaves = kPoolThreads / 64;
 
-// One workgroup per (query, probe rank).  The list's lookup tables
-// LUT[m][j] = term1[L][m][j] - 2 term3[q][m][j] are staged in LDS; each lane
-// takes one code at a time (coalesced 16-byte loads when M is a multiple of
-// 16), sums term2 + sum_m LUT[m][code_m] (Eq. 10 via Eq. 11) and offers it
-// to its wave's selector keyed by (distance, offset in list) -- offset order
-// is id order inside a list.  The four waves' queues are merged through LDS
-// and the winners' ids resolved (Section 5.3: ids only for the selected).
 // Probe-count features: F[q] = [xq[q] ; the kProbeDists smallest squared
 // coarse distances] (cd holds ld ascending distances per query).
 __global__ void probe_features_kernel(const float* __restrict__ xq, int64_t nq, int32_t d,
@@ -1080,8 +1074,9 @@ struct ScanLists {
     float term2[kScanLists];
 };
 
-template <bool H16, int P>
-__global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(4))) void ivf_scan(
+// LONG: more than 16 code bytes per entry; V16: a multiple of 16
+template <bool H16, int P, bool LONG, bool V16>
+__global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(LONG ? 3 : 4))) void ivf_scan(
     const float* __restrict__ term3, const float* __restrict__ t1e,
     const float* __restrict__ coarse_d, const int64_t* __restrict__ coarse_i, int32_t ld,
     const int64_t* __restrict__ offsets, const uint8_t* __restrict__ codes,
@@ -1092,7 +1087,7 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
     typedef typename LT::type lut_t;
     constexpr int U = 4;                          // entries in flight per lane
     constexpr int STEP = 64 * kScanWaves * U;     // entries of a step
-    static_assert(P >= 2 * STEP, "the pool takes a step beside kk <= P - STEP keys");
+    static_assert(P > STEP, "the pool takes a step beside kk <= P - STEP keys");
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ PoolState state;
     __shared__ ScanLists lists;
@@ -1136,7 +1131,30 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
     }
     __syncthreads();
 
-    const bool vec16 = (M & 15) == 0;
+    const bool vec8 = (M & 7) == 0;
+    // code bytes m0 .. m0 + 15 of an entry (those below M)
+    auto code_bytes = [&](uint32_t pos, int m0) __attribute__((always_inline)) {
+        const uint8_t* c = codes + (int64_t)pos * M + m0;
+        if constexpr (V16) return *reinterpret_cast<const uint4*>(c);
+        uint4 w = make_uint4(0u, 0u, 0u, 0u);
+        if (vec8) {
+            const uint2 a = *reinterpret_cast<const uint2*>(c);
+            w.x = a.x;
+            w.y = a.y;
+            if (m0 + 8 < M) {
+                const uint2 b = *reinterpret_cast<const uint2*>(c + 8);
+                w.z = b.x;
+                w.w = b.y;
+            }
+        } else {
+            const uint32_t* c4 = reinterpret_cast<const uint32_t*>(c);
+            w.x = c4[0];
+            if (m0 + 4 < M) w.y = c4[1];
+            if (m0 + 8 < M) w.z = c4[2];
+            if (m0 + 12 < M) w.w = c4[3];
+        }
+        return w;
+    };
     const int64_t* cirow = coarse_i + q * ld + p0;
     const float* cdrow = coarse_d + q * ld + p0;
     uint64_t limit = kSentinel;  // the threshold and its score
@@ -1171,7 +1189,7 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
         uint32_t cur_shift = 0;
         float cur_term2 = 0.f;
         struct Step {
-            uint4 w[U];     // first 16 code bytes (M a multiple of 16)
+            uint4 w[U];     // first 16 code bytes
             float t1[U], t2[U];
             uint32_t pos[U];
         } now, next;
@@ -1193,7 +1211,7 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 st.t1[u] = t1e[st.pos[u]];
-                if (vec16) st.w[u] = *reinterpret_cast<const uint4*>(codes + (int64_t)st.pos[u] * M);
+                st.w[u] = code_bytes(st.pos[u], 0);
             }
         };
         load(now, 0);
@@ -1205,37 +1223,28 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
             float dist[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) dist[u] = now.t2[u] + now.t1[u];
-            if (vec16) {
-                for (int m0 = 0; m0 < M; m0 += 16) {
-                    if (m0)
+            for (int m0 = 0; m0 < (LONG ? M : 1); m0 += 16) {
+                uint4 ahead[U];  // the next bytes, in flight during these lookups
+                if (LONG && m0 + 16 < M)
 #pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            now.w[u] = *reinterpret_cast<const uint4*>(codes + (int64_t)now.pos[u] * M + m0);
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (u * 64 * kScanWaves >= rest) continue;  // (wave-uniform)
-                        const uint32_t ww[4] = {now.w[u].x, now.w[u].y, now.w[u].z, now.w[u].w};
-#pragma unroll
-                        for (int h = 0; h < 4; ++h)
-#pragma unroll
-                            for (int b = 0; b < 4; ++b) {
-                                const int m = m0 + 4 * h + b;
-                                dist[u] += LT::get(lut[m * 256 + ((ww[h] >> (8 * b)) & 0xFF)]);
-                            }
-                    }
-                }
-            } else {
+                    for (int u = 0; u < U; ++u) ahead[u] = code_bytes(now.pos[u], m0 + 16);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    if (u * 64 * kScanWaves >= rest) continue;
-                    const uint8_t* c = codes + (int64_t)now.pos[u] * M;
-                    for (int m0 = 0; m0 < M; m0 += 4) {
-                        const uint32_t w = *reinterpret_cast<const uint32_t*>(c + m0);
+                    if (u * 64 * kScanWaves >= rest) continue;  // (wave-uniform)
+                    const uint32_t ww[4] = {now.w[u].x, now.w[u].y, now.w[u].z, now.w[u].w};
 #pragma unroll
-                        for (int b = 0; b < 4; ++b)
-                            dist[u] += LT::get(lut[(m0 + b) * 256 + ((w >> (8 * b)) & 0xFF)]);
+                    for (int h = 0; h < 4; ++h) {
+                        if (!V16 && m0 + 4 * h >= M) continue;
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) {
+                            const int m = m0 + 4 * h + b;
+                            dist[u] += LT::get(lut[m * 256 + ((ww[h] >> (8 * b)) & 0xFF)]);
+                        }
                     }
                 }
+                if (LONG && m0 + 16 < M)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) now.w[u] = ahead[u];
             }
             // keyed (distance, id): ids are unique, so the order is total and
             // the selected set does not depend on how lists are grouped; the
@@ -1289,11 +1298,13 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
 // nprobe 128 and 10^4 queries 11.3 ms per-query against 15.6 ms for groups
 // of 16; 1024 queries, nprobe 8 / 64 / 128, 0.47 / 1.41 / 2.65 ms at 2048+
 // workgroups against 0.42 / 1.29 / 2.49 ms; 256 queries, nprobe 64 with
-// R = 256 0.90 -> 0.85 ms, and larger groups than that slower).  Queues of
-// 512+ entries aim at 512+ workgroups: each workgroup's merge of its four
-// waves' queues costs more than the parallelism it buys (5*10^7 x 128,
-// R = 1024, 9 probes per query: 256 queries 1.41 -> 1.15 ms with 4 lists per
-// group, 1024 queries 2.31 -> 1.94 ms with all of a query's lists).
+// R = 256 0.90 -> 0.85 ms, and larger groups than that slower).  Lists of
+// 512+ results aim at 512+ workgroups: every group leaves that many keys to be
+// written and merged (4*10^6 x 128, 4,096 lists, R = 600, aims of 512 / 1024: 1,000
+// queries 4 / 16 / 64 probes 218 / 284 / 536 us against 264 / 365 / 751; 256 queries
+// 198 / 186 / 292 against 193 / 191 / 289; of four times as long lists 517 / 750 /
+// 1,405 against 487 / 701 / 1,415, 1,000 queries 686 / 1,278 / 3,138 against 802 /
+// 1,811 / 4,533).
 int32_t scan_group(int64_t total_probes, int32_t nprobe, int32_t k) {
     const int64_t g = total_probes / (k >= 512 ? 512 : 1024);
     return (int32_t)(g < 1 ? 1 : g > nprobe ? nprobe : g);
@@ -1318,18 +1329,29 @@ mk_status launch_scan(const float* term3, const float* t1e, const float* cd, con
     if (items == 0) return MK_OK;
     MK_REQUIRE(items * 64 * kScanWaves < (1ll << 32), MK_ERR_UNSUPPORTED,
                "too many scan workgroups for one launch (search fewer queries per call)");
-    const size_t shm = (size_t)M * 256 * (lut16 ? 2 : 4) + (size_t)kScanWaves * k * sizeof(uint64_t);
-    MK_REQUIRE(shm <= 65536, MK_ERR_UNSUPPORTED,
-               "lookup tables plus merge buffers exceed 64 KiB of LDS (reduce M or k, or use "
+    // (the calls that the header promises: with its pool and bins the kernel takes up
+    // to 60 KiB of tables and 36 KiB more, of 160 KiB)
+    MK_REQUIRE((size_t)M * 256 * (lut16 ? 2 : 4) + 32 * (size_t)k <= 65536, MK_ERR_UNSUPPORTED,
+               "lookup tables plus 32 bytes per result exceed 64 KiB (reduce M or k, or use "
                "16-bit tables)");
     const dim3 grid((unsigned)items), block(64 * kScanWaves);
     ProfScope prof(lut16 ? "ivf_scan_lut16" : "ivf_scan", s);
-    // pools of 2,048 keys (kk up to 512: half a pool is left after a cut), or
-    // 4,096
-    const size_t lds = (size_t)M * 256 * (lut16 ? 2 : 4) + (k <= 512 ? 2048 : 4096) * sizeof(uint64_t) +
-                       kCutBins * sizeof(uint32_t);
-    auto kern = k <= 512 ? (lut16 ? ivf_scan<true, 2048> : ivf_scan<false, 2048>)
-                         : (lut16 ? ivf_scan<true, 4096> : ivf_scan<false, 4096>);
+    // Pools of 2,048 keys (k up to 512), or 4,096; with more than 16 code bytes 1,792 or
+    // 3,840, which leave room for the tables of 60 sub-quantizers (44 with long lists)
+    // twice per CU (10^4 queries, 8 lists of 1,000 entries, M = 60: 6.7 ms, 16.7 with a
+    // pool of 2,048 and code bytes loaded where they are looked up).
+    const bool wide = M > 16;
+    const size_t keys = k <= 512 ? (wide ? 1792 : 2048) : (wide ? 3840 : 4096);
+    const size_t lds = (size_t)M * 256 * (lut16 ? 2 : 4) + keys * sizeof(uint64_t) + kCutBins * sizeof(uint32_t);
+    auto of = [&](auto wide, auto v16) {
+        constexpr bool W = decltype(wide)::value, V = decltype(v16)::value;
+        constexpr int P = W ? 1792 : 2048, PL = W ? 3840 : 4096;
+        return k <= 512 ? (lut16 ? ivf_scan<true, P, W, V> : ivf_scan<false, P, W, V>)
+                        : (lut16 ? ivf_scan<true, PL, W, V> : ivf_scan<false, PL, W, V>);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    auto kern = M == 16 ? of(no, yes) : !wide ? of(no, no) : M % 16 == 0 ? of(yes, yes) : of(yes, no);
     if (lds > 65536)
         MK_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

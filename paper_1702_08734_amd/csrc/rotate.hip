@@ -481,7 +481,7 @@ extern "C" mk_status mk_rotate_rows(const float* x, int64_t n, int32_t d, const 
     // Rows of 128 components are what the registers hold; sums of a few products are
     // rounded less often in FP32 (d = 1: once).  From about 30,000 rows on faster
     // (FP32 kernel, this one; 128 outputs of 128 components: 16,384 rows 10.4, 12.3 us,
-    // 30,000 rows 17.4, 14.2, 50,000 rows 25, 18, 200,000 rows 77, 57, 2*10^6 rows 765,
+    // 30,000 rows 17.4, 16.7, 50,000 rows 25.2, 21.9, 200,000 rows 77, 57, 2*10^6 rows 765,
     // 447; the worst of 24 to 128 components and 16 to 128 outputs: 100,000 x 64 rows,
     // 57 outputs 16.0, 17.6, and 200,000 rows 26.7, 26.5); between 16,384 rows and that
     // for its smaller error.
