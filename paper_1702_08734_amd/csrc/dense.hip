@@ -31,6 +31,20 @@ namespace mk {
 
 namespace {
 
+// Queries list[first .. min(*count, first + most)) of those left by another search;
+// none where there are more than limit.
+struct RestSpan {
+    const uint32_t* list;
+    const uint32_t* count;
+    int64_t first, most, limit;
+    __device__ __forceinline__ int64_t size() const {
+        const int64_t n = *count;
+        if (n > limit || n <= first) return 0;
+        return n - first < most ? n - first : most;
+    }
+    __device__ __forceinline__ int64_t at(int64_t i) const { return list[first + i]; }
+};
+
 struct QuadArgs {
     const float* xq;
     const float* xb;
@@ -42,6 +56,7 @@ struct QuadArgs {
     int32_t nqb;              // query blocks of 16 QB
     float* out;               // [nq][ld] least score of four rows
     int64_t ld;
+    RestSpan rest;            // if its list is given: these queries in the place of 0 .. nq - 1
 };
 
 // A wave takes 16 QB queries (B operands, in registers) and streams its rows 64
@@ -54,6 +69,13 @@ struct QuadArgs {
 // for everything in flight, and kept twice the registers (500 queries, 50,000 x 64
 // rows: 69 -> 47 us; 10^4 queries, 4,096 x 128 rows 175 -> 135 us, half of the
 // matrix cores' rate).
+// Groups of 64 rows per wave for more than 16 queries: four waves per SIMD's worth,
+// for an even end (fewer than 8,192 + nqb waves).
+__host__ __device__ inline int64_t quad_groups(int64_t groups, int64_t nqb) {
+    const int64_t n = groups * nqb / 4096;
+    return n > 1 ? n : 1;
+}
+
 enum class QuadNorms { kNone, kGiven, kOwn };  // inner products; L2 with and without yn
 template <int DP, int QB, bool VEC, QuadNorms NORMS>
 __global__ __launch_bounds__(256)
@@ -62,6 +84,12 @@ quad_min_kernel(QuadArgs a) {
     constexpr bool L2 = NORMS != QuadNorms::kNone;
     constexpr int S4 = DP / 16;  // granule steps of four floats per lane
     const int lane = lane_id(), li = lane & 15, lh = lane >> 4;
+    if (a.rest.list) {
+        a.nq = a.rest.size();
+        if (a.nq == 0) return;
+        a.nqb = (int32_t)((a.nq + 16 * QB - 1) / (16 * QB));
+        a.groups_per_wave = quad_groups(a.groups, a.nqb);
+    }
     const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // neighbouring waves: the query blocks of one stretch of rows
     const int64_t q0 = (w % a.nqb) * (16 * QB);
@@ -74,7 +102,7 @@ quad_min_kernel(QuadArgs a) {
     for (int qb = 0; qb < QB; ++qb) {
         const int64_t i = q0 + qb * 16 + li;
         const bool ok = i < a.nq;
-        const float* row = a.xq + (ok ? i : 0) * a.d;
+        const float* row = a.xq + (!ok ? 0 : a.rest.list ? a.rest.at(i) : i) * a.d;
 #pragma unroll
         for (int s = 0; s < S4; ++s) q[qb][s] = load_granule<OpF32, VEC>(row, 4 * s + lh, a.d, ok);
     }
@@ -186,7 +214,7 @@ __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
     const float* __restrict__ least, int64_t ld, const uint64_t* __restrict__ lists,
     int32_t nlists, int32_t kq, const float* __restrict__ xq, const float* __restrict__ xb,
     const float* __restrict__ yn, int64_t nb, int32_t d, int32_t vec, int32_t l2, int32_t k,
-    float* __restrict__ D, int64_t* __restrict__ I) {
+    RestSpan rest, float* __restrict__ D, int64_t* __restrict__ I) {
     __shared__ __align__(16) float xs[kMaxDim];
     __shared__ uint64_t pool[P];
     __shared__ float dist[N];
@@ -194,15 +222,20 @@ __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
     __shared__ PoolState st;
     __shared__ uint32_t ws[2][kPoolWaves];
     const int tid = threadIdx.x;
-    const int64_t q = blockIdx.x;
+    const int64_t i = blockIdx.x;
+    int64_t q = i;
+    if (rest.list) {
+        if (i >= rest.size()) return;
+        q = rest.at(i);
+    }
     for (int t = tid; t < d; t += kPoolThreads) xs[t] = xq[q * d + t];
     uint32_t found;
     if (lists) {
         uint64_t limit;
-        found = pool_stream<P>(lists + q * (int64_t)nlists * kq, (int64_t)nlists * kq, pool, bins,
+        found = pool_stream<P>(lists + i * (int64_t)nlists * kq, (int64_t)nlists * kq, pool, bins,
                                &st, kq, limit);
     } else {
-        found = pool_values<P, U, false>(least + q * ld, (uint32_t)ld, 0u, kq, pool, bins, &st, ws);
+        found = pool_values<P, U, false>(least + i * ld, (uint32_t)ld, 0u, kq, pool, bins, &st, ws);
         if (found > (uint32_t)kq) {
             pool_cut<P>(pool, bins, &st, found, kq);
             found = (uint32_t)kq;
@@ -346,13 +379,37 @@ mk_status quads(QuadArgs a, bool vec, bool l2, hipStream_t s) {
     constexpr int WIDE = DP > 96 ? 2 : 4;
     const int qb = a.nq <= 16 ? 1 : WIDE;
     a.nqb = (int32_t)ceil_div(a.nq, 16 * qb);
+    if (a.rest.list) {  // (how many there are is known on the device)
+        const int64_t waves = std::min<int64_t>(8192, a.groups * ceil_div(a.nq, 16 * WIDE)) + ceil_div(a.nq, 16 * WIDE);
+        return launch_quads<DP, WIDE>(a, vec, l2, waves, s);
+    }
     // few queries: long runs of rows per wave (one query, 10^6 x 64 rows, 2 waves per
-    // SIMD's worth 68 us, 8 waves 82); more: four, for an even end
-    a.groups_per_wave = qb == 1 ? ceil_div(a.groups, 2048)
-                                : std::max<int64_t>(1, a.groups * a.nqb / 4096);
+    // SIMD's worth 68 us, 8 waves 82)
+    a.groups_per_wave = qb == 1 ? ceil_div(a.groups, 2048) : quad_groups(a.groups, a.nqb);
     const int64_t waves = ceil_div(a.groups, a.groups_per_wave) * a.nqb;
     return qb == 1 ? launch_quads<DP, 1>(a, vec, l2, waves, s)
                    : launch_quads<DP, WIDE>(a, vec, l2, waves, s);
+}
+
+mk_status quads_any(const QuadArgs& a, bool vec, bool l2, hipStream_t s) {
+    if (a.d <= 32) return quads<32>(a, vec, l2, s);
+    if (a.d <= 64) return quads<64>(a, vec, l2, s);
+    if (a.d <= 96) return quads<96>(a, vec, l2, s);
+    if (a.d <= 128) return quads<128>(a, vec, l2, s);
+    return quads<256>(a, vec, l2, s);
+}
+
+// Selection and finish by a workgroup per query.
+mk_status finish_any(const QuadArgs& a, int64_t nq, const uint64_t* lists, int32_t nseg, int32_t kq,
+                     bool l2, bool vec, int32_t k, float* D, int64_t* I, hipStream_t s) {
+    auto kern = kq <= 64    ? quad_finish_kernel<1280, 1, 256>
+                : kq <= 512 ? quad_finish_kernel<2560, 2, 2048>
+                            : quad_finish_kernel<4096, 2, 4096>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, a.out, a.ld, lists, nseg,
+                       kq, a.xq, a.xb, l2 ? a.yn : nullptr, a.nb, a.d, (int32_t)vec, (int32_t)l2, k,
+                       a.rest, D, I);
+    MK_LAUNCHED();
+    return MK_OK;
 }
 
 int32_t groups_kept(int32_t k) { return std::min(k + kSlack, kMaxK); }
@@ -387,12 +444,8 @@ mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float
         scratch = mem.ptr;
     }
     float* least = static_cast<float*>(scratch);
-    QuadArgs a{xq, xb, yn, nq, nb, d, ceil_div(nb, 64), 1, 1, least, ld};
-    if (d <= 32) MK_TRY(quads<32>(a, vec, l2, s));
-    else if (d <= 64) MK_TRY(quads<64>(a, vec, l2, s));
-    else if (d <= 96) MK_TRY(quads<96>(a, vec, l2, s));
-    else if (d <= 128) MK_TRY(quads<128>(a, vec, l2, s));
-    else MK_TRY(quads<256>(a, vec, l2, s));
+    QuadArgs a{xq, xb, yn, nq, nb, d, ceil_div(nb, 64), 1, 1, least, ld, RestSpan{}};
+    MK_TRY(quads_any(a, vec, l2, s));
     uint64_t* lists = nullptr;
     int64_t nseg = segments(ld, kq, nq);
     if (nseg > 1) {
@@ -412,13 +465,35 @@ mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float
         MK_LAUNCHED();
         return MK_OK;
     }
-    auto kern = kq <= 64    ? quad_finish_kernel<1280, 1, 256>
-                : kq <= 512 ? quad_finish_kernel<2560, 2, 2048>
-                            : quad_finish_kernel<4096, 2, 4096>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, least, ld, lists,
-                       (int32_t)nseg, kq, xq, xb, l2 ? yn : nullptr, nb, d, (int32_t)vec,
-                       (int32_t)l2, k, D, I);
-    MK_LAUNCHED();
+    return finish_any(a, nq, lists, (int32_t)nseg, kq, l2, vec, k, D, I, s);
+}
+
+// The fused search has one workgroup for 64 queries and a sixteenth of the rows, and
+// needs as long for one query as for a batch that fills the chip: 34 of 1,000 queries
+// left, 10^6 x 128 rows: 3.4 ms of the call, here 0.5.
+mk_status dense_rest(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
+                     int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I, RestQueries* rest,
+                     hipStream_t s) {
+    rest->done = 0;
+    const int64_t most = dense_rest_most(nq, nb);
+    if (most == 0 || !dense_pays(nq, nb, k)) return MK_OK;
+    const int64_t rounds = ceil_div(nq, most), ld = ceil_div(nb, 64) * 16;
+    Scratch mem;
+    const mk_status st = mem.alloc((size_t)(most * ld) * sizeof(float), s);
+    if (st == MK_ERR_OOM) {
+        (void)hipGetLastError();
+        return MK_OK;
+    }
+    MK_TRY(st);
+    const bool all = rounds <= 2;
+    for (int64_t r = 0; r < (all ? rounds : 1); ++r) {
+        QuadArgs a{xq, xb, yn, most, nb, d, ceil_div(nb, 64), 1, 1, mem.as<float>(), ld,
+                   RestSpan{rest->list, rest->count, r * most, most, all ? nq : most}};
+        MK_TRY(quads_any(a, vec, l2, s));
+        ProfScope prof("dense_finish", s);
+        MK_TRY(finish_any(a, most, nullptr, 1, groups_kept(k), l2, vec, k, D, I, s));
+    }
+    rest->done = all ? nq : most;
     return MK_OK;
 }
 

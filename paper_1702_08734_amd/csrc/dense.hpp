@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "kselect.hpp"
 
 namespace mk {
 
@@ -33,5 +34,16 @@ inline bool dense_beats_sieve(int64_t nq, int64_t nb, int32_t d, int32_t k) {
 mk_status dense_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                        int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
                        void* scratch, hipStream_t s);
+
+// The queries that another search left (there are at most nq of them), for any number
+// up to dense_rest_most: up to two launches of it search them all, and *rest tells the
+// fused search what is left to it.
+inline int64_t dense_rest_most(int64_t nq, int64_t nb) {
+    const int64_t most = (1ll << 30) / ((nb + 63) / 64 * 64);
+    return most < 64 ? 0 : most < 4096 ? (most < nq ? most : nq) : nq < 4096 ? nq : 4096;
+}
+mk_status dense_rest(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
+                     int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I, RestQueries* rest,
+                     hipStream_t s);
 
 }  // namespace mk

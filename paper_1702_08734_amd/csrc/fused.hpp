@@ -1336,10 +1336,11 @@ inline void plan_chunks(int64_t nq, int64_t nb, int BQ, int BN, int KS, int64_t*
 // workgroups: as many as the grid holds, up to max_chunks (one query of 10^6 x 128
 // rows: 2.4 ms with 16 chunks, each workgroup as slow as with 64 queries).  Clears
 // the rank points that it needs.
-static __global__ void rest_bounds_kernel(const uint32_t* __restrict__ count, int32_t blocks, int64_t nb,
+static __global__ void rest_bounds_kernel(const uint32_t* __restrict__ count, int64_t done,
+                                          int32_t blocks, int64_t nb,
                                           int32_t BQ, int32_t BN, int32_t max_chunks,
                                           RestPlan* __restrict__ plan, uint32_t* __restrict__ bound) {
-    const int32_t n = (int32_t)*count;
+    const int32_t n = *count <= done ? 0 : (int32_t)*count;
     RestPlan r{BN, n, 1, (n + BQ - 1) / BQ, 0};
     if (n > 0 && nb > 0) {
         int64_t c = blocks / r.nqb;
@@ -1374,7 +1375,7 @@ mk_status fused_scratch(int64_t nq, int64_t nb, int64_t nqb, int64_t nchunks, co
     most = most > nchunks ? most : nchunks;
     const int64_t grid = ceil_div((int64_t)words, 1024);
     hipLaunchKernelGGL(rest_bounds_kernel, dim3((unsigned)(grid < 1024 ? grid : 1024)), dim3(256), 0, s,
-                       rest->count, (int32_t)(nqb * nchunks), nb, (int32_t)S::BQ, (int32_t)S::BN,
+                       rest->count, rest->done, (int32_t)(nqb * nchunks), nb, (int32_t)S::BQ, (int32_t)S::BN,
                        (int32_t)most, *plan, bound.as<uint32_t>());
     MK_LAUNCHED();
     return MK_OK;

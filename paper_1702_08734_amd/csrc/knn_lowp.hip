@@ -238,7 +238,7 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, R, false, D, I, s));
-    const RestQueries rest{w.rest, w.nrest};
+    const RestQueries rest{w.rest, w.nrest, 0};
     return lowp_dispatch_k<Fused, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2,
                                       D, I, s, &rest);
 }

@@ -59,11 +59,12 @@ struct Lend {
     void* ptr;
     size_t bytes;
 };
-// Queries that another search left to the fused one: list[0 .. *count), in device
-// memory, in any order.
+// Queries that another search left to be searched again: list[0 .. *count), in device
+// memory, in any order.  At most `done` of them: someone else takes them.
 struct RestQueries {
     const uint32_t* list;
     const uint32_t* count;
+    int64_t done;
 };
 mk_status knn_search(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, mk_metric metric, float* D, int64_t* I,

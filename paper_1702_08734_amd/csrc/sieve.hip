@@ -1,6 +1,7 @@
 // Threshold-first exact search of FP32 rows (sieve.hpp): host side.
 #include <algorithm>
 
+#include "dense.hpp"
 #include "knn_classes.hpp"
 #include "sieve.hpp"
 
@@ -43,6 +44,17 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
                        w.flags, w.rest, w.nrest, D, I);
     MK_LAUNCHED();
     return MK_OK;
+}
+
+// The queries that are left (none, as a rule): few by the small-side search, more by
+// the fused one.
+template <int DP>
+static mk_status search_rest(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
+                             int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
+                             RestQueries rest, hipStream_t s) {
+    MK_TRY(dense_rest(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, &rest, s));
+    if (rest.done >= nq) return MK_OK;
+    return knn_dispatch_k<DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, nullptr, &rest);
 }
 
 // Exact search by thresholds (sieve.hpp); yn may be null (norms of the rows
@@ -150,9 +162,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
         MK_TRY(launch(false, rows, yscale, yoff, n, r0));
     }
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s));
-    // the queries that are left (none, as a rule) take the fused search
-    const RestQueries rest{w.rest, w.nrest};
-    return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I, s, nullptr, &rest);
+    return search_rest<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I,
+                           RestQueries{w.rest, w.nrest, 0}, s);
 }
 
 
@@ -180,7 +191,6 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
     uint32_t* flags = reinterpret_cast<uint32_t*>(base + o_w);
     uint32_t *bad_db = flags + nq, *nrest = bad_db + 1;
-    const RestQueries rest{nrest + 1, nrest};
     float* norms = yn ? nullptr : floats(o_n);
     hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 2, 256), 1024)),
                        dim3(256), 0, s, flags, nq + 2);
@@ -213,8 +223,8 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
                        xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, nrest + 1, nrest, D, I);
     MK_LAUNCHED();
-    return knn_dispatch_k<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I, s, nullptr,
-                              &rest);
+    return search_rest<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I,
+                           RestQueries{nrest + 1, nrest, 0}, s);
 }
 
 #define MK_SIEVE_CLASS(DP)                                                                        \
