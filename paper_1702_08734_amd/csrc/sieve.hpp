@@ -815,8 +815,11 @@ __device__ __forceinline__ void leave_query(int64_t q, uint32_t* __restrict__ re
 // 2,000 queries, keff = 1,016, pools of about 2,500 keys: 210 us against 330 us by a
 // wave per query with a sorted register queue; 10^4 queries, keff = 400: 284 against
 // 450 us.  Bound by the gathers of the re-ranked rows (4.8 TB/s and 5.4 TB/s).
+// The registers are held to what the first round needs (the second one, in its place or
+// spilled, cost 10^4 queries with keff = 116 / 1,016 50 / 72 us more by fewer waves).
 template <int P>  // keff <= P / 2
-__global__ __launch_bounds__(kPoolThreads) void sieve_finish(
+__global__ __launch_bounds__(kPoolThreads)
+__attribute__((amdgpu_waves_per_eu(P == 1024 ? 8 : P == 2048 ? 5 : 4))) void sieve_finish(
     const uint64_t* __restrict__ pools, const uint32_t* __restrict__ cnt, uint32_t cap,
     const float* __restrict__ thr, int64_t thr_ld,
     const float* __restrict__ xq, const float* __restrict__ xb, int32_t d, int32_t vec,
@@ -825,7 +828,7 @@ __global__ __launch_bounds__(kPoolThreads) void sieve_finish(
     uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest, float* __restrict__ D,
     int64_t* __restrict__ I) {
     __shared__ uint64_t pool[P];
-    __shared__ uint32_t bins[kCutBins];
+    __shared__ __align__(8) uint32_t bins[kCutBins];
     __shared__ PoolState st;
     __shared__ __align__(16) float xs[kMaxDim];
     __shared__ float dist[P / 2];
@@ -859,7 +862,7 @@ __global__ __launch_bounds__(kPoolThreads) void sieve_finish(
                 return;
             }
             // the rest of the pool's rows whose bound does not clear the k-th
-            __shared__ uint64_t strip[kPoolThreads];
+            uint64_t* strip = reinterpret_cast<uint64_t*>(bins);  // (free between cuts)
             uint64_t enter = st.limit;
 #pragma unroll 1
             for (uint32_t e0 = 0; e0 < n; e0 += kPoolThreads) {
