@@ -111,13 +111,15 @@ mk_status mk_kselect(const float* a, int64_t nrows, int64_t len, int32_t k, int3
  * cancellation error of ||x||^2 + ||y||^2 - 2<x,y>.  nb must be < 2^31.
  * Supported d: 1..256.  Scratch (device), large calls: 4 DP bytes per query and per
  * row (DP: d rounded up to 32, 64, 96, 128 or 256; at most 512 MiB of rows at a
- * time), pools of a few times k + 16 keys and at most 1 GiB per batch of queries;
- * small calls: about nb bytes per query, at most 512 MiB.  Where that cannot be
- * allocated the fused search takes the call: nq x nchunks x S keys of 8 bytes,
- * nchunks <= 16, S = 64 R with R the smallest power of two such that 64 R
- * >= min(k + 16, 1024), doubled when 64 R >= 256 (candidate pools); plus
- * 16 bytes per (query, chunk) of shared rank points and, for L2 without
- * supplied norms, 4 bytes per database row.
+ * time), pools of a few times k + 16 keys and at most 1 GiB per batch of queries; when
+ * these have been given back, for the queries without a proof (however many there
+ * turn out to be), at most 1 GiB and the fused search's scratch for a batch; 12
+ * bytes per query and, for L2 without supplied norms, 4 per row throughout.  Small
+ * calls: about nb bytes per query, at most 512 MiB.  Where that cannot be allocated
+ * the fused search takes the call: nq x nchunks x S keys of 8 bytes, nchunks <= 16,
+ * S = 64 R with R the smallest power of two such that 64 R >= min(k + 16, 1024),
+ * doubled when 64 R >= 256 (candidate pools); plus 16 bytes per (query, chunk) of
+ * shared rank points and, for L2 without supplied norms, 4 bytes per database row.
  */
 mk_status mk_knn_search(const float* xq, int64_t nq, const float* xb, int64_t nb, int32_t d,
                         int32_t k, mk_metric metric, float* D, int64_t* I, mk_stream_t stream);

@@ -80,13 +80,13 @@ inline bool nearest_pays(int64_t nq, int64_t nb) {
     return nq >= 8192 && nb >= 256 && nb <= 65536 && nq * nb >= (1ll << 25);
 }
 
-// Queries per batch: at most 1 GiB of pools and of the sample's scores.
+// Queries per batch: at most 1 GiB of pools, and of the sample's scores.
 inline int64_t sieve_batch(int64_t nq, int64_t nb, int32_t keff) {
     const SievePlan p = plan_sieve(nb, keff);
     int64_t b = (1ll << 30) / (8 * p.cap);
     if (b > (1ll << 30) / p.sample) b = (1ll << 30) / p.sample;
-    b = b / 256 * 256;
-    if (b < 256) b = 256;
+    b = b >= 256 ? b / 256 * 256 : b / 64 * 64;  // (at least 64: a pool is below 8 MB)
+    if (b < 64) b = 64;
     return nq < b ? nq : b;
 }
 

@@ -126,3 +126,58 @@ def test_unproven_by_the_first_candidates(api, kind, scale, d, k):
                 err = gamma(d + 2) * ((x * x).sum() + (y * y).sum(1).max())
                 assert scale == 300 and (D[i] <= d64 + 2 * err).all(), (i, fails[:10])
                 assert (np.diff(D[i]) >= 0).all() and len(set(I[i])) == k
+
+
+# a second slab of split rows (524,288 of 1,024 bytes are one), shorter than a tile, that
+# holds the best rows; the same by supplied norms
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("given", [False, True])
+def test_sieve_second_slab(api, metric, given):
+    rng = np.random.default_rng(11)
+    nb, d, nq = 524_288 + 37, 132, 300
+    xb, xq = mixture(rng, nb, d), mixture(rng, nq, d)
+    xb[-37:] = 1.001 * xq[:37] + np.float32(1e-3) * rng.standard_normal((37, d)).astype(np.float32)
+    xb[524_287] = xq[40]
+    yn = api.norms(dev(xb)) if given else None
+    print(f"second slab {metric} {given}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), 7, metric, yn)
+    D, I = D.cpu().numpy(), I.cpu().numpy()
+    if metric == "l2":
+        assert (I[:37, 0] == np.arange(nb - 37, nb)).all() and I[40, 0] == 524_287
+    rows = np.array([0, 17, 36, 40, 41, 299])
+    fails = check_rows(D[rows], I[rows], xq, xb, rows, 7, metric)
+    assert not fails, fails[:10]
+
+
+def test_sieve_query_batches(api):
+    # 60,000 queries with pools for 39,936 at a time
+    rng = np.random.default_rng(12)
+    xb, xq = dev(mixture(rng, 200_000, 32)), dev(mixture(rng, 60_000, 32))
+    print("query batches", flush=True)
+    D, I = api.knn_search(xq, xb, 1000)
+    for lo in (0, 20_000, 40_000):
+        d2, i2 = api.knn_search(xq[lo:lo + 20_000].contiguous(), xb, 1000)
+        assert torch.equal(D[lo:lo + 20_000], d2) and torch.equal(I[lo:lo + 20_000], i2)
+
+
+def test_lowp_query_batches(api):
+    rng = np.random.default_rng(13)
+    xb, xq = dev(mixture(rng, 200_000, 32)), dev(mixture(rng, 60_000, 32))
+    lp, inv = api.quantize_rows(xb, "bf16")
+    print("lowp query batches", flush=True)
+    D, I = api.knn_search_lowp(xq, xb, lp, inv, 10, 1024, "bf16", "ip")
+    for lo in (0, 20_000, 40_000):
+        d2, i2 = api.knn_search_lowp(xq[lo:lo + 20_000].contiguous(), xb, lp, inv, 10, 1024, "bf16", "ip")
+        assert torch.equal(D[lo:lo + 20_000], d2) and torch.equal(I[lo:lo + 20_000], i2)
+
+
+def test_nearest_query_batches(api):
+    # 2^20 queries at a time
+    rng = np.random.default_rng(14)
+    n = (1 << 20) + 300
+    x, c = dev(mixture(rng, n, 8)), dev(mixture(rng, 260, 8))
+    print("nearest query batches", flush=True)
+    a, dist = api.kmeans_assign(x, c)
+    for lo in (0, (1 << 20) - 5000, n - 9000):
+        a2, d2 = api.kmeans_assign(x[lo:lo + 9000].contiguous(), c)
+        assert torch.equal(a[lo:lo + 9000], a2) and torch.equal(dist[lo:lo + 9000], d2)

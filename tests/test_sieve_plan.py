@@ -15,6 +15,12 @@ int row_bits() { return mk::kSieveRowBits; }
 void chunks(int64_t nqb, int64_t nb, int bn, int64_t* out) {
     mk::plan_sieve_chunks(nqb, nb, bn, &out[0], &out[1]);
 }
+void batch(int64_t nq, int64_t nb, int keff, int64_t* out) {
+    const mk::SievePlan p = mk::plan_sieve(nb, keff);
+    out[0] = mk::sieve_batch(nq, nb, keff);
+    out[1] = p.cap;
+    out[2] = p.sample;
+}
 }
 """
 
@@ -28,6 +34,7 @@ def plan(tmp_path_factory):
                    check=True)
     lib = ctypes.CDLL(str(so))
     lib.chunks.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
+    lib.batch.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.POINTER(ctypes.c_int64)]
     return lib
 
 
@@ -45,3 +52,15 @@ def test_chunks_fit_their_bits(plan, bn, nqb):
         n, length = out
         assert length < top and length % bn == 0, (nqb, nb, length)
         assert (n - 1) * length < nb <= n * length, (nqb, nb, n, length)
+
+
+# pools and sample scores of a batch of queries: at most 1 GiB each
+@pytest.mark.parametrize("keff", [17, 48, 116, 528, 1040])
+def test_batches_fit_their_memory(plan, keff):
+    for nb in [16384, 100_003, 1 << 20, 10_000_019, 1 << 27, 2**31 - 1]:
+        for nq in (1, 64, 1000, 100_000, 10_000_000):
+            out = (ctypes.c_int64 * 3)()
+            plan.batch(nq, nb, keff, out)
+            b, cap, sample = out
+            assert min(nq, 64) <= b <= nq
+            assert b * cap * 8 <= 1 << 30 and b * sample <= 1 << 30, (nq, nb, keff, b, cap)
