@@ -137,14 +137,9 @@ struct Scratch {
     }
     template <class T>
     T* as() const { return static_cast<T*>(ptr); }
-    // Give it back before the end of the scope: what the call takes on the same
-    // stream from here on may be the same memory.
-    void release() {
+    ~Scratch() {
         if (ptr && owned) (void)hipFreeAsync(ptr, stream);
-        ptr = nullptr;
-        owned = false;
     }
-    ~Scratch() { release(); }
 };
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }

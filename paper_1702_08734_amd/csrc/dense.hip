@@ -479,7 +479,7 @@ mk_status dense_rest(const float* xq, int64_t nq, const float* xb, const float* 
     if (most == 0 || !dense_pays(nq, nb, k)) return MK_OK;
     const int64_t rounds = ceil_div(nq, most), ld = ceil_div(nb, 64) * 16;
     Scratch mem;
-    const mk_status st = mem.alloc((size_t)(most * ld) * sizeof(float), s);
+    const mk_status st = mem.alloc(dense_rest_bytes(nq, nb, k), s);
     if (st == MK_ERR_OOM) {
         (void)hipGetLastError();
         return MK_OK;

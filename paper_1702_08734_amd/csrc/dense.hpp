@@ -42,6 +42,10 @@ inline int64_t dense_rest_most(int64_t nq, int64_t nb) {
     const int64_t most = (1ll << 30) / ((nb + 63) / 64 * 64);
     return most < 64 ? 0 : most < 4096 ? (most < nq ? most : nq) : nq < 4096 ? nq : 4096;
 }
+// Its scratch (0: it takes none of them).
+inline size_t dense_rest_bytes(int64_t nq, int64_t nb, int32_t k) {
+    return dense_pays(nq, nb, k) ? (size_t)dense_rest_most(nq, nb) * (size_t)((nb + 63) / 64 * 64) : 0;
+}
 mk_status dense_rest(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                      int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I, RestQueries* rest,
                      hipStream_t s);

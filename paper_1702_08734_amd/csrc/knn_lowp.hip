@@ -176,9 +176,8 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
         return at;
     };
     const size_t o_w = part(sizeof(uint32_t) * (size_t)(3 * nq + 1));
-    Scratch keep, mem;
-    MK_TRY(keep.alloc(used, s));
-    used = 0;
+    const size_t kept = used;
+    Scratch mem;
     const size_t o_s = part((size_t)plan.sample * stride), o_a = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_b = part(sizeof(float) * (size_t)plan.sample);
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
@@ -191,7 +190,7 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     SieveScratch w;
     w.pool = reinterpret_cast<uint64_t*>(base + o_p);
     w.cap = (uint32_t)plan.cap;
-    w.cnt = reinterpret_cast<uint32_t*>(keep.as<unsigned char>() + o_w);
+    w.cnt = reinterpret_cast<uint32_t*>(base + o_w);
     w.flags = w.cnt + nq;
     w.nrest = w.flags + nq;
     w.rest = w.nrest + 1;
@@ -240,8 +239,11 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     const bool vec = (d % 4 == 0) && (reinterpret_cast<uintptr_t>(xq) % 16 == 0) &&
                      (reinterpret_cast<uintptr_t>(xb) % 16 == 0);
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, R, false, D, I, s));
-    mem.release();
     const RestQueries rest{w.rest, w.nrest, 0};
+    Arena spent;  // (what the pass no longer needs)
+    spent.base = base + kept;
+    spent.size = used - kept;
+    ArenaScope scope(&spent);
     return lowp_dispatch_k<Fused, DP>(xq, xq_lp, xq_inv, nq, xb, xb_lp, xb_inv, yn, nb, d, k, R, l2,
                                       D, I, s, &rest);
 }

@@ -47,13 +47,21 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
 }
 
 // The queries that are left (none, as a rule): few by the small-side search, more by
-// the fused one.
+// the fused one.  Each has the caller's memory (256-byte aligned) as scratch, as far as
+// it goes (an allocation between the launches costs some 10 us).
 template <int DP>
 static mk_status search_rest(const float* xq, int64_t nq, const float* xb, const float* yn, int64_t nb,
                              int32_t d, int32_t k, bool l2, bool vec, float* D, int64_t* I,
-                             RestQueries rest, hipStream_t s) {
-    MK_TRY(dense_rest(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, &rest, s));
+                             RestQueries rest, unsigned char* scratch, size_t bytes, hipStream_t s) {
+    Arena first, second;
+    first.base = second.base = scratch;
+    first.size = second.size = bytes;
+    {
+        ArenaScope scope(&first);
+        MK_TRY(dense_rest(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, &rest, s));
+    }
     if (rest.done >= nq) return MK_OK;
+    ArenaScope scope(&second);
     return knn_dispatch_k<DP>(xq, nq, xb, yn, nb, d, k, l2, vec, D, I, s, nullptr, &rest);
 }
 
@@ -70,8 +78,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     // rows per launch: at most 512 MiB of split rows at a time
     const int64_t slab = std::min<int64_t>(nb, (512ll << 20) / RB / S::BN * S::BN);
 
-    // two allocations, carved (each part 256-byte aligned): what the search of the
-    // queries that are left needs too, and the rest, given back before it
+    // one allocation, carved (each part 256-byte aligned): first what the search of the
+    // queries that are left needs too; that search has the rest of it
     size_t used = 0;
     auto part = [&](size_t bytes) {
         const size_t at = used;
@@ -81,9 +89,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const bool own_norms = l2 && !yn;
     const size_t o_w = part(sizeof(uint32_t) * (size_t)(3 * nq + 2));
     const size_t o_n = part(own_norms ? sizeof(float) * (size_t)nb : 0);
-    Scratch keep, mem;
-    MK_TRY(keep.alloc(used, s));
-    used = 0;
+    const size_t kept = used;
+    Scratch mem;
     const size_t o_q = part((size_t)(nq * RB)), o_s = part((size_t)(plan.sample * RB));
     const size_t o_y = part((size_t)(slab * RB)), o_qs = part(sizeof(float) * (size_t)nq);
     const size_t o_qn = part(sizeof(float) * (size_t)nq);
@@ -94,6 +101,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
     const size_t o_ti = part(sizeof(int64_t) * (size_t)(nq * plan.rank));
+    used = std::max(used, kept + dense_rest_bytes(nq, nb, k));
     MK_TRY(mem.alloc(used, s));
     unsigned char* base = mem.as<unsigned char>();
     auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
@@ -101,8 +109,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     float *qscale = floats(o_qs), *qnorm = floats(o_qn), *sscale = floats(o_ss);
     float *soff = floats(o_so), *yscale = floats(o_ys), *yoff = floats(o_yo);
     float *scores = floats(o_sc), *top = floats(o_t);
-    float* norms = own_norms ? reinterpret_cast<float*>(keep.as<unsigned char>() + o_n) : nullptr;
-    uint32_t* words = reinterpret_cast<uint32_t*>(keep.as<unsigned char>() + o_w);
+    float* norms = own_norms ? reinterpret_cast<float*>(base + o_n) : nullptr;
+    uint32_t* words = reinterpret_cast<uint32_t*>(base + o_w);
     SieveScratch w;
     w.pool = reinterpret_cast<uint64_t*>(base + o_p);
     w.cap = (uint32_t)plan.cap;
@@ -166,9 +174,8 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
         MK_TRY(launch(false, rows, yscale, yoff, n, r0));
     }
     MK_TRY(sieve_finish_any(w, xq, nq, xb, d, vec, l2, k, keff, true, D, I, s));
-    mem.release();
     return search_rest<DP>(xq, nq, xb, yn ? yn : norms, nb, d, k, l2, vec, D, I,
-                           RestQueries{w.rest, w.nrest, 0}, s);
+                           RestQueries{w.rest, w.nrest, 0}, base + kept, used - kept, s);
 }
 
 
@@ -186,19 +193,19 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     };
     const size_t o_n = part(yn ? 0 : sizeof(float) * (size_t)nb);
     const size_t o_w = part(sizeof(uint32_t) * (size_t)(2 * nq + 2));
-    Scratch keep, mem;
-    MK_TRY(keep.alloc(used, s));
-    used = 0;
+    const size_t kept = used;
+    Scratch mem;
     const size_t o_q = part((size_t)(nq * RB)), o_y = part((size_t)(nb * RB));
     const size_t o_qs = part(sizeof(float) * (size_t)nq), o_qn = part(sizeof(float) * (size_t)nq);
     const size_t o_ys = part(sizeof(float) * (size_t)nb), o_yo = part(sizeof(float) * (size_t)nb);
     const size_t o_r = part(sizeof(uint4) * (size_t)nq);
+    used = std::max(used, kept + dense_rest_bytes(nq, nb, 1));
     MK_TRY(mem.alloc(used, s));
     unsigned char* base = mem.as<unsigned char>();
     auto floats = [&](size_t at) { return reinterpret_cast<float*>(base + at); };
-    uint32_t* flags = reinterpret_cast<uint32_t*>(keep.as<unsigned char>() + o_w);
+    uint32_t* flags = reinterpret_cast<uint32_t*>(base + o_w);
     uint32_t *bad_db = flags + nq, *nrest = bad_db + 1;
-    float* norms = yn ? nullptr : reinterpret_cast<float*>(keep.as<unsigned char>() + o_n);
+    float* norms = yn ? nullptr : reinterpret_cast<float*>(base + o_n);
     hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 2, 256), 1024)),
                        dim3(256), 0, s, flags, nq + 2);
     MK_LAUNCHED();
@@ -230,9 +237,8 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
                        xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, nrest + 1, nrest, D, I);
     MK_LAUNCHED();
-    mem.release();
     return search_rest<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I,
-                           RestQueries{nrest + 1, nrest, 0}, s);
+                           RestQueries{nrest + 1, nrest, 0}, base + kept, used - kept, s);
 }
 
 #define MK_SIEVE_CLASS(DP)                                                                        \
