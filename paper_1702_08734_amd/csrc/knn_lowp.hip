@@ -194,9 +194,7 @@ mk_status lowp_sieve(const float* xq, const void* xq_lp, const float* xq_inv, in
     w.flags = w.cnt + nq;
     w.nrest = w.flags + nq;
     w.rest = w.nrest + 1;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 1, 256), 1024)),
-                       dim3(256), 0, s, w.cnt, 2 * nq + 1);
-    MK_LAUNCHED();
+    MK_TRY(sieve_clear(w.cnt, 2 * nq + 1, xb, nb, d, nullptr, s));
     const float* side_a = Op::SCALED ? xb_inv : nullptr;
     const float* side_b = l2 ? yn : nullptr;
     hipLaunchKernelGGL(sample_rows_kernel, dim3((unsigned)ceil_div(plan.sample * (stride / 16), 256)),

@@ -11,12 +11,12 @@ namespace {
 
 template <int DP>
 mk_status split_rows(const float* x, int64_t n, int32_t d, bool vec, int kind,
-                     const float* yn, int64_t sample_of, void* out, float* scale,
-                     float* off, float* raw, uint32_t* bad, hipStream_t s) {
+                     const float* yn, const float* center, int64_t sample_of, void* out,
+                     float* scale, float* off, float* raw, uint32_t* bad, hipStream_t s) {
     const int64_t rows_per_block = 4 * (DP >= 96 ? 4 : 64 / (DP / 8));
     const int64_t blocks = ceil_div(n, rows_per_block);
     hipLaunchKernelGGL((split_rows_kernel<DP>), dim3((unsigned)(blocks < 16384 ? blocks : 16384)),
-                       dim3(256), 0, s, x, n, d, (int32_t)vec, (int32_t)kind, yn, sample_of,
+                       dim3(256), 0, s, x, n, d, (int32_t)vec, (int32_t)kind, yn, center, sample_of,
                        static_cast<unsigned char*>(out), scale, off, raw, bad);
     MK_LAUNCHED();
     return MK_OK;
@@ -99,6 +99,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_ys = part(sizeof(float) * (size_t)slab), o_yo = part(sizeof(float) * (size_t)slab);
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
+    const size_t o_c = part(sizeof(float) * DP);
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
     const size_t o_ti = part(sizeof(int64_t) * (size_t)(nq * plan.rank));
     used = std::max(used, kept + dense_rest_bytes(nq, nb, k));
@@ -120,12 +121,11 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     w.nrest = w.bad_db + 1;
     w.rest = w.nrest + 1;
     w.qnorm = qnorm;
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(2 * nq + 2, 256), 1024)),
-                       dim3(256), 0, s, words, 2 * nq + 2);
-    MK_LAUNCHED();
+    float* center = l2 ? floats(o_c) : nullptr;
+    MK_TRY(sieve_clear(words, 2 * nq + 2, xb, nb, d, center, s));
     const int kind = l2 ? kSplitDbL2 : kSplitDbIp;
-    MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, qrows, qscale, qnorm, nullptr, w.flags, s));
-    MK_TRY(split_rows<DP>(xb, plan.sample, d, vec, kind, yn, nb, srows, sscale, soff, nullptr, w.bad_db, s));
+    MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, center, 0, qrows, qscale, qnorm, nullptr, w.flags, s));
+    MK_TRY(split_rows<DP>(xb, plan.sample, d, vec, kind, yn, center, nb, srows, sscale, soff, nullptr, w.bad_db, s));
 
     SieveArgs a{};
     a.xq = qrows;
@@ -169,7 +169,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
                       reinterpret_cast<int64_t*>(base + o_ti), s));
     for (int64_t r0 = 0; r0 < nb; r0 += slab) {
         const int64_t n = std::min(slab, nb - r0);
-        MK_TRY(split_rows<DP>(xb + r0 * d, n, d, vec, kind, yn ? yn + r0 : nullptr, 0, rows,
+        MK_TRY(split_rows<DP>(xb + r0 * d, n, d, vec, kind, yn ? yn + r0 : nullptr, center, 0, rows,
                               yscale, yoff, norms ? norms + r0 : nullptr, w.bad_db, s));
         MK_TRY(launch(false, rows, yscale, yoff, n, r0));
     }
@@ -198,7 +198,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     const size_t o_q = part((size_t)(nq * RB)), o_y = part((size_t)(nb * RB));
     const size_t o_qs = part(sizeof(float) * (size_t)nq), o_qn = part(sizeof(float) * (size_t)nq);
     const size_t o_ys = part(sizeof(float) * (size_t)nb), o_yo = part(sizeof(float) * (size_t)nb);
-    const size_t o_r = part(sizeof(uint4) * (size_t)nq);
+    const size_t o_r = part(sizeof(uint4) * (size_t)nq), o_c = part(sizeof(float) * DP);
     used = std::max(used, kept + dense_rest_bytes(nq, nb, 1));
     MK_TRY(mem.alloc(used, s));
     unsigned char* base = mem.as<unsigned char>();
@@ -206,12 +206,10 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     uint32_t* flags = reinterpret_cast<uint32_t*>(base + o_w);
     uint32_t *bad_db = flags + nq, *nrest = bad_db + 1;
     float* norms = yn ? nullptr : reinterpret_cast<float*>(base + o_n);
-    hipLaunchKernelGGL(sieve_clear_kernel, dim3((unsigned)std::min<int64_t>(ceil_div(nq + 2, 256), 1024)),
-                       dim3(256), 0, s, flags, nq + 2);
-    MK_LAUNCHED();
-    MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, 0, base + o_q, floats(o_qs),
+    MK_TRY(sieve_clear(flags, nq + 2, xb, nb, d, floats(o_c), s));
+    MK_TRY(split_rows<DP>(xq, nq, d, vec, kSplitQuery, nullptr, floats(o_c), 0, base + o_q, floats(o_qs),
                           floats(o_qn), nullptr, flags, s));
-    MK_TRY(split_rows<DP>(xb, nb, d, vec, kSplitDbL2, yn, 0, base + o_y, floats(o_ys),
+    MK_TRY(split_rows<DP>(xb, nb, d, vec, kSplitDbL2, yn, floats(o_c), 0, base + o_y, floats(o_ys),
                           floats(o_yo), norms, bad_db, s));
     SieveArgs a{};
     a.xq = base + o_q;
