@@ -425,11 +425,13 @@ __global__ __launch_bounds__(kBlock) void pq_encode_any(const float* __restrict_
 // four code words and a bound of the rest (LowKeys).  The best group is then
 // evaluated as the plain kernel does, the second where the bound asks for it, and
 // every code word where that proves nothing either, so codes are the plain
-// kernel's.  Scores are lowered by kSplitErr (|r|^2 + |c|^2) as in sieve.hpp, and
+// kernel's.  Scores are lowered by kSplitErr (|r|^2 + |c|^2) as by split_err for sieve.hpp
+// (in units of 2^-24: 10 for the product, 16 for a norm, 4 for the last sums, of 32), and
 // by what the code words' common scale can lose.
 // Bound by vector operations (11 per lane and block of 4 x 16 scores, and as many
 // again per row for the split and the exact distances): 500,000 x 128, M = 16: 427
 // us; the plain kernel's 16 operations per row and code word took 764 us.
+constexpr float kSplitErr = 0x1p-19f;
 struct PqGroup {
     float score;
     int32_t code;
@@ -654,14 +656,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ?
             const int g1 = best[x].k1 & 63;
             PqGroup g{direct(v[x], 4 * g1 + lh), 4 * g1 + lh};
             g = row_best(g);
-            bool sure = ok[x] && g.score < (edge + b2) * (1.f - 0x1p-20f);
+            bool sure = ok[x] && g.score < (edge + b2) * (1.f - kDirectErr);
             if (__ballot(!sure)) {
                 const int g2 = best[x].k2 & 63;
                 PqGroup h{direct(v[x], 4 * g2 + lh), 4 * g2 + lh};
                 h = row_best(h);
                 if (!sure) {
                     if (h.score < g.score || (h.score == g.score && h.code < g.code)) g = h;
-                    sure = ok[x] && g.score < (edge + b3) * (1.f - 0x1p-20f);
+                    sure = ok[x] && g.score < (edge + b3) * (1.f - kDirectErr);
                 }
                 if (__ballot(!sure)) {
                     // every word, 64 per lane, in the plain kernel's order of

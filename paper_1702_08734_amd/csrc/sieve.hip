@@ -31,7 +31,7 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
     if (keff <= 64) {
         hipLaunchKernelGGL(sieve_finish_wave, dim3((unsigned)ceil_div(nq, kMergeWaves)),
                            dim3(64 * kMergeWaves), 0, s, w.pool, w.cnt, w.cap, w.thr, w.thr_ld, xq, nq, xb, d,
-                           (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
+                           (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.err, w.qnorm, w.bad_db,
                            w.flags, w.rest, w.nrest, D, I);
         MK_LAUNCHED();
         return MK_OK;
@@ -40,7 +40,7 @@ mk_status sieve_finish_any(const SieveScratch& w, const float* xq, int64_t nq, c
                 : keff <= 1024 ? sieve_finish<2048>
                                : sieve_finish<4096>;
     hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, w.pool, w.cnt, w.cap, w.thr,
-                       w.thr_ld, xq, xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.qnorm, w.bad_db,
+                       w.thr_ld, xq, xb, d, (int32_t)vec, (int32_t)l2, k, keff, (int32_t)cert, w.err, w.qnorm, w.bad_db,
                        w.flags, w.rest, w.nrest, D, I);
     MK_LAUNCHED();
     return MK_OK;
@@ -143,6 +143,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     a.bad_db = w.bad_db;
     w.thr = a.thr;
     w.thr_ld = a.thr_ld;
+    w.err = split_err(DP);
     const double fk = (double)plan.sample / (double)nb * k;  // of the k best, in the sample
     a.tail = (float)(std::log(plan.rank / fk) / std::log((double)plan.rank));
     a.scores = scores;
@@ -233,7 +234,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
         MK_LAUNCHED();
     }
     hipLaunchKernelGGL(nearest_finish, dim3((unsigned)ceil_div(nq, 16)), dim3(256), 0, s, a.near,
-                       xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, floats(o_qn), bad_db, flags, nrest + 1, nrest, D, I);
+                       xq, nq, xb, yn, (int32_t)nb, d, (int32_t)vec, split_err(DP), floats(o_qn), bad_db, flags, nrest + 1, nrest, D, I);
     MK_LAUNCHED();
     return search_rest<DP>(xq, nq, xb, yn ? yn : norms, nb, d, 1, true, vec, D, I,
                            RestQueries{nrest + 1, nrest, 0}, base + kept, used - kept, s);

@@ -40,16 +40,6 @@ namespace mk {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 
-// Relative bound on what the split product, the norm and the direct form can
-// err together: every score is lowered by kSplitErr * (||x||^2 + ||y||^2) (L2)
-// or 2 kSplitErr ||x|| ||y|| (inner product), which makes it a lower bound of
-// the row's true score.  Splitting leaves at most 2^-23 per factor and drops
-// l l <= 2^-24 of a product; the FP32 sums add the rest.  Measured against
-// float64 on five distributions, d = 17..256: at most 3.2e-7 (root mean square
-// 3e-8 to 7e-8) of that sum; the FP32 chain of the fused kernel 9.5e-7 (4e-8 to
-// 2e-7).
-constexpr float kSplitErr = 1.9073486328125e-6f;  // 2^-19
-
 struct SieveSplit {  // two FP16 planes per row: h, then l
     static constexpr int EPG = 8, BYTES = 2, PLANES = 2;
     static constexpr bool SCALED = true;
@@ -192,6 +182,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr int BQ = S::BQ, NBUF = S::NBUF, PL = Op::PLANES;
     constexpr bool SAMPLE = MODE == kSample, FILTER = MODE == kFilter, NEAREST = MODE == kNearest;
     constexpr bool HASB = L2 || Op::SHIFTED;
+    constexpr float ERR = split_err(DP);
     constexpr int NSIDE = (Op::SCALED ? 1 : 0) + (HASB ? 1 : 0);
     // granule c of tile row j sits at c ^ (j & SW), or where rows are 12
     // granules at c + j / 2 (mod 12): the rows of an operand read fall in
@@ -265,7 +256,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             }
         const float inv = Op::SCALED && ok ? args.qscale[q] : 1.f;
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
-        sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * kSplitErr * sqrtf(args.qnorm[q]) : 0.f;
+        sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * ERR * sqrtf(args.qnorm[q]) : 0.f;
         thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
         if constexpr (FILTER && PL > 1)
             if (ok && args.flags[q] != 0u) thr[qb] = -INFINITY;
@@ -278,7 +269,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if constexpr (FILTER && L2 && PL > 1)
             if (ok) {
                 const float* t = args.thr + q * args.thr_ld;
-                if ((t[0] - t[1 - args.thr_ld]) * args.tail < 2.f * kSplitErr * args.qnorm[q])
+                if ((t[0] - t[1 - args.thr_ld]) * args.tail < 2.f * ERR * args.qnorm[q])
                     thr[qb] = -INFINITY;
             }
         if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
@@ -669,7 +660,7 @@ __device__ __forceinline__ int64_t sample_row(int64_t i, int64_t n, int64_t nb) 
 // origin need not be far from the center (10^4 queries, 10^6 x 128 rows, 130
 // standard deviations from the origin, k = 100: 19.9 ms without, 6.2 with it).
 //   scale[i] = 2^-p;
-//   off[i]: DB rows, L2: ||y||^2 (1 - kSplitErr); DB rows, inner product: ||y||;
+//   off[i]: DB rows, L2: ||y||^2 (1 - split_err); DB rows, inner product: ||y||;
 //   queries: ||x||^2;
 //   raw[i] (if given): the row's own squared norm.
 // Supplied norms yn: a row whose norm is infinite or NaN has no score; one that is
@@ -769,13 +760,13 @@ __global__ __launch_bounds__(256) void split_rows_kernel(
                 if (raw) raw[i] = own;
                 float of = ss;
                 if (kind == kSplitDbL2) {
-                    of *= 1.f - kSplitErr;
+                    of *= 1.f - split_err(DP);
                     if (yn) {
                         const float y = yn[src], more = y - own;
                         if (!(fabsf(y) < INFINITY))
                             of = y;
                         else if (fabsf(more) > 0x1p-16f * own)
-                            of += more - kSplitErr * fabsf(more);
+                            of += more - split_err(DP) * fabsf(more);
                     }
                 } else if (kind == kSplitDbIp) {
                     of = sqrtf(ss);
@@ -850,9 +841,9 @@ inline mk_status sieve_clear(uint32_t* p, int64_t n, const float* xb, int64_t nb
 // ------------------------------------------------------------- finish
 // What the direct-form value (squared distance, or negated inner product) of a row
 // is at least, by its score in a pool: the scores are lower bounds of rows' true
-// scores less the per-query constant kSplitErr ||x||^2 (L2).
-__device__ __forceinline__ float row_bound(float score, float nx, int32_t l2) {
-    return l2 ? (nx * (1.f - kSplitErr) + score) * (1.f - 0x1p-20f) : score;
+// scores less the per-query constant err ||x||^2 (L2; err: split_err).
+__device__ __forceinline__ float row_bound(float score, float nx, float err, int32_t l2) {
+    return l2 ? (nx * (1.f - err) + score) * (1.f - kDirectErr) : score;
 }
 
 // Query q to the list of those that the fused search takes.
@@ -884,7 +875,7 @@ __attribute__((amdgpu_waves_per_eu(P == 1024 ? 8 : P == 2048 ? 5 : 4))) void sie
     const uint64_t* __restrict__ pools, const uint32_t* __restrict__ cnt, uint32_t cap,
     const float* __restrict__ thr, int64_t thr_ld,
     const float* __restrict__ xq, const float* __restrict__ xb, int32_t d, int32_t vec,
-    int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
+    int32_t l2, int32_t k, int32_t keff, int32_t cert, float err, const float* __restrict__ qnorm,
     const uint32_t* __restrict__ bad_db, const uint32_t* __restrict__ flags,
     uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest, float* __restrict__ D,
     int64_t* __restrict__ I) {
@@ -917,8 +908,8 @@ __attribute__((amdgpu_waves_per_eu(P == 1024 ? 8 : P == 2048 ? 5 : 4))) void sie
         pool_cut<P>(pool, bins, &st, left, k);
         left = (uint32_t)k;
         const float worst = key_score(st.limit - 1), s_last = key_score(limit - 1), nx = qnorm[q];
-        if (!(worst < row_bound(s_last, nx, l2))) {  // (uniform)
-            if (!(worst < row_bound(thr[q * thr_ld], nx, l2))) {
+        if (!(worst < row_bound(s_last, nx, err, l2))) {  // (uniform)
+            if (!(worst < row_bound(thr[q * thr_ld], nx, err, l2))) {
                 if (tid == 0) leave_query(q, rest, nrest);
                 return;
             }
@@ -928,7 +919,7 @@ __attribute__((amdgpu_waves_per_eu(P == 1024 ? 8 : P == 2048 ? 5 : 4))) void sie
 #pragma unroll 1
             for (uint32_t e0 = 0; e0 < n; e0 += kPoolThreads) {
                 uint64_t key = e0 + tid < n ? pools[q * (int64_t)cap + e0 + tid] : kSentinel;
-                if (key < limit || !(row_bound(key_score(key), nx, l2) <= worst)) key = kSentinel;
+                if (key < limit || !(row_bound(key_score(key), nx, err, l2) <= worst)) key = kSentinel;
                 if (!__syncthreads_or(key != kSentinel)) continue;
                 strip[tid] = key;
                 __syncthreads();
@@ -965,7 +956,7 @@ __attribute__((amdgpu_waves_per_eu(P == 1024 ? 8 : P == 2048 ? 5 : 4))) void sie
 static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
     const uint64_t* __restrict__ pool, const uint32_t* __restrict__ cnt, uint32_t cap,
     const float* __restrict__ thr, int64_t thr_ld, const float* __restrict__ xq, int64_t nq, const float* __restrict__ xb, int32_t d, int32_t vec,
-    int32_t l2, int32_t k, int32_t keff, int32_t cert, const float* __restrict__ qnorm,
+    int32_t l2, int32_t k, int32_t keff, int32_t cert, float err, const float* __restrict__ qnorm,
     const uint32_t* __restrict__ bad_db, const uint32_t* __restrict__ flags,
     uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest, float* __restrict__ D,
     int64_t* __restrict__ I) {
@@ -1021,8 +1012,8 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
     if (cert) {
         const float worst = key_score(ws_element<KR>(nk, k - 1));
         const float nx = qnorm[q];
-        if (!(worst < row_bound(key_score(last), nx, l2))) {
-            if (!(worst < row_bound(thr[q * thr_ld], nx, l2))) {
+        if (!(worst < row_bound(key_score(last), nx, err, l2))) {
+            if (!(worst < row_bound(thr[q * thr_ld], nx, err, l2))) {
                 if (lane == 0) leave_query(q, rest, nrest);
                 return;
             }
@@ -1032,7 +1023,7 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
 #pragma unroll 1
             for (uint32_t e0 = 0; e0 < n; e0 += 64) {
                 uint64_t key = e0 + lane < n ? p[e0 + lane] : kSentinel;
-                if (key <= last || !(row_bound(key_score(key), nx, l2) <= worst)) key = kSentinel;
+                if (key <= last || !(row_bound(key_score(key), nx, err, l2) <= worst)) key = kSentinel;
                 if (!__ballot(key != kSentinel)) continue;
                 kl[wave][lane] = key;
                 __builtin_amdgcn_wave_barrier();
@@ -1063,7 +1054,7 @@ static __global__ __launch_bounds__(64 * kMergeWaves) void sieve_finish_wave(
 static __global__ __launch_bounds__(256) void nearest_finish(
     const uint4* __restrict__ near, const float* __restrict__ xq, int64_t nq,
     const float* __restrict__ xb, const float* __restrict__ yn, int32_t nb, int32_t d, int32_t vec,
-    const float* __restrict__ qnorm, const uint32_t* __restrict__ bad_db,
+    float err, const float* __restrict__ qnorm, const uint32_t* __restrict__ bad_db,
     const uint32_t* __restrict__ flags, uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest,
     float* __restrict__ D, int64_t* __restrict__ I) {
     constexpr int NQ = 4;
@@ -1133,7 +1124,7 @@ static __global__ __launch_bounds__(256) void nearest_finish(
         c[p] = near[q];
         g[p] = c[p].x;
         const float nx = qnorm[q];
-        edge[p] = nx * (1.f - kSplitErr);
+        edge[p] = nx * (1.f - err);
         bad[p] = flags[q] != 0u || *bad_db != 0u;
     }
     group_best(g, key);
@@ -1141,7 +1132,7 @@ static __global__ __launch_bounds__(256) void nearest_finish(
 #pragma unroll
     for (int p = 0; p < NQ; ++p) {
         const float s = fminf(__uint_as_float(c[p].z), __uint_as_float(c[p].w));
-        const bool sure = key_score(key[p]) < (edge[p] + s) * (1.f - 0x1p-20f);
+        const bool sure = key_score(key[p]) < (edge[p] + s) * (1.f - kDirectErr);
         g2[p] = sure ? 0x3FFFFFFFu : c[p].y;  // (no such group)
         if (!sure && c[p].y >= 0x3FFFFFFFu) g2[p] = 0x3FFFFFFFu;
         more |= !sure;
@@ -1152,9 +1143,9 @@ static __global__ __launch_bounds__(256) void nearest_finish(
 #pragma unroll
         for (int p = 0; p < NQ; ++p) {
             const float s1 = fminf(__uint_as_float(c[p].z), __uint_as_float(c[p].w));
-            if (!(key_score(key[p]) < (edge[p] + s1) * (1.f - 0x1p-20f))) {
+            if (!(key_score(key[p]) < (edge[p] + s1) * (1.f - kDirectErr))) {
                 key[p] = umin64(key[p], k2[p]);
-                if (!(key_score(key[p]) < (edge[p] + __uint_as_float(c[p].w)) * (1.f - 0x1p-20f)))
+                if (!(key_score(key[p]) < (edge[p] + __uint_as_float(c[p].w)) * (1.f - kDirectErr)))
                     bad[p] = true;
             }
         }
@@ -1185,6 +1176,7 @@ struct SieveScratch {
     const float* qnorm = nullptr;
     const float* thr = nullptr;  // threshold of query q at thr[q * thr_ld] (exact search)
     int64_t thr_ld = 0;
+    float err = 0.f;             // split_err (exact search)
 };
 
 // Selection, re-rank and proof of every query of a search (sieve.hip).

@@ -12,6 +12,33 @@ inline int64_t plan_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // rows of one chunk are staged as this many bits
 constexpr int kSieveRowBits = 25;
 
+// Relative bound on what the split product, the norms and their sum can err together,
+// for rows of DP components: every score is lowered by split_err (||x||^2 + ||y||^2)
+// (L2) or 2 split_err ||x|| ||y|| (inner product), which makes it a lower bound of the
+// row's true score.  In units of 2^-24, of ||x||^2 + ||y||^2:
+//   8 + 3 DP / 32  the product: two factors split to 2^-23 and l l <= 2^-22 dropped,
+//                  and a rounding per matrix instruction of the chain (how an
+//                  instruction adds up its 32 products is not documented: measured on
+//                  10^6 pairs of rows of equal components, whose roundings all go one
+//                  way, the whole errs by at most 8.5, 10.7, 12.4, 16.3 and 27.7 units
+//                  for DP = 32 .. 256, where this is 11, 14, 17, 20 and 32);
+//   8 NG + log2 LPR  a norm: 8 products per granule and lane, then a sum over lanes;
+//   4              components less the center, each rounded once;
+//   4              the norm's factor, the score's last sum, and the bound's own.
+// So it is a bound if no matrix instruction rounds worse than those; the largest error
+// of whole scores against float64 that was seen on five distributions, d = 17 .. 256,
+// is a sixth of it (3.2e-7; the fused kernel's FP32 chain 9.5e-7).
+constexpr float split_err(int DP) {
+    const int granules = DP / 8, lanes = granules > 8 ? 16 : granules;
+    int sum = 0;
+    for (int l = lanes; l > 1; l /= 2) ++sum;
+    return (float)(8 + 3 * DP / 32 + 8 * ((granules + lanes - 1) / lanes) + sum + 8) * 0x1p-24f;
+}
+// What the direct form of a distance errs by, of the distance: up to 16 chained sums of
+// squares per lane of the rows' components (d <= 256), a sum over 16 lanes, and the
+// differences, rounded before they are squared: 22 units of 2^-24, and one for the bound.
+constexpr float kDirectErr = 0x1p-19f;
+
 // Sample size, threshold rank and pool capacity.  Of the keff best rows a
 // sample of fraction f holds about mu = f keff, so a rank of mu + 4.5
 // sqrt(mu) + 4.5 leaves a chance of about 1e-8 that the threshold admits fewer
