@@ -265,7 +265,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         // sample's best `rank` scores (their number grows exponentially) these are about
         // ln(rank / (f k)) / ln(rank) of the best and the last of them apart, f the
         // sample's share of the rows; where that is less than the bound, no row is let
-        // through, the finish finds too few, and a block of such queries ends here.
+        // through and the finish finds too few.
         if constexpr (FILTER && L2 && PL > 1)
             if (ok) {
                 const float* t = args.thr + q * args.thr_ld;
@@ -275,10 +275,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
     }
     if constexpr (FILTER && PL > 1) {
-        bool any = false;
+        // a block without a chance, or with few (the pass costs a fifth to a quarter of
+        // what the fused search takes for its queries)
+        __shared__ int chances;
+        if (threadIdx.x == 0) chances = 0;
+        __syncthreads();
+        int mine = 0;
+        if (rg == 0 && lh == 0)
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) any |= thr[qb] > -INFINITY;
-        if (!__syncthreads_or(any)) return;
+            for (int qb = 0; qb < QB; ++qb) mine += thr[qb] > -INFINITY ? 1 : 0;
+        if (mine) atomicAdd(&chances, mine);
+        __syncthreads();
+        if (5 * chances < (int)(args.nq - q0 < BQ ? args.nq - q0 : BQ)) return;
     }
     if (FILTER && threadIdx.x == 0) flush_at = -1;
 
