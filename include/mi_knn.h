@@ -128,8 +128,8 @@ mk_status mk_knn_search(const float* xq, int64_t nq, const float* xb, int64_t nb
  * Exact k-NN against a database held in host memory (Section 5.1: inputs
  * larger than the GPU's memory stream in from the CPU).  The database is
  * copied in chunks of chunk_rows rows into two device buffers on a second
- * stream, the copy of chunk c + 1 overlapping the fused search of chunk c
- * on `stream`; each chunk's k best (mk_knn_search semantics, rows numbered
+ * stream, the copy of chunk c + 1 overlapping the search of chunk c on
+ * `stream`; each chunk's k best (mk_knn_search semantics, rows numbered
  * globally) are kept and one final k-selection over the chunks' lists keyed
  * (distance, row) gives the result.  Same contract as mk_knn_search (squared
  * L2 ascending or inner product descending, ties to the lower row, padding).

@@ -414,13 +414,6 @@ extern "C" mk_status mk_knn_search_host(const float* xq, int64_t nq, const float
             return;
         fail(hipEventRecord(ready[b], cs), "record");
     };
-    // Up to 3,500 queries the fused search of a chunk, with its small scratch, hides
-    // behind the next copy (a row takes as long to copy as to search for some 3,000
-    // queries); the other searches slow the copies down (5 * 10^6 x 128 rows, fused
-    // and other searches: 1,000 queries 48.7, 63 ms; 4,000 queries 69, 65; 10^4
-    // queries 143, 70).
-    const mk::Lend none{nullptr, 0};
-    const mk::Lend* lend = nq <= 3500 ? &none : nullptr;
     if (st == MK_OK) copy(0);
     for (int64_t c = 0; c < nchunks && st == MK_OK; ++c) {
         if (c + 1 < nchunks) copy(c + 1);
@@ -429,8 +422,12 @@ extern "C" mk_status mk_knn_search_host(const float* xq, int64_t nq, const float
         const int64_t r0 = c * chunk_rows;
         const int64_t n = nb - r0 < chunk_rows ? nb - r0 : chunk_rows;
         if (fail(hipStreamWaitEvent(s, ready[b], 0), "wait")) break;
+        // (Each call takes the search that it would take on a resident database: timed in
+        // turn, 5 * 10^6 x 128 rows, k = 10 / 1,000, against the fused search for all: 100
+        // queries 47 / 47 against 54 / 67 ms, 1,000 queries 60 / 64 against 65 / 67, 3,500
+        // queries 48 / 66 against 70 / 92.)
         st = mk::knn_search(xq, nq, buf[b].as<float>(), nullptr, n, d, k, metric, Dc.as<float>(),
-                            Ic.as<int64_t>(), s, nullptr, lend);
+                            Ic.as<int64_t>(), s);
         if (st != MK_OK) break;
         hipLaunchKernelGGL(mk::chunk_keys_kernel,
                            dim3((unsigned)std::min<int64_t>(mk::ceil_div(nq * k, 256), 1 << 20)),
