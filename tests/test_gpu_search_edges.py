@@ -181,3 +181,20 @@ def test_nearest_query_batches(api):
     for lo in (0, (1 << 20) - 5000, n - 9000):
         a2, d2 = api.kmeans_assign(x[lo:lo + 9000].contiguous(), c)
         assert torch.equal(a[lo:lo + 9000], a2) and torch.equal(dist[lo:lo + 9000], d2)
+
+
+# rows in the order of their clusters, queries near one of them: the sample's entries are
+# of strata far apart
+@pytest.mark.parametrize("metric", ["l2", "ip"])
+@pytest.mark.parametrize("nb,d,nq,k", [(60_000, 64, 300, 100), (60_033, 128, 512, 10), (131_071, 32, 700, 300),
+                                       (99_990, 200, 260, 40)])
+def test_sieve_rows_by_cluster(api, nb, d, nq, k, metric):
+    rng = np.random.default_rng(nb)
+    mu = 3.0 * rng.standard_normal((30, d))
+    xb = (mu[np.sort(rng.integers(0, 30, nb))] + rng.standard_normal((nb, d))).astype(np.float32)
+    xq = (mu[29] + rng.standard_normal((nq, d))).astype(np.float32)
+    check_all = np.unique(np.linspace(0, nq - 1, 12).astype(int))
+    print(f"rows by cluster nb={nb} d={d} {metric}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k, metric)
+    fails = check_rows(D.cpu().numpy()[check_all], I.cpu().numpy()[check_all], xq, xb, check_all, k, metric)
+    assert not fails, fails[:10]
