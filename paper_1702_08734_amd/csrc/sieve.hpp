@@ -1070,10 +1070,10 @@ static __global__ __launch_bounds__(256) void nearest_finish(
     const uint32_t* __restrict__ flags, uint32_t* __restrict__ rest, uint32_t* __restrict__ nrest,
     float* __restrict__ D, int64_t* __restrict__ I) {
     constexpr int NQ = 4;
+    __shared__ uint32_t leaving[4], first_place;
     const int lane = lane_id(), sub = lane & 15, rsel = lane >> 4;
     const int64_t w = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-    const int64_t q0 = w * NQ;
-    if (q0 >= nq) return;
+    const int64_t q0 = w * NQ;  // (a wave without queries goes along, on query nq - 1's data)
     // distances of the four rows of group g[p] to query q0 + p, as keys; the
     // least of the four in every lane
     auto group_best = [&](const uint32_t (&g)[NQ], uint64_t (&key)[NQ]) __attribute__((always_inline)) {
@@ -1084,7 +1084,7 @@ static __global__ __launch_bounds__(256) void nearest_finish(
         for (int p = 0; p < NQ; ++p) {
             const int64_t row = (int64_t)g[p] * 4 + rsel;
             live[p] = q0 + p < nq && row < nb && has_score(yn, xb, row, d);
-            x[p] = xq + (q0 + p < nq ? q0 + p : q0) * d;
+            x[p] = xq + (q0 + p < nq ? q0 + p : nq - 1) * d;
             y[p] = xb + (live[p] ? row : 0) * d;
             acc[p] = 0.f;
         }
@@ -1132,7 +1132,7 @@ static __global__ __launch_bounds__(256) void nearest_finish(
     float edge[NQ];
 #pragma unroll
     for (int p = 0; p < NQ; ++p) {
-        const int64_t q = q0 + p < nq ? q0 + p : q0;
+        const int64_t q = q0 + p < nq ? q0 + p : nq - 1;
         c[p] = near[q];
         g[p] = c[p].x;
         const float nx = qnorm[q];
@@ -1162,15 +1162,32 @@ static __global__ __launch_bounds__(256) void nearest_finish(
             }
         }
     }
+    // (one entry into the list per workgroup: 500,000 queries, all of them left, 5 ms for
+    // an entry each)
+    uint32_t mine = 0;
+#pragma unroll
+    for (int p = 0; p < NQ; ++p)
+        if (q0 + p < nq && bad[p]) ++mine;
+    if (lane == 0) leaving[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w4 = 0; w4 < 4; ++w4) {
+        before += w4 < (int)(threadIdx.x >> 6) ? leaving[w4] : 0u;
+        all += leaving[w4];
+    }
+    if (threadIdx.x == 0 && all) first_place = atomicAdd(nrest, all);
+    __syncthreads();
+    uint32_t place = first_place + before;
 #pragma unroll
     for (int p = 0; p < NQ; ++p) {
-        if (lane == p && q0 + p < nq) {
-            if (bad[p]) {
-                leave_query(q0 + p, rest, nrest);
-            } else {
-                D[q0 + p] = key_score(key[p]);
-                I[q0 + p] = (int64_t)key_index(key[p]);
-            }
+        if (q0 + p >= nq) break;
+        if (bad[p]) {
+            if (lane == p) rest[place] = (uint32_t)(q0 + p);
+            ++place;
+        } else if (lane == p) {
+            D[q0 + p] = key_score(key[p]);
+            I[q0 + p] = (int64_t)key_index(key[p]);
         }
     }
 }

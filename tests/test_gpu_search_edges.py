@@ -198,3 +198,26 @@ def test_sieve_rows_by_cluster(api, nb, d, nq, k, metric):
     D, I = api.knn_search(dev(xq), dev(xb), k, metric)
     fails = check_rows(D.cpu().numpy()[check_all], I.cpu().numpy()[check_all], xq, xb, check_all, k, metric)
     assert not fails, fails[:10]
+
+
+# nearest row: queries that leave for the general search, entered into its list together by
+# a workgroup's waves, the last of which may have no query at all
+@pytest.mark.parametrize("d", [24, 96, 250])
+@pytest.mark.parametrize("nq", [8192, 8193, 8215, 9001])
+@pytest.mark.parametrize("every", [1, 3, 40])
+def test_nearest_queries_left_together(api, d, nq, every):
+    rng = np.random.default_rng(nq + d + every)
+    x = dev(rng.standard_normal((nq, d)).astype(np.float32))
+    c = dev(rng.standard_normal((700, d)).astype(np.float32))
+    left = torch.zeros(nq, dtype=torch.bool, device="cuda")
+    left[::every] = True
+    left[-3:] = True
+    y = torch.where(left[:, None], torch.full_like(x, float("nan")), x)
+    print(f"nearest left together d={d} nq={nq} every={every}", flush=True)
+    a, dist = api.kmeans_assign(x, c)
+    a2, dist2 = api.kmeans_assign(y, c)
+    part = y[left][:4000].contiguous()  # (too few for the nearest-row search)
+    a3, dist3 = api.kmeans_assign(part, c)
+    assert torch.equal(a2[~left], a[~left]) and torch.equal(dist2[~left], dist[~left])
+    assert torch.equal(a2[left][:4000], a3)
+    assert torch.equal(dist2[left][:4000].view(torch.int32), dist3.view(torch.int32))
