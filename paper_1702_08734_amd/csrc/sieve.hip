@@ -99,7 +99,7 @@ mk_status sieve_dispatch(const float* xq, int64_t nq, const float* xb, const flo
     const size_t o_ys = part(sizeof(float) * (size_t)slab), o_yo = part(sizeof(float) * (size_t)slab);
     const size_t o_p = part(sizeof(uint64_t) * (size_t)(nq * plan.cap));
     const size_t o_sc = part(sizeof(float) * (size_t)(nq * (plan.sample / S::PER)));
-    const size_t o_c = part(sizeof(float) * DP);
+    const size_t o_c = part(sizeof(float) * (kCenterOn + 1));
     const size_t o_t = part(sizeof(float) * (size_t)(nq * plan.rank));
     const size_t o_ti = part(sizeof(int64_t) * (size_t)(nq * plan.rank));
     used = std::max(used, kept + dense_rest_bytes(nq, nb, k));
@@ -199,7 +199,7 @@ mk_status nearest_dispatch(const float* xq, int64_t nq, const float* xb, const f
     const size_t o_q = part((size_t)(nq * RB)), o_y = part((size_t)(nb * RB));
     const size_t o_qs = part(sizeof(float) * (size_t)nq), o_qn = part(sizeof(float) * (size_t)nq);
     const size_t o_ys = part(sizeof(float) * (size_t)nb), o_yo = part(sizeof(float) * (size_t)nb);
-    const size_t o_r = part(sizeof(uint4) * (size_t)nq), o_c = part(sizeof(float) * DP);
+    const size_t o_r = part(sizeof(uint4) * (size_t)nq), o_c = part(sizeof(float) * (kCenterOn + 1));
     used = std::max(used, kept + dense_rest_bytes(nq, nb, 1));
     MK_TRY(mem.alloc(used, s));
     unsigned char* base = mem.as<unsigned char>();

@@ -665,6 +665,8 @@ __device__ __forceinline__ int64_t sample_row(int64_t i, int64_t n, int64_t nb) 
     return lo + (int64_t)(h % (uint64_t)(hi - lo));
 }
 
+constexpr int kCenterRows = 32, kCenterOn = 256;  // (see sieve_clear_kernel)
+
 // Rows of d floats as two FP16 planes of DP elements (zero padded): x 2^p =
 // h + l, p the row's own power of two with max |x| 2^p in [2^13, 2^14).  With a
 // center (L2) x stands for the row less it, here and in all scores and bounds, which
@@ -694,14 +696,15 @@ __global__ __launch_bounds__(256) void split_rows_kernel(
     const int64_t rows_per_wave = 64 / LPR;
     const int64_t w0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
     const int64_t nw = (int64_t)gridDim.x * 4;
-    float mid[NG][8];  // this lane's components of the center
+    const bool centered = center && center[kCenterOn] != 0.f;
+    // this lane's components of the center (kept in registers where these allow as many
+    // waves with them)
+    auto middle = [&](int t) __attribute__((always_inline)) {
+        return centered && t < d ? center[t] : 0.f;
+    };
+    float mid[8];
 #pragma unroll
-    for (int g = 0; g < NG; ++g)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int t = (g * LPR + sub) * 8 + e;
-            mid[g][e] = center && t < d ? center[t] : 0.f;
-        }
+    for (int e = 0; e < 8; ++e) mid[e] = NG == 1 ? middle(sub * 8 + e) : 0.f;
     for (int64_t r0 = w0 * rows_per_wave; r0 < n; r0 += nw * rows_per_wave) {
         const int64_t i = r0 + lane / LPR;
         const bool live = i < n;
@@ -722,11 +725,11 @@ __global__ __launch_bounds__(256) void split_rows_kernel(
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[g][e] = (live && e0 + e < d) ? p[e0 + e] : 0.f;
             }
-            if (center)
+            if (centered)
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     own = fmaf(v[g][e], v[g][e], own);
-                    v[g][e] -= mid[g][e];
+                    v[g][e] -= NG == 1 ? mid[e] : middle(e0 + e);
                 }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(256) void split_rows_kernel(
             m = fmaxf(m, __shfl_xor(m, o, LPR));
             ss += __shfl_xor(ss, o, LPR);
         }
-        if (center) {
+        if (centered) {
 #pragma unroll
             for (int o = LPR / 2; o >= 1; o >>= 1) own += __shfl_xor(own, o, LPR);
         } else {
@@ -817,26 +820,49 @@ static __global__ void sample_rows_kernel(const unsigned char* __restrict__ xb, 
 }
 
 // Clears n words; with a center (a workgroup more) also takes the mean of 32 rows, as a
-// point that is near the rows for their distances (0 where it is out of the split's
-// range).
-constexpr int kCenterRows = 32;
+// point that is near the rows for their distances.  center[0 .. d), center[kCenterOn]:
+// whether rows are to be taken less it: not where it is out of the split's range, nor
+// where the rows are less than 8 deviations from the origin (proofs succeed there without
+// it -- they did at 10 deviations at every size measured and failed from 30 on -- and the
+// split is bound by vector operations too: 167 queries, 681,348 x 236 rows 668 us with
+// the center, 630 without).
 static __global__ __launch_bounds__(256) void sieve_clear_kernel(uint32_t* __restrict__ p, int64_t n,
                                                                 const float* __restrict__ xb,
                                                                 int64_t nb, int32_t d,
                                                                 float* __restrict__ center) {
     const int64_t blocks = gridDim.x - (center ? 1 : 0);
     if ((int64_t)blockIdx.x == blocks) {
+        __shared__ float part[2][4];
         const int t = threadIdx.x;
-        if (t >= d) return;
         const int rows = nb < kCenterRows ? (int)nb : kCenterRows;
-        float v[kCenterRows], sum = 0.f;
+        float v[kCenterRows], mean = 0.f, squares = 0.f;
 #pragma unroll
         for (int i = 0; i < kCenterRows; ++i)
-            v[i] = i < rows ? xb[(i * nb / kCenterRows) * d + t] : 0.f;
+            v[i] = i < rows && t < d ? xb[(i * nb / kCenterRows) * d + t] : 0.f;
 #pragma unroll
-        for (int i = 0; i < kCenterRows; ++i) sum += v[i];
-        sum /= (float)rows;
-        center[t] = fabsf(sum) < 0x1p50f ? sum : 0.f;
+        for (int i = 0; i < kCenterRows; ++i) {
+            mean += v[i];
+            squares = fmaf(v[i], v[i], squares);
+        }
+        mean /= (float)rows;
+        squares /= (float)rows;
+        float own = mean * mean;
+        // (one component out of range spoils the sum)
+        if (!(fabsf(mean) < 0x1p50f)) own = NAN;
+#pragma unroll
+        for (int o = 1; o < 64; o *= 2) {
+            own += __shfl_xor(own, o);
+            squares += __shfl_xor(squares, o);
+        }
+        if ((t & 63) == 0) {
+            part[0][t >> 6] = own;
+            part[1][t >> 6] = squares;
+        }
+        __syncthreads();
+        own = part[0][0] + part[0][1] + part[0][2] + part[0][3];
+        squares = part[1][0] + part[1][1] + part[1][2] + part[1][3];
+        if (t < d) center[t] = mean;
+        if (t == 0) center[kCenterOn] = own * 64.f >= squares * 63.f ? 1.f : 0.f;
         return;
     }
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += blocks * 256) p[i] = 0u;

@@ -200,6 +200,37 @@ def test_sieve_rows_by_cluster(api, nb, d, nq, k, metric):
     assert not fails, fails[:10]
 
 
+# rows nearer to the origin and further from it than the eight deviations from which on
+# the pass takes them less a center, rows of one point, and a component out of its range
+@pytest.mark.parametrize("kind", ["6", "9", "one point", "zeros", "huge component"])
+@pytest.mark.parametrize("nb,d,nq,k", [(60_000, 64, 300, 100), (50_021, 130, 260, 10), (90_000, 256, 300, 300)])
+def test_sieve_center(api, nb, d, nq, k, kind):
+    rng = np.random.default_rng(nb + d)
+    xb = rng.standard_normal((nb, d)).astype(np.float32)
+    xq = rng.standard_normal((nq, d)).astype(np.float32)
+    if kind in ("6", "9"):
+        xb, xq = xb + np.float32(kind), xq + np.float32(kind)
+    elif kind == "one point":
+        xb[:] = 5.0 + xb[0]
+        xb[::nb // 400] += rng.standard_normal((len(xb[::nb // 400]), d)).astype(np.float32)
+        xq = xq + np.float32(5)
+    elif kind == "zeros":
+        xb[:] = 0.0
+    else:
+        xb[:, 3] = np.float32(2.0 ** 51)
+        xq[:, 3] = np.float32(2.0 ** 51)
+    rows = np.unique(np.linspace(0, nq - 1, 12).astype(int))
+    print(f"center {kind} nb={nb} d={d}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k, "l2")
+    if kind == "huge component":  # (nothing of the other components is left in a score)
+        D64 = ((xq[rows, None].astype(np.float64) - xb[I.cpu().numpy()[rows]]) ** 2).sum(2)
+        np.testing.assert_allclose(D.cpu().numpy()[rows], D64, rtol=gamma(d) * 4)
+        return
+    # (equal rows: the band reaches over all of them)
+    fails = check_rows(D.cpu().numpy()[rows], I.cpu().numpy()[rows], xq, xb, rows, k, "l2", extra=nb - k)
+    assert not fails, fails[:10]
+
+
 # nearest row: queries that leave for the general search, entered into its list together by
 # a workgroup's waves, the last of which may have no query at all
 @pytest.mark.parametrize("d", [24, 96, 250])
