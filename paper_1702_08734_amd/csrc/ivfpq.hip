@@ -113,11 +113,41 @@ __global__ void fill_u32_kernel(unsigned int* __restrict__ a, int64_t n);
 // points, 4,096 clusters: 156 us in all; 64 million FP64 atomics took 437 us.
 constexpr int kSegRows = 256;
 
+// One to at[a] for every lane with 0 <= a < K, and the lane's place among them: of the
+// clusters of four lanes, those that eight lanes share or more are added once for all of
+// these (500,000 points in the order of 16 clusters: 11.4 ms with an atomic each, 0.24), the
+// others' by themselves.  Whole waves.
+__device__ __forceinline__ uint32_t wave_counts(int32_t a, int32_t K, uint32_t* __restrict__ at) {
+    const bool live = a >= 0 && a < K;
+    const int lane = lane_id();
+    uint64_t todo = __ballot(live), single = 0;
+    uint32_t place = 0;
+#pragma unroll 1
+    for (int r = 0; r < 4 && todo; ++r) {
+        const int src = __builtin_ctzll(todo);
+        const int32_t v = __builtin_amdgcn_readlane(a, src);
+        const uint64_t same = __ballot(live && a == v);
+        todo &= ~same;
+        if (__popcll(same) < 8) {
+            single |= same;
+            continue;
+        }
+        uint32_t base = 0;
+        if (lane == src) base = atomicAdd(&at[v], (uint32_t)__popcll(same));
+        base = (uint32_t)__builtin_amdgcn_readlane((int)base, src);
+        if (live && a == v)
+            place = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+    }
+    if ((todo | single) >> lane & 1) place = atomicAdd(&at[a], 1u);
+    return place;
+}
+
 __global__ void km_count(const int64_t* __restrict__ assign, int64_t n, int32_t K,
                          uint32_t* __restrict__ counts) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += kStride) {
-        const int64_t a = assign[i];
-        if (a >= 0 && a < K) atomicAdd(&counts[a], 1u);  // others are ignored
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < n; i0 += kStride) {
+        const int64_t a = i0 + threadIdx.x < n ? assign[i0 + threadIdx.x] : -1;
+        (void)wave_counts(a >= 0 && a < K ? (int32_t)a : -1, K, counts);  // others are ignored
     }
 }
 
@@ -170,9 +200,12 @@ __global__ __launch_bounds__(1024) void km_prefix(const uint32_t* __restrict__ c
 __global__ void km_order(const int64_t* __restrict__ assign, int64_t n, int32_t K,
                          uint32_t* __restrict__ cursor, uint32_t* __restrict__ order,
                          const uint32_t* __restrict__ seg, uint32_t* __restrict__ seg_cluster) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += kStride) {
-        const int64_t a = assign[i];
-        if (a >= 0 && a < K) order[atomicAdd(&cursor[a], 1u)] = (uint32_t)i;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock; i0 < n; i0 += kStride) {
+        const int64_t i = i0 + threadIdx.x;
+        const int64_t a = i < n ? assign[i] : -1;
+        const bool live = a >= 0 && a < K;
+        const uint32_t place = wave_counts(live ? (int32_t)a : -1, K, cursor);
+        if (live) order[place] = (uint32_t)i;
     }
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < K; j += kStride)
         for (uint32_t t = seg[j]; t < seg[j + 1]; ++t) seg_cluster[t] = (uint32_t)j;

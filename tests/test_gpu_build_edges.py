@@ -26,3 +26,35 @@ def test_update_more_clusters_than_a_grid(api):
     c, counts = api.kmeans_update(x, assign, torch.zeros((K, d), device="cuda"))
     assert (counts == 1).all()
     assert torch.equal(c[assign], x)
+
+
+# points in the order of their clusters, all in one, half in one, and points that are
+# ignored: the sums by cluster put waves of them in order at once
+@pytest.mark.parametrize("kind", ["sorted", "one", "half", "even", "ignored"])
+@pytest.mark.parametrize("n,K,d", [(4099, 5, 32), (100_003, 700, 64), (70_000, 16, 36)])
+def test_update_orders(api, kind, n, K, d):
+    rng = np.random.default_rng(n + K)
+    x = rng.integers(-8, 9, size=(n, d)).astype(np.float32)
+    a = rng.integers(0, K, n)
+    if kind == "sorted":
+        a = np.sort(a)
+    elif kind == "one":
+        a[:] = K // 2
+    elif kind == "half":
+        a[rng.random(n) < 0.5] = 1
+    elif kind == "ignored":
+        a[::3] = -1
+        a[1::7] = K
+    print(f"update {kind} n={n} K={K} d={d}", flush=True)
+    c, counts = api.kmeans_update(torch.from_numpy(x).cuda(), torch.from_numpy(a).cuda(),
+                                  torch.zeros((K, d), device="cuda"))
+    live = (a >= 0) & (a < K)
+    want = np.bincount(a[live], minlength=K)
+    sums = np.zeros((K, d))
+    np.add.at(sums, a[live], x[live].astype(np.float64))
+    if kind != "one":  # (an empty cluster splits another)
+        assert (want > 0).all() and (counts.cpu().numpy() == want).all()
+        np.testing.assert_array_equal(c.cpu().numpy(), (sums / want[:, None]).astype(np.float32))
+    else:
+        assert counts.sum().item() == n
+        np.testing.assert_allclose(c.cpu().numpy()[K // 2], sums[K // 2] / n, rtol=0.02, atol=1e-6)
