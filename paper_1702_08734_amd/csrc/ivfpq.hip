@@ -536,7 +536,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ?
         half8 h, l;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float v = fine ? cb[(b * 16 + li) * DS + t0 + e] * cup : 0.f;
+            const float v = fine && e < DS ? cb[(b * 16 + li) * DS + (e < DS ? t0 + e : 0)] * cup : 0.f;
             h[e] = (_Float16)v;
             l[e] = (_Float16)(v - (float)h[e]);
         }
@@ -603,6 +603,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ?
     const int64_t step = nwg * (kBlock / 64) * 16 * NB;
     const int64_t start = (wg * (kBlock / 64) + wave) * 16 * NB;
     if (start < n) load(start);
+    int skip = 0, streak = 3;
 #pragma unroll 1
     for (int64_t i0 = start; i0 < n; i0 += step) {
         float v[NB][DS], nr[NB], mq[NB];
@@ -631,7 +632,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ?
             mq[x] = -2.f * __uint_as_float((uint32_t)(127 - re) << 23) * cdn;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float y = C == 1 || !(lh & 1) ? v[x][e] : v[x][(8 + e) % DS];
+                const float lo = e < DS ? v[x][e % DS] : 0.f, hi = v[x][(8 + e) % DS];
+                const float y = C == 1 || !(lh & 1) ? lo : hi;
                 // (what is not finite spoils its own row's scores only)
                 const float xs = y * rup;
                 const _Float16 h = (_Float16)xs, l = (_Float16)(xs - (float)h), z = (_Float16)0.f;
@@ -643,79 +645,117 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DS > 8 ?
                 }
             }
         }
-        // a score plus |r|^2 (a little more than it, so that none is negative)
-        // is a lower bound of a distance
-        LowKeys best[NB];
-        float shift[NB];
+        PqGroup g[NB];
+        bool sure[NB];
 #pragma unroll
         for (int x = 0; x < NB; ++x) {
-            best[x].init();
-            shift[x] = nr[x] * (1.f + 4.f * kSplitErr) + 0x1p-120f;
+            g[x] = PqGroup{INFINITY, 0};
+            sure[x] = false;
         }
-#pragma unroll
-        for (int b = 0; b < 16; ++b) {
-            const floatx4 cnv = *reinterpret_cast<const floatx4*>(&cn[b * 16 + 4 * lh]);
+        if (skip == 0) {
+            // a score plus |r|^2 (a little more than it, so that none is negative)
+            // is a lower bound of a distance
+            LowKeys best[NB];
+            float shift[NB];
 #pragma unroll
             for (int x = 0; x < NB; ++x) {
-                floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < C; ++c)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b][c], q[x][c], acc, 0, 0, 0);
-                float s[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s[e] = fmaf(acc[e], mq[x], cnv[e]);
-                const float low = fminf(fminf(fminf(s[0], s[1]), s[2]), s[3]) + shift[x];
-                best[x].offer((int32_t)((__float_as_uint(low) & ~63u) | (uint32_t)(b * 4 + lh)));
+                best[x].init();
+                shift[x] = nr[x] * (1.f + 4.f * kSplitErr) + 0x1p-120f;
             }
-        }
 #pragma unroll
-        for (int x = 0; x < NB; ++x) {
+            for (int b = 0; b < 16; ++b) {
+                const floatx4 cnv = *reinterpret_cast<const floatx4*>(&cn[b * 16 + 4 * lh]);
 #pragma unroll
-            for (int o = 16; o <= 32; o <<= 1) {
-                const int32_t k1 = __shfl_xor(best[x].k1, o), k2 = __shfl_xor(best[x].k2, o),
-                              k3 = __shfl_xor(best[x].k3, o);
-                best[x].offer(k1);
-                best[x].offer(k2);
-                best[x].offer(k3);
-            }
-        }
+                for (int x = 0; x < NB; ++x) {
+                    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int x = 0; x < NB; ++x) {
-            // lane lh takes word lh of the best group
-            const float edge =
-                -nr[x] * (6.f * kSplitErr) - sqrtf(nr[x]) * big * 0x1p-24f - 0x1p-119f;
-            const float b2 = __uint_as_float((uint32_t)best[x].k2 & ~63u);
-            const float b3 = __uint_as_float((uint32_t)best[x].k3 & ~63u);
-            const int g1 = best[x].k1 & 63;
-            PqGroup g{direct(v[x], 4 * g1 + lh), 4 * g1 + lh};
-            g = row_best(g);
-            bool sure = ok[x] && g.score < (edge + b2) * (1.f - kDirectErr);
-            if (__ballot(!sure)) {
-                const int g2 = best[x].k2 & 63;
-                PqGroup h{direct(v[x], 4 * g2 + lh), 4 * g2 + lh};
-                h = row_best(h);
-                if (!sure) {
-                    if (h.score < g.score || (h.score == g.score && h.code < g.code)) g = h;
-                    sure = ok[x] && g.score < (edge + b3) * (1.f - kDirectErr);
+                    for (int c = 0; c < C; ++c)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[b][c], q[x][c], acc, 0, 0, 0);
+                    float s[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] = fmaf(acc[e], mq[x], cnv[e]);
+                    const float low = fminf(fminf(fminf(s[0], s[1]), s[2]), s[3]) + shift[x];
+                    best[x].offer((int32_t)((__float_as_uint(low) & ~63u) | (uint32_t)(b * 4 + lh)));
                 }
-                if (__ballot(!sure)) {
-                    // every word, 64 per lane, in the plain kernel's order of
-                    // preference (a row of NaN distances: code 0)
-                    PqGroup f{INFINITY, lh == 0 ? 0 : 256};
-#pragma unroll 1
-                    for (int j = 64 * lh; j < 64 * lh + 64; ++j) {
-                        const float s = direct(v[x], j);
-                        if (s < f.score) {
-                            f.score = s;
-                            f.code = j;
-                        }
+            }
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+#pragma unroll
+                for (int o = 16; o <= 32; o <<= 1) {
+                    const int32_t k1 = __shfl_xor(best[x].k1, o), k2 = __shfl_xor(best[x].k2, o),
+                                  k3 = __shfl_xor(best[x].k3, o);
+                    best[x].offer(k1);
+                    best[x].offer(k2);
+                    best[x].offer(k3);
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < NB; ++x) {
+                // lane lh takes word lh of the best group
+                const float edge =
+                    -nr[x] * (6.f * kSplitErr) - sqrtf(nr[x]) * big * 0x1p-24f - 0x1p-119f;
+                const float b2 = __uint_as_float((uint32_t)best[x].k2 & ~63u);
+                const float b3 = __uint_as_float((uint32_t)best[x].k3 & ~63u);
+                const int g1 = best[x].k1 & 63;
+                g[x] = row_best(PqGroup{direct(v[x], 4 * g1 + lh), 4 * g1 + lh});
+                sure[x] = ok[x] && g[x].score < (edge + b2) * (1.f - kDirectErr);
+                if (__ballot(!sure[x])) {
+                    const int g2 = best[x].k2 & 63;
+                    const PqGroup h = row_best(PqGroup{direct(v[x], 4 * g2 + lh), 4 * g2 + lh});
+                    if (!sure[x]) {
+                        if (h.score < g[x].score || (h.score == g[x].score && h.code < g[x].code))
+                            g[x] = h;
+                        sure[x] = ok[x] && g[x].score < (edge + b3) * (1.f - kDirectErr);
                     }
-                    f = row_best(f);
-                    if (!sure) g = f;
                 }
             }
+        } else {
+            --skip;
+        }
+        // every word for rows x0 .. x1, a quarter of them per lane, in the plain kernel's
+        // order of preference (a row of NaN distances: code 0)
+        auto every = [&](int x0, int x1) __attribute__((always_inline)) {
+            PqGroup f[NB];
+#pragma unroll
+            for (int x = x0; x < x1; ++x) f[x] = PqGroup{INFINITY, lh == 0 ? 0 : 256};
+#pragma unroll 2
+            for (int j = lh; j < 256; j += 4)  // (a row's four lanes in different LDS banks)
+#pragma unroll
+                for (int x = x0; x < x1; ++x) {
+                    const float s = direct(v[x], j);
+                    if (s < f[x].score) {
+                        f[x].score = s;
+                        f[x].code = j;
+                    }
+                }
+#pragma unroll
+            for (int x = x0; x < x1; ++x) {
+                f[x] = row_best(f[x]);
+                if (!sure[x]) g[x] = f[x];
+            }
+        };
+        const bool first = __ballot(!sure[0]), last = __ballot(!sure[NB - 1]);
+        if (first || last) {
+            if (NB == 1 || (first && last))
+                every(0, NB);
+            else if (first)
+                every(0, 1);
+            else
+                every(NB - 1, NB);
+            // Where four steps in five need it (code words or rows in ties, out of the
+            // split's range, far from the origin) products cost more than they save, and
+            // are tried again after 15 steps.
+            if (skip == 0) {
+                streak = streak < 6 ? streak + 1 : 6;
+                if (streak == 6) skip = 15;
+            }
+        } else {
+            streak = streak > 4 ? streak - 4 : 0;
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
             const int64_t i = i0 + x * 16 + li;
-            if (lh == 0 && i < n) codes[i * M + m] = (uint8_t)g.code;
+            if (lh == 0 && i < n) codes[i * M + m] = (uint8_t)g[x].code;
         }
     }
 }
@@ -732,8 +772,9 @@ mk_status pq_encode(const float* r, int64_t n, int32_t d, int32_t M, const float
         if (wgs > 1536 / M) wgs = std::max<int64_t>(1, 1536 / M);
         const dim3 g((unsigned)(wgs * M));
         const bool vec = ds % 4 == 0 && reinterpret_cast<uintptr_t>(r) % 16 == 0;
-        auto kern = ds <= 8 ? (vec ? pq_encode_mfma<8, true> : pq_encode_mfma<8, false>)
-                            : (vec ? pq_encode_mfma<16, true> : pq_encode_mfma<16, false>);
+        auto kern = ds <= 4   ? (vec ? pq_encode_mfma<4, true> : pq_encode_mfma<4, false>)
+                    : ds <= 8 ? (vec ? pq_encode_mfma<8, true> : pq_encode_mfma<8, false>)
+                              : (vec ? pq_encode_mfma<16, true> : pq_encode_mfma<16, false>);
         hipLaunchKernelGGL(kern, g, dim3(kBlock), 0, s, r, n, d, M, ds, books, codes);
         MK_LAUNCHED();
         return MK_OK;

@@ -58,3 +58,37 @@ def test_update_orders(api, kind, n, K, d):
     else:
         assert counts.sum().item() == n
         np.testing.assert_allclose(c.cpu().numpy()[K // 2], sums[K // 2] / n, rtol=0.02, atol=1e-6)
+
+
+# rows and code words whose nearest word the products cannot tell (ties, repeated words,
+# components out of the split's range, rows of NaN, rows far from the origin): the codes of
+# the plain kernel, which calls of fewer than 2,048 rows take
+@pytest.mark.parametrize("kind", ["integers", "repeated", "tiny", "tiny rows", "nan rows", "far", "mixed"])
+@pytest.mark.parametrize("M,ds", [(4, 2), (4, 3), (8, 4), (4, 5), (8, 8), (4, 12), (4, 16)])
+def test_encode_without_proof(api, kind, M, ds):
+    rng = np.random.default_rng(M * ds)
+    n = 20_003
+    r = rng.standard_normal((n, M * ds)).astype(np.float32)
+    books = rng.standard_normal((M, 256, ds)).astype(np.float32)
+    if kind == "integers":
+        r, books = np.round(r), np.round(books)
+    elif kind == "repeated":
+        books[:, 128:] = books[:, :128]
+        books[:, 3] = books[:, 200]
+    elif kind == "tiny":
+        r, books = r * np.float32(1e-20), books * np.float32(1e-20)
+    elif kind == "tiny rows":
+        r *= np.float32(1e-20)
+    elif kind == "nan rows":
+        r[::9, 1] = np.nan
+    elif kind == "far":
+        r, books = r + np.float32(300), books + np.float32(300)
+    else:  # stretches of rows with and without
+        r[4000:9000] = np.round(r[4000:9000])
+        books[:, ::2] = np.round(books[:, ::2])
+        r[12_000:12_100] = np.inf
+    print(f"encode {kind} M={M} ds={ds}", flush=True)
+    rd, bd = torch.from_numpy(r).cuda(), torch.from_numpy(books).cuda()
+    codes = api.pq_encode(rd, bd)
+    part = torch.cat([api.pq_encode(rd[i:i + 2000].contiguous(), bd) for i in range(0, n, 2000)])
+    assert torch.equal(codes, part)
