@@ -166,8 +166,9 @@ __device__ __forceinline__ void pool_cut(uint64_t* pool, uint32_t* bins, PoolSta
 // The k smallest of the pool's n keys in order: emit(rank, key) for ranks below
 // min(n, k).  Buckets of a histogram over the range, each key ranked inside its
 // own; where a bucket is crowded (a cluster of near-equal scores far from the
-// rest), a bitonic network over the k smallest instead (the next power of two of
-// min(n, k) <= P).
+// rest), the k smallest: of up to kPoolThreads keys each counts the smaller ones,
+// and more go through a bitonic network (the next power of two of their number,
+// <= P).
 template <int P, class F>
 __device__ __forceinline__ void pool_emit(uint64_t* pool, uint32_t* bins, PoolState* st, uint32_t n,
                                           uint32_t k, F emit) {
@@ -193,9 +194,20 @@ __device__ __forceinline__ void pool_emit(uint64_t* pool, uint32_t* bins, PoolSt
     }
     (void)pool_sum(tot, st->wsum, run);
     if (__syncthreads_or(crowded || most > kCrowd)) {
-        if (n > k) {
+        if (n > (uint32_t)NT && n > k) {
             pool_cut<P>(pool, bins, st, n, (int)k);
             n = k;
+        }
+        if (n <= (uint32_t)NT) {  // each counts the smaller ones
+            const uint64_t mine = tid < (int)n ? pool[tid] : kSentinel;
+            uint32_t rank = 0;
+#pragma unroll 4
+            for (uint32_t e = 0; e < n; ++e) {
+                const uint64_t o = pool[e];
+                rank += o < mine || (o == mine && e < (uint32_t)tid) ? 1u : 0u;
+            }
+            if (tid < (int)n && rank < k) emit(rank, mine);
+            return;
         }
         uint32_t size = 64;
         while (size < n) size *= 2;
@@ -295,7 +307,9 @@ __device__ __forceinline__ uint32_t pool_stream(const uint64_t* __restrict__ p, 
 // fit beside its keys: a row of L values sees about kk (1 + ln(L / kk)) insertions
 // and a cut for every P - kk of them.  (Steps of 4,096 values need a second place
 // for cuts in the loop and the registers for it: fewer waves, 5 to 10% slower.)
-// NaN never enters.  ws: LDS words of its own.
+// Places ascend from step to step, so that a value equal to the threshold's score comes
+// too late (rows of few different values: 10^4 x 10,000, k = 65, 160 us when such values
+// were looked at one by one, 142).  NaN never enters.  ws: LDS words of its own.
 template <int P, int U, bool LARGEST>  // kk <= P - 1024 U
 __device__ __forceinline__ uint32_t pool_values(const float* __restrict__ rp, uint32_t n,
                                                 uint32_t first, int32_t kk, uint64_t* pool,
@@ -307,14 +321,14 @@ __device__ __forceinline__ uint32_t pool_values(const float* __restrict__ rp, ui
     // value j of quarter u is 1,024 u + 4 tid + j (aligned) or + 256 j + tid
     const uint32_t mine = aligned ? 4u * tid : (uint32_t)tid, stride = aligned ? 1u : (uint32_t)NT;
     uint32_t have = 0;
-    uint64_t limit = kSentinel;
-    float limit_f = INFINITY;
+    float limit_f = INFINITY;  // (looked at once the pool was cut)
+    bool open = true;
     int turn = 0;
     auto cut = [&]() __attribute__((always_inline)) {
         pool_cut<P>(pool, bins, st, have, kk);
         have = (uint32_t)kk;
-        limit = st->limit;
-        limit_f = key_score(limit - 1);
+        limit_f = key_score(st->limit - 1);
+        open = false;
     };
     // a step's values, the next step's while this one is looked at
     float next[U][4];
@@ -360,16 +374,15 @@ __device__ __forceinline__ uint32_t pool_values(const float* __restrict__ rp, ui
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (LARGEST) v[u][j] = -v[u][j];
-                any |= v[u][j] <= limit_f;
+                any |= v[u][j] < limit_f;
             }
-        if (!__syncthreads_or(any)) continue;
-        // which values enter: below the threshold's score, or at it and before it
+        if (!__syncthreads_or(any || open)) continue;
+        // which values enter
         auto takes = [&](int u) __attribute__((always_inline)) {
             uint32_t mask = 0;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const bool t = v[u][j] < limit_f ||
-                               (v[u][j] == limit_f && at(u, j) < (uint32_t)limit);
+                const bool t = open ? v[u][j] == v[u][j] : v[u][j] < limit_f;
                 mask |= t ? 1u << j : 0u;
             }
             return mask;
