@@ -40,7 +40,7 @@ SPLIT_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 3
 KS = (1, 32, 256, 1024)
 PMC_FILE = os.path.join(ROOT, "profiles", "sieve_tiles_exact_large_pmc.json")
 # sources of the dominant kernel and its launch configuration
-KERNEL_SOURCES = ["sieve.hpp", "sieve.hip", "fused.hpp"]
+KERNEL_SOURCES = ["sieve.hpp", "sieve_plan.hpp", "sieve.hip", "fused.hpp"]
 
 
 def kernel_source_hash() -> str:
@@ -787,7 +787,7 @@ def main() -> int:
     achieved = flops_search * tile_n / (tile_ms / 1e3) / 1e12 if tile_ms > 0 else None
     traffic = traffic_from_counters()
     out = {
-        "metric": "brute-force k-NN TFLOP/s (exact L2, fused MFMA distance + k-selection)",
+        "metric": "brute-force k-NN TFLOP/s (exact L2, MFMA distances + k-selection)",
         "value": round(value, 3),
         "unit": "TFLOP/s",
         "n_gpus": 1,

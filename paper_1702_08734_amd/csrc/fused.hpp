@@ -200,8 +200,6 @@ struct MultiSelect {
 // s_waitcnt immediate (gfx9 encoding) that waits for all LDS operations.
 constexpr int waitcnt_lgkm0() { return 0xF | (0x7 << 4) | (0x0 << 8) | (0x3 << 14); }
 
-// Wave-wide reductions and scans over all 64 lanes.
-
 // QW selectors for queues of 256 entries and more, whose candidates live in
 // device memory -- the kernel's own partial-result rows.  A candidate that
 // beats its query's threshold is appended to the query's pool (one store per

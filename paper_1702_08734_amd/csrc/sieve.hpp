@@ -14,18 +14,18 @@
 //   3. sieve_finish selects the keff best of the pool, re-ranks them in the
 //      direct FP32 form and writes the k best.
 //
-// What bounds it: the matrix cores.  10,000 queries x 1,000,000 x 128, k = 32:
-// sieve_tiles 6.7 ms (1,140 TFLOP/s of FP16 products; 5.8 ms, 1,330 TFLOP/s,
-// when no score passes), the whole search 6.7 ms against 27.1 ms by the fused
-// kernel (95 TFLOP/s of FP32 products, and FP32 products cannot take less than
-// 16.3 ms); 2,000 queries, k = 1000: 2.1 against 9.6 ms; 500 queries x 50,000 x
-// 64, k = 10: 0.12 against 0.39 ms.
+// What bounds it: the matrix cores, and the vector operations beside them.  10,000
+// queries x 1,000,000 x 128, k = 32: sieve_tiles 6.0 to 6.4 ms from card to card (1,200
+// to 1,280 TFLOP/s of FP16 products; 5.8 ms when no score passes), the whole search 6.3
+// to 6.6 ms against 27.1 ms by the fused kernel (95 TFLOP/s of FP32 products, and FP32
+// products cannot take less than 16.3 ms); 2,000 queries, k = 1000: 1.7 against 9.6 ms.
 //
-// Nothing is taken on trust: a query whose pool overflowed or came out short,
-// or (FP32 search) whose result the error bound below does not prove, goes to a
-// list of queries that the fused kernel searches; its workgroups return at once
-// when there are none.  (One zero query in 30, inner products, 10^6 x 128 rows, 10,000
-// queries: whole blocks of 64 searched again 42.5 ms, the list 15.1.)
+// Nothing is taken on trust: a query whose pool overflowed or came out short, or (FP32
+// search) whose result the error bound does not prove, goes to a list of queries that
+// are searched again: few of them by dense.hpp's search, the others by the fused kernel,
+// whose workgroups return at once when there are none.  (One zero query in 30, inner
+// products, 10^6 x 128 rows, 10,000 queries, k = 10: whole blocks of 64 searched again by
+// the fused kernel 40.0 ms, the list 8.2, 6.5 without zero queries.)
 //
 // FP32 rows are multiplied as pairs of FP16 rows (h + l, each row scaled by a
 // power of two): three FP16 matrix products (h l, l h, h h) carry 22+ bits of
