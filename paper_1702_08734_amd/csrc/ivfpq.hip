@@ -151,6 +151,46 @@ __global__ void km_count(const int64_t* __restrict__ assign, int64_t n, int32_t 
     }
 }
 
+// Few clusters: a workgroup counts kCountPoints points in LDS and adds up once per
+// cluster.  One word per cluster takes the atomics of n / K points one by one: 500,000
+// points of 32 components in 256 clusters 506 us with wave_counts alone, 97.  From a
+// quarter of kCountPoints clusters on there are about as many additions as points.
+constexpr int kCountPoints = 4096, kCountClusters = kCountPoints / 4;
+struct FewCounts {
+    uint32_t bins[kCountClusters];
+    // the clusters of this thread's points of the chunk at i0 (-1: none) and, in bins,
+    // the chunk's counts; the points' places in them
+    __device__ __forceinline__ void take(const int64_t* __restrict__ assign, int64_t i0, int64_t n,
+                                         int32_t K, int32_t (&a)[kCountPoints / kBlock],
+                                         uint32_t (&place)[kCountPoints / kBlock]) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < K; j += kBlock) bins[j] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kCountPoints / kBlock; ++e) {
+            const int64_t i = i0 + e * kBlock + threadIdx.x;
+            const int64_t v = i < n ? assign[i] : -1;
+            a[e] = v >= 0 && v < K ? (int32_t)v : -1;  // others are ignored
+        }
+#pragma unroll
+        for (int e = 0; e < kCountPoints / kBlock; ++e)
+            place[e] = a[e] >= 0 ? atomicAdd(&bins[a[e]], 1u) : 0u;
+        __syncthreads();
+    }
+};
+
+__global__ __launch_bounds__(kBlock) void km_count_few(const int64_t* __restrict__ assign, int64_t n,
+                                                       int32_t K, uint32_t* __restrict__ counts) {
+    __shared__ FewCounts few;
+    int32_t a[kCountPoints / kBlock];
+    uint32_t place[kCountPoints / kBlock];
+    for (int64_t i0 = (int64_t)blockIdx.x * kCountPoints; i0 < n; i0 += (int64_t)gridDim.x * kCountPoints) {
+        few.take(assign, i0, n, K, a, place);
+        for (int j = threadIdx.x; j < K; j += kBlock)
+            if (few.bins[j]) atomicAdd(&counts[j], few.bins[j]);
+    }
+}
+
 // Exclusive prefix of the counts (first[K]: their sum) and of the stretches, the
 // cursors, and the counts as 64-bit words.  One workgroup.
 __global__ __launch_bounds__(1024) void km_prefix(const uint32_t* __restrict__ counts, int32_t K,
@@ -206,6 +246,26 @@ __global__ void km_order(const int64_t* __restrict__ assign, int64_t n, int32_t 
         const bool live = a >= 0 && a < K;
         const uint32_t place = wave_counts(live ? (int32_t)a : -1, K, cursor);
         if (live) order[place] = (uint32_t)i;
+    }
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < K; j += kStride)
+        for (uint32_t t = seg[j]; t < seg[j + 1]; ++t) seg_cluster[t] = (uint32_t)j;
+}
+
+__global__ __launch_bounds__(kBlock) void km_order_few(
+    const int64_t* __restrict__ assign, int64_t n, int32_t K, uint32_t* __restrict__ cursor,
+    uint32_t* __restrict__ order, const uint32_t* __restrict__ seg, uint32_t* __restrict__ seg_cluster) {
+    __shared__ FewCounts few;
+    int32_t a[kCountPoints / kBlock];
+    uint32_t place[kCountPoints / kBlock];
+    for (int64_t i0 = (int64_t)blockIdx.x * kCountPoints; i0 < n; i0 += (int64_t)gridDim.x * kCountPoints) {
+        few.take(assign, i0, n, K, a, place);
+        for (int j = threadIdx.x; j < K; j += kBlock)
+            if (few.bins[j]) few.bins[j] = atomicAdd(&cursor[j], few.bins[j]);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kCountPoints / kBlock; ++e)
+            if (a[e] >= 0)
+                order[few.bins[a[e]] + place[e]] = (uint32_t)(i0 + e * kBlock + threadIdx.x);
     }
     for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < K; j += kStride)
         for (uint32_t t = seg[j]; t < seg[j + 1]; ++t) seg_cluster[t] = (uint32_t)j;
@@ -340,12 +400,16 @@ mk_status kmeans_update(const float* x, int64_t n, int32_t d, const int64_t* ass
         uint32_t *order = seg + K + 1, *seg_cluster = order + n;
         hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_of(K)), dim3(kBlock), 0, s, count, (int64_t)K);
         MK_LAUNCHED();
-        hipLaunchKernelGGL(km_count, dim3(grid_of(n)), dim3(kBlock), 0, s, assign, n, K, count);
+        const bool few = K <= kCountClusters;
+        const dim3 chunks((unsigned)std::min<int64_t>(ceil_div(n, kCountPoints), 1 << 16));
+        hipLaunchKernelGGL(few ? km_count_few : km_count, few ? chunks : dim3(grid_of(n)),
+                           dim3(kBlock), 0, s, assign, n, K, count);
         MK_LAUNCHED();
         hipLaunchKernelGGL(km_prefix, dim3(1), dim3(1024), 0, s, count, K, first, cursor, seg,
                            cnt.as<unsigned long long>());
         MK_LAUNCHED();
-        hipLaunchKernelGGL(km_order, dim3(grid_of(std::max<int64_t>(n, K))), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL(few ? km_order_few : km_order,
+                           few ? chunks : dim3(grid_of(std::max<int64_t>(n, K))), dim3(kBlock), 0, s,
                            assign, n, K, cursor, order, seg, seg_cluster);
         MK_LAUNCHED();
         hipLaunchKernelGGL(km_segment_sums, dim3((unsigned)std::min<int64_t>(segs, 1 << 16)), dim3(kBlock), 0, s, x, d, K, first,

@@ -92,3 +92,31 @@ def test_encode_without_proof(api, kind, M, ds):
     codes = api.pq_encode(rd, bd)
     part = torch.cat([api.pq_encode(rd[i:i + 2000].contiguous(), bd) for i in range(0, n, 2000)])
     assert torch.equal(codes, part)
+
+
+# both sides of the cluster count up to which workgroups count in LDS, and of its chunk
+@pytest.mark.parametrize("kind", ["even", "sorted", "half"])
+@pytest.mark.parametrize("n,K", [(4096, 1), (4097, 2), (4097, 1024), (22_001, 30), (21_000, 30), (32_768, 1024),
+                                 (32_769, 1024), (40_000, 1025), (300_007, 256)])
+def test_update_counts(api, n, K, kind):
+    rng = np.random.default_rng(n)
+    d = 32
+    x = rng.integers(-8, 9, size=(n, d)).astype(np.float32)
+    a = rng.integers(0, K, n)
+    if kind == "half":
+        a[rng.random(n) < 0.5] = K - 1
+    a[:K] = rng.permutation(K)
+    if kind == "sorted":
+        a = np.sort(a)
+    a[K + 5:K + 50:9] = -1
+    a[K + 60] = K
+    print(f"update counts {kind} n={n} K={K}", flush=True)
+    c, counts = api.kmeans_update(torch.from_numpy(x).cuda(), torch.from_numpy(a).cuda(),
+                                  torch.zeros((K, d), device="cuda"))
+    live = (a >= 0) & (a < K)
+    want = np.bincount(a[live], minlength=K)
+    assert (want > 0).all()  # (an empty cluster splits another)
+    sums = np.zeros((K, d))
+    np.add.at(sums, a[live], x[live].astype(np.float64))
+    assert (counts.cpu().numpy() == want).all()
+    np.testing.assert_array_equal(c.cpu().numpy(), (sums / want[:, None]).astype(np.float32))
