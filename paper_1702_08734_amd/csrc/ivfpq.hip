@@ -381,10 +381,16 @@ mk_status kmeans_update(const float* x, int64_t n, int32_t d, const int64_t* ass
     }
     MK_HIP(hipMemsetAsync(sums.ptr, 0, sizeof(double) * (size_t)K * d, s));
     MK_HIP(hipMemsetAsync(cnt.ptr, 0, sizeof(unsigned long long) * (size_t)K, s));
-    // long rows by cluster; short ones (a sub-quantizer's) are cheaper to add
-    // where they belong than to gather (32-byte rows: 27 us for 500,000 x 8)
-    bool by_cluster = d >= 32 && d % 4 == 0 && d <= 4 * kBlock && n >= 4096 &&
-                      n < (1ll << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0;
+    // By cluster, except for few points in clusters enough that the atomics of the plain
+    // sums do not wait for each other: there the launches set the time.  Plain / by
+    // cluster, us: 4,096 x 128 points in 64 clusters 56 / 81; in 4, 8,192 x 64 141 / 100; in
+    // 64, 16,384 74 / 97, 32,768 124 / 99; in 256, 32,768 59 / 97, 65,536 93 / 97; 100,000 x
+    // 32 in 1,000, all alike 60 / 97, half of them in one 1,363 / 167.  Rows of less than
+    // 32 components are cheaper to add where they belong than to gather (500,000 x 8: 330
+    // us in 256 clusters, 73 in 4,096).
+    bool by_cluster = d >= 32 && d % 4 == 0 && d <= 4 * kBlock && n >= 4096 && n < (1ll << 31) &&
+                      (n > 32768 || n * n >= 16000000ll * K) &&
+                      reinterpret_cast<uintptr_t>(x) % 16 == 0;
     const int64_t segs = ceil_div(n, kSegRows) + K;
     Scratch words;
     if (by_cluster) {

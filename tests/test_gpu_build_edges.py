@@ -94,7 +94,8 @@ def test_encode_without_proof(api, kind, M, ds):
     assert torch.equal(codes, part)
 
 
-# both sides of the cluster count up to which workgroups count in LDS, and of its chunk
+# both sides of the cluster count up to which workgroups count in LDS, of its chunk, and of
+# the sizes from which sums go by cluster at all
 @pytest.mark.parametrize("kind", ["even", "sorted", "half"])
 @pytest.mark.parametrize("n,K", [(4096, 1), (4097, 2), (4097, 1024), (22_001, 30), (21_000, 30), (32_768, 1024),
                                  (32_769, 1024), (40_000, 1025), (300_007, 256)])
