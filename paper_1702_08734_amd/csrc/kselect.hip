@@ -3,9 +3,9 @@
 // per-segment partial results (the second pass of the two-pass k-selection of
 // Section 5.3).
 //
-// Pass 1 streams each (row, segment) once with 16-byte coalesced loads: k <= 64 one
-// wave and its sorted register queue, more one workgroup and an unsorted LDS pool
-// (pool.hpp).  A row that fits one segment writes its final result directly;
+// Pass 1 streams each (row, segment) once with 16-byte coalesced loads: k <= 64 (128 for
+// short rows) one wave and its sorted register queue, more one workgroup and an unsorted
+// LDS pool (pool.hpp).  A row that fits one segment writes its final result directly;
 // otherwise its k best keys go to a scratch list and pass 2 (one workgroup per
 // row) selects over the segments' keys.
 #include <algorithm>
@@ -311,7 +311,7 @@ mk_status kselect_pools(const float* a, int64_t nrows, int64_t len, int32_t k, f
 template <bool LARGEST>
 mk_status kselect_dispatch(const float* a, int64_t nrows, int64_t len, int32_t k, float* vals,
                            int64_t* idx, hipStream_t s) {
-    // a register queue of 64 costs a wave little; from there on a pool per
+    // a register queue of 64 costs a wave little; from there on, as a rule, a pool per
     // workgroup (one dimension of a grid: fewer than 2^24 workgroups of 256)
     if (k <= 64) return kselect_waves<1, LARGEST>(a, nrows, len, k, vals, idx, s);
     if (nrows >= (1ll << 23)) {
@@ -319,6 +319,16 @@ mk_status kselect_dispatch(const float* a, int64_t nrows, int64_t len, int32_t k
         MK_TRY((kselect_dispatch<LARGEST>(a, half, len, k, vals, idx, s)));
         return kselect_dispatch<LARGEST>(a + half * len, nrows - half, len, k, vals + half * k,
                                          idx + half * k, s);
+    }
+    // (short rows, for which a pool's passes are the larger part: 30,000 rows of 100 / 300 /
+    // 500 values, k = 65: 75 / 106 / 124 us by a queue of 128, 122 / 127 / 130 by a pool)
+    if (k <= 128 && len <= 512) {
+        ProfScope prof("kselect_pass1", s);
+        hipLaunchKernelGGL((kselect_pass1<2, SelParams<2>::T, LARGEST>),
+                           dim3((unsigned)ceil_div(nrows, kWavesPerBlock)), dim3(64 * kWavesPerBlock),
+                           0, s, a, nrows, len, k, 1, (int64_t)512, vals, idx, (uint64_t*)nullptr);
+        MK_LAUNCHED();
+        return MK_OK;
     }
     return k <= 512 ? kselect_pools<2560, LARGEST>(a, nrows, len, k, vals, idx, s)
                     : kselect_pools<3072, LARGEST>(a, nrows, len, k, vals, idx, s);

@@ -41,3 +41,25 @@ def test_pool_ties(api, kind, nrows, length, k, largest):
     want = np.argsort(-a if largest else a, axis=1, kind="stable")[:, :k]
     np.testing.assert_array_equal(i.cpu().numpy(), want)
     np.testing.assert_array_equal(v.cpu().numpy(), np.take_along_axis(a, want, 1))
+
+
+# rows on both sides of the length up to which a wave's queue takes k = 65 to 128, shorter
+# than k, empty, and off the 16-byte grid
+@pytest.mark.parametrize("largest", [False, True])
+@pytest.mark.parametrize("k", [65, 100, 128, 129])
+@pytest.mark.parametrize("nrows,length", [(3, 0), (5, 40), (9, 127), (301, 128), (2, 511), (70, 512), (70, 513)])
+@pytest.mark.parametrize("kind", ["random", "few", "signed"])
+def test_short_rows(api, kind, nrows, length, k, largest):
+    rng = np.random.default_rng(length + k)
+    a = rng.random((nrows, length)).astype(np.float32)
+    if kind == "few":
+        a = np.round(a * 4)
+    elif kind == "signed":
+        a = np.exp(20 * a) * np.where(a < 0.4, np.float32(-1), np.float32(1))
+    v, i = api.kselect(torch.from_numpy(a).cuda(), k, largest)
+    n = min(k, length)
+    want = np.argsort(-a if largest else a, axis=1, kind="stable")[:, :n]
+    v, i = v.cpu().numpy(), i.cpu().numpy()
+    np.testing.assert_array_equal(i[:, :n], want)
+    np.testing.assert_array_equal(v[:, :n], np.take_along_axis(a, want, 1))
+    assert (i[:, n:] == -1).all() and (v[:, n:] == (-np.inf if largest else np.inf)).all()
