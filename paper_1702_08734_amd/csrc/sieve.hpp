@@ -257,9 +257,11 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const float inv = Op::SCALED && ok ? args.qscale[q] : 1.f;
         mq[qb] = (L2 ? -2.f : -1.f) * inv;
         sh[qb] = (!L2 && Op::SHIFTED && ok) ? -2.f * ERR * sqrtf(args.qnorm[q]) : 0.f;
-        thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : -INFINITY;
+        // (no query, or a threshold withdrawn: NaN, which lets no score through; below
+        // -infinity comes the score of a row whose supplied norm is that)
+        thr[qb] = (FILTER && ok) ? args.thr[q * args.thr_ld] : NAN;
         if constexpr (FILTER && PL > 1)
-            if (ok && args.flags[q] != 0u) thr[qb] = -INFINITY;
+            if (ok && args.flags[q] != 0u) thr[qb] = NAN;
         // Queries without a chance of a proof: far from the origin the error bound of
         // the scores is more than the k-th best row and the threshold lie apart.  By the
         // sample's best `rank` scores (their number grows exponentially) these are about
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (ok) {
                 const float* t = args.thr + q * args.thr_ld;
                 if ((t[0] - t[1 - args.thr_ld]) * args.tail < 2.f * ERR * args.qnorm[q])
-                    thr[qb] = -INFINITY;
+                    thr[qb] = NAN;
             }
         if (FILTER && rg == 0 && lh == 0) lthr[(qg * QB + qb) * 16 + li] = thr[qb];
     }
@@ -283,7 +285,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         int mine = 0;
         if (rg == 0 && lh == 0)
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) mine += thr[qb] > -INFINITY ? 1 : 0;
+            for (int qb = 0; qb < QB; ++qb) mine += thr[qb] == thr[qb] ? 1 : 0;
         if (mine) atomicAdd(&chances, mine);
         __syncthreads();
         if (5 * chances < (int)(args.nq - q0 < BQ ? args.nq - q0 : BQ)) return;
@@ -435,7 +437,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 const int64_t q = qw0 + qb * 16 + li;
                 if (q < args.nq &&
                     __hip_atomic_load(&args.cnt[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > args.cap)
-                    thr[qb] = -INFINITY;
+                    thr[qb] = NAN;
             }
         }
         __builtin_amdgcn_s_waitcnt(0);

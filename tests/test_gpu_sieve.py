@@ -316,3 +316,23 @@ def test_host_chunks_alike(api, nq, metric):
     D, I = api.knn_search_host(xq, xb, 12, metric, 25_000)
     D2, I2 = api.knn_search(xq, xb.cuda(), 12, metric)
     assert torch.equal(D, D2) and torch.equal(I, I2)
+
+
+@pytest.mark.parametrize("nq", [257, 300, 512])
+@pytest.mark.parametrize("d,k", [(40, 12), (128, 100), (200, 300)])
+def test_sieve_norms_of_minus_infinity(api, nq, d, k):
+    # such rows pass every threshold and no more: the k nearest are the oracle's, also
+    # where the last block of queries is not full
+    rng = np.random.default_rng(d + nq)
+    xb, xq = mixture(rng, 70_000, d), mixture(rng, nq, d)
+    yn = api.norms(dev(xb))
+    yn[5::14_001] = float("-inf")
+    print(f"norms of -inf nq={nq} d={d} k={k}", flush=True)
+    D, I = api.knn_search(dev(xq), dev(xb), k, "l2", yn)
+    rows = np.arange(0, nq, 17)
+    fails = check_rows(D.cpu().numpy()[rows], I.cpu().numpy()[rows], xq, xb, rows, k, "l2")
+    assert not fails, fails[:10]
+    # calls of 32 queries, which need no thresholds
+    for r in (0, nq - 32):
+        Ds, Is = api.knn_search(dev(xq[r:r + 32]), dev(xb), k, "l2", yn)
+        assert torch.equal(D[r:r + 32], Ds) and torch.equal(I[r:r + 32], Is)
