@@ -56,9 +56,17 @@ struct QuadArgs {
     int32_t nqb;              // query blocks of 16 QB
     float* out;               // [nq][ld] least score of four rows
     int64_t ld;
-    RestSpan rest;            // if its list is given: these queries in the place of 0 .. nq - 1
+    RestSpan rest;            // REST: these queries in the place of 0 .. nq - 1
 };
 
+// Groups of 64 rows per wave for more than 16 queries: four waves per SIMD's worth,
+// for an even end (fewer than 8,192 + nqb waves).
+__host__ __device__ inline int64_t quad_groups(int64_t groups, int64_t nqb) {
+    const int64_t n = groups * nqb / 4096;
+    return n > 1 ? n : 1;
+}
+
+enum class QuadNorms { kNone, kGiven, kOwn };  // inner products; L2 with and without yn
 // A wave takes 16 QB queries (B operands, in registers) and streams its rows 64
 // at a time: block b of four, A row m is row 16 (m / 4) + 4 b + m % 4 of them, so
 // that lane (query li, quarter lh) ends up with groups 4 lh .. 4 lh + 3 of four
@@ -69,22 +77,16 @@ struct QuadArgs {
 // for everything in flight, and kept twice the registers (500 queries, 50,000 x 64
 // rows: 69 -> 47 us; 10^4 queries, 4,096 x 128 rows 175 -> 135 us, half of the
 // matrix cores' rate).
-// Groups of 64 rows per wave for more than 16 queries: four waves per SIMD's worth,
-// for an even end (fewer than 8,192 + nqb waves).
-__host__ __device__ inline int64_t quad_groups(int64_t groups, int64_t nqb) {
-    const int64_t n = groups * nqb / 4096;
-    return n > 1 ? n : 1;
-}
-
-enum class QuadNorms { kNone, kGiven, kOwn };  // inner products; L2 with and without yn
-template <int DP, int QB, bool VEC, QuadNorms NORMS>
+// REST: the queries of a list (by itself: asked at run time, the searches without one
+// took 80.6 us, 77.6 so: 500 queries, 50,000 x 64 rows).
+template <int DP, int QB, bool VEC, QuadNorms NORMS, bool REST>
 __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(DP <= 32 || (DP <= 64 && QB == 1) ? 3 : DP <= 128 ? 2 : 1))) void
 quad_min_kernel(QuadArgs a) {
     constexpr bool L2 = NORMS != QuadNorms::kNone;
     constexpr int S4 = DP / 16;  // granule steps of four floats per lane
     const int lane = lane_id(), li = lane & 15, lh = lane >> 4;
-    if (a.rest.list) {
+    if constexpr (REST) {
         a.nq = a.rest.size();
         if (a.nq == 0) return;
         a.nqb = (int32_t)((a.nq + 16 * QB - 1) / (16 * QB));
@@ -102,7 +104,7 @@ quad_min_kernel(QuadArgs a) {
     for (int qb = 0; qb < QB; ++qb) {
         const int64_t i = q0 + qb * 16 + li;
         const bool ok = i < a.nq;
-        const float* row = a.xq + (!ok ? 0 : a.rest.list ? a.rest.at(i) : i) * a.d;
+        const float* row = a.xq + (!ok ? 0 : REST ? a.rest.at(i) : i) * a.d;
 #pragma unroll
         for (int s = 0; s < S4; ++s) q[qb][s] = load_granule<OpF32, VEC>(row, 4 * s + lh, a.d, ok);
     }
@@ -209,7 +211,7 @@ __device__ __forceinline__ bool is_distance(float v, uint64_t key, int32_t l2) {
 // (lists null) or from the nlists lists of kq keys of a first pass over its
 // segments; exact distances of the groups' rows (16 rows per wave and step, as in
 // the fused search's re-rank); the k best of them by (distance, row).
-template <int P, int U, int N>  // kq <= P - 1024 U, kq <= P / 2, 4 kq <= N <= P
+template <int P, int U, int N, bool REST>  // kq <= P - 1024 U, kq <= P / 2, 4 kq <= N <= P
 __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
     const float* __restrict__ least, int64_t ld, const uint64_t* __restrict__ lists,
     int32_t nlists, int32_t kq, const float* __restrict__ xq, const float* __restrict__ xb,
@@ -224,7 +226,7 @@ __global__ __launch_bounds__(kPoolThreads) void quad_finish_kernel(
     const int tid = threadIdx.x;
     const int64_t i = blockIdx.x;
     int64_t q = i;
-    if (rest.list) {
+    if constexpr (REST) {
         if (i >= rest.size()) return;
         q = rest.at(i);
     }
@@ -358,14 +360,14 @@ __global__ __launch_bounds__(64 * kMergeWaves) void quad_finish_wave(
     emit_reranked<1>(ws.w, k, l2, D + q * k, I + q * k);
 }
 
-template <int DP, int QB>
+template <int DP, int QB, bool REST = false>
 mk_status launch_quads(const QuadArgs& a, bool vec, bool l2, int64_t waves, hipStream_t s) {
     ProfScope prof("dense_quads", s);
     auto of = [&](auto v) {
         constexpr bool V = decltype(v)::value;
-        return !l2    ? quad_min_kernel<DP, QB, V, QuadNorms::kNone>
-               : a.yn ? quad_min_kernel<DP, QB, V, QuadNorms::kGiven>
-                      : quad_min_kernel<DP, QB, V, QuadNorms::kOwn>;
+        return !l2    ? quad_min_kernel<DP, QB, V, QuadNorms::kNone, REST>
+               : a.yn ? quad_min_kernel<DP, QB, V, QuadNorms::kGiven, REST>
+                      : quad_min_kernel<DP, QB, V, QuadNorms::kOwn, REST>;
     };
     auto kern = vec ? of(std::true_type{}) : of(std::false_type{});
     hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(waves, 4)), dim3(256), 0, s, a);
@@ -381,7 +383,7 @@ mk_status quads(QuadArgs a, bool vec, bool l2, hipStream_t s) {
     a.nqb = (int32_t)ceil_div(a.nq, 16 * qb);
     if (a.rest.list) {  // (how many there are is known on the device)
         const int64_t waves = std::min<int64_t>(8192, a.groups * ceil_div(a.nq, 16 * WIDE)) + ceil_div(a.nq, 16 * WIDE);
-        return launch_quads<DP, WIDE>(a, vec, l2, waves, s);
+        return launch_quads<DP, WIDE, true>(a, vec, l2, waves, s);
     }
     // few queries: long runs of rows per wave (one query, 10^6 x 64 rows, 2 waves per
     // SIMD's worth 68 us, 8 waves 82)
@@ -402,9 +404,13 @@ mk_status quads_any(const QuadArgs& a, bool vec, bool l2, hipStream_t s) {
 // Selection and finish by a workgroup per query.
 mk_status finish_any(const QuadArgs& a, int64_t nq, const uint64_t* lists, int32_t nseg, int32_t kq,
                      bool l2, bool vec, int32_t k, float* D, int64_t* I, hipStream_t s) {
-    auto kern = kq <= 64    ? quad_finish_kernel<1280, 1, 256>
-                : kq <= 512 ? quad_finish_kernel<2560, 2, 2048>
-                            : quad_finish_kernel<4096, 2, 4096>;
+    auto of = [&](auto with_list) {
+        constexpr bool R = decltype(with_list)::value;
+        return kq <= 64    ? quad_finish_kernel<1280, 1, 256, R>
+               : kq <= 512 ? quad_finish_kernel<2560, 2, 2048, R>
+                           : quad_finish_kernel<4096, 2, 4096, R>;
+    };
+    auto kern = a.rest.list ? of(std::true_type{}) : of(std::false_type{});
     hipLaunchKernelGGL(kern, dim3((unsigned)nq), dim3(kPoolThreads), 0, s, a.out, a.ld, lists, nseg,
                        kq, a.xq, a.xb, l2 ? a.yn : nullptr, a.nb, a.d, (int32_t)vec, (int32_t)l2, k,
                        a.rest, D, I);
