@@ -1222,7 +1222,8 @@ struct ScanLists {
     float term2[kScanLists];
 };
 
-// LONG: more than 16 code bytes per entry; V16: a multiple of 16
+// LONG: more than 16 code bytes per entry; V16: a multiple of 16 (neither long nor
+// another: 16, a constant)
 template <bool H16, int P, bool LONG, bool V16>
 __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(LONG ? 3 : 4))) void ivf_scan(
     const float* __restrict__ term3, const float* __restrict__ t1e,
@@ -1271,8 +1272,14 @@ __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu
     // neighbour (no exclusion when excl_base < 0; ids are >= 0)
     const int64_t excl = excl_base >= 0 ? excl_base + q : -1;
 
+    if constexpr (V16 && !LONG) M = 16;
     const float* t3 = term3 + q * (int64_t)M * 256;
-    for (int e = threadIdx.x; e < M * 256; e += 64 * kScanWaves) lut[e] = LT::make(-2.f * t3[e]);
+    static_assert(64 * kScanWaves == 256, "a table per step");
+#pragma unroll 4
+    for (int m = 0; m < M; ++m) {
+        const int e = m * 256 + (int)threadIdx.x;
+        lut[e] = LT::make(-2.f * t3[e]);
+    }
     if (threadIdx.x == 0) {
         state.count = 0u;
         state.limit = kSentinel;
