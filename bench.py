@@ -378,7 +378,7 @@ def scan_options_section(api, torch, ix, xq, w, sizes, probe):
 
 def host_db_section(api, synth, torch):
     """Exact search against a database held in pinned host memory, streamed
-    in chunks (copies overlapping the fused search of the previous chunk),
+    in chunks (copies overlapping the search of the previous chunk),
     next to the same search on a device-resident copy: the 10,000,000 x 128
     mixture of the IVFADC workload (5.1 GB), k = 10."""
     w = synth.ivfpq_workload(nq=10_000)

@@ -111,9 +111,10 @@ mk_status mk_kselect(const float* a, int64_t nrows, int64_t len, int32_t k, int3
  * cancellation error of ||x||^2 + ||y||^2 - 2<x,y>.  nb must be < 2^31.
  * Supported d: 1..256.  Scratch (device), large calls: 4 DP bytes per query and per
  * row (DP: d rounded up to 32, 64, 96, 128 or 256; at most 512 MiB of rows at a
- * time), pools of a few times k + 16 keys and at most 1 GiB per batch of queries; when
- * these have been given back, for the queries without a proof (however many there
- * turn out to be), at most 1 GiB and the fused search's scratch for a batch; 12
+ * time), pools of a few times k + 16 keys and at most 1 GiB per batch of queries; the
+ * queries without a proof (however many there turn out to be) use the spent part of
+ * that, raised to 1 GiB at most, and take beside it what the fused search's scratch
+ * for a batch needs beyond; 12
  * bytes per query and, for L2 without supplied norms, 4 per row throughout.  Small
  * calls: about nb bytes per query, at most 512 MiB.  Where that cannot be allocated
  * the fused search takes the call: nq x nchunks x S keys of 8 bytes, nchunks <= 16,
@@ -168,7 +169,8 @@ mk_status mk_knn_search_noalloc(const float* xq, int64_t nq, const float* xb, in
 /*
  * As mk_knn_search, with the database norms ||y_i||^2 supplied by the caller
  * (e.g. from mk_norms on a resident database; ignored for MK_METRIC_IP and
- * may then be NULL).  yn [nb] float32.
+ * may then be NULL).  yn [nb] float32; a row with a norm of +infinity or NaN that is not
+ * its own has no score and is not returned.
  */
 mk_status mk_knn_search_prenorm(const float* xq, int64_t nq, const float* xb, const float* yn,
                                 int64_t nb, int32_t d, int32_t k, mk_metric metric, float* D,
