@@ -1194,9 +1194,10 @@ __global__ void entry_term1_kernel(const int64_t* __restrict__ offsets, int32_t 
 // 1,024, the next step's codes and terms in flight: a step of its own per list
 // leaves most of its last lanes idle and starts with three loads in a row (list,
 // offset, code).  10^4 queries, 8 lists of about 1,000 entries, 256 kept: queues
-// 919, pool 608, one range 506 us; 64 queries, 32 lists, 100 kept: 80, 44, 41 us.
+// 919, pool 608, one range 506 us; 64 queries, 32 lists, 100 kept: 80, 44, 41 us.  With
+// 16 code bytes as a constant, on another card: 475 -> 443 and 40.1 -> 38.5 us.
 // What is left is the table lookups: 1.25 * 10^9 LDS gathers with random banks,
-// about 7 cycles per wave and gather, are 230 of the 506 us.
+// about 7 cycles per wave and gather, are 230 of the 443 us.
 // Item -> (query, group): fixed probe count nprobe (= ld) when work is null,
 // else query q owns items work[q] .. work[q + 1] - 1 and probes tau[q] lists.
 
